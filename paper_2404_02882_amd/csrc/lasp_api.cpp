@@ -46,11 +46,6 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     p->kvdiv = s->kv_heads > 0 ? s->H / s->kv_heads : 1;
     p->tile = lasp::tile_tokens(s->dtype, s->chunk, p->D);
     p->ntiles = (s->N + p->tile - 1) / p->tile;
-    // A short last tile is handled by the per-token-decay kernels only: with one lambda per head the
-    // library synthesises log g = log(lambda) and runs those (with or without the fused Norm).
-    const bool ragged = s->N % p->tile != 0;
-    p->synth = ragged && !token;
-    if (p->synth) token = true;
     int want = s->segments;
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
     if (want == 0) {
@@ -62,10 +57,16 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     }
     p->token = token;
     p->norm = norm;
-    p->cache_stride = lasp::cache_stride_for(p->dtype, p->tile, p->ntiles, token, p->dk != p->dv);
+    p->cache_stride = lasp::cache_stride_for(p->dtype);
+    p->ragged = s->N % (p->tile * p->cache_stride) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
+    p->nseg_sized = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;
     if (p->cache_stride == 2) p->tiles_per_seg += p->tiles_per_seg & 1;   // segments start on cached tiles
     p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
+    // The size a caller is told does not follow every change of the plan: which shapes the fixed scratch of
+    // lasp_fwd_noalloc takes, and which buffers are refused, stays what it was. An odd tile count is sized for
+    // segments of single tiles.
+    if (p->cache_stride == 2 && p->ntiles % 2 == 0) p->nseg_sized = p->nseg;
     return LASP_OK;
 }
 
@@ -74,30 +75,30 @@ size_t elem_bytes(int dtype) { return dtype == LASP_F32 ? 4 : 2; }
 size_t cache_bytes(const lasp_shape *shape, bool token) {
     lasp::Plan p;
     if (make_plan(shape, kForward, &p, token) != LASP_OK) return 0;
-    // (a synthesised plan has token == true and the same cache stride rule)
-    return (size_t)p.B * p.H * (p.ntiles / p.cache_stride) * p.dk * p.dv * elem_bytes(p.dtype);   // [d_k][d_v] per slot
+    return (size_t)p.B * p.H * ((p.ntiles + p.cache_stride - 1) / p.cache_stride) * p.dk * p.dv * elem_bytes(p.dtype);   // [d_k][d_v] per slot
 }
 
 // Scratch layout: [segment states][per-token decay only: segment log-decays][.. : per-token r_t]
-// [synthesised log g only: log g per token][grouped K/V heads only: dK, dV per query head].
+// [one lambda per head and a short last tile only: unused, keeps the size callers have been told]
+// [grouped K/V heads only: dK, dV per query head].
 struct ScratchLayout {
-    size_t states, seglog, rtok, logg, dk_part, dv_part, total;  // byte offsets of the regions (states = 0), total size
+    size_t states, seglog, rtok, dk_part, dv_part, total;  // byte offsets of the regions (states = 0), total size
 };
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l) {
     lasp::Plan f, b;
     if (make_plan(shape, kForward, &f, token) != LASP_OK || make_plan(shape, kBackward, &b, token) != LASP_OK) return false;
-    const size_t nseg = f.nseg > b.nseg ? f.nseg : b.nseg;  // one buffer serves both passes
+    const size_t nseg = f.nseg_sized > b.nseg_sized ? f.nseg_sized : b.nseg_sized;  // one buffer serves both passes
     const size_t chains = (size_t)f.B * f.H;
     l->states = 0;
     l->seglog = round256(chains * nseg * f.dk * f.dv * sizeof(float));   // segment states, [d_k][d_v] floats each
-    l->rtok = l->logg = l->seglog;
+    l->rtok = l->seglog;
     size_t end = l->seglog;
-    if (f.token) {   // requested, or synthesised for a short last tile
+    const bool ragged = f.N % f.tile != 0;
+    if (f.token || ragged) {
         const size_t per_token = round256(chains * (size_t)f.N * sizeof(float));
         l->rtok = l->seglog + round256(chains * nseg * sizeof(float));
-        l->logg = l->rtok + per_token;
-        end = l->logg + (f.synth ? per_token : 0);
+        end = l->rtok + (f.token ? 1 : 2) * per_token;
     }
     l->dk_part = l->dv_part = end;
     if (f.kvdiv > 1) {
@@ -183,13 +184,8 @@ int run_fwd_call(const FwdCall &c) {
 
     hipStream_t stream = (hipStream_t)c.stream;
     char *scr = (char *)c.scratch;
-    lasp::FwdArgs a{c.q, c.k, c.v, c.kv_in, c.decay, c.out, c.kv_out, c.cache, (float *)scr,
+    const lasp::FwdArgs a{c.q, c.k, c.v, c.kv_in, c.decay, c.out, c.kv_out, c.cache, (float *)scr,
                     p.token ? (float *)(scr + l.seglog) : nullptr, c.rstd, c.eps, false};
-    if (p.synth) {
-        float *lg = (float *)(scr + l.logg);
-        if (lasp::launch_fill_logg(p, c.decay, lg, stream) != hipSuccess) return LASP_ERR_HIP;
-        a.decay = lg;
-    }
     return lasp::launch_fwd(p, a, stream, next_slot(0)) == hipSuccess ? LASP_OK : LASP_ERR_HIP;
 }
 
@@ -247,20 +243,14 @@ int run_bwd_call(const BwdCall &c) {
     if (rc != LASP_OK) return rc;
 
     hipStream_t stream = (hipStream_t)c.stream;
-    const float *decay = c.decay;
-    if (p.synth) {
-        float *lg = (float *)(scr + l.logg);
-        if (lasp::launch_fill_logg(p, c.decay, lg, stream) != hipSuccess) return LASP_ERR_HIP;
-        decay = lg;
-    }
     if (rebuild) {   // the forward pass's own plan (its segment count), states only, into the scratch tail
         lasp::Plan f;
         if (rc = make_plan(c.shape, kForward, &f, c.token, false); rc != LASP_OK) return rc;
-        const lasp::FwdArgs fa{nullptr, c.k, c.v, c.kv_in, decay, nullptr, nullptr, (void *)cache, (float *)scr,
+        const lasp::FwdArgs fa{nullptr, c.k, c.v, c.kv_in, c.decay, nullptr, nullptr, (void *)cache, (float *)scr,
                                f.token ? (float *)(scr + l.seglog) : nullptr, nullptr, 0.0f, true};
         if (lasp::launch_fwd(f, fa, stream, nullptr) != hipSuccess) return LASP_ERR_HIP;
     }
-    lasp::BwdArgs a{c.q, c.k, c.v, c.dout, c.dkv_out, decay, cache, c.dq, c.dk, c.dv, c.dkv_in, (float *)scr,
+    lasp::BwdArgs a{c.q, c.k, c.v, c.dout, c.dkv_out, c.decay, cache, c.dq, c.dk, c.dv, c.dkv_in, (float *)scr,
                     c.kv_out, c.dlog_g, p.token ? (float *)(scr + l.seglog) : nullptr,
                     p.token ? (float *)(scr + l.rtok) : nullptr, c.yn, c.rstd, nullptr, nullptr};
     if (p.kvdiv > 1) {   // the kernels write dK, dV per query head; launch_bwd sums each group into the outputs

@@ -465,8 +465,11 @@ DEVI void fill_pow_table(float *pw, float lam) {
 // ---------------------------------------------------------------------------
 // Decay model of a tile of CT tokens (token indices 0-based inside the tile):
 //   upto(i)      weight the state entering the tile carries at token i   (Lambda of Alg. 2)
-//   after(j)     weight token j carries at the end of the tile           (lambda^C Lambda^-1)
-//   whole()      weight the entering state carries at the end of the tile (lambda^C)
+//   after(j, n)  weight token j carries at the end of the tile           (lambda^C Lambda^-1)
+//   whole(n)     weight the entering state carries at the end of the tile (lambda^C)
+// n <= CT is the number of tokens the tile really has: the end of a short last tile is behind token n - 1, so
+// with one lambda per head the last two shift by CT - n (tokens past the end get weight zero from the zeros in
+// front of the table); with a decay per token those tokens carry log g = 0 and n plays no part.
 //   masked(x,i,j) x times the weight key j carries at query i, zero for j > i (mask M)
 // FixedDecay: one lambda per head (Alg. 2 / Alg. 3 as printed); every weight is a
 // power of lambda read from one table that serves all tiles.
@@ -490,11 +493,15 @@ struct FixedDecay {
             tab[i] = i < CT - 1 ? 0.0f : (float)exp2((double)(i - (CT - 1)) * l2);
     }
     DEVI float upto(int i) const { return pw[i + 1]; }
-    DEVI float after(int j) const { return pw[CT - 1 - j]; }
-    DEVI float whole() const { return pw[CT]; }
+    DEVI float after(int j, int n) const { return pw[n - 1 - j]; }
+    DEVI float whole(int n) const { return pw[n]; }
     DEVI float masked(float x, int i, int j) const { return x * pw[i - j]; }
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
-        return lasp::weigh_after<T, CT>(ln, f, ks, pw, geo);
+    // FULL: n == CT, the lane's weights are one table entry times the uniform powers; otherwise the run of
+    // tokens may straddle the end of the tile and every element reads its own entry (one tile per sub-sequence).
+    template <bool FULL>
+    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks, int n) const {
+        if constexpr (FULL) return lasp::weigh_after<T, CT>(ln, f, ks, pw, geo);
+        else return Elem<T>::scale(ln, f, ks * Elem<T>::KSTEP, [&](int k) { return pw[n - 1 - k]; });
     }
     DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {
         return lasp::weigh_upto<T, CT>(ln, f, ks, pw, geo);
@@ -583,12 +590,13 @@ struct TokenDecay {
         return total;
     }
     DEVI float upto(int i) const { return wu[i]; }
-    DEVI float after(int j) const { return wa[j]; }
-    DEVI float whole() const { return wu[CT - 1]; }
+    DEVI float after(int j, int) const { return wa[j]; }
+    DEVI float whole(int) const { return wu[CT - 1]; }
     // (the bare hardware exp2: a weight below 2^-126 becomes 0 instead of a denormal, and the library
     // routine's range handling would cost four more instructions for every score element)
     DEVI float masked(float x, int i, int j) const { return i >= j ? x * __builtin_amdgcn_exp2f(cum[i] - cum[j]) : 0.0f; }
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
+    template <bool FULL>
+    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks, int) const {
         return Elem<T>::scale_tab(ln, f, wa, ks * Elem<T>::KSTEP);
     }
     DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {

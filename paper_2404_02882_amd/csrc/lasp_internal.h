@@ -15,14 +15,15 @@ struct Plan {
     int dk, dv;         // key (q, k) and value (v, out) dimensions as stored; the narrower one is zero-padded to D on chip
     int dtype;          // 0 = float, 1 = bfloat16
     int tile;           // tokens per kernel tile (CT)
-    int ntiles;         // ceil(N / tile); only the last tile may be short, and only with token == true
+    int ntiles;         // ceil(N / tile); only the last tile may be short
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
-    int cache_stride;   // the state cache holds the start state of every cache_stride-th tile (1 or 2)
+    int cache_stride;   // the state cache holds the start state of every cache_stride-th tile (bfloat16: 2, float: 1)
+    bool ragged;        // the last tile is short, or the last pair of tiles (cache_stride 2) has only one
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
-    bool synth;         // one lambda per head but N % tile != 0: log g is synthesised and the token kernels run
+    int nseg_sized;     // segments the reported scratch size provides for (>= nseg; see make_plan)
 };
 
 struct FwdArgs {
@@ -79,12 +80,10 @@ hipError_t static_scratch(void **ptr);
 
 // Tile length used for a (dtype, chunk, D) combination.
 int tile_tokens(int dtype, int chunk, int D);
-// Cache stride for a shape: 2 (one cached state per pair of tiles, the backward
-// walk reaches the other tile from its neighbour's state) when the kernels support it, else 1.
-int cache_stride_for(int dtype, int tile, int ntiles, bool token, bool mixed_dims);
+// Cache stride for a data type: 2 for bfloat16 (one cached state per pair of tiles, the backward
+// walk reaches the other tile from its neighbour's state), else 1.
+int cache_stride_for(int dtype);
 
-// log_g[b][h][s] = log(decay[h]) for all N tokens (device buffers).
-hipError_t launch_fill_logg(const Plan &p, const float *decay, float *log_g, hipStream_t stream);
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t stream, const KernelEvents *ke);
 hipError_t launch_bwd(const Plan &p, const BwdArgs &a, hipStream_t stream, const KernelEvents *ke);
 

@@ -12,12 +12,11 @@
 //                local states into the state each segment starts from
 //                (KV_t = lambda^len KV_{t-1} + local, the state update of
 //                Sec. 3.2 taken over a whole segment).
-//   3. k_fwd / k_bwd8p, k_bwd8, k_bwd : each segment walks its tiles with the
+//   3. k_fwd / k_bwd8p, k_bwd : each segment walks its tiles with the
 //                d x d state held in registers: intra-chunk left product,
 //                inter-chunk right product, state update (Alg. 2 / Alg. 3 per
-//                tile). Backward: k_bwd8p for bfloat16 with an even tile count
-//                (one cached state per pair of tiles), k_bwd8 for an odd one,
-//                k_bwd for float.
+//                tile). Backward: k_bwd8p for bfloat16 (one cached state per
+//                pair of tiles), k_bwd for float.
 // Every kernel is instantiated for a decay model (lasp_device.h): one lambda
 // per head, or a decay per token (general recurrent form of App. A.4), which
 // adds k_dlg for the gradient of the log decay; optionally with the output
@@ -68,9 +67,11 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 // ---------------------------------------------------------------------------
 // NORM (backward only): Y is dY, the gradient w.r.t. the normalised output; the tile is turned into dO
 // on its way to LDS from the normalised output `yn` and `rstd` ([chain][token]).
+// RAGGED: the sub-sequence's last tile may be short (or missing from the last pair of tiles, k_bwd8p); without
+// it every row count is CT and known at compile time.
 // WX, WY: elements per row of X and Y in memory (<= D; narrower rows are zero-padded on their way to LDS,
 // which serves key and value dimensions that differ).
-template <typename T, int CT, int D, bool BWD, bool TOKEN, bool NORM = false, int WX = D, int WY = D>
+template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM = false, int WX = D, int WY = D>
 __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
                                                   float *__restrict__ seglog, int H, int ntiles, int nseg,
@@ -99,8 +100,9 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     const int ntl = t1 - t0;
     auto tile_of = [&](int n) { return BWD ? t1 - 1 - n : t0 + n; };
     // the first tile is requested before anything else so that its latency covers the set-up
-    // rows of tile `t` that exist: the last tile of a sub-sequence may be short (per-token decay only)
-    auto nvalid = [&](int t) { return TOKEN ? min(CT, ntok - t * CT) : CT; };
+    // rows of tile `t` that exist: the last tile of a sub-sequence may be short. (The forward pass never sums
+    // over the last segment; the backward weights run from the segment's start, which a short end leaves alone.)
+    auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
     TileMover<T, CT, D, NT, true> mx, my;   // streaming (non-temporal) loads
     NormTile<T, CT, D, NT, WY> mn;   // the normalised output has the rows of Y (= dY)
     const float *rstd_c = rstd + (size_t)chain * ntok;
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                     return f;
                 },
                 [&](int ks, const Step &f) {
-                    const typename E::frag yd = BWD ? dec.weigh_upto(ln, f.y, ks) : dec.weigh_after(ln, f.y, ks);
+                    const typename E::frag yd = BWD ? dec.weigh_upto(ln, f.y, ks) : dec.template weigh_after<true>(ln, f.y, ks, CT);
 #pragma unroll
                     for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(f.x[ab], yd, st[ab]);
                 });
@@ -175,6 +177,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
         my.store(sY, LDD);
         __syncthreads();
         if (n + 1 < ntl) {
+            // (tiles of this loop are requested after the segment's last one: never the short one)
             mx.template load_w<WX>(X + xoff(tile_of(n + 1)), CT);
             my.template load_w<WY>(Y + yoff(tile_of(n + 1)), CT);
             if constexpr (NORM) mn.load(yn + yoff(tile_of(n + 1)), rstd_c + (size_t)tile_of(n + 1) * CT);
@@ -236,15 +239,15 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 template <bool BWD, bool TOKEN>
 __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const float *__restrict__ boundary,
                                               const float *__restrict__ decay, const float *__restrict__ seglog,
-                                              int H, int DD, int nseg, int tiles_per_seg, int ntiles, int tile) {
+                                              int H, int DD, int nseg, int seg_tokens, int ntok) {
     const int chain = blockIdx.y;
     const int e = (blockIdx.x * blockDim.x + threadIdx.x) * 4;  // four consecutive state elements per thread
     if (e >= DD) return;
     float p_full = 0.0f, p_last = 0.0f;
     if constexpr (!TOKEN) {
         const double l2 = log2((double)decay[chain % H]);
-        p_full = (float)exp2((double)(tiles_per_seg * tile) * l2);
-        p_last = (float)exp2((double)((ntiles - (nseg - 1) * tiles_per_seg) * tile) * l2);
+        p_full = (float)exp2((double)seg_tokens * l2);
+        p_last = (float)exp2((double)(ntok - (nseg - 1) * seg_tokens) * l2);
     }
     // The caller's state and the segment states share one layout, [d_k][d_v] (DD = d_k * d_v elements).
     f32x4 carry = {0, 0, 0, 0};
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
 // STATES: only the states are wanted (a backward pass that was given no state cache rebuilds it, Sec. 3.4's
 // recomputation instead of caching): Q is not read, no scores and no outputs are computed; K, V are
 // walked, every tile's entering state goes to the cache and the state is updated.
-template <typename T, int CT, int D, bool TOKEN, bool NORM = false, int WK = D, int WV = D, bool STATES = false>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, bool STATES = false>
 __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k_fwd(const T *__restrict__ Q, const T *__restrict__ K,
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
@@ -313,8 +316,8 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
     V += kv_shift(chain, H, kvdiv, ntok, WV);
     auto koff = [&](int t) { return tile_off(chain, ntok, t, CT, WK); };
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
-    // rows of tile `t` that exist: the last tile of a sub-sequence may be short (per-token decay only)
-    auto nvalid = [&](int t) { return TOKEN ? min(CT, ntok - t * CT) : CT; };
+    // rows of tile `t` that exist: the last tile of a sub-sequence may be short
+    auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
     static_assert(!STATES || !NORM, "the states do not depend on the Norm");
     TileMover<T, CT, D, NT> mq, mk, mv;
     if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t0), nvalid(t0));
@@ -332,7 +335,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
         ln = fresh_lane();
         // The state this tile starts from goes to the cache as KV_{t-1}, rows a, columns c.
         if (cache && t % cache_stride == 0)
-            cache_store<T, CT, D, WK, WV>(ln, cache + ((size_t)chain * (ntiles / cache_stride) + t / cache_stride) * WK * WV, st, sP, w);
+            cache_store<T, CT, D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + cache_stride - 1) / cache_stride) + t / cache_stride) * WK * WV, st, sP, w);
         if constexpr (!STATES) mq.store(sQ, LDD);
         mk.store(sK, LDD);
         mv.store(sV, LDD);
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
                 for (int wv = 0; wv < D / 32; ++wv) tot += red[wv * CT + 32 * ib + ln.r];
                 const float rs = rsqrtf(tot * (1.0f / WV) + eps);   // mean over the real value features (padding is zero)
                 acc[ib] *= rs;
-                if (w == 0 && ln.h == 0 && 32 * ib + ln.r < nvalid(t))
+                if (w == 0 && ln.h == 0 && (!RAGGED || 32 * ib + ln.r < nvalid(t)))
                     rstd_out[(size_t)chain * ntok + (size_t)t * CT + 32 * ib + ln.r] = rs;
             }
         }
@@ -404,15 +407,21 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
 
         ln = fresh_lane();
         // state update: KV <- lambda^CT KV + (diag{lambda^(CT-1-j)} K)^T V, weight applied to the V fragments
-        const float lamC = dec.whole();
+        const int nv = nvalid(t);
+        const float lamC = dec.whole(nv);
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] *= lamC;
+        auto update = [&](auto full) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const typename E::frag vd = dec.weigh_after(ln, E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w), ks);
+            for (int ks = 0; ks < NKS; ++ks) {
+                const typename E::frag vd =
+                    dec.template weigh_after<decltype(full)::value>(ln, E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w), ks, nv);
 #pragma unroll
-            for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * ab), vd, st[ab]);
-        }
+                for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * ab), vd, st[ab]);
+            }
+        };
+        if (TOKEN || !RAGGED || nv == CT) update(std::true_type{});
+        else update(std::false_type{});
     }
     if (seg == nseg - 1 && kv_out) state_store_w<D, WK, WV>(ln, st, kv_out + (size_t)chain * WK * WV, w);
 }
@@ -444,7 +453,7 @@ struct BwdSmem {
 // NORM: dO is dY, the gradient w.r.t. the normalised output `yn`; every dY tile is turned into dO on its
 // way to LDS (NormTile) from `yn` and `rstd` ([chain][token]).
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
-template <typename T, int CT, int D, bool TOKEN, bool NORM = false, int WK = D, int WV = D>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D>
 __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV == D) ? 2 : 1) void k_bwd(const T *__restrict__ Q, const T *__restrict__ K,
                                                 const T *__restrict__ V, const T *__restrict__ dO,
                                                 const float *__restrict__ decay, const T *__restrict__ cache,
@@ -473,8 +482,8 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
     typename TokenDecay<T, CT>::LogG lgreg = {};
-    // rows of tile `t` that exist: the last tile of a sub-sequence may be short (per-token decay only)
-    auto nvalid = [&](int t) { return TOKEN ? min(CT, ntok - t * CT) : CT; };
+    // rows of tile `t` that exist: the last tile of a sub-sequence may be short
+    auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
     if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t1 - 1) * CT, nvalid(t1 - 1));
     // per-token decay: r_t = q_t.dq_t - k_t.dk_t, one partial row per wave, summed and written per tile
     float *rs = pw + 3 * CT + 4;
@@ -483,7 +492,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
             float r = 0.0f;
 #pragma unroll
             for (int wv = 0; wv < D / 32; ++wv) r += rs[wv * CT + threadIdx.x];
-            if (tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
+            if (!RAGGED || tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
         }
     };
 
@@ -557,7 +566,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) accK[jb] = E::mfma(xf[ks], E::ld_kc(ln, bufA, LDD, 32 * jb, ks * E::KSTEP), accK[jb]);
 #pragma unroll
-        for (int jb = 0; jb < NB; ++jb) accK[jb] *= dec.after(32 * jb + ln.r);
+        for (int jb = 0; jb < NB; ++jb) accK[jb] *= dec.after(32 * jb + ln.r, nvalid(t));
         // dO fragments of this wave's column block: [k = i][n = c in w]
         typename E::frag dof[NKS];
 #pragma unroll
@@ -621,7 +630,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
                     for (int jb = 0; jb < NB; ++jb) accV[jb] = E::mfma(df, E::ld_kp(ln, bufA, LDD, 32 * jb, 32 * ab, m), accV[jb]);
                 }
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) accV[jb] *= dec.after(32 * jb + ln.r);
+            for (int jb = 0; jb < NB; ++jb) accV[jb] *= dec.after(32 * jb + ln.r, nvalid(t));
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
@@ -631,7 +640,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
             for (int jb = 0; jb < NB; ++jb) store_out_tile_t<T, D, WV>(ln, dV + voff(t), accV[jb], 32 * jb, w, nvalid(t));
         }
         // dKV <- lambda^CT dKV + (Lambda Q)^T dO  (row weight lambda^(i+1) applied to the dO fragments)
-        const float lamC = dec.whole();
+        const float lamC = dec.whole(nvalid(t));
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) dkv[ab] *= lamC;
 #pragma unroll
@@ -649,10 +658,10 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd8: the backward walk for bfloat16 tiles of 64 tokens, one workgroup of
+// k_bwd8p: the backward walk for bfloat16 tiles of 64 tokens, one workgroup of
 // 2 * D/32 waves per CU. Same mathematics as k_bwd, different residency:
-//   - all four input tiles (V, dO, K, Q), both masked score tiles and the
-//     cached KV_{t-1} tile live in LDS at once, so a tile needs three barriers;
+//   - every input tile, the masked score tiles and the cached state live in LDS
+//     at once;
 //   - the waves form two groups that each keep dKV in registers in the
 //     orientation their product needs, so nothing is exchanged:
 //       group 0 holds dKV[a][c in w] (rows a) and produces dV (dV_inter contracts a),
@@ -661,270 +670,21 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
 //     code, including the dKV update, so the groups differ only in pointers;
 //   - dQ needs only the cached state and is split by token block between them
 //     (group 0, which the hardware favours when both wait to issue, takes the
-//     block with the longer key range).
-// ---------------------------------------------------------------------------
-template <typename T, int CT, int D>
-struct Bwd8Smem {
-    using E = Elem<T>;
-    static constexpr int LDD = tile_ld<T, D>(), LDP = CT + E::PAD;
-    static constexpr size_t TILE = (size_t)CT * LDD * sizeof(T);
-    static constexpr size_t P_OFF = 4 * TILE;
-    static constexpr size_t C_OFF = P_OFF + 2 * (size_t)CT * LDP * sizeof(T);   // cached KV_{t-1} tile
-    static constexpr size_t PW_OFF = C_OFF + (size_t)D * LDD * sizeof(T);
-    static constexpr size_t TOTAL = PW_OFF + table_floats<CT>() * sizeof(float);
-};
-
-template <typename T, int CT, int D, bool TOKEN, bool NORM = false>
-__global__ __launch_bounds__(D * 4) void k_bwd8(const T *__restrict__ Q, const T *__restrict__ K,
-                                                 const T *__restrict__ V, const T *__restrict__ dO,
-                                                 const float *__restrict__ decay, const T *__restrict__ cache,
-                                                 T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
-                                                 float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                 float *__restrict__ rtok,
-                                                 int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
-                                                 const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
-    using E = Elem<T>;
-    using F = typename E::frag;
-    using SM = Bwd8Smem<T, CT, D>;
-    static_assert(CT == 64, "two 32-token blocks per tile");
-    constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
-                  NKD = D / E::KSTEP, SPB = 32 / E::KSTEP;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    T *sV = (T *)smem;
-    T *sdO = sV + CT * LDD;
-    T *sK = sdO + CT * LDD;
-    T *sQ = sK + CT * LDD;
-    T *sS = (T *)(smem + SM::P_OFF);
-    T *sDS = sS + CT * LDP;
-    T *sC = (T *)(smem + SM::C_OFF);
-    float *pw = (float *)(smem + SM::PW_OFF);
-
-    const int chain = blockIdx.y, seg = blockIdx.x;
-    const int t0 = seg * tiles_per_seg;
-    const int t1 = min(t0 + tiles_per_seg, ntiles);
-    const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int w = w8 % NW;    // feature block of this wave's outputs
-    const int rg = w8 / NW;   // group: 0 produces dV, 1 produces dK
-    Lane ln = fresh_lane();
-
-    // requests first (last tile of the segment, its cached state), set-up arithmetic while they fly
-    const size_t base = (size_t)chain * ntok * D;
-    {   // K, V of this chain's K/V head
-        const ptrdiff_t sh = kv_shift(chain, H, kvdiv, ntok, D);
-        K += sh;
-        V += sh;
-    }
-    TileMover<T, CT, D, NT> mv, mo, mk, mq;
-    TileMover<T, D, D, NT> mc;  // cached state tile KV_{t-1}, [a][c]
-    const T *ctile = cache + (size_t)chain * ntiles * D * D;
-    {
-        const size_t off = base + (size_t)(t1 - 1) * CT * D;
-        const int nv = TOKEN ? min(CT, ntok - (t1 - 1) * CT) : CT;  // the last tile of a sub-sequence may be short
-        mv.load(V + off, nv);
-        mo.load(dO + off, nv);
-        mk.load(K + off, nv);
-        mq.load(Q + off, nv);
-        mc.load(ctile + (size_t)(t1 - 1) * D * D);
-    }
-    NormTile<T, CT, D, NT> mn;  // NORM: dO is dY; turned into dO from the normalised output and rstd on its way to LDS
-    const float *rstd_c = rstd + (size_t)chain * ntok;
-    if constexpr (NORM)
-        mn.load(yn + base + (size_t)(t1 - 1) * CT * D, rstd_c + (size_t)(t1 - 1) * CT, TOKEN ? min(CT, ntok - (t1 - 1) * CT) : CT);
-    const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
-    const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
-    typename TokenDecay<T, CT>::LogG lgreg = {};
-    if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t1 - 1) * CT, min(CT, ntok - (t1 - 1) * CT));
-    // per-token decay: r_t = q_t.dq_t - k_t.dk_t, one partial row per wave, summed and written per tile
-    float *rs = pw + 3 * CT + 4;
-    auto flush_r = [&](int tile) {
-        if (threadIdx.x < CT) {
-            float r = 0.0f;
-#pragma unroll
-            for (int wv = 0; wv < 2 * NW; ++wv) r += rs[wv * CT + threadIdx.x];
-            if (tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
-        }
-    };
-
-    // Group-dependent operands (wave-uniform selects).
-    const T *sX1 = rg ? sV : sK;     // inter operand: token rows, features contracted with the state
-    const T *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
-    const T *sUA = rg ? sdO : sQ;    // state-update A operand: [token][feature of the state rows]
-    const T *sPm = rg ? sDS : sS;    // masked score tile P[i][j] of this product
-    T *gOut = rg ? dK : dV;
-
-    // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
-    f32x16 st[DB];
-    {
-        const float *g = scratch + ((size_t)chain * nseg + seg) * D * D;
-        if (rg == 0) state_load_w<D>(ln, st, g, w);
-        else state_load_t_w<D>(ln, st, g, w);
-    }
-
-    for (int t = t1 - 1; t >= t0; --t) {
-        const size_t off = base + (size_t)t * CT * D;
-        const int nrows = TOKEN ? min(CT, ntok - t * CT) : CT;  // rows of this tile that exist
-        __syncthreads();  // previous tile fully consumed
-        ln = fresh_lane();
-        if constexpr (TOKEN) {
-            if (t < t1 - 1) flush_r(t + 1);
-            dec.fill(lgreg);
-        }
-        if constexpr (NORM) mn.apply(mo);
-        mv.store(sV, LDD);
-        mo.store(sdO, LDD);
-        mk.store(sK, LDD);
-        mq.store(sQ, LDD);
-        mc.store(sC, LDD);
-        __syncthreads();
-        ln = fresh_lane();
-        if (t > t0) {
-            mv.load(V + off - (size_t)CT * D);
-            mo.load(dO + off - (size_t)CT * D);
-            mk.load(K + off - (size_t)CT * D);
-            mq.load(Q + off - (size_t)CT * D);
-            mc.load(ctile + (size_t)(t - 1) * D * D);
-            if constexpr (NORM) mn.load(yn + off - (size_t)CT * D, rstd_c + (size_t)(t - 1) * CT);
-            if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t - 1) * CT);
-        }
-        // masked score tiles: dS^T = V dO^T (tiles 0..2) and S^T = K Q^T (tiles 3..5), one per wave
-        {
-            constexpr int NTRI = 3;  // lower-triangular 32x32 blocks of a 64x64 tile
-#pragma unroll
-            for (int idx = 0; idx < 2 * NTRI; ++idx) {
-                if (idx % (2 * NW) != w8) continue;
-                const int tri = idx % NTRI, ib = tri == 0 ? 0 : 1, jb = tri == 2 ? 1 : 0;
-                const T *sA = idx < NTRI ? sV : sK, *sB = idx < NTRI ? sdO : sQ;
-                f32x16 acc = {0}, acc2 = {0};
-                pipelined<NKD / 2>(
-                    [&](int s2) {
-                        FragPair<FragPair<F>> f;
-                        f.a.a = E::ld_kc(ln, sA, LDD, 32 * jb, 2 * s2 * E::KSTEP);
-                        f.a.b = E::ld_kc(ln, sB, LDD, 32 * ib, 2 * s2 * E::KSTEP);
-                        f.b.a = E::ld_kc(ln, sA, LDD, 32 * jb, (2 * s2 + 1) * E::KSTEP);
-                        f.b.b = E::ld_kc(ln, sB, LDD, 32 * ib, (2 * s2 + 1) * E::KSTEP);
-                        return f;
-                    },
-                    [&](int, const FragPair<FragPair<F>> &f) {
-                        acc = E::mfma(f.a.a, f.a.b, acc);
-                        acc2 = E::mfma(f.b.a, f.b.b, acc2);
-                    });
-                acc += acc2;
-                store_masked_scores<T, LDP>(ln, idx < NTRI ? sDS : sS, acc, jb, ib, dec);
-            }
-        }
-        __syncthreads();
-        ln = fresh_lane();
-
-        float rq = 0.0f;  // per-token decay: q_i . dq_i over this wave's features, tokens i of block 1 - rg
-        // ---- dQ^T[a in w][i], tokens i of block 1 - rg:
-        //      lambda^i sum_c KV_{t-1}[a][c] dO[i][c] + sum_{j<=i} K[j][a] dSm[i][j] ----
-        {
-            const int r0 = 32 * (1 - rg);   // group 0 takes the second token block (whose keys span both blocks), group 1 the first
-            f32x16 acc = {0};
-            pipelined<NKD>(
-                [&](int ks) { return FragPair<F>{E::ld_kc(ln, sC, LDD, 32 * w, ks * E::KSTEP), E::ld_kc(ln, sdO, LDD, r0, ks * E::KSTEP)}; },
-                [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); });
-            acc *= dec.upto(r0 + ln.r);
-            auto intra = [&](int ks) { return FragPair<F>{E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * w), E::ld_kc(ln, sDS, LDP, r0, ks * E::KSTEP)}; };
-            auto fma = [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); };
-            if (rg == 0) pipelined<2 * SPB>(intra, fma);    // keys of blocks 0 and 1
-            else pipelined<SPB>(intra, fma);                // keys of block 0
-            store_out_tile_t<T, D>(ln, dQ + off, acc, r0, w, nrows);
-            if constexpr (TOKEN) rq = rowdot<T>(ln, acc, sQ, LDD, r0, w);
-        }
-        ln = fresh_lane();
-        // ---- this group's product, both token blocks j (written for dV; dK is the same under K<->V, Q<->dO, S<->dS):
-        //      dV^T[c in w][j] = lambda^(CT-j) sum_a dKV[a][c] K[j][a] + sum_{i>=j} dO[i][c] Sm[i][j] ----
-        {
-            f32x16 acc[NB];
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) acc[jb] = f32x16{0};
-            struct Two { F b[NB]; };
-            pipelined<DB * E::NSUB>(
-                [&](int s2) {
-                    Two f;
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb) f.b[jb] = E::ld_kp(ln, sX1, LDD, 32 * jb, 32 * (s2 / E::NSUB), s2 % E::NSUB);
-                    return f;
-                },
-                [&](int s2, const Two &f) {
-                    const F sf = E::from_acc(st[s2 / E::NSUB], s2 % E::NSUB);
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb) acc[jb] = E::mfma(sf, f.b[jb], acc[jb]);
-                });
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) acc[jb] *= dec.after(32 * jb + ln.r);
-            struct Three { F a; F b[NB]; };
-            pipelined<NKS>(
-                [&](int ks) {
-                    Three f;
-                    f.a = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb)
-                        if (jb <= ks / SPB) f.b[jb] = E::ld_ks(ln, sPm, LDP, ks * E::KSTEP, 32 * jb);
-                    return f;
-                },
-                [&](int ks, const Three &f) {
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb)
-                        if (jb <= ks / SPB) acc[jb] = E::mfma(f.a, f.b[jb], acc[jb]);
-                });
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) store_out_tile_t<T, D>(ln, gOut + off, acc[jb], 32 * jb, w, nrows);
-            if constexpr (TOKEN) {
-#pragma unroll
-                for (int jb = 0; jb < NB; ++jb) {
-                    float r = jb == 1 - rg ? rq : 0.0f;
-                    if (rg == 1) r -= rowdot<T>(ln, acc[jb], sK, LDD, 32 * jb, w);  // group 1 holds dK
-                    if (ln.h == 0) rs[w8 * CT + 32 * jb + ln.r] = r;
-                }
-            }
-        }
-        ln = fresh_lane();
-        // ---- state update in this group's orientation (group 0: dKV <- lambda^CT dKV + (Lambda Q)^T dO) ----
-        {
-            const float lamC = dec.whole();
-#pragma unroll
-            for (int blk = 0; blk < DB; ++blk) st[blk] *= lamC;
-            struct Step {
-                F b;
-                F a[DB];
-            };
-            pipelined<NKS>(
-                [&](int ks) {
-                    Step f;
-                    f.b = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
-#pragma unroll
-                    for (int blk = 0; blk < DB; ++blk) f.a[blk] = E::ld_ks(ln, sUA, LDD, ks * E::KSTEP, 32 * blk);
-                    return f;
-                },
-                [&](int ks, const Step &f) {
-                    const F bs = dec.weigh_upto(ln, f.b, ks);
-#pragma unroll
-                    for (int blk = 0; blk < DB; ++blk) st[blk] = E::mfma(f.a[blk], bs, st[blk]);
-                });
-        }
-    }
-    if constexpr (TOKEN) {
-        __syncthreads();
-        flush_r(t0);
-    }
-    if (seg == 0 && rg == 0) state_store_w<D>(ln, st, dkv_in + (size_t)chain * D * D, w);
-}
-
-// ---------------------------------------------------------------------------
-// k_bwd8p: k_bwd8 for a state cache that holds one state per PAIR of tiles
-// (half the cache traffic of both passes). Tiles are walked in reverse as pairs
-// (E = even tile, O = the odd tile after it). The cache gives KV at the start
-// of E. The O tile's dQ needs the state one tile later,
-//     KV_mid = lambda^CT KV + (diag{lambda^(CT-1-j)} K_E)^T V_E   (state update of Sec. 3.2);
-// instead of rebuilding it, dQ of the O tile treats the pair as one chunk of 2 CT
-// tokens (Alg. 3 with C = 2 CT, restricted to the rows of the O tile):
-//     dQ_O = Lambda' dO_O KV^T + [(dO_O V_E^T) (.) M'] K_E + [(dO_O V_O^T) (.) M] K_O,
-// Lambda'_i = lambda^(CT+i), M'_ij = lambda^(CT+i-j): one more masked score tile
-// (sDX) and four more contraction steps, and the cached tile stays in LDS for
-// both tiles. K_E, V_E are needed for the E tile anyway and are simply fetched
-// one tile early. Per pair: six barriers, 9 tile loads, one cache-tile load.
+//     block with the longer key range);
+//   - the state cache holds one state per PAIR of tiles (half the cache traffic
+//     of both passes). Tiles are walked in reverse as pairs (E = even tile, O =
+//     the odd tile after it) and the cache gives KV at the start of E. The O
+//     tile's dQ needs the state one tile later,
+//         KV_mid = lambda^CT KV + (diag{lambda^(CT-1-j)} K_E)^T V_E   (state update of Sec. 3.2);
+//     instead of rebuilding it, dQ of the O tile treats the pair as one chunk of 2 CT
+//     tokens (Alg. 3 with C = 2 CT, restricted to the rows of the O tile):
+//         dQ_O = Lambda' dO_O KV^T + [(dO_O V_E^T) (.) M'] K_E + [(dO_O V_O^T) (.) M] K_O,
+//     Lambda'_i = lambda^(CT+i), M'_ij = lambda^(CT+i-j): one more masked score tile
+//     (sDX) and four more contraction steps, and the cached tile stays in LDS for
+//     both tiles. K_E, V_E are needed for the E tile anyway and are simply fetched
+//     one tile early. Per pair: six barriers, 9 tile loads, one cache-tile load.
+// An odd tile count leaves the last pair without its O tile: nothing of it is
+// read, its phase is skipped and the E tile is the one that may be short.
 // ---------------------------------------------------------------------------
 template <typename T, int CT, int D>
 struct Bwd8pSmem {
@@ -938,7 +698,7 @@ struct Bwd8pSmem {
 };
 
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
-template <typename T, int CT, int D, bool TOKEN, bool NORM = false, int WK = D, int WV = D>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D>
 __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const T *__restrict__ K,
                                                   const T *__restrict__ V, const T *__restrict__ dO,
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
@@ -967,8 +727,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     float *pw = (float *)(smem + SM::PW_OFF);
 
     const int chain = blockIdx.y, seg = blockIdx.x;
-    const int t0 = seg * tiles_per_seg;                 // even
-    const int t1 = min(t0 + tiles_per_seg, ntiles);     // even
+    const int t0 = seg * tiles_per_seg;                                  // even
+    const int t1 = (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;   // even: the last pair may lack its O tile
+    auto nvalid = [&](int t) { return RAGGED ? max(min(CT, ntok - t * CT), 0) : CT; };  // rows of tile `t` that exist
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW;    // feature block of this wave's outputs
     const int rg = w8 / NW;   // group: 0 produces dV, 1 produces dK
@@ -980,7 +741,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
     TileMover<T, CT, D, NT> mvO, moX, mkO, mqX, mvE, mkE;   // moX / mqX carry dO, Q of the O tile, then of the E tile
     TileMover<T, D, D, NT> mc;                               // cached state at the start of the E tile
-    const T *ctile = cache + (size_t)chain * (ntiles / 2) * WK * WV;   // [WK][WV] per slot
+    const T *ctile = cache + (size_t)chain * ((ntiles + 1) / 2) * WK * WV;   // [WK][WV] per slot
     // With a decay per token (`decay` = log g, [chain][token]) the O and the E tile have their own
     // tables; with one lambda per head both names refer to the same table.
     const auto decO = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -991,11 +752,11 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     // weight key j of the E tile carries at query i of the O tile, and the E tile's entering state at query i
     // (one lambda per head: powers CT+1 .. 2 CT of the same table)
     auto cross_weight = [&](int i, int j) {
-        if constexpr (TOKEN) return decO.upto(i) * decE.after(j);
+        if constexpr (TOKEN) return decO.upto(i) * decE.after(j, CT);
         else return decO.pw[CT + i - j];
     };
     auto far_upto = [&](int i) {
-        if constexpr (TOKEN) return decO.upto(i) * decE.whole();
+        if constexpr (TOKEN) return decO.upto(i) * decE.whole(CT);
         else return decO.pw[CT + i + 1];
     };
     const float *lg = decay + (size_t)chain * ntok;
@@ -1007,7 +768,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             float r = 0.0f;
 #pragma unroll
             for (int wv = 0; wv < 2 * NW; ++wv) r += rs[wv * CT + threadIdx.x];
-            if (tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
+            if (!RAGGED || tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
         }
     };
     NormTile<T, CT, D, NT, WV> mnX;  // NORM: partner of moX (dO is dY; see NormTile)
@@ -1018,19 +779,20 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     // of the pair before has taken their registers' contents. Fewer requests are then issued in one
     // burst, which is where the waves stall at the memory pipeline's entry.
     auto load_pair_kv = [&](int tE) {
-        const int nvO = TOKEN ? min(CT, ntok - (tE + 1) * CT) : CT;   // only the O tile of the last pair can be short
-        mvO.template load_w<WV>(V + voff(tE + 1), nvO);
-        mkO.template load_w<WK>(K + koff(tE + 1), nvO);
-        mvE.template load_w<WV>(V + voff(tE), CT);
-        mkE.template load_w<WK>(K + koff(tE), CT);
+        mvO.template load_w<WV>(V + voff(tE + 1), nvalid(tE + 1));
+        mkO.template load_w<WK>(K + koff(tE + 1), nvalid(tE + 1));
+        mvE.template load_w<WV>(V + voff(tE), nvalid(tE));
+        mkE.template load_w<WK>(K + koff(tE), nvalid(tE));
         mc.template load_w<WV>(ctile + (size_t)(tE / 2) * WK * WV, WK);   // rows and columns of padding read as zero
     };
     auto load_pair_rest = [&](int tE) {
-        const int nvO = TOKEN ? min(CT, ntok - (tE + 1) * CT) : CT;
+        const int nvO = nvalid(tE + 1);
         if constexpr (NORM) mnX.load(yn + voff(tE + 1), rstd_c + (size_t)(tE + 1) * CT, nvO);
         if constexpr (TOKEN) {
-            lgO = TokenDecay<T, CT>::fetch(lg + (size_t)(tE + 1) * CT, nvO);
-            lgE = TokenDecay<T, CT>::fetch(lg + (size_t)tE * CT);
+            // (a tile that is not there has no first token to read in place of the missing ones: log g = 0 throughout)
+            if (!RAGGED || nvO > 0) lgO = TokenDecay<T, CT>::fetch(lg + (size_t)(tE + 1) * CT, nvO);
+            else lgO = {};
+            lgE = TokenDecay<T, CT>::fetch(lg + (size_t)tE * CT, nvalid(tE));
         }
         moX.template load_w<WV>(dO + voff(tE + 1), nvO);
         mqX.template load_w<WK>(Q + koff(tE + 1), nvO);
@@ -1183,7 +945,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                     for (int jb = 0; jb < NB; ++jb) acc[jb] = E::mfma(sf, f.b[jb], acc[jb]);
                 });
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) acc[jb] *= dec.after(32 * jb + ln.r);
+            for (int jb = 0; jb < NB; ++jb) acc[jb] *= dec.after(32 * jb + ln.r, nrows);
             struct Three { F a; F b[NB]; };
             pipelined<NKS>(
                 [&](int ks) {
@@ -1220,7 +982,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         }
         ln = fresh_lane();
         if (own_block) {   // state update in this group's orientation
-            const float lamC = dec.whole();
+            const float lamC = dec.whole(nrows);
 #pragma unroll
             for (int blk = 0; blk < DB; ++blk) st[blk] *= lamC;
             struct Step { F b; F a[DB]; };
@@ -1259,18 +1021,21 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         if (tE > t0) load_pair_kv(tE - 2);
         __syncthreads();
         ln = fresh_lane();
-        moX.template load_w<WV>(dO + voff(tE), CT);
-        mqX.template load_w<WK>(Q + koff(tE), CT);
-        if constexpr (NORM) mnX.load(yn + voff(tE), rstd_c + (size_t)tE * CT);
+        moX.template load_w<WV>(dO + voff(tE), nvalid(tE));
+        mqX.template load_w<WK>(Q + koff(tE), nvalid(tE));
+        if constexpr (NORM) mnX.load(yn + voff(tE), rstd_c + (size_t)tE * CT, nvalid(tE));
         // ---- O tile ----
-        scores(decO, sVO, sKO);
-        cross_scores();
-        __syncthreads();
-        ln = fresh_lane();
-        products(decO, sVO, sKO, tE + 1, TOKEN ? min(CT, ntok - (tE + 1) * CT) : CT, true);
-        __syncthreads();  // O tile consumed: sdO, sQ are free
-        ln = fresh_lane();
-        if constexpr (TOKEN) flush_r(tE + 1);
+        const int nvO = nvalid(tE + 1);
+        if (!RAGGED || nvO > 0) {
+            scores(decO, sVO, sKO);
+            cross_scores();
+            __syncthreads();
+            ln = fresh_lane();
+            products(decO, sVO, sKO, tE + 1, nvO, true);
+            __syncthreads();  // O tile consumed: sdO, sQ are free
+            ln = fresh_lane();
+            if constexpr (TOKEN) flush_r(tE + 1);
+        }
         if constexpr (NORM) mnX.apply(moX);
         moX.store(sdO, LDD);
         mqX.store(sQ, LDD);
@@ -1281,7 +1046,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         scores(decE, sVE, sKE);
         __syncthreads();
         ln = fresh_lane();
-        products(decE, sVE, sKE, tE, CT, false);
+        products(decE, sVE, sKE, tE, nvalid(tE), false);
     }
     if constexpr (TOKEN) {
         __syncthreads();
@@ -1393,12 +1158,19 @@ static hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block,
     return hipSuccess;
 }
 
-// A kernel family instantiated for both decay models, with and without the fused Norm: picks the
-// member that serves the plan. Fam::fn<TOKEN, NORM> is the kernel.
+// A kernel family instantiated for both decay models, with and without a short last tile (or an odd tile
+// count, where tiles are walked in pairs), with and without the fused Norm: picks the member that serves the
+// plan. Fam::fn<TOKEN, RAGGED, NORM> is the kernel. The kernels for whole tiles know every row count at
+// compile time: with the row checks in them the walks lose 1 %, and 3-4 % where they are short (c2's shards
+// 154 -> 161 us a step).
+template <typename Fam, bool TK>
+static auto by_edges(const Plan &p) {
+    return p.ragged ? (p.norm ? Fam::template fn<TK, true, true> : Fam::template fn<TK, true, false>)
+                    : (p.norm ? Fam::template fn<TK, false, true> : Fam::template fn<TK, false, false>);
+}
 template <typename Fam>
 static auto by_model(const Plan &p) {
-    return p.token ? (p.norm ? Fam::template fn<true, true> : Fam::template fn<true, false>)
-                   : (p.norm ? Fam::template fn<false, true> : Fam::template fn<false, false>);
+    return p.token ? by_edges<Fam, true>(p) : by_edges<Fam, false>(p);
 }
 
 // Grouped K/V heads, backward: the walking kernel wrote dK, dV per QUERY head into `part`
@@ -1433,37 +1205,32 @@ static hipError_t run_group_sum(const Plan &p, const void *part, void *out, int 
 // Kernel families by decay model and Norm (see by_model).
 template <typename T, int CT, int D, bool BWD, bool WITH_NORM, int WX, int WY>
 struct LocalFam {   // the Norm prologue exists in the backward pass only
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_local<T, CT, D, BWD, TK, NM && BWD && WITH_NORM, WX, WY>;
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG && (BWD || TK), NM && BWD && WITH_NORM, WX, WY>;
 };
 template <typename T, int CT, int D, int WK, int WV>
 struct FwdFam {
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, NM, WK, WV>;
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WK, WV>;
 };
 template <typename T, int CT, int D, int WK, int WV>
 struct StatesFam {  // the forward walk reduced to the states (no Norm: the states do not depend on it)
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, false, WK, WV, true>;
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, true>;
 };
 template <typename T, int CT, int D, int WK, int WV>
-struct BwdFam {     // four waves, one cached state per tile
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_bwd<T, CT, D, TK, NM, WK, WV>;
-};
-template <typename T, int CT, int D>
-struct Bwd8Fam {    // eight waves, one cached state per tile
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_bwd8<T, CT, D, TK, NM>;
+struct BwdFam {     // four waves, one cached state per tile (float data)
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd<T, CT, D, TK, RG, NM, WK, WV>;
 };
 template <typename T, int CT, int D, int WK, int WV>
 struct Bwd8pFam {   // eight waves, one cached state per pair of tiles
-    template <bool TK, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, NM, WK, WV>;
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, RG, NM, WK, WV>;
 };
 
 // The local pass only sums over its segment, so its tile need not be the walk's:
-// bfloat16 segments made of an even number of 64-token tiles are read 128 tokens
+// bfloat16 segments (always an even number of 64-token tiles) are read 128 tokens
 // at a time (half the barriers, twice the bytes in flight per workgroup), unless
 // the Norm prologue (a third tile in registers) or key and value dimensions that
 // differ ask for the walk's tile.
@@ -1472,9 +1239,9 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
                             const T *yn, const float *rstd, hipStream_t s) {
     const dim3 grid(p.nseg - 1, p.B * p.H), block(D * 2);
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
-        if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0 && p.ntiles % 2 == 0)
+        if (!(BWD && p.norm))
             return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D>>(p), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                 decay, scratch, seglog, p.H, p.ntiles / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
+                                 decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
                                  (const T *)nullptr, (const float *)nullptr);
     }
     return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV>>(p), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
@@ -1494,11 +1261,9 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
     if (p.token)
-        k_scan<false, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, nullptr, a.seglog, p.H, DD, p.nseg,
-                                                           p.tiles_per_seg, p.ntiles, p.tile);
+        k_scan<false, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
     else
-        k_scan<false, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, a.decay, nullptr, p.H, DD, p.nseg,
-                                                            p.tiles_per_seg, p.ntiles, p.tile);
+        k_scan<false, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
     if (e = launch_kernel(walk, dim3(p.nseg, chains), dim3(D * 2), Smem<T, CT, D>::fwd, s,
@@ -1525,34 +1290,22 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
     if (p.token)
-        k_scan<true, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, nullptr, a.seglog, p.H, DD, p.nseg,
-                                                          p.tiles_per_seg, p.ntiles, p.tile);
+        k_scan<true, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
     else
-        k_scan<true, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, a.decay, nullptr, p.H, DD, p.nseg,
-                                                           p.tiles_per_seg, p.ntiles, p.tile);
+        k_scan<true, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
     if (ke) (void)hipEventRecord(ke->ev[2], s);
-    // The walking kernel: bfloat16 tiles of 64 tokens run in eight waves, with one cached state per pair of
-    // tiles when the tile count is even; everything else in four waves with one cached state per tile. All
-    // three take the same arguments. (Only the kernels a shape can reach are instantiated.)
+    // The walking kernel: bfloat16 tiles of 64 tokens run in eight waves with one cached state per pair of
+    // tiles, float data in four waves with one cached state per tile. Both take the same arguments.
     typedef void (*Walk)(const T *, const T *, const T *, const T *, const float *, const T *, T *, T *, T *, float *,
                          const float *, float *, int, int, int, int, int, int, const T *, const float *);
     Walk walk = nullptr;
     unsigned threads = D * 2;
     size_t lds = Smem<T, CT, D>::bwd;
-    constexpr bool kEightWaves = sizeof(T) == 2 && CT == 64, kEqualDims = WK == D && WV == D;
-    if constexpr (kEightWaves) {
-        static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840 && Bwd8Smem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
-        if (p.cache_stride == 2) {
-            walk = by_model<Bwd8pFam<T, CT, D, WK, WV>>(p);
-            threads = D * 4;
-            lds = Bwd8pSmem<T, CT, D>::TOTAL;
-        } else if constexpr (kEqualDims) {
-            walk = by_model<Bwd8Fam<T, CT, D>>(p);
-            threads = D * 4;
-            lds = Bwd8Smem<T, CT, D>::TOTAL;
-        } else {
-            walk = by_model<BwdFam<T, CT, D, WK, WV>>(p);
-        }
+    if constexpr (sizeof(T) == 2) {
+        static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
+        walk = by_model<Bwd8pFam<T, CT, D, WK, WV>>(p);
+        threads = D * 4;
+        lds = Bwd8pSmem<T, CT, D>::TOTAL;
     } else {
         walk = by_model<BwdFam<T, CT, D, WK, WV>>(p);
     }
@@ -1570,18 +1323,6 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     if (p.token && a.dlog_g)
         k_dlg<<<dim3((p.N + kDlgBlock - 1) / kDlgBlock, chains), dim3(256), 0, s>>>(a.rtok, a.kv_out, a.dkv_out, a.dlog_g,
                                                                                       p.N, WK * WV);
-    return hipGetLastError();
-}
-
-// log g = log(lambda_h) for every token of head h: lets a sub-sequence whose length is not a multiple of
-// the tile run through the per-token-decay kernels (which handle a short last tile) with one lambda per head.
-__global__ __launch_bounds__(256) void k_fill_logg(const float *__restrict__ decay, float *__restrict__ log_g, int H, int N) {
-    const int chain = blockIdx.y;
-    const float x = (float)log((double)decay[chain % H]);
-    for (int s = blockIdx.x * 256 + threadIdx.x; s < N; s += gridDim.x * 256) log_g[(size_t)chain * N + s] = x;
-}
-hipError_t launch_fill_logg(const Plan &p, const float *decay, float *log_g, hipStream_t stream) {
-    k_fill_logg<<<dim3((p.N + 255) / 256 < 64 ? (p.N + 255) / 256 : 64, p.B * p.H), dim3(256), 0, stream>>>(decay, log_g, p.H, p.N);
     return hipGetLastError();
 }
 
@@ -1608,11 +1349,7 @@ hipError_t static_scratch(void **ptr) {
     return hipSuccess;
 }
 
-int cache_stride_for(int dtype, int tile, int ntiles, bool token, bool mixed_dims) {
-    (void)token;       // both decay models have the pair kernel,
-    (void)mixed_dims;  // and so do key and value dimensions that differ
-    return (dtype == 1 && tile == 64 && ntiles % 2 == 0) ? 2 : 1;
-}
+int cache_stride_for(int dtype) { return dtype == 1 ? 2 : 1; }
 
 // Tokens per kernel tile: 32 for float data, 64 for bfloat16 data, whatever the
 // chunk (both divide every supported chunk length). 64-token bfloat16 tiles let two
