@@ -13,12 +13,18 @@
 
 namespace {
 
-// Segments per head when the caller leaves the choice to the library: enough
-// workgroups (B*H*segments) to fill a 256-CU device at the residency of the
-// walking kernel of each pass (forward: two 4-wave workgroups per CU; backward
-// on bfloat16: one 8-wave workgroup per CU), never more than one per tile.
-constexpr int kTargetWorkgroupsFwd = 512;
-constexpr int kTargetWorkgroupsBwd = 256;
+// Segments per head when the caller leaves the choice to the library: about as many workgroups (B*H*segments) as
+// the device has CUs, never more than one segment per tile. A second forward workgroup per CU (512) hides more
+// latency but doubles the segment states that go through memory: bf16 d=128 forward, 512 against 256 workgroups,
+// 16 heads x 32768 tokens 208 / 197 us, 32 x 4096 69 / 65, 256 x 4096 (two segments / one, no local pass) 345 / 285.
+// With a key or value dimension of 64 a state is a quarter or half of the bytes and a tile brings less to stream,
+// so 512 win: 16 x 32768 at d=64 87 / 107 us; d_k=64, d_v=128 norm step of 32 x 5504, two shards, 352 / 376.
+// The backward walk (bfloat16: one workgroup per CU) never takes more workgroups than CUs where it can: a few left
+// over are a whole second round (12 heads x 32768: 22 segments 348 us, 20 segments 235). The forward walk can share
+// a CU, so it takes the nearest count. Float tiles are half as long and their walks bound by latency: 512
+// workgroups in both passes.
+constexpr int kTargetWorkgroups = 256;
+constexpr int kTargetWorkgroupsLatencyBound = 512;
 enum Pass { kForward = 0, kBackward = 1 };
 
 bool valid_dims(const lasp_shape *s) {
@@ -49,9 +55,10 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     int want = s->segments;
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
     if (want == 0) {
-        int64_t chains = (int64_t)s->B * s->H;
-        const int target = (pass == kBackward && s->dtype == LASP_BF16) ? kTargetWorkgroupsBwd : kTargetWorkgroupsFwd;
-        want = (int)((target + chains - 1) / chains);
+        const int64_t chains = (int64_t)s->B * s->H;
+        const bool two_per_cu = s->dtype == LASP_F32 || (pass == kForward && (p->dk == 64 || p->dv == 64));
+        const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
+        want = (int)((target + (pass == kForward ? chains / 2 : 0)) / chains);
         if (want > p->ntiles) want = p->ntiles;
         if (want < 1) want = 1;
     }
@@ -60,13 +67,8 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     p->cache_stride = lasp::cache_stride_for(p->dtype);
     p->ragged = s->N % (p->tile * p->cache_stride) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
-    p->nseg_sized = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;
     if (p->cache_stride == 2) p->tiles_per_seg += p->tiles_per_seg & 1;   // segments start on cached tiles
     p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
-    // The size a caller is told does not follow every change of the plan: which shapes the fixed scratch of
-    // lasp_fwd_noalloc takes, and which buffers are refused, stays what it was. An odd tile count is sized for
-    // segments of single tiles.
-    if (p->cache_stride == 2 && p->ntiles % 2 == 0) p->nseg_sized = p->nseg;
     return LASP_OK;
 }
 
@@ -88,7 +90,7 @@ size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l) {
     lasp::Plan f, b;
     if (make_plan(shape, kForward, &f, token) != LASP_OK || make_plan(shape, kBackward, &b, token) != LASP_OK) return false;
-    const size_t nseg = f.nseg_sized > b.nseg_sized ? f.nseg_sized : b.nseg_sized;  // one buffer serves both passes
+    const size_t nseg = f.nseg > b.nseg ? f.nseg : b.nseg;  // one buffer serves both passes
     const size_t chains = (size_t)f.B * f.H;
     l->states = 0;
     l->seglog = round256(chains * nseg * f.dk * f.dv * sizeof(float));   // segment states, [d_k][d_v] floats each

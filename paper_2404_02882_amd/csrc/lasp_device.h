@@ -684,6 +684,52 @@ DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[D / 32], float *g, in
         for (int i = 0; i < 16; ++i) gstore<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo, st[ab][i]);
 }
 
+// Decay over whole segments, for carrying a state across them: one lambda per head (`full` tokens' worth for every
+// segment but the last, `last` for that), or with a decay per token 2^seglog[j], written by the local pass.
+template <bool TOKEN>
+struct SegDecay {
+    float full = 0.0f, last = 0.0f;
+    const float *seglog;
+    int nseg;
+    DEVI SegDecay(const float *decay, const float *seglog_all, int chain, int H, int nseg_, int seg_tokens, int ntok)
+        : seglog(TOKEN ? seglog_all + (size_t)chain * nseg_ : nullptr), nseg(nseg_) {
+        if constexpr (!TOKEN) {
+            const double l2 = log2((double)decay[chain % H]);
+            full = (float)exp2((double)seg_tokens * l2);
+            last = (float)exp2((double)(ntok - (nseg - 1) * seg_tokens) * l2);
+        }
+    }
+    DEVI float operator()(int j) const {
+        if constexpr (TOKEN) return exp2f(seglog[j]);
+        else return j == nseg - 1 ? last : full;
+    }
+};
+
+// The state segment `seg` starts from, in a walk's registers. Either k_scan has already put it into the segment's
+// slot of `states` (the chain's segment states), or (CARRY) the slots still hold the local states and the walk
+// carries the boundary state over the segments before its own itself, in the scan's order and arithmetic
+// (forward: segments 0 .. seg - 1, backward: nseg - 1 .. seg + 1): a few more reads, one launch less.
+// load(st, slot) loads a state in the orientation the wave keeps it in.
+template <bool BWD, bool TOKEN, int DB, typename Load>
+DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int seg,
+                      int nseg, int slot_elems, Load load) {
+    if (boundary) {
+        load(st, boundary);
+    } else {
+#pragma unroll
+        for (int ab = 0; ab < DB; ++ab) st[ab] = f32x16{0};
+    }
+    const int steps = BWD ? nseg - 1 - seg : seg;
+    for (int n = 0; n < steps; ++n) {
+        const int j = BWD ? nseg - 1 - n : n;
+        f32x16 local[DB];
+        load(local, states + (size_t)j * slot_elems);
+        const float f = factor(j);
+#pragma unroll
+        for (int ab = 0; ab < DB; ++ab) st[ab] = f * st[ab] + local[ab];
+    }
+}
+
 // Masked score tile (Alg. 2 / Alg. 3 mask M): the wave holds the transposed
 // 32x32 block ST[j][i] = sum_d A[j][d] B[i][d] in accumulator layout (row = key j,
 // column = query i), multiplies by lambda^(i-j) for i >= j (zero above the

@@ -23,7 +23,6 @@ struct Plan {
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
-    int nseg_sized;     // segments the reported scratch size provides for (>= nseg; see make_plan)
 };
 
 struct FwdArgs {

@@ -243,12 +243,7 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
     const int chain = blockIdx.y;
     const int e = (blockIdx.x * blockDim.x + threadIdx.x) * 4;  // four consecutive state elements per thread
     if (e >= DD) return;
-    float p_full = 0.0f, p_last = 0.0f;
-    if constexpr (!TOKEN) {
-        const double l2 = log2((double)decay[chain % H]);
-        p_full = (float)exp2((double)seg_tokens * l2);
-        p_last = (float)exp2((double)(ntok - (nseg - 1) * seg_tokens) * l2);
-    }
+    const SegDecay<TOKEN> seg_decay(decay, seglog, chain, H, nseg, seg_tokens, ntok);
     // The caller's state and the segment states share one layout, [d_k][d_v] (DD = d_k * d_v elements).
     f32x4 carry = {0, 0, 0, 0};
     if (boundary) carry = *(const f32x4 *)(boundary + (size_t)chain * DD + e);
@@ -262,8 +257,7 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
             const int n = n0 + u, j = BWD ? nseg - 1 - n : n;
             const bool has_local = n < nseg && (BWD ? (j > 0) : (j < nseg - 1));
             local[u] = has_local ? *(const f32x4 *)(s + (size_t)j * DD) : f32x4{0, 0, 0, 0};
-            if constexpr (TOKEN) factor[u] = has_local ? exp2f(seglog[(size_t)chain * nseg + j]) : 0.0f;
-            else factor[u] = j == nseg - 1 ? p_last : p_full;
+            factor[u] = !TOKEN || has_local ? seg_decay(j) : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -294,6 +288,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, const float *__restrict__ scratch,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
                                                 int H, int ntiles, int nseg, int tiles_per_seg, int cache_stride, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out = nullptr, float eps = 0.0f) {
     using E = Elem<T>;
@@ -324,7 +319,14 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2) ? 2 : 1) void k
     mk.template load_w<WK>(K + koff(t0), nvalid(t0));
     mv.template load_w<WV>(V + voff(t0), nvalid(t0));
     f32x16 st[DB];
-    state_load_w<D, WK, WV>(ln, st, scratch + ((size_t)chain * nseg + seg) * WK * WV, w);
+    {
+        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        auto load = [&](f32x16(&s)[DB], const float *g) { state_load_w<D, WK, WV>(ln, s, g, w); };
+        if (carry)
+            start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
+        else load(st, states + (size_t)seg * WK * WV);
+    }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
     typename TokenDecay<T, CT>::LogG lgreg = {};
@@ -459,6 +461,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
                                                 const float *__restrict__ decay, const T *__restrict__ cache,
                                                 T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
                                                 float *__restrict__ dkv_in, const float *__restrict__ scratch,
+                                                const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                 float *__restrict__ rtok,
                                                 int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
@@ -501,7 +504,14 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
     auto koff = [&](int t) { return tile_off(chain, ntok, t, CT, WK); };
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
     f32x16 dkv[DB];
-    state_load_w<D, WK, WV>(ln, dkv, scratch + ((size_t)chain * nseg + seg) * WK * WV, w);
+    {
+        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        auto load = [&](f32x16(&s)[DB], const float *g) { state_load_w<D, WK, WV>(ln, s, g, w); };
+        if (carry)
+            start_state<true>(dkv, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
+        else load(dkv, states + (size_t)seg * WK * WV);
+    }
 
     TileMover<T, CT, D, NT> ma, mb;
     ma.template load_w<WV>(V + voff(t1 - 1), nvalid(t1 - 1));
@@ -704,6 +714,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
                                                   T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
                                                   float *__restrict__ dkv_in, const float *__restrict__ scratch,
+                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                   float *__restrict__ rtok,
                                                   int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                   const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
@@ -811,9 +822,15 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
     f32x16 st[DB];
     {
-        const float *g = scratch + ((size_t)chain * nseg + seg) * WK * WV;
-        if (rg == 0) state_load_w<D, WK, WV>(ln, st, g, w);
-        else state_load_t_w<D, WK, WV>(ln, st, g, w);
+        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        auto load = [&](f32x16(&s)[DB], const float *g) {
+            if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
+            else state_load_t_w<D, WK, WV>(ln, s, g, w);
+        };
+        if (carry)
+            start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
+        else load(st, states + (size_t)seg * WK * WV);
     }
 
     // masked score tiles of the tile whose V, K are at pV, pK (dO, Q in sdO, sQ): one 32x32 block per wave
@@ -1248,6 +1265,13 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
                          scratch, seglog, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd);
 }
 
+// Whether the walk carries the boundary state over the segments before its own itself (start_state) instead of
+// a scan kernel filling every segment's slot. Each segment carried over costs the walk 1.3 - 1.8 us before its
+// first tile (a state's loads, one after the other), the scan 3 - 11 us and a launch. bf16 d=128 forward / backward:
+// 128 heads x 1024 tokens (2 segments) 63.9 / 88.2 -> 56.8 / 79.2 us, 64 x 8192 (4) 195.4 / 302.4 -> 188.0 / 301.9,
+// but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
+static bool walk_carries(const Plan &p) { return p.nseg <= 4; }
+
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const int chains = p.B * p.H, DD = WK * WV;   // states hold the real rows and columns only
@@ -1260,15 +1284,19 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
-    if (p.token)
-        k_scan<false, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
-    else
-        k_scan<false, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+    const bool carry = walk_carries(p);
+    if (!carry) {
+        if (p.token)
+            k_scan<false, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+        else
+            k_scan<false, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.kv_in, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+    }
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
     if (e = launch_kernel(walk, dim3(p.nseg, chains), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                           (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                          (const float *)a.scratch, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.cache_stride, p.N, p.kvdiv,
+                          (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
+                          p.tiles_per_seg, p.cache_stride, p.N, p.kvdiv,
                           a.rstd_out, a.eps);
         e != hipSuccess)
         return e;
@@ -1289,15 +1317,18 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
-    if (p.token)
-        k_scan<true, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
-    else
-        k_scan<true, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+    const bool carry = walk_carries(p);
+    if (!carry) {
+        if (p.token)
+            k_scan<true, true><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, nullptr, a.seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+        else
+            k_scan<true, false><<<scan_grid, dim3(256), 0, s>>>(a.scratch, a.dkv_out, a.decay, nullptr, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+    }
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     // The walking kernel: bfloat16 tiles of 64 tokens run in eight waves with one cached state per pair of
     // tiles, float data in four waves with one cached state per tile. Both take the same arguments.
     typedef void (*Walk)(const T *, const T *, const T *, const T *, const float *, const T *, T *, T *, T *, float *,
-                         const float *, float *, int, int, int, int, int, int, const T *, const float *);
+                         const float *, const float *, const float *, int, float *, int, int, int, int, int, int, const T *, const float *);
     Walk walk = nullptr;
     unsigned threads = D * 2;
     size_t lds = Smem<T, CT, D>::bwd;
@@ -1311,7 +1342,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     }
     if (e = launch_kernel(walk, dim3(p.nseg, chains), dim3(threads), lds, s, (const T *)a.q, (const T *)a.k, (const T *)a.v,
                           (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                          (const float *)a.scratch, a.rtok, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
+                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
                           (const T *)a.yn, a.rstd);
         e != hipSuccess)
         return e;
