@@ -9,7 +9,7 @@
 //   k_bidir_apply : Out = X S or X S^T for a d x d state held in registers,
 //       forward O = Q KV; backward dQ = dO KV^T, dK = V dKV^T, dV = K dKV (the
 //       three as one launch).
-// Wave tiling and MFMA shapes as in lasp_kernels.hip: wave w owns the 32-wide
+// Wave tiling and MFMA shapes as in lasp_walks.hip: wave w owns the 32-wide
 // column block w of the state and of every output tile.
 #include <hip/hip_runtime.h>
 

@@ -1,7 +1,7 @@
 // Device-side building blocks of the LASP kernels (gfx950 / CDNA4): MFMA operand
 // fragments and their LDS fetch patterns, tile movement, LDS layouts, the two
 // decay models, the Norm prologue and the small tile-level helpers the kernels
-// in lasp_kernels.hip are assembled from. Device code only; included once.
+// in lasp_walks.hip are assembled from. Device code only.
 #ifndef LASP_DEVICE_H
 #define LASP_DEVICE_H
 

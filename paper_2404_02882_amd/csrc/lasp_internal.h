@@ -1,5 +1,5 @@
 // Internal interface between the C-ABI host layer (lasp_api.cpp) and the HIP
-// kernels (lasp_kernels.hip). Not installed; the public boundary is include/lasp.h.
+// kernels (lasp_kernels.hip, lasp_walks.hip). Not installed; the public boundary is include/lasp.h.
 #ifndef LASP_INTERNAL_H
 #define LASP_INTERNAL_H
 
@@ -82,6 +82,21 @@ int tile_tokens(int dtype, int chunk, int D);
 // Cache stride for a data type: 2 for bfloat16 (one cached state per pair of tiles, the backward
 // walk reaches the other tile from its neighbour's state), else 1.
 int cache_stride_for(int dtype);
+
+// Over the segments of every head, in place in `states` ([chain][nseg][d_k][d_v]): local states -> start states.
+hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boundary, const float *decay, const float *seglog,
+                       hipStream_t s);
+hipError_t launch_dlg(const Plan &p, const BwdArgs &a, hipStream_t s);
+// out[K/V head] = sum of part[its query heads], rows of `width` elements
+hipError_t launch_group_sum(const Plan &p, const void *part, void *out, int width, hipStream_t s);
+
+// The passes for one data type and one (d_k, d_v), each in a translation unit of its own (lasp_walks.hip).
+#define LASP_PASSES(NAME)                                                                         \
+    hipError_t fwd_##NAME(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke); \
+    hipError_t bwd_##NAME(const Plan &p, const BwdArgs &a, hipStream_t s, const KernelEvents *ke);
+LASP_PASSES(f32_64) LASP_PASSES(f32_128) LASP_PASSES(f32_64_128) LASP_PASSES(f32_128_64)
+LASP_PASSES(bf16_64) LASP_PASSES(bf16_128) LASP_PASSES(bf16_64_128) LASP_PASSES(bf16_128_64)
+#undef LASP_PASSES
 
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t stream, const KernelEvents *ke);
 hipError_t launch_bwd(const Plan &p, const BwdArgs &a, hipStream_t stream, const KernelEvents *ke);
