@@ -496,12 +496,17 @@ struct FixedDecay {
     DEVI float after(int j, int n) const { return pw[n - 1 - j]; }
     DEVI float whole(int n) const { return pw[n]; }
     DEVI float masked(float x, int i, int j) const { return x * pw[i - j]; }
-    // FULL: n == CT, the lane's weights are one table entry times the uniform powers; otherwise the run of
-    // tokens may straddle the end of the tile and every element reads its own entry (one tile per sub-sequence).
+    // Whole tiles only (FULL): the lane's weights are one table entry times the uniform powers. Where the tile may
+    // end inside the lane's run of tokens they are read from a table of their own, which set_end() fills for a
+    // tile of n tokens (every thread calls it, between the same barriers as TokenDecay::fill).
+    DEVI float *after_tab() const { return const_cast<float *>(pw) - (CT - 1) + kTableFloats + 4 + 4 * CT; }
+    DEVI void set_end(int n) const {
+        if (threadIdx.x < CT) after_tab()[threadIdx.x] = pw[n - 1 - (int)threadIdx.x];
+    }
     template <bool FULL>
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks, int n) const {
+    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
         if constexpr (FULL) return lasp::weigh_after<T, CT>(ln, f, ks, pw, geo);
-        else return Elem<T>::scale(ln, f, ks * Elem<T>::KSTEP, [&](int k) { return pw[n - 1 - k]; });
+        else return Elem<T>::scale_tab(ln, f, after_tab(), ks * Elem<T>::KSTEP);
     }
     DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {
         return lasp::weigh_upto<T, CT>(ln, f, ks, pw, geo);
@@ -596,7 +601,7 @@ struct TokenDecay {
     // routine's range handling would cost four more instructions for every score element)
     DEVI float masked(float x, int i, int j) const { return i >= j ? x * __builtin_amdgcn_exp2f(cum[i] - cum[j]) : 0.0f; }
     template <bool FULL>
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks, int) const {
+    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
         return Elem<T>::scale_tab(ln, f, wa, ks * Elem<T>::KSTEP);
     }
     DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {
@@ -616,7 +621,8 @@ struct DecaySel<true, T, CT> {
 };
 
 // floats of LDS behind the tiles of every kernel: decay tables, and one row of
-// per-token partial sums per wave (backward walk with per-token decay)
+// per-token partial sums per wave (backward walk with per-token decay); the forward
+// walk's sums (Norm) take four rows, the next holds FixedDecay's after_tab
 template <int CT>
 constexpr int table_floats() { return 3 * CT + 4 + 8 * CT; }
 
