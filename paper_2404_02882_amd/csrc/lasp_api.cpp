@@ -21,8 +21,9 @@ namespace {
 // so 512 win: 16 x 32768 at d=64 87 / 107 us; d_k=64, d_v=128 norm step of 32 x 5504, two shards, 352 / 376.
 // The backward walk (bfloat16: one workgroup per CU) never takes more workgroups than CUs where it can: a few left
 // over are a whole second round (12 heads x 32768: 22 segments 348 us, 20 segments 235). The forward walk can share
-// a CU, so it takes the nearest count. Float tiles are half as long and their walks bound by latency: 512
-// workgroups in both passes.
+// a CU, so it takes the nearest count. Float walks are bound by vector and matrix instructions issued one after the
+// other, which a second workgroup per CU overlaps: 512 (16 x 8192 at d=128 forward 157 / 148 us), except the 8-wave
+// backward walk at d=128, of which one fits (per-token decay 386 / 409 us).
 constexpr int kTargetWorkgroups = 256;
 constexpr int kTargetWorkgroupsLatencyBound = 512;
 enum Pass { kForward = 0, kBackward = 1 };
@@ -56,7 +57,7 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
     if (want == 0) {
         const int64_t chains = (int64_t)s->B * s->H;
-        const bool two_per_cu = s->dtype == LASP_F32 || (pass == kForward && (p->dk == 64 || p->dv == 64));
+        const bool two_per_cu = s->dtype == LASP_F32 ? pass == kForward || p->D == 64 : pass == kForward && (p->dk == 64 || p->dv == 64);
         const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
         want = (int)((target + (pass == kForward ? chains / 2 : 0)) / chains);
         if (want > p->ntiles) want = p->ntiles;
@@ -245,15 +246,16 @@ int run_bwd_call(const BwdCall &c) {
     if (rc != LASP_OK) return rc;
 
     hipStream_t stream = (hipStream_t)c.stream;
-    if (rebuild) {   // the forward pass's own plan (its segment count), states only, into the scratch tail
-        lasp::Plan f;
-        if (rc = make_plan(c.shape, kForward, &f, c.token, false); rc != LASP_OK) return rc;
+    lasp::Plan f;   // the forward pass's own plan (its segment count)
+    if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm); rc != LASP_OK) return rc;
+    if (rebuild && p.dtype == LASP_BF16) {   // states only, into the scratch tail
         const lasp::FwdArgs fa{nullptr, c.k, c.v, c.kv_in, c.decay, nullptr, nullptr, (void *)cache, (float *)scr,
                                f.token ? (float *)(scr + l.seglog) : nullptr, nullptr, 0.0f, true};
         if (lasp::launch_fwd(f, fa, stream, nullptr) != hipSuccess) return LASP_ERR_HIP;
     }
+    if (rebuild && p.dtype == LASP_F32) cache = nullptr;   // (rebuilds its segment states itself, in the states' region)
     lasp::BwdArgs a{c.q, c.k, c.v, c.dout, c.dkv_out, c.decay, cache, c.dq, c.dk, c.dv, c.dkv_in, (float *)scr,
-                    c.kv_out, c.dlog_g, p.token ? (float *)(scr + l.seglog) : nullptr,
+                    &f, c.kv_in, c.kv_out, c.dlog_g, p.token ? (float *)(scr + l.seglog) : nullptr,
                     p.token ? (float *)(scr + l.rtok) : nullptr, c.yn, c.rstd, nullptr, nullptr};
     if (p.kvdiv > 1) {   // the kernels write dK, dV per query head; launch_bwd sums each group into the outputs
         a.dk_out = c.dk;

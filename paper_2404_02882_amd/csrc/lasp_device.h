@@ -55,6 +55,7 @@ DEVI void pipelined_flat(Load load, Use use) {
         const auto cur = ring[i % AHEAD];
         if (i + AHEAD < N) ring[i % AHEAD] = load(i + AHEAD);
         use(i, cur);
+        __builtin_amdgcn_sched_barrier(0);   // (without it every load of the run is hoisted to its start, and spills)
     }
 }
 template <typename F>
@@ -132,24 +133,11 @@ struct Elem<float> {
     static DEVI f32x16 mfma(frag a, frag b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
     static DEVI frag ld_kc(const Lane &ln, const float *X, int ld, int row0, int k0) { return X[(row0 + ln.r) * ld + k0 + ln.h]; }
     static DEVI frag ld_ks(const Lane &ln, const float *X, int ld, int k0, int col0) { return X[(k0 + ln.h) * ld + col0 + ln.r]; }
-    // ld_kc from global memory: uniform tile pointer, row block row0, contraction step k0
-    static DEVI frag ld_kc_g(const Lane &ln, const float *X, int ld, int row0, int k0) {
-        return gload<float>(X + k0, ((row0 + ln.r) * ld + ln.h) * sizeof(float));
-    }
     static DEVI frag ld_kp(const Lane &ln, const float *X, int ld, int row0, int kb, int m) {
         return X[(row0 + ln.r) * ld + kb + ln.acc_row(m)];
     }
     // accumulator tile -> fragment for sub-step m
     static DEVI frag from_acc(const f32x16 &t, int m) { return t[m]; }
-    // multiply each contraction element k of the fragment by w[k]
-    template <typename W>
-    static DEVI frag scale(const Lane &ln, frag f, int k0, W w) { return f * w(k0 + ln.h); }
-    // Elements per lane of one fragment, and the geometric form of a row weight:
-    // every contraction element e of the fragment is multiplied by a * g[e].
-    static constexpr int KH = 1;
-    static DEVI frag scale_geo(frag f, float a, const float (&g)[8]) { return f * (a * g[0]); }
-    // multiply contraction element k of the fragment of step k0 by tab[k] (tab in LDS)
-    static DEVI frag scale_tab(const Lane &ln, frag f, const float *tab, int k0) { return f * tab[k0 + ln.h]; }
     // store 4 values of consecutive columns
     static DEVI void st4(float *p, float a, float b, float c, float d) { *(f32x4 *)p = f32x4{a, b, c, d}; }
     static DEVI void st1(float *p, float a) { *p = a; }
@@ -174,9 +162,6 @@ struct Elem<bf16_t> {
             return *(const bf16x8 *)(X + (row0 + ln.r) * kSwzLd + (((k0 >> 3) ^ t) << 3));
         }
         return *(const bf16x8 *)(X + (row0 + ln.r) * ld + k0 + 8 * ln.h);
-    }
-    static DEVI frag ld_kc_g(const Lane &ln, const bf16_t *X, int ld, int row0, int k0) {
-        return gload<bf16x8>(X + k0, ((row0 + ln.r) * ld + 8 * ln.h) * sizeof(bf16_t));
     }
     // LDS only: two transposing reads (ds_read_b64_tr_b16). Within each group of
     // 16 lanes, lane i ends up with element (row e, column i) of the 4 x 16 block
@@ -223,13 +208,8 @@ struct Elem<bf16_t> {
         for (int e = 0; e < 8; ++e) x[e] = t[8 * m + e];
         return __builtin_convertvector(x, bf16x8);
     }
-    template <typename W>
-    static DEVI frag scale(const Lane &ln, frag f, int k0, W w) {
-        f32x8 x = __builtin_convertvector(f, f32x8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] *= w(k0 + 8 * ln.h + e);
-        return __builtin_convertvector(x, bf16x8);
-    }
+    // Elements per lane of one fragment, and the geometric form of a row weight:
+    // every contraction element e of the fragment is multiplied by a * g[e].
     static constexpr int KH = 8;
     static DEVI frag scale_geo(frag f, float a, const float (&g)[8]) {
         f32x8 x = __builtin_convertvector(f, f32x8);
@@ -237,6 +217,7 @@ struct Elem<bf16_t> {
         for (int e = 0; e < 8; ++e) x[e] *= a * g[e];
         return __builtin_convertvector(x, bf16x8);
     }
+    // multiply contraction element k of the fragment of step k0 by tab[k] (tab in LDS)
     static DEVI frag scale_tab(const Lane &ln, frag f, const float *tab, int k0) {
         const f32x4 *t = (const f32x4 *)(tab + k0 + 8 * ln.h);  // 16-byte aligned: tab is, k0 % 16 == 0
         const f32x4 lo = t[0], hi = t[1];
@@ -262,6 +243,131 @@ struct Elem<bf16_t> {
     }
     static DEVI void gst1(bf16_t *base, unsigned lane_bytes, float a) { gstore<__bf16>(base, lane_bytes, (__bf16)a); }
 };
+
+// ---------------------------------------------------------------------------
+// WalkElem: the operands of the causal kernels. bfloat16 data are their own. A float is kept as the sum of three
+// bfloat16, x = hi + mid + lo (8 significant bits each, exact down to the smallest exponents), and a product of two
+// takes six bfloat16 MFMAs with fp32 accumulation; the three terms left out (mid lo, lo mid, lo lo) are below
+// 2^-25 of the product. Six 32-cycle instructions replace eight of 64 cycles (v_mfma_f32_32x32x2_f32), and the
+// measured error against 64 bits is smaller: 3.2e-7 against 5.5e-7 at 16 heads x 8192 tokens, d=128, and smaller in
+// every one of the drawn float cases (the fp32 instruction rounds its accumulator after every two products). A
+// non-finite value splits into NaN, so where an infinity used to meet only finite terms the result is NaN.
+// LDS tiles of float data are three planes of kPlaneRows rows, one per part: split once where a tile is stored,
+// not by every wave that reads it.
+// ---------------------------------------------------------------------------
+constexpr int kPlaneRows = 32;   // tokens per tile of float data
+template <typename T>
+struct WalkElem;
+template <>
+struct WalkElem<float> {
+    typedef Elem<bf16_t> B;
+    struct frag {
+        bf16x8 p[3];   // hi, mid, lo
+    };
+    static constexpr int KSTEP = B::KSTEP, NSUB = B::NSUB, PAD = B::PAD, KH = B::KH, PLANES = 3;
+    // Parts of a pair of floats, one dword each: 3 conversions, 4 shifts / masks and 4 subtractions (left to element
+    // conversions the compiler converts every element twice).
+    static DEVI void split2(float x0, float x1, unsigned (&s)[3]) {
+        typedef __attribute__((ext_vector_type(2))) float f32x2;
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            s[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
+            if (i < 2) {
+                x0 -= __uint_as_float(s[i] << 16);
+                x1 -= __uint_as_float(s[i] & 0xffff0000u);
+            }
+        }
+    }
+    static DEVI frag split(const f32x8 &x) {
+        u32x4 d[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            unsigned s[3];
+            split2(x[2 * e], x[2 * e + 1], s);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) d[i][e] = s[i];
+        }
+        return {{__builtin_bit_cast(bf16x8, d[0]), __builtin_bit_cast(bf16x8, d[1]), __builtin_bit_cast(bf16x8, d[2])}};
+    }
+    static DEVI f32x8 join(const frag &s) {
+        f32x8 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            auto part = [&](int i) { return __builtin_bit_cast(u32x4, s.p[i])[e]; };
+            x[2 * e] = __uint_as_float(part(0) << 16) + (__uint_as_float(part(1) << 16) + __uint_as_float(part(2) << 16));
+            x[2 * e + 1] = __uint_as_float(part(0) & 0xffff0000u) +
+                           (__uint_as_float(part(1) & 0xffff0000u) + __uint_as_float(part(2) & 0xffff0000u));
+        }
+        return x;
+    }
+    // a b + c, smallest terms first
+    static DEVI f32x16 mfma(const frag &a, const frag &b, f32x16 c) {
+        return B::mfma(a.p[0], b.p[0], mfma_low(a, b, c));
+    }
+    // the five small terms alone
+    static DEVI f32x16 mfma_low(const frag &a, const frag &b, f32x16 c) {
+        c = B::mfma(a.p[0], b.p[2], c);
+        c = B::mfma(a.p[2], b.p[0], c);
+        c = B::mfma(a.p[1], b.p[1], c);
+        c = B::mfma(a.p[0], b.p[1], c);
+        return B::mfma(a.p[1], b.p[0], c);
+    }
+    static DEVI f32x16 mfma_high(const frag &a, const frag &b, f32x16 c) { return B::mfma(a.p[0], b.p[0], c); }
+    static DEVI frag ld_kc(const Lane &ln, const bf16_t *X, int ld, int row0, int k0) {
+        const int ps = kPlaneRows * ld;
+        return {{B::ld_kc(ln, X, ld, row0, k0), B::ld_kc(ln, X + ps, ld, row0, k0), B::ld_kc(ln, X + 2 * ps, ld, row0, k0)}};
+    }
+    static DEVI frag ld_ks(const Lane &ln, const bf16_t *X, int ld, int k0, int col0) {
+        const int ps = kPlaneRows * ld;
+        return {{B::ld_ks(ln, X, ld, k0, col0), B::ld_ks(ln, X + ps, ld, k0, col0), B::ld_ks(ln, X + 2 * ps, ld, k0, col0)}};
+    }
+    static DEVI frag ld_kp(const Lane &ln, const bf16_t *X, int ld, int row0, int kb, int m) {
+        const int ps = kPlaneRows * ld;
+        return {{B::ld_kp(ln, X, ld, row0, kb, m), B::ld_kp(ln, X + ps, ld, row0, kb, m), B::ld_kp(ln, X + 2 * ps, ld, row0, kb, m)}};
+    }
+    static DEVI frag from_acc(const f32x16 &t, int m) {
+        f32x8 x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = t[8 * m + e];
+        return split(x);
+    }
+    static DEVI frag scale_geo(const frag &f, float a, const float (&g)[8]) {
+        f32x8 x = join(f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] *= a * g[e];
+        return split(x);
+    }
+    static DEVI frag scale_tab(const Lane &ln, const frag &f, const float *tab, int k0) {
+        const f32x4 *w = (const f32x4 *)(tab + k0 + 8 * ln.h);
+        return split(join(f) * __builtin_shufflevector(w[0], w[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    // four values of consecutive columns of the row at p, in a tile of row stride ld
+    static DEVI void st4(bf16_t *p, int ld, const f32x4 &x) {
+        unsigned a[3], b[3];
+        split2(x[0], x[1], a);
+        split2(x[2], x[3], b);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) *(u32x2 *)(p + i * kPlaneRows * ld) = u32x2{a[i], b[i]};
+    }
+    static DEVI f32x4 ld4(const bf16_t *p, int ld) {
+        auto part = [&](int i) { return __builtin_convertvector(*(const bf16x4 *)(p + i * kPlaneRows * ld), f32x4); };
+        return part(0) + (part(1) + part(2));
+    }
+};
+template <>
+struct WalkElem<bf16_t> : Elem<bf16_t> {
+    static constexpr int PLANES = 1;
+    using Elem<bf16_t>::st4;
+    static DEVI void st4(bf16_t *p, int, const f32x4 &x) { *(bf16x4 *)p = __builtin_convertvector(x, bf16x4); }
+    static DEVI f32x4 ld4(const bf16_t *p, int) { return __builtin_convertvector(*(const bf16x4 *)p, f32x4); }
+};
+// row stride of the causal kernels' LDS tiles, and the elements a tile takes
+// (float, D = 64: rows of 72 elements are free of conflicts too and let two workgroups of the walks share a CU)
+template <typename T, int D>
+constexpr int walk_ld() { return sizeof(T) == 4 && D == 64 ? 72 : tile_ld<bf16_t, D>(); }
+template <typename T>
+constexpr int walk_tile(int rows, int ld) { return WalkElem<T>::PLANES * rows * ld; }
 
 // ---------------------------------------------------------------------------
 // Tile movement: global -> registers -> LDS in 16-byte pieces. Splitting the
@@ -319,6 +425,23 @@ struct TileMover {
         const unsigned lo = lane_off(ld);
 #pragma unroll
         for (int i = 0; i < NV; ++i) *(u32x4 *)(s + i * (NT / VPR) * ld + lo) = r[i];
+    }
+    // float data into the three planes of WalkElem<float>; every row multiplied by weight(row)
+    template <typename S, typename = std::enable_if_t<std::is_same_v<S, bf16_t> && std::is_same_v<T, float>>>
+    DEVI void store(S *s, int ld) const {
+        store_weighted(s, ld, [](int) { return 1.0f; });
+    }
+    template <typename W>
+    DEVI void store_weighted(bf16_t *s, int ld, W weight) const {
+        static_assert(ROWS == kPlaneRows, "plane stride");
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int row = threadIdx.x / VPR + i * (NT / VPR), col = (threadIdx.x % VPR) * EPV;
+            f32x4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(r[i][e]) * weight(row);
+            WalkElem<float>::st4(s + lds_off(ld, row, col), ld, x);
+        }
     }
 };
 
@@ -439,20 +562,20 @@ struct GeoWeights {
         const float l2f = (float)log2((double)lam);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            after[e] = e < Elem<T>::KH ? uniform(exp2f((float)(Elem<T>::KH - 1 - e) * l2f)) : 1.0f;
-            upto[e] = e < Elem<T>::KH ? uniform(exp2f((float)e * l2f)) : 1.0f;
+            after[e] = e < WalkElem<T>::KH ? uniform(exp2f((float)(WalkElem<T>::KH - 1 - e) * l2f)) : 1.0f;
+            upto[e] = e < WalkElem<T>::KH ? uniform(exp2f((float)e * l2f)) : 1.0f;
         }
     }
 };
 template <typename T, int CT>
-DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks, const float *pw, const GeoWeights<T> &g) {
-    const int k_first = ks * Elem<T>::KSTEP + Elem<T>::KH * ln.h;
-    return Elem<T>::scale_geo(f, pw[CT - Elem<T>::KH - k_first], g.after);
+DEVI typename WalkElem<T>::frag weigh_after(const Lane &ln, typename WalkElem<T>::frag f, int ks, const float *pw, const GeoWeights<T> &g) {
+    const int k_first = ks * WalkElem<T>::KSTEP + WalkElem<T>::KH * ln.h;
+    return WalkElem<T>::scale_geo(f, pw[CT - WalkElem<T>::KH - k_first], g.after);
 }
 template <typename T, int CT>
-DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks, const float *pw, const GeoWeights<T> &g) {
-    const int k_first = ks * Elem<T>::KSTEP + Elem<T>::KH * ln.h;
-    return Elem<T>::scale_geo(f, pw[k_first + 1], g.upto);
+DEVI typename WalkElem<T>::frag weigh_upto(const Lane &ln, typename WalkElem<T>::frag f, int ks, const float *pw, const GeoWeights<T> &g) {
+    const int k_first = ks * WalkElem<T>::KSTEP + WalkElem<T>::KH * ln.h;
+    return WalkElem<T>::scale_geo(f, pw[k_first + 1], g.upto);
 }
 
 // lambda^n for n = 0..CT into LDS, evaluated in double so that the table adds
@@ -504,11 +627,11 @@ struct FixedDecay {
         if (threadIdx.x < CT) after_tab()[threadIdx.x] = pw[n - 1 - (int)threadIdx.x];
     }
     template <bool FULL>
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
+    DEVI typename WalkElem<T>::frag weigh_after(const Lane &ln, typename WalkElem<T>::frag f, int ks) const {
         if constexpr (FULL) return lasp::weigh_after<T, CT>(ln, f, ks, pw, geo);
-        else return Elem<T>::scale_tab(ln, f, after_tab(), ks * Elem<T>::KSTEP);
+        else return WalkElem<T>::scale_tab(ln, f, after_tab(), ks * WalkElem<T>::KSTEP);
     }
-    DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {
+    DEVI typename WalkElem<T>::frag weigh_upto(const Lane &ln, typename WalkElem<T>::frag f, int ks) const {
         return lasp::weigh_upto<T, CT>(ln, f, ks, pw, geo);
     }
 };
@@ -601,11 +724,11 @@ struct TokenDecay {
     // routine's range handling would cost four more instructions for every score element)
     DEVI float masked(float x, int i, int j) const { return i >= j ? x * __builtin_amdgcn_exp2f(cum[i] - cum[j]) : 0.0f; }
     template <bool FULL>
-    DEVI typename Elem<T>::frag weigh_after(const Lane &ln, typename Elem<T>::frag f, int ks) const {
-        return Elem<T>::scale_tab(ln, f, wa, ks * Elem<T>::KSTEP);
+    DEVI typename WalkElem<T>::frag weigh_after(const Lane &ln, typename WalkElem<T>::frag f, int ks) const {
+        return WalkElem<T>::scale_tab(ln, f, wa, ks * WalkElem<T>::KSTEP);
     }
-    DEVI typename Elem<T>::frag weigh_upto(const Lane &ln, typename Elem<T>::frag f, int ks) const {
-        return Elem<T>::scale_tab(ln, f, wu, ks * Elem<T>::KSTEP);
+    DEVI typename WalkElem<T>::frag weigh_upto(const Lane &ln, typename WalkElem<T>::frag f, int ks) const {
+        return WalkElem<T>::scale_tab(ln, f, wu, ks * WalkElem<T>::KSTEP);
     }
 };
 template <bool TOKEN, typename T, int CT>
@@ -630,21 +753,14 @@ constexpr int table_floats() { return 3 * CT + 4 + 8 * CT; }
 // lane's token (accT: a transposed output tile in accumulator layout, X: the LDS tile
 // with token rows starting at row0). Both half-waves end up with the full sum.
 template <typename T>
-DEVI float rowdot(const Lane &ln, const f32x16 &acc, const T *sX, int ld, int row0, int w) {
+DEVI float rowdot(const Lane &ln, const f32x16 &acc, const bf16_t *sX, int ld, int row0, int w) {
     float s = 0.0f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         // the lane's four features of this register group are consecutive in the row (inside one 16-byte chunk)
-        const T *p = sX + lds_off(ld, row0 + ln.r, 32 * w + 8 * q + 4 * ln.h);
-        if constexpr (sizeof(T) == 2) {
-            const f32x4 x = __builtin_convertvector(*(const bf16x4 *)p, f32x4);
+        const f32x4 x = WalkElem<T>::ld4(sX + lds_off(ld, row0 + ln.r, 32 * w + 8 * q + 4 * ln.h), ld);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s += acc[4 * q + e] * x[e];
-        } else {
-            const f32x4 x = *(const f32x4 *)p;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s += acc[4 * q + e] * x[e];
-        }
+        for (int e = 0; e < 4; ++e) s += acc[4 * q + e] * x[e];
     }
     return add_other_half(s);
 }
@@ -736,13 +852,27 @@ DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *bounda
     }
 }
 
+// Float data: st[blk] = decay st[blk] + sum over a tile's tokens of A[token][32 blk + .] b[token][.], with A in LDS and
+// b (both contraction steps) in registers. The tile's sum is built from zero, so the running state is rounded once
+// a tile and the addition rides on the multiplication.
+template <typename E, int DB, int NKS>
+DEVI void decay_and_add(const Lane &ln, f32x16 (&st)[DB], float decay, const bf16_t *sA, int ld, const typename E::frag (&b)[NKS]) {
+    f32x16 sum;
+    pipelined_flat<DB * NKS, 1>([&](int i) { return E::ld_ks(ln, sA, ld, (i % NKS) * E::KSTEP, 32 * (i / NKS)); },
+                                [&](int i, const typename E::frag &a) {
+                                    if (i % NKS == 0) sum = f32x16{0};
+                                    sum = E::mfma(a, b[i % NKS], sum);
+                                    if (i % NKS == NKS - 1) st[i / NKS] = decay * st[i / NKS] + sum;
+                                });
+}
+
 // Masked score tile (Alg. 2 / Alg. 3 mask M): the wave holds the transposed
 // 32x32 block ST[j][i] = sum_d A[j][d] B[i][d] in accumulator layout (row = key j,
 // column = query i), multiplies by lambda^(i-j) for i >= j (zero above the
 // diagonal) and writes it as P[i][j] so that four consecutive keys land in one
 // store.
 template <typename T, int LDP, typename DK>
-DEVI void store_masked_scores(const Lane &ln, T *sP, const f32x16 &acc, int jb, int ib, const DK &dec) {
+DEVI void store_masked_scores(const Lane &ln, bf16_t *sP, const f32x16 &acc, int jb, int ib, const DK &dec) {
     const int iq = 32 * ib + ln.r;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -750,7 +880,7 @@ DEVI void store_masked_scores(const Lane &ln, T *sP, const f32x16 &acc, int jb, 
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = dec.masked(acc[4 * g + e], iq, j0 + e);
-        Elem<T>::st4(sP + iq * LDP + j0, x[0], x[1], x[2], x[3]);
+        WalkElem<T>::st4(sP + iq * LDP + j0, LDP, f32x4{x[0], x[1], x[2], x[3]});
     }
 }
 
@@ -758,8 +888,8 @@ DEVI void store_masked_scores(const Lane &ln, T *sP, const f32x16 &acc, int jb, 
 // contraction index contiguous), for every lower-triangular block assigned to
 // this wave; result masked and stored to sP.
 template <typename T, int CT, int D, int LDD, int LDP, typename DK>
-DEVI void masked_scores(const Lane &ln, T *sP, const T *sA, const T *sB, const DK &dec, int w) {
-    using E = Elem<T>;
+DEVI void masked_scores(const Lane &ln, bf16_t *sP, const bf16_t *sA, const bf16_t *sB, const DK &dec, int w) {
+    using E = WalkElem<T>;
     constexpr int NB = CT / 32, NW = D / 32;
     int idx = 0;
 #pragma unroll
@@ -768,9 +898,17 @@ DEVI void masked_scores(const Lane &ln, T *sP, const T *sA, const T *sB, const D
         for (int jb = 0; jb <= ib; ++jb, ++idx) {
             if (idx % NW != w) continue;
             f32x16 acc = {0};
+            if constexpr (E::PLANES == 3) {
+                pipelined_flat<D / E::KSTEP, 1>(
+                    [&](int k) {
+                        return FragPair<typename E::frag>{E::ld_kc(ln, sA, LDD, 32 * jb, k * E::KSTEP), E::ld_kc(ln, sB, LDD, 32 * ib, k * E::KSTEP)};
+                    },
+                    [&](int, const FragPair<typename E::frag> &f) { acc = E::mfma(f.a, f.b, acc); });
+            } else {
 #pragma unroll
-            for (int k0 = 0; k0 < D; k0 += E::KSTEP)
-                acc = E::mfma(E::ld_kc(ln, sA, LDD, 32 * jb, k0), E::ld_kc(ln, sB, LDD, 32 * ib, k0), acc);
+                for (int k0 = 0; k0 < D; k0 += E::KSTEP)
+                    acc = E::mfma(E::ld_kc(ln, sA, LDD, 32 * jb, k0), E::ld_kc(ln, sB, LDD, 32 * ib, k0), acc);
+            }
             store_masked_scores<T, LDP>(ln, sP, acc, jb, ib, dec);
         }
 }
@@ -849,52 +987,42 @@ DEVI void store_out_tile_t(const Lane &ln, T *g, const f32x16 &acc, int row0, in
 }
 
 // Store a wave's column block of the state into the cache tile g ([a][c], [WK][WV] real rows and columns,
-// row stride WV). Accumulator layout gives each lane four consecutive a for one c,
-// the wrong way round for wide stores, so for bfloat16 the wave transposes one
+// row stride WV), for bfloat16 data. Accumulator layout gives each lane four consecutive a for one c,
+// the wrong way round for wide stores, so the wave transposes one
 // 32x32 block at a time through a private slice of an idle LDS buffer (written
 // [c][a], read back with transposing reads) and stores 16 bytes per lane:
-// 64-byte row segments instead of single elements. Other types store element
-// by element. The LDS slice is only touched by this wave (LDS operations of one
+// 64-byte row segments instead of single elements. The LDS slice is only touched by this wave (LDS operations of one
 // wave execute in order); the caller's next barrier orders it against later use.
 // Waves whose column block is padding (32 w >= WV) and row blocks of padding (ab >= WK / 32) store nothing.
-template <typename T, int CT, int D, int WK = D, int WV = D>
-DEVI void cache_store(const Lane &ln, T *g, const f32x16 (&st)[D / 32], T *idle_lds, int w) {
-    using E = Elem<T>;
+template <int D, int WK = D, int WV = D>
+DEVI void cache_store(const Lane &ln, bf16_t *g, const f32x16 (&st)[D / 32], bf16_t *idle_lds, int w) {
+    using E = Elem<bf16_t>;
     constexpr int LDS_ROW = 36;  // 32 a + 4 pad elements: 8-byte aligned rows, staggered banks
-    constexpr bool STAGED = sizeof(T) == 2 && (D / 32) * 32 * LDS_ROW <= CT * (CT + E::PAD);
     if constexpr (WV < D) {
         if (32 * w >= WV) return;
     }
-    if constexpr (STAGED) {
-        T *R = idle_lds + w * 32 * LDS_ROW;
-        const int l = ln.id, bl = l >> 4, i = l & 15;
-        const unsigned glo = (i * WV + 32 * w + 8 * bl) * sizeof(T);
-        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    bf16_t *R = idle_lds + w * 32 * LDS_ROW;
+    const int l = ln.id, bl = l >> 4, i = l & 15;
+    const unsigned glo = (i * WV + 32 * w + 8 * bl) * sizeof(bf16_t);
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 #pragma unroll
-        for (int ab = 0; ab < WK / 32; ++ab) {
+    for (int ab = 0; ab < WK / 32; ++ab) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                E::st4(R + ln.r * LDS_ROW + 8 * q + 4 * ln.h, st[ab][4 * q], st[ab][4 * q + 1], st[ab][4 * q + 2],
-                       st[ab][4 * q + 3]);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+        for (int q = 0; q < 4; ++q)
+            E::st4(R + ln.r * LDS_ROW + 8 * q + 4 * ln.h, st[ab][4 * q], st[ab][4 * q + 1], st[ab][4 * q + 2],
+                   st[ab][4 * q + 3]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                const T *p = R + (8 * bl + (i >> 2)) * LDS_ROW + 16 * it + 4 * (i & 3);
-                union { struct { s16x4 a, b; } s; u32x4 v; } u;
-                u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
-                u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * LDS_ROW));
-                gstore<u32x4>(g + (32 * ab + 16 * it) * WV, glo, u.v);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+        for (int it = 0; it < 2; ++it) {
+            const bf16_t *p = R + (8 * bl + (i >> 2)) * LDS_ROW + 16 * it + 4 * (i & 3);
+            union { struct { s16x4 a, b; } s; u32x4 v; } u;
+            u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+            u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * LDS_ROW));
+            gstore<u32x4>(g + (32 * ab + 16 * it) * WV, glo, u.v);
         }
-    } else {
-        const unsigned slo = (4 * ln.h * WV + 32 * w + ln.r) * sizeof(T);
-#pragma unroll
-        for (int ab = 0; ab < WK / 32; ++ab)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) E::gst1(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, slo, st[ab][i]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 

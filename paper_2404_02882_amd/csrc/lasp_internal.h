@@ -18,7 +18,8 @@ struct Plan {
     int ntiles;         // ceil(N / tile); only the last tile may be short
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
-    int cache_stride;   // the state cache holds the start state of every cache_stride-th tile (bfloat16: 2, float: 1)
+    int cache_stride;   // tiles per slot of the state cache: bfloat16 2 (walked in pairs); float 1 (of which only one
+                        // slot per segment is used)
     bool ragged;        // the last tile is short, or the last pair of tiles (cache_stride 2) has only one
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
@@ -47,6 +48,9 @@ struct BwdArgs {
     void *dq, *dk, *dv;
     float *dkv_in;
     float *scratch;
+    // float data only: the plan of the forward pass (its segments), and, when cache is null, the state it started from
+    const Plan *fwd;
+    const float *kv_in;
     // per-token decay only
     const float *kv_out;  // state the forward pass returned (needed when dkv_out is given)
     float *dlog_g;        // [B][H][N]

@@ -12,11 +12,12 @@
 //                local states into the state each segment starts from
 //                (KV_t = lambda^len KV_{t-1} + local, the state update of
 //                Sec. 3.2 taken over a whole segment).
-//   3. k_fwd / k_bwd8p, k_bwd : each segment walks its tiles with the
+//   3. k_fwd / k_bwd8p, k_bwdkv : each segment walks its tiles with the
 //                d x d state held in registers: intra-chunk left product,
 //                inter-chunk right product, state update (Alg. 2 / Alg. 3 per
 //                tile). Backward: k_bwd8p for bfloat16 (one cached state per
-//                pair of tiles), k_bwd for float.
+//                pair of tiles); float: dQ by k_fwd over dO, V, K, then k_bwdkv
+//                for dK and dV.
 // Every kernel is instantiated for a decay model (lasp_device.h): one lambda
 // per head, or a decay per token (general recurrent form of App. A.4), which
 // adds k_dlg for the gradient of the log decay; optionally with the output
@@ -32,8 +33,8 @@
 // MFMA accumulator layout can be fed back as the B operand of the next product
 // without leaving registers (the contraction index is permuted identically on
 // the A side). All products use 32x32 MFMA tiles: v_mfma_f32_32x32x16_bf16 for
-// bfloat16 data, v_mfma_f32_32x32x2_f32 for float data; accumulation and the
-// state are always fp32.
+// both data types, float data as three bfloat16 parts (WalkElem, lasp_device.h);
+// accumulation and the state are always fp32.
 #include <hip/hip_runtime.h>
 
 #include "lasp_internal.h"
@@ -76,12 +77,12 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                                                   int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn = nullptr,
                                                   const float *__restrict__ rstd = nullptr) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
-    using E = Elem<T>;
-    constexpr int NT = D * 2, LDD = tile_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP;
+    using E = WalkElem<T>;
+    constexpr int NT = D * 2, LDD = walk_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    T *sX = (T *)smem;
-    T *sY = sX + CT * LDD;
-    float *pw = (float *)(sY + CT * LDD);
+    bf16_t *sX = (bf16_t *)smem;
+    bf16_t *sY = sX + TILE;
+    float *pw = (float *)(sY + TILE);
 
     const int chain = blockIdx.y;
     const int seg = BWD ? blockIdx.x + 1 : blockIdx.x;
@@ -112,6 +113,20 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     f32x16 st[DB];
 #pragma unroll
     for (int ab = 0; ab < DB; ++ab) st[ab] = f32x16{0};
+    // Float data: the five small terms of every product are summed apart for the length of the segment.
+    f32x16 low[DB];
+    auto add_tile = [&](const typename E::frag(&y)[NKS]) __attribute__((always_inline)) {
+        if constexpr (E::PLANES == 3)
+            pipelined_flat<DB * NKS, 1>([&](int i) { return E::ld_ks(ln, sX, LDD, (i % NKS) * E::KSTEP, 32 * (i / NKS)); },
+                                        [&](int i, const typename E::frag &x) {
+                                            st[i / NKS] = E::mfma_high(x, y[i % NKS], st[i / NKS]);
+                                            low[i / NKS] = E::mfma_low(x, y[i % NKS], low[i / NKS]);
+                                        });
+    };
+    if constexpr (E::PLANES == 3) {
+#pragma unroll
+        for (int ab = 0; ab < DB; ++ab) low[ab] = f32x16{0};
+    }
 
     if constexpr (TOKEN) {
         // `decay` is log g, [chain][token]. The sum over the segment's tokens is taken walking AWAY from the
@@ -142,11 +157,19 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                 if constexpr (NORM) mn.load(yn + yoff(tn), rstd_c + (size_t)tn * CT, nvalid(tn));
                 lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)tn * CT, nvalid(tn));
             }
+            auto weigh = [&](const typename E::frag &f, int ks) { return BWD ? dec.weigh_upto(ln, f, ks) : dec.template weigh_after<true>(ln, f, ks); };
+            if constexpr (E::PLANES == 3) {
+                typename E::frag yd[NKS];
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) yd[ks] = weigh(E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w), ks);
+                add_tile(yd);
+                continue;
+            }
             struct Step {
                 typename E::frag y;
                 typename E::frag x[DB];
             };
-            pipelined<NKS>(
+            if constexpr (E::PLANES == 1) pipelined<NKS>(
                 [&](int ks) {
                     Step f;
                     f.y = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
@@ -155,7 +178,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                     return f;
                 },
                 [&](int ks, const Step &f) {
-                    const typename E::frag yd = BWD ? dec.weigh_upto(ln, f.y, ks) : dec.template weigh_after<true>(ln, f.y, ks);
+                    const typename E::frag yd = weigh(f.y, ks);
 #pragma unroll
                     for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(f.x[ab], yd, st[ab]);
                 });
@@ -172,7 +195,11 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
         ln = fresh_lane();
         if constexpr (NORM) mn.apply(my);
         mx.store(sX, LDD);
-        my.store(sY, LDD);
+        // Token weight relative to the whole segment, so the accumulators are never rescaled:
+        // forward lambda^(tokens after it in the segment), backward lambda^(its 1-based position).
+        const float tile_factor = exp2f((float)((ntl - 1 - n) * CT) * l2f);  // tiles between this one and the segment edge
+        if constexpr (E::PLANES == 3) my.store_weighted(sY, LDD, [&](int row) { return tile_factor * pw[BWD ? row + 1 : CT - 1 - row]; });
+        else my.store(sY, LDD);
         __syncthreads();
         if (n + 1 < ntl) {
             // (tiles of this loop are requested after the segment's last one: never the short one)
@@ -180,15 +207,17 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
             my.template load_w<WY>(Y + yoff(tile_of(n + 1)), CT);
             if constexpr (NORM) mn.load(yn + yoff(tile_of(n + 1)), rstd_c + (size_t)tile_of(n + 1) * CT);
         }
-        // Token weight relative to the whole segment, so the accumulators are never rescaled:
-        // forward lambda^(tokens after it in the segment), backward lambda^(its 1-based position).
-        // It factors as (tile factor) * (table entry of the lane's first element) * g[e].
-        const float tile_factor = exp2f((float)((ntl - 1 - n) * CT) * l2f);  // tiles between this one and the segment edge
+        // bfloat16: the weight factors as (tile factor) * (table entry of the lane's first element) * g[e].
         auto weight_of = [&](int ks) {
             const int k_first = ks * E::KSTEP + E::KH * ln.h;  // lane's first token of this fragment
             return tile_factor * (BWD ? pw[k_first + 1] : pw[CT - E::KH - k_first]);
         };
-        if constexpr (NKS * (1 + DB) * sizeof(typename E::frag) <= 80 * 4) {
+        if constexpr (E::PLANES == 3) {
+            typename E::frag y[NKS];   // already weighted
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) y[ks] = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
+            add_tile(y);
+        } else if constexpr (NKS * (1 + DB) * sizeof(typename E::frag) <= 80 * 4) {
             // small tiles: request every operand fragment at once (one exposed LDS latency per tile)
             typename E::frag yf[NKS], xf[NKS][DB];
 #pragma unroll
@@ -224,6 +253,10 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
         }
     }
     }
+    if constexpr (E::PLANES == 3) {
+#pragma unroll
+        for (int ab = 0; ab < DB; ++ab) st[ab] += low[ab];
+    }
     state_store_w<D, WX, WY>(ln, st, scratch + ((size_t)chain * nseg + seg) * WX * WY, w);
 }
 
@@ -235,8 +268,8 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 // The state KV_{t-1} each tile starts from is optionally written to the cache.
 // Everything that does not need P (Q KV, the state update, the cache store) runs
 // between the score phase and the barrier that publishes P, where the waves
-// without a score block used to wait; V has two LDS buffers, so the next tile's
-// stores need no barrier of their own: two a tile. With one workgroup per CU the
+// without a score block used to wait; V of the wave's columns stays in registers
+// across it, so the next tile's stores need no barrier of their own: two a tile. With one workgroup per CU the
 // walk is bound by this chain (one wave per SIMD): d=128, 16 heads x 1024 tokens in
 // one segment 70.8 -> 61.6 us; the step of 4 x 32 heads x 16384 1780 -> 1752 us.
 // ---------------------------------------------------------------------------
@@ -246,23 +279,38 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 // STATES: only the states are wanted (a backward pass that was given no state cache rebuilds it, Sec. 3.4's
 // recomputation instead of caching): Q is not read, no scores and no outputs are computed; K, V are
 // walked, every tile's entering state goes to the cache and the state is updated.
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, bool STATES = false>
-__global__ __launch_bounds__(D * 2, 2) void k_fwd(const T *__restrict__ Q, const T *__restrict__ K,
+// ROLE kDq (float data): the walk over dO, V, K instead of Q, K, V, which produces dQ,
+//     dQ_s = sum_{i<=s} lambda^(s-i) (do_s . v_i) k_i + lambda^s KV_in do_s,
+// the same sums with the state transposed, from the segment states the forward pass kept (WK, WV are then the
+// widths of V and K). NORM: dO is dY and becomes dO on its way to LDS (NormTile). With a decay per token the row
+// dots q.dq (q_rows: Q) go to rtok.
+enum Role { kOutputs, kStates, kDq };
+// LDS of the walk: row stride of the score tile (float: unpadded, so that two workgroups share a CU) and the
+// staging area of the cache stores.
+template <typename T, int CT>
+constexpr int fwd_ldp() { return sizeof(T) == 4 ? CT : CT + WalkElem<T>::PAD; }
+template <typename T, int D>
+constexpr int fwd_stage() { return sizeof(T) == 4 ? 0 : D * 36; }
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, Role ROLE = kOutputs>
+__global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq && (TOKEN || NORM)) ? 1 : 2) void k_fwd(const T *__restrict__ Q, const T *__restrict__ K,
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
-                                                int H, int ntiles, int nseg, int tiles_per_seg, int cache_stride, int ntok, int kvdiv,
-                                                float *__restrict__ rstd_out = nullptr, float eps = 0.0f) {
-    using E = Elem<T>;
-    constexpr int NT = D * 2, LDD = tile_ld<T, D>(), LDP = CT + E::PAD, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
-                  SPB = 32 / E::KSTEP;
+                                                int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
+                                                float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
+                                                const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok) {
+    using E = WalkElem<T>;
+    constexpr bool STATES = ROLE == kStates, DQ = ROLE == kDq;
+    constexpr int NT = D * 2, LDD = walk_ld<T, D>(), LDP = fwd_ldp<T, CT>(), DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
+                  SPB = 32 / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    T *sQ = (T *)smem;
-    T *sK = sQ + CT * LDD;
-    T *sV = sK + CT * LDD;
-    T *sP = sV + 2 * CT * LDD;   // two V buffers
-    float *pw = (float *)(sP + CT * LDP);
+    bf16_t *sQ = (bf16_t *)smem;
+    bf16_t *sK = sQ + TILE;
+    bf16_t *sV = sK + TILE;
+    bf16_t *sP = sV + TILE;
+    bf16_t *sStage = sP + walk_tile<T>(CT, LDP);   // cache stores, bfloat16
+    float *pw = (float *)(sStage + fwd_stage<T, D>());
 
     const int chain = blockIdx.y, seg = blockIdx.x;
     const int t0 = seg * tiles_per_seg;
@@ -281,10 +329,16 @@ __global__ __launch_bounds__(D * 2, 2) void k_fwd(const T *__restrict__ Q, const
     if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t0), nvalid(t0));
     mk.template load_w<WK>(K + koff(t0), nvalid(t0));
     mv.template load_w<WV>(V + voff(t0), nvalid(t0));
+    NormTile<T, CT, D, NT, WK> mn;   // kDq only
+    const float *rstd_c = rstd + (size_t)chain * ntok;
+    if constexpr (DQ && NORM) mn.load(yn + koff(t0), rstd_c + (size_t)t0 * CT, nvalid(t0));
     f32x16 st[DB];
     {
         const float *states = scratch + (size_t)chain * nseg * WK * WV;
-        auto load = [&](f32x16(&s)[DB], const float *g) { state_load_w<D, WK, WV>(ln, s, g, w); };
+        auto load = [&](f32x16(&s)[DB], const float *g) {
+            if constexpr (DQ) state_load_t_w<D, WV, WK>(ln, s, g, w);   // stored [d_k][d_v] = [WV][WK]
+            else state_load_w<D, WK, WV>(ln, s, g, w);
+        };
         if (carry)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
                                SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
@@ -295,31 +349,38 @@ __global__ __launch_bounds__(D * 2, 2) void k_fwd(const T *__restrict__ Q, const
     typename TokenDecay<T, CT>::LogG lgreg = {};
     if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t0 * CT, nvalid(t0));
 
-    // The state tile `t` starts from goes to the cache as KV_{t-1}, rows a, columns c (staged through `idle`).
-    auto to_cache = [&](int t, T *idle) __attribute__((always_inline)) {
-        if (cache && t % cache_stride == 0)
-            cache_store<T, CT, D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + cache_stride - 1) / cache_stride) + t / cache_stride) * WK * WV, st, idle, w);
+    // State cache. bfloat16: the state every second tile `t` starts from, KV_{t-1}, rows a, columns c. Float: the state the segment starts from, all that the kDq walk needs.
+    auto to_cache = [&](int t) __attribute__((always_inline)) {
+        if constexpr (sizeof(T) == 2) {
+            if (cache && t % 2 == 0)
+                cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * WK * WV, st, sStage, w);
+        }
     };
-    to_cache(t0, sV + CT * LDD);
+    if constexpr (sizeof(T) == 4) {
+        if (cache) state_store_w<D, WK, WV>(ln, st, cache + ((size_t)chain * nseg + seg) * WK * WV, w);
+    }
+    to_cache(t0);
     if constexpr (RAGGED && !TOKEN) {
         __syncthreads();   // the power table
         dec.set_end(nvalid(t0));
     }
 
     for (int t = t0; t < t1; ++t) {
-        // Every wave is past the previous tile's second barrier, so Q, K, the tables and this V buffer are free;
-        // only the other V buffer and P may still be read.
+        // bfloat16: every wave is past the previous tile's second barrier, so Q, K, V and the tables are free; only P
+        // may still be read. Float: V may be, too (its fragments are three times as large, too many to keep).
+        if constexpr (E::PLANES == 3) __syncthreads();
         ln = fresh_lane();
-        T *sVt = sV + ((t - t0) & 1) * CT * LDD;
+        if constexpr (DQ && NORM) mn.apply(mq);
         if constexpr (!STATES) mq.store(sQ, LDD);
         mk.store(sK, LDD);
-        mv.store(sVt, LDD);
+        mv.store(sV, LDD);
         if constexpr (TOKEN) dec.fill(lgreg);
         else if constexpr (RAGGED) {
             if (t > t0 && nvalid(t) < CT) dec.set_end(nvalid(t));
         }
         __syncthreads();
         if (t + 1 < t1) {
+            if constexpr (DQ && NORM) mn.load(yn + koff(t + 1), rstd_c + (size_t)(t + 1) * CT, nvalid(t + 1));
             if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t + 1), nvalid(t + 1));
             mk.template load_w<WK>(K + koff(t + 1), nvalid(t + 1));
             mv.template load_w<WV>(V + voff(t + 1), nvalid(t + 1));
@@ -333,42 +394,86 @@ __global__ __launch_bounds__(D * 2, 2) void k_fwd(const T *__restrict__ Q, const
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) acc[ib] = f32x16{0};
             // inter: OT[c][i] = sum_a KV_{t-1}[a][c] Q[i][a], a taken in accumulator order
+            if constexpr (E::PLANES == 3) {
+                static_assert(NB == 1, "one 32-token block per tile");
+                pipelined_flat<DB * E::NSUB, 1>([&](int i) { return E::ld_kp(ln, sQ, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); },
+                                                [&](int i, const typename E::frag &f) {
+                                                    acc[0] = E::mfma(E::from_acc(st[i / E::NSUB], i % E::NSUB), f, acc[0]);
+                                                });
+            } else {
 #pragma unroll
-            for (int ab = 0; ab < DB; ++ab)
+                for (int ab = 0; ab < DB; ++ab)
 #pragma unroll
-                for (int m = 0; m < E::NSUB; ++m) {
-                    const typename E::frag sf = E::from_acc(st[ab], m);
+                    for (int m = 0; m < E::NSUB; ++m) {
+                        const typename E::frag sf = E::from_acc(st[ab], m);
 #pragma unroll
-                    for (int ib = 0; ib < NB; ++ib) acc[ib] = E::mfma(sf, E::ld_kp(ln, sQ, LDD, 32 * ib, 32 * ab, m), acc[ib]);
-                }
+                        for (int ib = 0; ib < NB; ++ib) acc[ib] = E::mfma(sf, E::ld_kp(ln, sQ, LDD, 32 * ib, 32 * ab, m), acc[ib]);
+                    }
+            }
             // Lambda: token r (1-based) carries lambda^r; the token is this lane's column
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) acc[ib] *= dec.upto(32 * ib + ln.r);
         }
-        // state update: KV <- lambda^CT KV + (diag{lambda^(CT-1-j)} K)^T V, weight applied to the V fragments
+        // V of this wave's columns, for the state update and, behind the barrier, for P V
         ln = fresh_lane();
+        typename E::frag vf[NKS];
+        auto load_vf = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) vf[ks] = E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w);
+        };
+        load_vf();
+        // state update: KV <- lambda^CT KV + (diag{lambda^(CT-1-j)} K)^T V, weight applied to the V fragments
         const float lamC = dec.whole(nvalid(t));
+        if constexpr (E::PLANES == 3) {
 #pragma unroll
-        for (int ab = 0; ab < DB; ++ab) st[ab] *= lamC;
+            for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<!RAGGED>(ln, vf[ks], ks);
+            decay_and_add<E>(ln, st, lamC, sK, LDD, vf);
+        } else {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const typename E::frag vd = dec.template weigh_after<!RAGGED>(ln, E::ld_ks(ln, sVt, LDD, ks * E::KSTEP, 32 * w), ks);
-#pragma unroll
-            for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * ab), vd, st[ab]);
-        }
-        if (t + 1 < t1) to_cache(t + 1, sV + ((t + 1 - t0) & 1) * CT * LDD);
-
-        __syncthreads();  // P visible; Q, K and the tables consumed
-        if constexpr (!STATES) {
-            ln = fresh_lane();
-            // intra: OT[c][i] += sum_{j<=i} V[j][c] P[i][j]
+            for (int ab = 0; ab < DB; ++ab) st[ab] *= lamC;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
-                const typename E::frag vf = E::ld_ks(ln, sVt, LDD, ks * E::KSTEP, 32 * w);
+                const typename E::frag vd = dec.template weigh_after<!RAGGED>(ln, vf[ks], ks);
 #pragma unroll
-                for (int ib = ks / SPB; ib < NB; ++ib) acc[ib] = E::mfma(vf, E::ld_kc(ln, sP, LDP, 32 * ib, ks * E::KSTEP), acc[ib]);
+                for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * ab), vd, st[ab]);
             }
-            if constexpr (NORM) {
+        }
+        if (t + 1 < t1) to_cache(t + 1);
+
+        __syncthreads();  // P visible; Q, K, V and the tables consumed
+        if constexpr (!STATES) {
+            ln = fresh_lane();
+            if constexpr (E::PLANES == 3) load_vf();
+            // intra: OT[c][i] += sum_{j<=i} V[j][c] P[i][j]
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                for (int ib = ks / SPB; ib < NB; ++ib) acc[ib] = E::mfma(vf[ks], E::ld_kc(ln, sP, LDP, 32 * ib, ks * E::KSTEP), acc[ib]);
+            if constexpr (DQ && TOKEN) {   // q.dq over this wave's 32 features, then over the waves
+                float *red = pw + 3 * CT + 4;
+#pragma unroll
+                for (int ib = 0; ib < NB; ++ib) {
+                    float s = 0.0f;
+                    if (32 * w < WV && 32 * ib + ln.r < nvalid(t)) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 x = gload<f32x4>(q_rows + voff(t) + 32 * ib * WV + 32 * w + 8 * q, (ln.r * WV + 4 * ln.h) * sizeof(T));
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) s += acc[ib][4 * q + e] * x[e];
+                        }
+                    }
+                    s = add_other_half(s);
+                    if (ln.h == 0) red[w * CT + 32 * ib + ln.r] = s;
+                }
+                __syncthreads();
+                if ((int)threadIdx.x < nvalid(t)) {
+                    float r = 0.0f;
+#pragma unroll
+                    for (int wv = 0; wv < D / 32; ++wv) r += red[wv * CT + threadIdx.x];
+                    rtok[(size_t)chain * ntok + (size_t)t * CT + threadIdx.x] = r;
+                }
+            }
+            if constexpr (NORM && !DQ) {
                 // sum of squares of a token's row: this wave's 32 features, then the other waves' through LDS
                 float *red = pw + 3 * CT + 4;
 #pragma unroll
@@ -400,242 +505,188 @@ __global__ __launch_bounds__(D * 2, 2) void k_fwd(const T *__restrict__ Q, const
 }
 
 // ---------------------------------------------------------------------------
-// k_bwd: one segment of one head, tiles descending (Alg. 3 per tile):
+// Backward walks, one segment of one head, tiles descending (Alg. 3 per tile):
 //   dSm = (dO V^T) (.) M,  Sm = (Q K^T) (.) M
 //   dQ  = dSm K + Lambda (dO KV_{t-1}^T)
 //   dK  = dSm^T Q + (lambda^CT Lambda^-1) (V dKV^T)
 //   dV  = Sm^T dO + (lambda^CT Lambda^-1) (K dKV)
 //   dKV <- lambda^CT dKV + (Lambda Q)^T dO
-// dKV is the state received from the right (gradient w.r.t. KV_t). The wave
-// keeps its column block dKV[:, c in w] in registers, which serves dV directly;
-// dK needs the transposed block, fetched once per tile through an LDS exchange.
-// LDS is time-shared: first {V, dO}, then {K, Q}.
+// dKV is the state received from the right (gradient w.r.t. KV_t).
+//
+// k_bwdkv (float data) produces dK, dV and the dKV update only; dQ, which needs no
+// dKV but the forward states, is a forward walk of its own (k_fwd, kDq) from one
+// kept state per segment. A float state per 32-token tile would be as many bytes as
+// Q, K, V and O together, written by the forward pass and read here (the cache this
+// replaces: 268 MB each way at 16 heads x 8192 tokens, d=128; that step 667 -> 439 us
+// with this, the operand split of WalkElem and 512 forward workgroups, of it backward
+// 488 -> 318). Both walks are bound by the split's vector instructions and the matrix
+// instructions, which a wave issues one after the other (1250 and 120 a tile).
+// Workgroups of 2 * D/32 waves. Two groups of waves keep dKV in registers in the
+// orientation their product needs, so nothing is exchanged:
+//   group 0 holds dKV[a][c in w] (rows a) and produces dV (dV_inter contracts a),
+//   group 1 holds dKV[a in w][c] (rows c) and produces dK (dK_inter contracts c);
+// under the exchange K<->V, Q<->dO, S<->dS the two are the same code. The products
+// that do not need the scores run before the barrier that publishes them, where the
+// waves without a score block would wait.
+// NORM: dO is dY, the gradient w.r.t. the normalised output `yn`; every dY tile is turned into dO on its
+// way to LDS (NormTile) from `yn` and `rstd` ([chain][token]).
+// WK, WV: elements per row of Q, K, dK and of V, dO, dV in memory (<= D; see k_local).
+// TOKEN: rtok holds q.dq on entry and q.dq - k.dk on exit.
 // ---------------------------------------------------------------------------
 template <typename T, int CT, int D>
-struct BwdSmem {
-    using E = Elem<T>;
-    static constexpr int LDD = tile_ld<T, D>(), LDP = CT + E::PAD;
-    static constexpr size_t IN_BYTES = 2 * (size_t)CT * LDD * sizeof(T);   // two input tiles
-    static constexpr size_t X_BYTES = (size_t)D * LDD * sizeof(T);         // exchange buffer
-    static constexpr bool OVERLAY = X_BYTES <= IN_BYTES;                    // exchange reuses the input tiles
-    static constexpr size_t P_OFF = IN_BYTES + (OVERLAY ? 0 : X_BYTES);
-    static constexpr size_t PW_OFF = P_OFF + 2 * (size_t)CT * LDP * sizeof(T);
+struct BwdkvSmem {
+    static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
+    static constexpr int TILE = walk_tile<T>(CT, LDD), PTILE = walk_tile<T>(CT, LDP);   // elements
+    static constexpr size_t PW_OFF = (4 * (size_t)TILE + 2 * PTILE) * sizeof(bf16_t);
     static constexpr size_t TOTAL = PW_OFF + table_floats<CT>() * sizeof(float);
 };
 
-// NORM: dO is dY, the gradient w.r.t. the normalised output `yn`; every dY tile is turned into dO on its
-// way to LDS (NormTile) from `yn` and `rstd` ([chain][token]).
-// WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
 template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D>
-__global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV == D) ? 2 : 1) void k_bwd(const T *__restrict__ Q, const T *__restrict__ K,
-                                                const T *__restrict__ V, const T *__restrict__ dO,
-                                                const float *__restrict__ decay, const T *__restrict__ cache,
-                                                T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
-                                                float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
-                                                float *__restrict__ rtok,
-                                                int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
-                                                const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
-    using E = Elem<T>;
-    using SM = BwdSmem<T, CT, D>;
-    constexpr int NT = D * 2, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
-                  NKD = D / E::KSTEP, SPB = 32 / E::KSTEP;
+__global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
+                                                 const T *__restrict__ dO, const float *__restrict__ decay, T *__restrict__ dK,
+                                                 T *__restrict__ dV, float *__restrict__ dkv_in, const float *__restrict__ scratch,
+                                                 const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
+                                                 float *__restrict__ rtok, int H, int ntiles, int nseg, int tiles_per_seg, int ntok,
+                                                 int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd) {
+    using E = WalkElem<T>;
+    using F = typename E::frag;
+    using SM = BwdkvSmem<T, CT, D>;
+    static_assert(CT == 32, "one 32-token block per tile");
+    constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NKS = CT / E::KSTEP;
+    constexpr int KB = WK / 32, VB = WV / 32;   // real 32-wide feature blocks of the key and value side
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    T *bufA = (T *)smem;
-    T *bufB = bufA + CT * LDD;
-    T *sX = SM::OVERLAY ? bufA : (T *)(smem + SM::IN_BYTES);
-    T *sS = (T *)(smem + SM::P_OFF);
-    T *sDS = sS + CT * LDP;
+    bf16_t *sV = (bf16_t *)smem;
+    bf16_t *sdO = sV + SM::TILE;
+    bf16_t *sK = sdO + SM::TILE;
+    bf16_t *sQ = sK + SM::TILE;
+    bf16_t *sS = sQ + SM::TILE;
+    bf16_t *sDS = sS + SM::PTILE;
     float *pw = (float *)(smem + SM::PW_OFF);
 
     const int chain = blockIdx.y, seg = blockIdx.x;
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
+    const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = w8 % NW;    // feature block of this wave's output
+    const int rg = w8 / NW;   // group: 0 produces dV, 1 produces dK
+    const bool own_block = rg ? w < KB : w < VB;   // (dimensions that differ: the block is not padding)
     Lane ln = fresh_lane();
-    const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
-    const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
-    typename TokenDecay<T, CT>::LogG lgreg = {};
-    // rows of tile `t` that exist: the last tile of a sub-sequence may be short
+    // rows of tile `t` that exist: only the first tile walked, the sub-sequence's last, may be short
     auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
-    if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t1 - 1) * CT, nvalid(t1 - 1));
-    // per-token decay: r_t = q_t.dq_t - k_t.dk_t, one partial row per wave, summed and written per tile
-    float *rs = pw + 3 * CT + 4;
-    auto flush_r = [&](int tile) {
-        if (threadIdx.x < CT) {
-            float r = 0.0f;
-#pragma unroll
-            for (int wv = 0; wv < D / 32; ++wv) r += rs[wv * CT + threadIdx.x];
-            if (!RAGGED || tile * CT + (int)threadIdx.x < ntok) rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] = r;
-        }
-    };
-
     K += kv_shift(chain, H, kvdiv, ntok, WK);   // K, V of this chain's K/V head
     V += kv_shift(chain, H, kvdiv, ntok, WV);
     auto koff = [&](int t) { return tile_off(chain, ntok, t, CT, WK); };
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
-    f32x16 dkv[DB];
-    {
-        const float *states = scratch + (size_t)chain * nseg * WK * WV;
-        auto load = [&](f32x16(&s)[DB], const float *g) { state_load_w<D, WK, WV>(ln, s, g, w); };
-        if (carry)
-            start_state<true>(dkv, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
-        else load(dkv, states + (size_t)seg * WK * WV);
-    }
 
-    TileMover<T, CT, D, NT> ma, mb;
-    ma.template load_w<WV>(V + voff(t1 - 1), nvalid(t1 - 1));
-    mb.template load_w<WV>(dO + voff(t1 - 1), nvalid(t1 - 1));
+    TileMover<T, CT, D, NT> mv, mo, mk, mq;
     NormTile<T, CT, D, NT, WV> mn;
     const float *rstd_c = rstd + (size_t)chain * ntok;
-    if constexpr (NORM) mn.load(yn + voff(t1 - 1), rstd_c + (size_t)(t1 - 1) * CT, nvalid(t1 - 1));
+    const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
+    typename TokenDecay<T, CT>::LogG lgreg = {};
+    auto request = [&](int t, int n) __attribute__((always_inline)) {
+        mv.template load_w<WV>(V + voff(t), n);
+        mo.template load_w<WV>(dO + voff(t), n);
+        mk.template load_w<WK>(K + koff(t), n);
+        mq.template load_w<WK>(Q + koff(t), n);
+        if constexpr (NORM) mn.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
+        if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
+    };
+    request(t1 - 1, nvalid(t1 - 1));
+    const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
+    float *rs = pw + 3 * CT + 4;   // one row of k.dk sums per wave of group 1
+    auto flush_r = [&](int tile) {
+        if ((int)threadIdx.x < nvalid(tile)) {
+            float r = 0.0f;
+#pragma unroll
+            for (int wv = 0; wv < NW; ++wv) r += rs[wv * CT + threadIdx.x];
+            rtok[(size_t)chain * ntok + (size_t)tile * CT + threadIdx.x] -= r;
+        }
+    };
+
+    const bf16_t *sX1 = rg ? sV : sK;     // inter operand: token rows, features contracted with the state
+    const bf16_t *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
+    const bf16_t *sUA = rg ? sdO : sQ;    // state-update A operand: [token][feature of the state rows]
+    const bf16_t *sPm = rg ? sDS : sS;    // masked score tile P[i][j] of this product
+
+    // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
+    f32x16 st[DB];
+    {
+        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        auto load = [&](f32x16(&s)[DB], const float *g) {
+            if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
+            else state_load_t_w<D, WK, WV>(ln, s, g, w);
+        };
+        if (carry)
+            start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
+        else load(st, states + (size_t)seg * WK * WV);
+    }
 
     for (int t = t1 - 1; t >= t0; --t) {
-        // ---- exchange: dKV^T fragments for dK_inter (B[k = c][n = a in w]) ----
+        __syncthreads();  // previous tile fully consumed
+        ln = fresh_lane();
+        if constexpr (NORM) mn.apply(mo);
+        mv.store(sV, LDD);
+        mo.store(sdO, LDD);
+        mk.store(sK, LDD);
+        mq.store(sQ, LDD);
+        if constexpr (TOKEN) dec.fill(lgreg);
         __syncthreads();
         ln = fresh_lane();
         if constexpr (TOKEN) {
             if (t < t1 - 1) flush_r(t + 1);
         }
-#pragma unroll
-        for (int ab = 0; ab < DB; ++ab)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                E::st4(sX + lds_off(LDD, 32 * w + ln.r, 32 * ab + 8 * g + 4 * ln.h), dkv[ab][4 * g], dkv[ab][4 * g + 1],
-                       dkv[ab][4 * g + 2], dkv[ab][4 * g + 3]);
-        __syncthreads();
-        typename E::frag xf[NKD];
-#pragma unroll
-        for (int ks = 0; ks < NKD; ++ks) xf[ks] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, 32 * w);
-        __syncthreads();
-
-        // ---- step 1: V (bufA), dO (bufB) ----
-        if constexpr (NORM) mn.apply(mb);
-        ma.store(bufA, LDD);
-        mb.store(bufB, LDD);
-        if constexpr (TOKEN) dec.fill(lgreg);
-        __syncthreads();
-        ma.template load_w<WK>(K + koff(t), nvalid(t));
-        mb.template load_w<WK>(Q + koff(t), nvalid(t));
-        if constexpr (TOKEN) {
-            if (t > t0) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t - 1) * CT);   // only the last tile can be short
-        }
-
-        masked_scores<T, CT, D, LDD, LDP>(ln, sDS, bufA, bufB, dec, w);  // dS^T = V dO^T
-
-        // All output tiles are accumulated transposed (feature x token), this wave's feature block.
-        f32x16 accQ[NB], accK[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) accQ[b] = accK[b] = f32x16{0};
-        // dQ_inter^T[a][i] = lambda^i sum_c KV_{t-1}[a][c] dO[i][c]; KV rows are read from the cache in place
-        {
-            const T *c = cache + ((size_t)chain * ntiles + t) * WK * WV;   // [WK][WV]: rows and columns of padding are not there
-#pragma unroll
-            for (int ks = 0; ks < NKD; ++ks) {
-                typename E::frag kvf = {};
-                if (32 * w < WK && ks * E::KSTEP < WV) kvf = E::ld_kc_g(ln, c, WV, 32 * w, ks * E::KSTEP);
-#pragma unroll
-                for (int ib = 0; ib < NB; ++ib) accQ[ib] = E::mfma(kvf, E::ld_kc(ln, bufB, LDD, 32 * ib, ks * E::KSTEP), accQ[ib]);
-            }
-#pragma unroll
-            for (int ib = 0; ib < NB; ++ib) accQ[ib] *= dec.upto(32 * ib + ln.r);
-        }
-        // dK_inter^T[a][j] = lambda^(CT-j) sum_c dKV[a][c] V[j][c]
-#pragma unroll
-        for (int ks = 0; ks < NKD; ++ks)
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) accK[jb] = E::mfma(xf[ks], E::ld_kc(ln, bufA, LDD, 32 * jb, ks * E::KSTEP), accK[jb]);
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb) accK[jb] *= dec.after(32 * jb + ln.r, nvalid(t));
-        // dO fragments of this wave's column block: [k = i][n = c in w]
-        typename E::frag dof[NKS];
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) dof[ks] = E::ld_ks(ln, bufB, LDD, ks * E::KSTEP, 32 * w);
-
-        // ---- step 2: K (bufA), Q (bufB) ----
-        __syncthreads();
+        if (t > t0) request(t - 1, CT);
+        // masked scores: one wave S^T = K Q^T, one on another SIMD dS^T = V dO^T
+        auto score = [&](const bf16_t *sA, const bf16_t *sB, bf16_t *dst, auto steps) __attribute__((always_inline)) {
+            f32x16 acc = {0};
+            pipelined_flat<decltype(steps)::value, 1>(
+                [&](int k) { return FragPair<F>{E::ld_kc(ln, sA, LDD, 0, k * E::KSTEP), E::ld_kc(ln, sB, LDD, 0, k * E::KSTEP)}; },
+                [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); });
+            store_masked_scores<T, LDP>(ln, dst, acc, 0, 0, dec);
+        };
+        if (w8 == 0) score(sK, sQ, sS, std::integral_constant<int, WK / E::KSTEP>{});
+        else if (w8 == NW + 1) score(sV, sdO, sDS, std::integral_constant<int, WV / E::KSTEP>{});
         ln = fresh_lane();
-        ma.store(bufA, LDD);
-        mb.store(bufB, LDD);
-        __syncthreads();
-        if (t > t0) {
-            ma.template load_w<WV>(V + voff(t - 1), CT);
-            mb.template load_w<WV>(dO + voff(t - 1), CT);
-            if constexpr (NORM) mn.load(yn + voff(t - 1), rstd_c + (size_t)(t - 1) * CT);
-        }
-        masked_scores<T, CT, D, LDD, LDP>(ln, sS, bufA, bufB, dec, w);  // S^T = K Q^T
-        __syncthreads();
 
-        // dQ^T[a][i] += sum_{j<=i} K[j][a] dSm[i][j]
+        const int nv = nvalid(t);
+        f32x16 acc = {0};   // dV^T[c in w][j] (group 0) or dK^T[a in w][j] (group 1)
+        F x2[NKS];
+        auto load_x2 = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const typename E::frag kf = E::ld_ks(ln, bufA, LDD, ks * E::KSTEP, 32 * w);
+            for (int ks = 0; ks < NKS; ++ks) x2[ks] = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
+        };
+        if (own_block) {
+            pipelined_flat<DB * E::NSUB, 1>([&](int i) { return E::ld_kp(ln, sX1, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); },
+                                            [&](int i, const F &f) { acc = E::mfma(E::from_acc(st[i / E::NSUB], i % E::NSUB), f, acc); });
+            acc *= dec.after(ln.r, nv);
+            load_x2();
+            // dKV <- lambda^CT dKV + (Lambda Q)^T dO, in this group's orientation
 #pragma unroll
-            for (int ib = ks / SPB; ib < NB; ++ib) accQ[ib] = E::mfma(kf, E::ld_kc(ln, sDS, LDP, 32 * ib, ks * E::KSTEP), accQ[ib]);
+            for (int ks = 0; ks < NKS; ++ks) x2[ks] = dec.weigh_upto(ln, x2[ks], ks);
+            decay_and_add<E>(ln, st, dec.whole(nv), sUA, LDD, x2);
         }
+        __syncthreads();  // scores visible
+        ln = fresh_lane();
+        if (own_block) {
+            load_x2();
 #pragma unroll
-        for (int ib = 0; ib < NB; ++ib) store_out_tile_t<T, D, WK>(ln, dQ + koff(t), accQ[ib], 32 * ib, w, nvalid(t));
-        float rpart[NB];
+            for (int ks = 0; ks < NKS; ++ks) acc = E::mfma(x2[ks], E::ld_ks(ln, sPm, LDP, ks * E::KSTEP, 0), acc);
+            if (rg) store_out_tile_t<T, D, WK>(ln, dK + koff(t), acc, 0, w, nv);
+            else store_out_tile_t<T, D, WV>(ln, dV + voff(t), acc, 0, w, nv);
+        }
         if constexpr (TOKEN) {
-#pragma unroll
-            for (int ib = 0; ib < NB; ++ib) rpart[ib] = rowdot<T>(ln, accQ[ib], bufB, LDD, 32 * ib, w);
-        }
-        // dK^T[a][j] += sum_{i>=j} Q[i][a] dSm[i][j]
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const typename E::frag qf = E::ld_ks(ln, bufB, LDD, ks * E::KSTEP, 32 * w);
-#pragma unroll
-            for (int jb = 0; jb <= ks / SPB; ++jb) accK[jb] = E::mfma(qf, E::ld_ks(ln, sDS, LDP, ks * E::KSTEP, 32 * jb), accK[jb]);
-        }
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb) store_out_tile_t<T, D, WK>(ln, dK + koff(t), accK[jb], 32 * jb, w, nvalid(t));
-        if constexpr (TOKEN) {
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                rpart[jb] -= rowdot<T>(ln, accK[jb], bufA, LDD, 32 * jb, w);
-                if (ln.h == 0) rs[w * CT + 32 * jb + ln.r] = rpart[jb];
+            if (rg == 1) {
+                const float s = own_block ? rowdot<T>(ln, acc, sK, LDD, 0, w) : 0.0f;
+                if (ln.h == 0) rs[w * CT + ln.r] = s;
             }
-        }
-        // dV^T[c][j] = lambda^(CT-j) sum_a dKV[a][c] K[j][a] + sum_{i>=j} dO[i][c] Sm[i][j]
-        {
-            f32x16 accV[NB];
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) accV[jb] = f32x16{0};
-#pragma unroll
-            for (int ab = 0; ab < DB; ++ab)
-#pragma unroll
-                for (int m = 0; m < E::NSUB; ++m) {
-                    const typename E::frag df = E::from_acc(dkv[ab], m);
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb) accV[jb] = E::mfma(df, E::ld_kp(ln, bufA, LDD, 32 * jb, 32 * ab, m), accV[jb]);
-                }
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) accV[jb] *= dec.after(32 * jb + ln.r, nvalid(t));
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-                for (int jb = 0; jb <= ks / SPB; ++jb)
-                    accV[jb] = E::mfma(dof[ks], E::ld_ks(ln, sS, LDP, ks * E::KSTEP, 32 * jb), accV[jb]);
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) store_out_tile_t<T, D, WV>(ln, dV + voff(t), accV[jb], 32 * jb, w, nvalid(t));
-        }
-        // dKV <- lambda^CT dKV + (Lambda Q)^T dO  (row weight lambda^(i+1) applied to the dO fragments)
-        const float lamC = dec.whole(nvalid(t));
-#pragma unroll
-        for (int ab = 0; ab < DB; ++ab) dkv[ab] *= lamC;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const typename E::frag dos = dec.weigh_upto(ln, dof[ks], ks);
-#pragma unroll
-            for (int ab = 0; ab < DB; ++ab) dkv[ab] = E::mfma(E::ld_ks(ln, bufB, LDD, ks * E::KSTEP, 32 * ab), dos, dkv[ab]);
         }
     }
     if constexpr (TOKEN) {
         __syncthreads();
         flush_r(t0);
     }
-    if (seg == 0) state_store_w<D, WK, WV>(ln, dkv, dkv_in + (size_t)chain * WK * WV, w);
+    if (seg == 0 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_in + (size_t)chain * WK * WV, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -669,7 +720,7 @@ __global__ __launch_bounds__(D * 2, (CT <= 64 && sizeof(T) == 2 && WK == D && WV
 // ---------------------------------------------------------------------------
 template <typename T, int CT, int D>
 struct Bwd8pSmem {
-    static constexpr int LDD = tile_ld<T, D>(), LDP = CT + Elem<T>::PAD;
+    static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
     static constexpr size_t TILE = (size_t)CT * LDD * sizeof(T);
     static constexpr size_t P_OFF = 6 * TILE;
     static constexpr size_t C_OFF = P_OFF + 3 * (size_t)CT * LDP * sizeof(T);   // S, dS and the cross tile dS(O x E)
@@ -689,7 +740,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   float *__restrict__ rtok,
                                                   int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                   const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
-    using E = Elem<T>;
+    using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = Bwd8pSmem<T, CT, D>;
     static_assert(CT == 64, "two 32-token blocks per tile");
@@ -1048,10 +1099,11 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
 // ---------------------------------------------------------------------------
 template <typename T, int CT, int D>
 struct Smem {
-    using E = Elem<T>;
-    static constexpr size_t local = 2 * (size_t)CT * tile_ld<T, D>() * sizeof(T) + table_floats<CT>() * sizeof(float);
-    static constexpr size_t fwd = (4 * (size_t)CT * tile_ld<T, D>() + (size_t)CT * (CT + E::PAD)) * sizeof(T) + table_floats<CT>() * sizeof(float);
-    static constexpr size_t bwd = BwdSmem<T, CT, D>::TOTAL;
+    static constexpr size_t tile = (size_t)walk_tile<T>(CT, walk_ld<T, D>()) * sizeof(bf16_t),
+                            scores = (size_t)(walk_tile<T>(CT, fwd_ldp<T, CT>()) + fwd_stage<T, D>()) * sizeof(bf16_t),
+                            tables = table_floats<CT>() * sizeof(float);
+    static constexpr size_t local = 2 * tile + tables;
+    static constexpr size_t fwd = 3 * tile + scores + tables;
 };
 
 // One launch of a kernel with `lds` bytes of dynamic LDS. Kernels that need more than the 64 KB default
@@ -1092,12 +1144,17 @@ struct FwdFam {
 template <typename T, int CT, int D, int WK, int WV>
 struct StatesFam {  // the forward walk reduced to the states (no Norm: the states do not depend on it)
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, true>;
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, kStates>;
 };
 template <typename T, int CT, int D, int WK, int WV>
-struct BwdFam {     // four waves, one cached state per tile (float data)
+struct DqFam {      // dQ as a forward walk over dO, V, K
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd<T, CT, D, TK, RG, NM, WK, WV>;
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WV, WK, kDq>;
+};
+template <typename T, int CT, int D, int WK, int WV>
+struct BwdkvFam {
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwdkv<T, CT, D, TK, RG, NM, WK, WV>;
 };
 template <typename T, int CT, int D, int WK, int WV>
 struct Bwd8pFam {   // eight waves, one cached state per pair of tiles
@@ -1131,40 +1188,70 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
 static bool walk_carries(const Plan &p) { return p.nseg <= 4; }
 
-template <typename T, int CT, int D, int WK = D, int WV = D>
-static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
-    const int chains = p.B * p.H;
-    hipError_t e;
-    if (ke) (void)hipEventRecord(ke->ev[0], s);
+// Local pass and scan of the forward states over K, V; `carry`: the scan is left to the walk.
+template <typename T, int CT, int D, int WK, int WV>
+static hipError_t run_states(const Plan &p, const void *k, const void *v, const float *kv_in, const float *decay, float *scratch,
+                             float *seglog, bool carry, hipStream_t s, const KernelEvents *ke) {
     if (p.nseg > 1) {
-        if (e = run_local<T, CT, D, false, WK, WV>(p, (const T *)a.k, (const T *)a.v, a.decay, a.scratch, a.seglog, nullptr, nullptr, s);
+        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, s);
             e != hipSuccess)
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
+    return carry ? hipSuccess : launch_scan(p, false, scratch, kv_in, decay, seglog, s);
+}
+
+template <typename T, int CT, int D, int WK = D, int WV = D>
+static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const bool carry = walk_carries(p);
-    if (!carry) {
-        if (e = launch_scan(p, false, a.scratch, a.kv_in, a.decay, a.seglog, s); e != hipSuccess) return e;
-    }
+    hipError_t e;
+    if (ke) (void)hipEventRecord(ke->ev[0], s);
+    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
-    const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
-    if (e = launch_kernel(walk, dim3(p.nseg, chains), dim3(D * 2), Smem<T, CT, D>::fwd, s,
+    auto walk = by_model<FwdFam<T, CT, D, WK, WV>>(p);
+    if constexpr (sizeof(T) == 2) {
+        if (a.states_only) walk = by_model<StatesFam<T, CT, D, WK, WV>>(p);
+    }
+    if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                           (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
                           (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
-                          p.tiles_per_seg, p.cache_stride, p.N, p.kvdiv,
-                          a.rstd_out, a.eps);
+                          p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
+                          (const T *)nullptr, (float *)nullptr);
         e != hipSuccess)
         return e;
     if (ke) (void)hipEventRecord(ke->ev[3], s);
     return hipGetLastError();
 }
 
+// dQ of float data: from the segment states the forward pass kept (a.cache), or, when it is given none, from the
+// states rebuilt into the scratch buffer, which the backward states overwrite afterwards.
+template <typename T, int CT, int D, int WK, int WV>
+static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
+    const Plan &f = *a.fwd;   // the forward pass's plan: its segments
+    const bool carry = !a.cache && walk_carries(f);
+    if (!a.cache) {
+        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, nullptr); e != hipSuccess)
+            return e;
+    }
+    return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
+                         (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
+                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry,
+                         f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
+                         (const T *)a.q, a.rtok);
+}
+
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const int chains = p.B * p.H;
+    const bool carry = walk_carries(p);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
+    if constexpr (sizeof(T) == 4) {
+        if (!a.cache) {
+            if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
+        }
+    }
     if (p.nseg > 1) {
         if (e = run_local<T, CT, D, true, WK, WV>(p, (const T *)a.q, (const T *)a.dout, a.decay, a.scratch, a.seglog, (const T *)a.yn,
                                           a.rstd, s);
@@ -1172,33 +1259,29 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
-    const bool carry = walk_carries(p);
     if (!carry) {
         if (e = launch_scan(p, true, a.scratch, a.dkv_out, a.decay, a.seglog, s); e != hipSuccess) return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[2], s);
-    // The walking kernel: bfloat16 tiles of 64 tokens run in eight waves with one cached state per pair of
-    // tiles, float data in four waves with one cached state per tile. Both take the same arguments.
-    typedef void (*Walk)(const T *, const T *, const T *, const T *, const float *, const T *, T *, T *, T *, float *,
-                         const float *, const float *, const float *, int, float *, int, int, int, int, int, int, const T *, const float *);
-    static_assert(Smem<T, CT, D>::bwd <= 163840, "LDS budget of one gfx950 CU exceeded");
-    Walk walk = nullptr;
-    unsigned threads = D * 2;
-    size_t lds = Smem<T, CT, D>::bwd;
+    // The walks: bfloat16 in one kernel with one cached state per pair of tiles; float dQ and dK, dV apart.
+    const dim3 grid(p.nseg, chains), block(D * 4);
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
-        walk = by_model<Bwd8pFam<T, CT, D, WK, WV>>(p);
-        threads = D * 4;
-        lds = Bwd8pSmem<T, CT, D>::TOTAL;
+        e = launch_kernel(by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block, Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                          (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
+                          (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H,
+                          p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd);
     } else {
-        walk = by_model<BwdFam<T, CT, D, WK, WV>>(p);
+        static_assert(BwdkvSmem<T, CT, D>::TOTAL <= 163840 / (D == 128 ? 1 : 2), "LDS of one gfx950 CU for the workgroups meant to share it");
+        if (a.cache) {
+            if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
+        }
+        e = launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                          (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
+                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H, p.ntiles, p.nseg,
+                          p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd);
     }
-    if (e = launch_kernel(walk, dim3(p.nseg, chains), dim3(threads), lds, s, (const T *)a.q, (const T *)a.k, (const T *)a.v,
-                          (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
-                          (const T *)a.yn, a.rstd);
-        e != hipSuccess)
-        return e;
+    if (e != hipSuccess) return e;
     if (p.kvdiv > 1) {
         if (e = launch_group_sum(p, a.dk, a.dk_out, p.dk, s); e != hipSuccess) return e;
         if (e = launch_group_sum(p, a.dv, a.dv_out, p.dv, s); e != hipSuccess) return e;
