@@ -167,8 +167,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:   # the raw handle: building a Stream object takes 2.7 us of a 9 us call
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
