@@ -189,7 +189,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     const float lam = decay[chain % H];
     fill_pow_table<CT>(pw, lam);
     const GeoWeights<T> geo(lam);
-    const float l2f = (float)log2((double)lam);
+    const double lamC = pow_n(lam, CT);
     for (int n = 0; n < ntl; ++n) {
         __syncthreads();  // previous tile fully consumed (and pw visible on the first pass)
         ln = fresh_lane();
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
         mx.store(sX, LDD);
         // Token weight relative to the whole segment, so the accumulators are never rescaled:
         // forward lambda^(tokens after it in the segment), backward lambda^(its 1-based position).
-        const float tile_factor = exp2f((float)((ntl - 1 - n) * CT) * l2f);  // tiles between this one and the segment edge
+        const float tile_factor = (float)pow_n(lamC, ntl - 1 - n);  // tiles between this one and the segment edge
         if constexpr (E::PLANES == 3) my.store_weighted(sY, LDD, [&](int row) { return tile_factor * pw[BWD ? row + 1 : CT - 1 - row]; });
         else my.store(sY, LDD);
         __syncthreads();
