@@ -57,9 +57,10 @@ typedef enum { LASP_F32 = 0, LASP_BF16 = 1 } lasp_dtype;
  * Problem shape of one call.
  *   N        tokens in this sub-sequence (the paper's per-rank length N/T), any
  *            positive number. When N is not a multiple of lasp_tile_tokens() the
- *            last tile is short; the per-token-decay kernels handle that, so
- *            lasp_fwd / lasp_bwd then run those with log g = log(lambda) filled in
- *            by the library (about 10 % slower, more scratch).
+ *            last tile is short, which every kernel takes (lasp_scratch_bytes()
+ *            is a little larger then). A forward call of at most 12 tokens that
+ *            keeps no state cache and does not normalise runs the token recurrence
+ *            in one kernel.
  *   chunk    the chunk length C of Alg. 2 / Alg. 3: 64, 128 or 256. It is checked
  *            and otherwise NOT USED: the kernels always walk the sub-sequence in
  *            tiles of lasp_tile_tokens() tokens, which divide every allowed chunk.
@@ -112,10 +113,10 @@ int32_t lasp_num_segments(const lasp_shape *shape);
 /*
  * Bytes of the state cache: the states KV_{t-1} that tiles start from, written
  * by lasp_fwd and read by lasp_bwd for dQ_inter (the paper caches the state a
- * rank receives, Alg. 2 "save KV_{t-1}", Sec. 3.4; this build caches one state
- * per tile, or one per two tiles where the backward kernel reaches the other
- * tile from its neighbour's state, so that the backward pass never reruns the
- * forward recurrence).
+ * rank receives, Alg. 2 "save KV_{t-1}", Sec. 3.4; for bfloat16 one state per two
+ * tiles is cached, since the backward kernel reaches the other tile from its
+ * neighbour's state; for float one per segment is used, from which the walk that
+ * produces dQ runs the recurrence again).
  * The layout is private to the library; slot 0 is kv_in. Stored in `dtype`.
  * 0 on an invalid shape.
  */
@@ -183,7 +184,7 @@ size_t lasp_noalloc_scratch_limit(void);
  *                to caching (Sec. 3.4, "KV state caching" on / off). The call then
  *                rebuilds the states first, from k, v and kv_in, with the forward
  *                kernels reduced to their states (Alg. 2 without the outputs),
- *                into the tail of `scratch`, which must then hold at least
+ *                into `scratch`, which must then hold at least
  *                lasp_bwd_recompute_scratch_bytes(). Nothing has to be kept between
  *                the forward and the backward pass but kv_in; the price is one more
  *                pass over k, v.
