@@ -781,12 +781,13 @@ DEVI float rowdot(const Lane &ln, const f32x16 &acc, const bf16_t *sX, int ld, i
 // hold only the real rows and columns; on chip the kernels work on the zero-padded [D][D] state in
 // accumulator layout, st[ab][i] = S[32 ab + ln.acc_row(i)][32 w + ln.r]. Nothing outside [WK][WV] is touched
 // in memory: padding is loaded as zero and never stored.
-template <int D, int WK = D, int WV = D>
-DEVI void state_load_w(const Lane &ln, f32x16 (&st)[D / 32], const float *g, int w) {
+// (a wave may hold fewer row blocks, BLK of them: g then points at the first of its rows)
+template <int D, int WK = D, int WV = D, int BLK = D / 32>
+DEVI void state_load_w(const Lane &ln, f32x16 (&st)[BLK], const float *g, int w) {
     const bool cols = 32 * w < WV;   // (wave-uniform) this wave's column block holds real columns
     const unsigned lo = (4 * ln.h * WV + 32 * w + ln.r) * sizeof(float);
 #pragma unroll
-    for (int ab = 0; ab < D / 32; ++ab)
+    for (int ab = 0; ab < BLK; ++ab)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             st[ab][i] = (ab < WK / 32 && cols) ? gload<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo) : 0.0f;
@@ -805,14 +806,14 @@ DEVI void state_load_t_w(const Lane &ln, f32x16 (&st)[D / 32], const float *g, i
             for (int e = 0; e < 4; ++e) st[cb][4 * q + e] = x[e];
         }
 }
-template <int D, int WK = D, int WV = D>
-DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[D / 32], float *g, int w) {
+template <int D, int WK = D, int WV = D, int BLK = D / 32>
+DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[BLK], float *g, int w) {
     if constexpr (WV < D) {
         if (32 * w >= WV) return;
     }
     const unsigned lo = (4 * ln.h * WV + 32 * w + ln.r) * sizeof(float);
 #pragma unroll
-    for (int ab = 0; ab < WK / 32; ++ab)
+    for (int ab = 0; ab < (BLK < WK / 32 ? BLK : WK / 32); ++ab)
 #pragma unroll
         for (int i = 0; i < 16; ++i) gstore<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo, st[ab][i]);
 }
@@ -897,10 +898,10 @@ DEVI void store_masked_scores(const Lane &ln, bf16_t *sP, const f32x16 &acc, int
 // ST[jb][ib] = A[jb] B[ib]^T over the feature dimension (both operands have the
 // contraction index contiguous), for every lower-triangular block assigned to
 // this wave; result masked and stored to sP.
-template <typename T, int CT, int D, int LDD, int LDP, typename DK>
+template <typename T, int CT, int D, int LDD, int LDP, int NW, typename DK>
 DEVI void masked_scores(const Lane &ln, bf16_t *sP, const bf16_t *sA, const bf16_t *sB, const DK &dec, int w) {
     using E = WalkElem<T>;
-    constexpr int NB = CT / 32, NW = D / 32;
+    constexpr int NB = CT / 32;
     int idx = 0;
 #pragma unroll
     for (int ib = 0; ib < NB; ++ib)
@@ -999,24 +1000,24 @@ DEVI void store_out_tile_t(const Lane &ln, T *g, const f32x16 &acc, int row0, in
 // Store a wave's column block of the state into the cache tile g ([a][c], [WK][WV] real rows and columns,
 // row stride WV), for bfloat16 data. Accumulator layout gives each lane four consecutive a for one c,
 // the wrong way round for wide stores, so the wave transposes one
-// 32x32 block at a time through a private slice of an idle LDS buffer (written
+// 32x32 block at a time through a private slice of LDS (`stage`; written
 // [c][a], read back with transposing reads) and stores 16 bytes per lane:
 // 64-byte row segments instead of single elements. The LDS slice is only touched by this wave (LDS operations of one
 // wave execute in order); the caller's next barrier orders it against later use.
 // Waves whose column block is padding (32 w >= WV) and row blocks of padding (ab >= WK / 32) store nothing.
-template <int D, int WK = D, int WV = D>
-DEVI void cache_store(const Lane &ln, bf16_t *g, const f32x16 (&st)[D / 32], bf16_t *idle_lds, int w) {
+template <int D, int WK = D, int WV = D, int BLK = D / 32>
+DEVI void cache_store(const Lane &ln, bf16_t *g, const f32x16 (&st)[BLK], bf16_t *stage, int w) {
     using E = Elem<bf16_t>;
     constexpr int LDS_ROW = 36;  // 32 a + 4 pad elements: 8-byte aligned rows, staggered banks
     if constexpr (WV < D) {
         if (32 * w >= WV) return;
     }
-    bf16_t *R = idle_lds + w * 32 * LDS_ROW;
+    bf16_t *R = stage;   // this wave's slice
     const int l = ln.id, bl = l >> 4, i = l & 15;
     const unsigned glo = (i * WV + 32 * w + 8 * bl) * sizeof(bf16_t);
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 #pragma unroll
-    for (int ab = 0; ab < WK / 32; ++ab) {
+    for (int ab = 0; ab < (BLK < WK / 32 ? BLK : WK / 32); ++ab) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             E::st4(R + ln.r * LDS_ROW + 8 * q + 4 * ln.h, st[ab][4 * q], st[ab][4 * q + 1], st[ab][4 * q + 2],

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     auto to_cache = [&](int t) __attribute__((always_inline)) {
         if constexpr (sizeof(T) == 2) {
             if (cache && t % 2 == 0)
-                cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * WK * WV, st, sStage, w);
+                cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * WK * WV, st, sStage + w * 32 * 36, w);
         }
     };
     if constexpr (sizeof(T) == 4) {
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         f32x16 acc[NB];
         if constexpr (!STATES) {
             // masked scores P (all waves share the lower-triangular blocks)
-            masked_scores<T, CT, D, LDD, LDP>(ln, sP, sK, sQ, dec, w);
+            masked_scores<T, CT, D, LDD, LDP, D / 32>(ln, sP, sK, sQ, dec, w);
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) acc[ib] = f32x16{0};
             // inter: OT[c][i] = sum_a KV_{t-1}[a][c] Q[i][a], a taken in accumulator order
@@ -502,6 +502,175 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         }
     }
     if (seg == nseg - 1 && kv_out) state_store_w<D, WK, WV>(ln, st, kv_out + (size_t)chain * WK * WV, w);
+}
+
+// ---------------------------------------------------------------------------
+// k_fwd8: k_fwd for bfloat16 at d = 128 in eight waves, one workgroup per CU. Two groups of four waves split the
+// state by rows (a) and the output tile by token block:
+//   group g holds KV[a in half g][c in w]: half the state update, half of Q KV for both token blocks;
+//   the half of Q KV that belongs to the other group's token block goes through LDS (32 KB a tile), after which
+//   group g finishes token block g: P V, Norm, store.
+// Per wave and tile 16 - 30 matrix instructions instead of 38 - 46, half of the conversions and stores, and a second
+// wave per SIMD to run while one waits. Bound by the traffic on whole tiles with one lambda per head (16 heads x 32768
+// tokens, whole forward 172.9 -> 171.8 us); where every value fragment is weighted from a table, by that work, which
+// the waves now share (ragged 179.1 -> 172.9, a decay per token 195.9 -> 180.2), as is Norm's (185.3 -> 179.5).
+// ---------------------------------------------------------------------------
+template <typename T, int CT, int D>
+struct Fwd8Smem {
+    static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
+    static constexpr size_t P_OFF = 3 * (size_t)CT * LDD * sizeof(T);
+    static constexpr size_t STAGE_OFF = P_OFF + (size_t)CT * LDP * sizeof(T);            // cache stores: 8 waves x 32 x 36
+    static constexpr size_t X_OFF = STAGE_OFF + 8 * 32 * 36 * sizeof(T);                 // exchange: 8 waves x 32 x 32 float
+    static constexpr size_t PW_OFF = X_OFF + 8 * 1024 * sizeof(float);
+    static constexpr size_t TOTAL = PW_OFF + table_floats<CT>() * sizeof(float);
+};
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, Role ROLE = kOutputs>
+__global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
+                                                const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
+                                                T *__restrict__ cache, const float *__restrict__ scratch,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
+                                                int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
+                                                float *__restrict__ rstd_out, float eps) {
+    using E = WalkElem<T>;
+    using F = typename E::frag;
+    using SM = Fwd8Smem<T, CT, D>;
+    static_assert(sizeof(T) == 2 && D == 128 && CT == 64, "two row halves, two token blocks");
+    constexpr bool STATES = ROLE == kStates;
+    constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, HB = D / 64, NB = CT / 32, NKS = CT / E::KSTEP, SPB = 32 / E::KSTEP;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    T *sQ = (T *)smem;
+    T *sK = sQ + CT * LDD;
+    T *sV = sK + CT * LDD;
+    T *sP = (T *)(smem + SM::P_OFF);
+    float *sX = (float *)(smem + SM::X_OFF);
+    float *pw = (float *)(smem + SM::PW_OFF);
+
+    const int chain = blockIdx.y, seg = blockIdx.x;
+    const int t0 = seg * tiles_per_seg;
+    const int t1 = min(t0 + tiles_per_seg, ntiles);
+    const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = w8 % NW, g = w8 / NW;   // value-feature block; row half of the state and token block of the output
+    const int a0 = 64 * g;                // first state row of this wave
+    T *stage = (T *)(smem + SM::STAGE_OFF) + w8 * 32 * 36;
+    Lane ln = fresh_lane();
+    K += kv_shift(chain, H, kvdiv, ntok, D);
+    V += kv_shift(chain, H, kvdiv, ntok, D);
+    auto off = [&](int t) { return tile_off(chain, ntok, t, CT, D); };
+    auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
+    TileMover<T, CT, D, NT> mq, mk, mv;
+    const float *lg = decay + (size_t)chain * ntok;
+    typename TokenDecay<T, CT>::LogG lgreg = {};
+    auto request = [&](int t) __attribute__((always_inline)) {
+        if constexpr (!STATES) mq.load(Q + off(t), nvalid(t));
+        mk.load(K + off(t), nvalid(t));
+        mv.load(V + off(t), nvalid(t));
+        if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
+    };
+    request(t0);
+    f32x16 st[HB];   // st[ab][i] = KV[a0 + 32 ab + acc_row(i)][32 w + r]
+    {
+        const float *states = scratch + (size_t)chain * nseg * D * D;
+        auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
+        if (carry)
+            start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, D * D, load);
+        else load(st, states + (size_t)seg * D * D);
+    }
+    const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
+    auto to_cache = [&](int t) __attribute__((always_inline)) {
+        if (cache && t % 2 == 0)
+            cache_store<D, D, D, HB>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * D * D + a0 * D, st, stage, w);
+    };
+    to_cache(t0);
+    if constexpr (RAGGED && !TOKEN) {
+        __syncthreads();   // the power table
+        dec.set_end(nvalid(t0));
+    }
+
+    for (int t = t0; t < t1; ++t) {
+        // Every wave is past the previous tile's second barrier: only P, the exchange and (Norm) the row sums may still
+        // be read, and those are written behind the next barrier.
+        ln = fresh_lane();
+        if constexpr (!STATES) mq.store(sQ, LDD);
+        mk.store(sK, LDD);
+        mv.store(sV, LDD);
+        if constexpr (TOKEN) dec.fill(lgreg);
+        else if constexpr (RAGGED) {
+            if (t > t0 && nvalid(t) < CT) dec.set_end(nvalid(t));
+        }
+        __syncthreads();
+        if (t + 1 < t1) request(t + 1);
+        f32x16 own = {0};   // OT[c][i], c in w, i in token block g
+        if constexpr (!STATES) {
+            masked_scores<T, CT, D, LDD, LDP, 2 * NW>(ln, sP, sK, sQ, dec, w8);
+            // this row half's share of Q KV, both token blocks
+            f32x16 acc[NB];
+#pragma unroll
+            for (int ib = 0; ib < NB; ++ib) acc[ib] = f32x16{0};
+#pragma unroll
+            for (int ab = 0; ab < HB; ++ab)
+#pragma unroll
+                for (int m = 0; m < E::NSUB; ++m) {
+                    const F sf = E::from_acc(st[ab], m);
+#pragma unroll
+                    for (int ib = 0; ib < NB; ++ib) acc[ib] = E::mfma(sf, E::ld_kp(ln, sQ, LDD, 32 * ib, a0 + 32 * ab, m), acc[ib]);
+                }
+            // the other group's block to LDS, lane-contiguous
+            const f32x16 give = g ? acc[0] : acc[1];
+            own = g ? acc[1] : acc[0];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4 *)(sX + (w8 * 4 + q) * 256 + 4 * ln.id) = f32x4{give[4 * q], give[4 * q + 1], give[4 * q + 2], give[4 * q + 3]};
+        }
+        const float up = STATES ? 0.0f : dec.upto(32 * g + ln.r);
+        ln = fresh_lane();
+        F vf[NKS];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) vf[ks] = E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w);
+        const float lamC = dec.whole(nvalid(t));
+#pragma unroll
+        for (int ab = 0; ab < HB; ++ab) st[ab] *= lamC;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            const F vd = dec.template weigh_after<!RAGGED>(ln, vf[ks], ks);
+#pragma unroll
+            for (int ab = 0; ab < HB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, a0 + 32 * ab), vd, st[ab]);
+        }
+        if (t + 1 < t1) to_cache(t + 1);
+
+        __syncthreads();  // P and the exchange visible; Q, K, V and the tables consumed
+        if constexpr (!STATES) {
+            ln = fresh_lane();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 x = *(const f32x4 *)(sX + (((1 - g) * NW + w) * 4 + q) * 256 + 4 * ln.id);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) own[4 * q + e] += x[e];
+            }
+            own *= up;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                if (g == 1 || ks < SPB) own = E::mfma(vf[ks], E::ld_kc(ln, sP, LDP, 32 * g, ks * E::KSTEP), own);
+            if constexpr (NORM) {
+                float *red = pw + 3 * CT + 4;
+                float ss = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ss += own[i] * own[i];
+                ss = add_other_half(ss);
+                if (ln.h == 0) red[w * CT + 32 * g + ln.r] = ss;
+                __syncthreads();
+                float tot = 0.0f;
+#pragma unroll
+                for (int wv = 0; wv < NW; ++wv) tot += red[wv * CT + 32 * g + ln.r];
+                const float rs = rsqrtf(tot * (1.0f / D) + eps);
+                own *= rs;
+                if (w == 0 && ln.h == 0 && (!RAGGED || 32 * g + ln.r < nvalid(t)))
+                    rstd_out[(size_t)chain * ntok + (size_t)t * CT + 32 * g + ln.r] = rs;
+            }
+            store_out_tile_t<T, D>(ln, O + off(t), own, 32 * g, w, nvalid(t));
+        }
+    }
+    if (seg == nseg - 1 && kv_out) state_store_w<D, D, D, HB>(ln, st, kv_out + (size_t)chain * D * D + a0 * D, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -1146,6 +1315,11 @@ struct StatesFam {  // the forward walk reduced to the states (no Norm: the stat
     template <bool TK, bool RG, bool NM>
     static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, kStates>;
 };
+template <typename T, int CT, int D, Role ROLE>
+struct Fwd8Fam {
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd8<T, CT, D, TK, RG, NM && ROLE == kOutputs, ROLE>;
+};
 template <typename T, int CT, int D, int WK, int WV>
 struct DqFam {      // dQ as a forward walk over dO, V, K
     template <bool TK, bool RG, bool NM>
@@ -1209,6 +1383,25 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
+    if constexpr (sizeof(T) == 2 && WK == 128 && WV == 128) {
+        static_assert(Fwd8Smem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
+        // Up to 256 workgroups a CU has one, and four waves leave each SIMD only one; from 257 on two workgroups of
+        // k_fwd share a CU (70 KB of LDS each; k_fwd8 takes 112), need no exchange and do not wait for each other.
+        // Forward, k_fwd / k_fwd8, us: 256 workgroups, 128 heads x 8192 tokens 309.0 / 300.1, x 4000 165.0 / 156.4,
+        // x 8192 with a decay per token 357.6 / 315.2; 512 workgroups, 512 heads x 2048 221.7 / 235.7, x 2000
+        // 231.3 / 238.8, x 2048 with a decay per token 223.0 / 253.3.
+        if (p.nseg * p.B * p.H <= 256) {
+            const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
+            if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                                  (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, (const float *)a.scratch,
+                                  a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
+                                  a.rstd_out, a.eps);
+                e != hipSuccess)
+                return e;
+            if (ke) (void)hipEventRecord(ke->ev[3], s);
+            return hipGetLastError();
+        }
+    }
     auto walk = by_model<FwdFam<T, CT, D, WK, WV>>(p);
     if constexpr (sizeof(T) == 2) {
         if (a.states_only) walk = by_model<StatesFam<T, CT, D, WK, WV>>(p);
