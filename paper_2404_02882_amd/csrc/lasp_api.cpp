@@ -39,6 +39,16 @@ bool valid_dims(const lasp_shape *s) {
     return true;
 }
 
+// Segments per head of a pass when the caller leaves the choice to the library.
+int auto_segments(const lasp::Plan &p, Pass pass) {
+    const int64_t chains = (int64_t)p.B * p.H;
+    const bool two_per_cu = p.dtype == LASP_F32 ? pass == kForward || p.D == 64 : pass == kForward && (p.dk == 64 || p.dv == 64);
+    const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
+    int want = (int)((target + (pass == kForward ? chains / 2 : 0)) / chains);
+    if (want > p.ntiles) want = p.ntiles;
+    return want < 1 ? 1 : want;
+}
+
 int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false, bool norm = false) {
     if (!s) return LASP_ERR_NULL;
     if (s->dtype != LASP_F32 && s->dtype != LASP_BF16) return LASP_ERR_DTYPE;
@@ -55,20 +65,15 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     p->ntiles = (s->N + p->tile - 1) / p->tile;
     int want = s->segments;
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
-    if (want == 0) {
-        const int64_t chains = (int64_t)s->B * s->H;
-        const bool two_per_cu = s->dtype == LASP_F32 ? pass == kForward || p->D == 64 : pass == kForward && (p->dk == 64 || p->dv == 64);
-        const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
-        want = (int)((target + (pass == kForward ? chains / 2 : 0)) / chains);
-        if (want > p->ntiles) want = p->ntiles;
-        if (want < 1) want = 1;
-    }
+    if (want == 0) want = auto_segments(*p, pass);
+    const bool pairs = p->dtype == LASP_BF16;   // tiles are walked in pairs
     p->token = token;
     p->norm = norm;
-    p->cache_stride = lasp::cache_stride_for(p->dtype);
-    p->ragged = s->N % (p->tile * p->cache_stride) != 0;
+    const int fwd_auto = auto_segments(*p, kForward);
+    p->cache_tiles = pairs ? 2 : (p->ntiles + fwd_auto - 1) / fwd_auto;
+    p->ragged = s->N % (pairs ? 2 * p->tile : p->tile) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
-    if (p->cache_stride == 2) p->tiles_per_seg += p->tiles_per_seg & 1;   // segments start on cached tiles
+    if (pairs) p->tiles_per_seg += p->tiles_per_seg & 1;   // segments start on cached tiles
     p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
     return LASP_OK;
 }
@@ -78,7 +83,7 @@ size_t elem_bytes(int dtype) { return dtype == LASP_F32 ? 4 : 2; }
 size_t cache_bytes(const lasp_shape *shape, bool token) {
     lasp::Plan p;
     if (make_plan(shape, kForward, &p, token) != LASP_OK) return 0;
-    return (size_t)p.B * p.H * ((p.ntiles + p.cache_stride - 1) / p.cache_stride) * p.dk * p.dv * elem_bytes(p.dtype);   // [d_k][d_v] per slot
+    return (size_t)p.B * p.H * ((p.ntiles + p.cache_tiles - 1) / p.cache_tiles) * p.dk * p.dv * elem_bytes(p.dtype);   // [d_k][d_v] per slot
 }
 
 // Scratch layout: [segment states][per-token decay only: segment log-decays][.. : per-token r_t]
@@ -248,12 +253,16 @@ int run_bwd_call(const BwdCall &c) {
     hipStream_t stream = (hipStream_t)c.stream;
     lasp::Plan f;   // the forward pass's own plan (its segment count)
     if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm); rc != LASP_OK) return rc;
-    if (rebuild && p.dtype == LASP_BF16) {   // states only, into the scratch tail
+    if (rebuild && p.dtype == LASP_F32 && f.tiles_per_seg == f.cache_tiles) {
+        cache = nullptr;   // the segments' start states, which launch_bwd rebuilds in the states' region, are the cache
+    } else if (rebuild) {   // states only, into the scratch tail
         const lasp::FwdArgs fa{nullptr, c.k, c.v, c.kv_in, c.decay, nullptr, nullptr, (void *)cache, (float *)scr,
                                f.token ? (float *)(scr + l.seglog) : nullptr, nullptr, 0.0f, true};
         if (lasp::launch_fwd(f, fa, stream, nullptr) != hipSuccess) return LASP_ERR_HIP;
     }
-    if (rebuild && p.dtype == LASP_F32) cache = nullptr;   // (rebuilds its segment states itself, in the states' region)
+    lasp_shape cut = *c.shape;   // dQ of float data: the segments whose start states the cache holds
+    cut.segments = 0;
+    if (rc = make_plan(&cut, kForward, &f, c.token, c.norm); rc != LASP_OK) return rc;
     lasp::BwdArgs a{c.q, c.k, c.v, c.dout, c.dkv_out, c.decay, cache, c.dq, c.dk, c.dv, c.dkv_in, (float *)scr,
                     &f, c.kv_in, c.kv_out, c.dlog_g, p.token ? (float *)(scr + l.seglog) : nullptr,
                     p.token ? (float *)(scr + l.rtok) : nullptr, c.yn, c.rstd, nullptr, nullptr};

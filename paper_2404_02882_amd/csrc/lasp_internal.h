@@ -18,9 +18,10 @@ struct Plan {
     int ntiles;         // ceil(N / tile); only the last tile may be short
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
-    int cache_stride;   // tiles per slot of the state cache: bfloat16 2 (walked in pairs); float 1 (of which only one
-                        // slot per segment is used)
-    bool ragged;        // the last tile is short, or the last pair of tiles (cache_stride 2) has only one
+    int cache_tiles;    // the state cache holds the state every cache_tiles-th tile starts from, whatever `segments` a
+                        // call asks for: bfloat16 2 (the backward walk takes tiles in pairs), float the segments of
+                        // the forward pass at segments = 0 (where the walk that produces dQ starts)
+    bool ragged;        // the last tile is short, or (bfloat16) the last pair of tiles has only one
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
@@ -48,7 +49,8 @@ struct BwdArgs {
     void *dq, *dk, *dv;
     float *dkv_in;
     float *scratch;
-    // float data only: the plan of the forward pass (its segments), and, when cache is null, the state it started from
+    // float data only: the plan of the walk that produces dQ, one segment per cached state; and, when cache is null,
+    // the state the forward pass started from
     const Plan *fwd;
     const float *kv_in;
     // per-token decay only
@@ -83,9 +85,6 @@ hipError_t static_scratch(void **ptr);
 
 // Tile length used for a (dtype, chunk, D) combination.
 int tile_tokens(int dtype, int chunk, int D);
-// Cache stride for a data type: 2 for bfloat16 (one cached state per pair of tiles, the backward
-// walk reaches the other tile from its neighbour's state), else 1.
-int cache_stride_for(int dtype);
 
 // Over the segments of every head, in place in `states` ([chain][nseg][d_k][d_v]): local states -> start states.
 hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boundary, const float *decay, const float *seglog,

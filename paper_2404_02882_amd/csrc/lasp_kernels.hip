@@ -203,8 +203,6 @@ hipError_t static_scratch(void **ptr) {
     return hipSuccess;
 }
 
-int cache_stride_for(int dtype) { return dtype == 1 ? 2 : 1; }
-
 // Tokens per kernel tile: 32 for float data, 64 for bfloat16 data, whatever the
 // chunk (both divide every supported chunk length). 64-token bfloat16 tiles let two
 // forward workgroups, or one backward workgroup with every tile it needs, live on a CU.

@@ -281,7 +281,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 // walked, every tile's entering state goes to the cache and the state is updated.
 // ROLE kDq (float data): the walk over dO, V, K instead of Q, K, V, which produces dQ,
 //     dQ_s = sum_{i<=s} lambda^(s-i) (do_s . v_i) k_i + lambda^s KV_in do_s,
-// the same sums with the state transposed, from the segment states the forward pass kept (WK, WV are then the
+// the same sums with the state transposed, a segment from each state the forward pass kept (WK, WV are then the
 // widths of V and K). NORM: dO is dY and becomes dO on its way to LDS (NormTile). With a decay per token the row
 // dots q.dq (q_rows: Q) go to rtok.
 enum Role { kOutputs, kStates, kDq };
@@ -295,7 +295,7 @@ template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false,
 __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq && (TOKEN || NORM)) ? 1 : 2) void k_fwd(const T *__restrict__ Q, const T *__restrict__ K,
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
-                                                T *__restrict__ cache, const float *__restrict__ scratch,
+                                                T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
                                                 int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
@@ -349,16 +349,23 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     typename TokenDecay<T, CT>::LogG lgreg = {};
     if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t0 * CT, nvalid(t0));
 
-    // State cache. bfloat16: the state every second tile `t` starts from, KV_{t-1}, rows a, columns c. Float: the state the segment starts from, all that the kDq walk needs.
+    // State cache: the state KV_{t-1} that tile `t` starts from, rows a, columns c. bfloat16: every second tile. Float:
+    // every cache_tiles-th, where the kDq walk starts; these are the segments' starts unless the caller chose the segments.
+    [[maybe_unused]] int slot = 0;
+    if constexpr (sizeof(T) == 4 && !DQ) {
+        if (cache) slot = (t0 + cache_tiles - 1) / cache_tiles;   // the next to be written
+    }
     auto to_cache = [&](int t) __attribute__((always_inline)) {
         if constexpr (sizeof(T) == 2) {
             if (cache && t % 2 == 0)
                 cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * WK * WV, st, sStage + w * 32 * 36, w);
+        } else if constexpr (!DQ) {
+            if (cache && t == slot * cache_tiles) {
+                const int slots = (ntiles + cache_tiles - 1) / cache_tiles;
+                state_store_w<D, WK, WV>(ln, st, cache + ((size_t)chain * slots + slot++) * WK * WV, w);
+            }
         }
     };
-    if constexpr (sizeof(T) == 4) {
-        if (cache) state_store_w<D, WK, WV>(ln, st, cache + ((size_t)chain * nseg + seg) * WK * WV, w);
-    }
     to_cache(t0);
     if constexpr (RAGGED && !TOKEN) {
         __syncthreads();   // the power table
@@ -1402,13 +1409,10 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
             return hipGetLastError();
         }
     }
-    auto walk = by_model<FwdFam<T, CT, D, WK, WV>>(p);
-    if constexpr (sizeof(T) == 2) {
-        if (a.states_only) walk = by_model<StatesFam<T, CT, D, WK, WV>>(p);
-    }
+    const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
     if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                           (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                          (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
+                          p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
                           p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
                           (const T *)nullptr, (float *)nullptr);
         e != hipSuccess)
@@ -1417,18 +1421,18 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     return hipGetLastError();
 }
 
-// dQ of float data: from the segment states the forward pass kept (a.cache), or, when it is given none, from the
+// dQ of float data: from the states the forward pass kept (a.cache), or, when it is given none, from the
 // states rebuilt into the scratch buffer, which the backward states overwrite afterwards.
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
-    const Plan &f = *a.fwd;   // the forward pass's plan: its segments
+    const Plan &f = *a.fwd;   // a segment per cached state
     const bool carry = !a.cache && walk_carries(f);
     if (!a.cache) {
         if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, nullptr); e != hipSuccess)
             return e;
     }
     return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
-                         (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
+                         (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr, f.cache_tiles,
                          a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry,
                          f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
                          (const T *)a.q, a.rtok);
