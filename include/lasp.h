@@ -26,6 +26,11 @@
  *   - Every function returns a lasp_status; nothing throws or aborts. All
  *     argument checks run on the host before anything is launched.
  *   - Every buffer is 16-byte aligned (the kernels move 16-byte pieces).
+ *   - LASP_F32: products are taken in three bfloat16 parts per factor and summed in
+ *     float, with the error of float products for factors from 2^-110 up (below,
+ *     a factor is rounded to a multiple of 2^-133). Infinities, NaN and the largest
+ *     floats enter sums as in float arithmetic; a product of two finite floats that
+ *     exceeds the largest float by more than 2^8 may come out NaN instead of infinite.
  *   - Outputs must not alias inputs or each other. Calls that share a scratch
  *     or state_cache buffer must be ordered on one stream.
  */

@@ -401,13 +401,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
 #pragma unroll
             for (int ib = 0; ib < NB; ++ib) acc[ib] = f32x16{0};
             // inter: OT[c][i] = sum_a KV_{t-1}[a][c] Q[i][a], a taken in accumulator order
-            if constexpr (E::PLANES == 3) {
-                static_assert(NB == 1, "one 32-token block per tile");
-                pipelined_flat<DB * E::NSUB, 1>([&](int i) { return E::ld_kp(ln, sQ, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); },
-                                                [&](int i, const typename E::frag &f) {
-                                                    acc[0] = E::mfma(E::from_acc(st[i / E::NSUB], i % E::NSUB), f, acc[0]);
-                                                });
-            } else {
+            if constexpr (E::PLANES == 1) {   // (float data: below)
 #pragma unroll
                 for (int ab = 0; ab < DB; ++ab)
 #pragma unroll
@@ -418,8 +412,10 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
                     }
             }
             // Lambda: token r (1-based) carries lambda^r; the token is this lane's column
+            if constexpr (E::PLANES == 1) {
 #pragma unroll
-            for (int ib = 0; ib < NB; ++ib) acc[ib] *= dec.upto(32 * ib + ln.r);
+                for (int ib = 0; ib < NB; ++ib) acc[ib] *= dec.upto(32 * ib + ln.r);
+            }
         }
         // V of this wave's columns, for the state update and, behind the barrier, for P V
         ln = fresh_lane();
@@ -428,14 +424,27 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) vf[ks] = E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w);
         };
-        load_vf();
         // state update: KV <- lambda^CT KV + (diag{lambda^(CT-1-j)} K)^T V, weight applied to the V fragments
         const float lamC = dec.whole(nvalid(t));
         if constexpr (E::PLANES == 3) {
+            unsigned lows = 0;
+            auto inter_and_weigh = [&](auto edge) __attribute__((always_inline)) {
+                constexpr bool EDGE = decltype(edge)::value;
+                if constexpr (!STATES) {
+                    static_assert(NB == 1, "one 32-token block per tile");
+                    acc[0] = state_product<E, EDGE>(st, lows, [&](int i) { return E::ld_kp(ln, sQ, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); });
+                    acc[0] *= dec.upto(ln.r);
+                    ln = fresh_lane();
+                }
+                load_vf();
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<!RAGGED>(ln, vf[ks], ks);
+                for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<!RAGGED, EDGE>(ln, vf[ks], ks, &lows);
+            };
+            inter_and_weigh(std::false_type{});
+            if (E::edge(lows)) inter_and_weigh(std::true_type{});
             decay_and_add<E>(ln, st, lamC, sK, LDD, vf);
         } else {
+            load_vf();
 #pragma unroll
             for (int ab = 0; ab < DB; ++ab) st[ab] *= lamC;
 #pragma unroll
@@ -833,13 +842,18 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             for (int ks = 0; ks < NKS; ++ks) x2[ks] = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
         };
         if (own_block) {
-            pipelined_flat<DB * E::NSUB, 1>([&](int i) { return E::ld_kp(ln, sX1, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); },
-                                            [&](int i, const F &f) { acc = E::mfma(E::from_acc(st[i / E::NSUB], i % E::NSUB), f, acc); });
-            acc *= dec.after(ln.r, nv);
-            load_x2();
-            // dKV <- lambda^CT dKV + (Lambda Q)^T dO, in this group's orientation
+            unsigned lows = 0;
+            auto inter_and_weigh = [&](auto edge) __attribute__((always_inline)) {
+                constexpr bool EDGE = decltype(edge)::value;
+                acc = state_product<E, EDGE>(st, lows, [&](int i) { return E::ld_kp(ln, sX1, LDD, 0, 32 * (i / E::NSUB), i % E::NSUB); });
+                acc *= dec.after(ln.r, nv);
+                load_x2();
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) x2[ks] = dec.weigh_upto(ln, x2[ks], ks);
+                for (int ks = 0; ks < NKS; ++ks) x2[ks] = dec.template weigh_upto<EDGE>(ln, x2[ks], ks, &lows);
+            };
+            inter_and_weigh(std::false_type{});
+            if (E::edge(lows)) inter_and_weigh(std::true_type{});
+            // dKV <- lambda^CT dKV + (Lambda Q)^T dO, in this group's orientation
             decay_and_add<E>(ln, st, dec.whole(nv), sUA, LDD, x2);
         }
         __syncthreads();  // scores visible
