@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lasp_internal.h"
+#include "lasp_rules.h"
 #include "lasp_device.h"
 
 namespace lasp {
@@ -236,20 +237,13 @@ static hipError_t run_bidir_apply(const BidirPlan &p, const BidirOps &ops, int n
     static_assert(2 * lds <= 163840, "two workgroups per CU");
     if (hipError_t e = allow_dynamic_lds((const void *)k_bidir_apply<T, CT, D>, lds); e != hipSuccess) return e;
     const int ntiles = (p.N + CT - 1) / CT;
-    // At most as many workgroups as are resident at once (where that leaves one per chain and product): the few that
-    // rounding up left over ran as a second round, alone. Three products of 16 heads x 32768 tokens, bf16 d=128, as
-    // 528 workgroups of 24 tiles / 480 of 26: the step 372 / 338 us.
-    int nblk = kBidirTargetWorkgroups / (chains * nops);
-    if (nblk < 1) nblk = 1;
-    if (nblk > ntiles) nblk = ntiles;
-    const int tiles_per_blk = (ntiles + nblk - 1) / nblk;
-    nblk = (ntiles + tiles_per_blk - 1) / tiles_per_blk;  // every block non-empty
+    const Blocks blk = blocks_for(ntiles, (long long)chains * nops, kBidirTargetWorkgroups);
     if (ke) {
         (void)hipEventRecord(ke->ev[0], s);
         (void)hipEventRecord(ke->ev[1], s);
         (void)hipEventRecord(ke->ev[2], s);
     }
-    k_bidir_apply<T, CT, D><<<dim3(nblk, chains, nops), dim3(D * 2), lds, s>>>(ops, ntiles, tiles_per_blk, p.N);
+    k_bidir_apply<T, CT, D><<<dim3(blk.count, chains, nops), dim3(D * 2), lds, s>>>(ops, ntiles, blk.tiles, p.N);
     if (ke) (void)hipEventRecord(ke->ev[3], s);
     return hipGetLastError();
 }

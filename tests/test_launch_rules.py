@@ -1,0 +1,55 @@
+"""Launch rules that are plain arithmetic (csrc/lasp_rules.h), compiled with the host compiler."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def blocks_for(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "rules.so"
+    src.write_text(f'#include "{ROOT}/paper_2404_02882_amd/csrc/lasp_rules.h"\n'
+                   'extern "C" void blocks(int ntiles, long long chains, int slots, int *out) {\n'
+                   '    const lasp::Blocks b = lasp::blocks_for(ntiles, chains, slots);\n'
+                   '    out[0] = b.tiles;\n    out[1] = b.count;\n}\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    fn = ctypes.CDLL(str(lib)).blocks
+
+    def call(ntiles, chains, slots=512):
+        out = (ctypes.c_int * 2)()
+        fn(ntiles, ctypes.c_longlong(chains), slots, out)
+        return out[0], out[1]
+    return call
+
+
+def time_of(tiles, count, chains, slots=512):
+    return -(-chains * count // slots) * tiles
+
+
+def test_bidirectional_blocks(blocks_for):
+    """Every tile in exactly one block, and never more rounds x tiles than the share rounded down or up alone gives;
+    as long, never fewer workgroups."""
+    for chains in (1, 2, 6, 16, 24, 36, 48, 72, 96, 144, 170, 171, 192, 264, 288, 384, 511, 512, 513, 600, 3000):
+        for ntiles in (1, 2, 3, 5, 6, 8, 12, 20, 40, 256, 257):
+            tiles, count = blocks_for(ntiles, chains)
+            assert tiles >= 1 and (count - 1) * tiles < ntiles <= count * tiles
+            for want in (512 // chains, -(-512 // chains)):
+                t = -(-ntiles // min(max(want, 1), ntiles))
+                n = -(-ntiles // t)
+                other = time_of(t, n, chains)
+                assert time_of(tiles, count, chains) <= other, (chains, ntiles)
+                if time_of(tiles, count, chains) == other:
+                    assert count >= n, (chains, ntiles)
+
+
+def test_measured_shapes(blocks_for):
+    """Three products of 16 heads x 32768 tokens (128-token tiles) in one round; of 32 heads x 768 tokens in one-tile
+    blocks rather than half as many of two; of 128 heads in two blocks each."""
+    assert blocks_for(256, 48) == (26, 10)
+    assert blocks_for(6, 96) == (1, 6)
+    assert blocks_for(20, 384) == (10, 2)
+    assert blocks_for(20, 512) == (20, 1)
