@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "lasp_internal.h"
+#include "lasp_rules.h"
 
 namespace {
 
@@ -17,15 +18,18 @@ namespace {
 // the device has CUs, never more than one segment per tile. A second forward workgroup per CU (512) hides more
 // latency but doubles the segment states that go through memory: bf16 d=128 forward, 512 against 256 workgroups,
 // 16 heads x 32768 tokens 208 / 197 us, 32 x 4096 69 / 65, 256 x 4096 (two segments / one, no local pass) 345 / 285.
+// Never more workgroups than CUs where it can be helped: a few left over are a whole second round (backward, 12 heads x
+// 32768: 22 segments 348 us, 20 segments 235), and the forward walk in eight waves takes a CU to itself (forward, the
+// nearest count / rounded down: 24 heads x 16384 tokens 264 / 240 workgroups 200 / 152 us, 56 x 4096 111 / 86,
+// 136 x 16384 950 / 805 with 272 / 136).
 // With a key or value dimension of 64 a state is a quarter or half of the bytes and a tile brings less to stream,
-// so 512 win: 16 x 32768 at d=64 87 / 107 us; d_k=64, d_v=128 norm step of 32 x 5504, two shards, 352 / 376.
-// The backward walk (bfloat16: one workgroup per CU) never takes more workgroups than CUs where it can: a few left
-// over are a whole second round (12 heads x 32768: 22 segments 348 us, 20 segments 235). The forward walk can share
-// a CU, so it takes the nearest count. Float walks are bound by vector and matrix instructions issued one after the
+// so 512 forward workgroups win, and two share a CU, so the count may be the nearest: 16 x 32768 at d=64 87 / 107 us;
+// d_k=64, d_v=128 norm step of 32 x 5504, two shards, 352 / 376.
+// Float walks are bound by vector and matrix instructions issued one after the
 // other, which a second workgroup per CU overlaps: 512 (16 x 8192 at d=128 forward 157 / 148 us), except the 8-wave
 // backward walk at d=128, of which one fits (per-token decay 386 / 409 us).
-constexpr int kTargetWorkgroups = 256;
-constexpr int kTargetWorkgroupsLatencyBound = 512;
+constexpr int kTargetWorkgroups = lasp::kOnePerCu;
+constexpr int kTargetWorkgroupsLatencyBound = 2 * lasp::kOnePerCu;
 enum Pass { kForward = 0, kBackward = 1 };
 
 bool valid_dims(const lasp_shape *s) {
@@ -44,7 +48,7 @@ int auto_segments(const lasp::Plan &p, Pass pass) {
     const int64_t chains = (int64_t)p.B * p.H;
     const bool two_per_cu = p.dtype == LASP_F32 ? pass == kForward || p.D == 64 : pass == kForward && (p.dk == 64 || p.dv == 64);
     const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
-    int want = (int)((target + (pass == kForward ? chains / 2 : 0)) / chains);
+    int want = (int)((target + (two_per_cu && pass == kForward ? chains / 2 : 0)) / chains);
     if (want > p.ntiles) want = p.ntiles;
     return want < 1 ? 1 : want;
 }

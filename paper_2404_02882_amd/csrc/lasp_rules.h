@@ -4,6 +4,10 @@
 
 namespace lasp {
 
+// Workgroups up to which every one has a CU (of 256) of its own: the target of the launches that want no more, and the line
+// up to which the bfloat16 forward walk takes eight waves a workgroup.
+constexpr int kOnePerCu = 256;
+
 // Blocks of tiles per chain for `chains` independent rows of `ntiles` tiles where `slots` workgroups are resident at
 // once. Two counts come into question, the share of the slots rounded down and up: the launch takes as many rounds as
 // its workgroups fill the slots, each as long as the tiles of a block. The shorter is taken, and if both are as long the

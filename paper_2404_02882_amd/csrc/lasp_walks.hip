@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lasp_internal.h"
+#include "lasp_rules.h"
 #include "lasp_device.h"
 
 namespace lasp {
@@ -1411,7 +1412,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         // Forward, k_fwd / k_fwd8, us: 256 workgroups, 128 heads x 8192 tokens 309.0 / 300.1, x 4000 165.0 / 156.4,
         // x 8192 with a decay per token 357.6 / 315.2; 512 workgroups, 512 heads x 2048 221.7 / 235.7, x 2000
         // 231.3 / 238.8, x 2048 with a decay per token 223.0 / 253.3.
-        if (p.nseg * p.B * p.H <= 256) {
+        if ((int64_t)p.nseg * p.B * p.H <= kOnePerCu) {
             const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
             if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                   (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, (const float *)a.scratch,

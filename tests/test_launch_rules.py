@@ -53,3 +53,16 @@ def test_measured_shapes(blocks_for):
     assert blocks_for(6, 96) == (1, 6)
     assert blocks_for(20, 384) == (10, 2)
     assert blocks_for(20, 512) == (20, 1)
+
+
+@pytest.mark.parametrize("dims", [dict(D=128), dict(D=128, kv_heads=1)])
+def test_forward_workgroups_stay_within_the_cus(dims):
+    """bfloat16 d=128: the automatic forward cut never makes more workgroups than there are CUs while there are no more
+    heads than CUs, and uses at least half of them where the sequence has the tiles."""
+    from paper_2404_02882_amd import lasp
+    for chains in (1, 2, 6, 12, 16, 20, 24, 44, 56, 68, 88, 96, 120, 128, 136, 160, 170, 192, 255, 256):
+        for N in (64 * 16, 64 * 64, 64 * 256, 64 * 2048):
+            n = lasp.num_segments(lasp.make_shape(1, chains, N, chunk=64, dtype="bf16", **dims))
+            assert chains * n <= 256, (chains, N, n)
+            # (segments are whole pairs of tiles of one length, so up to half of the share may be lost to rounding)
+            assert chains * n >= min(128, chains * (N // 128) // 2), (chains, N, n)
