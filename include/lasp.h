@@ -120,7 +120,8 @@ int32_t lasp_num_segments(const lasp_shape *shape);
  * by lasp_fwd and read by lasp_bwd for dQ_inter (the paper caches the state a
  * rank receives, Alg. 2 "save KV_{t-1}", Sec. 3.4; for bfloat16 one state per two
  * tiles is cached, since the backward kernel reaches the other tile from its
- * neighbour's state; for float one per segment of the automatic cut, from which the
+ * neighbour's state, or one per tile where the tiles are odd in number and the
+ * sequence is short or D is 64; for float one per segment of the automatic cut, from which the
  * walk that produces dQ runs the recurrence again).
  * Size and layout do not depend on `segments`: the forward and the backward call of
  * a shape may name different ones. The layout is private to the library; slot 0 is

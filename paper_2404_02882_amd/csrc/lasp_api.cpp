@@ -48,7 +48,17 @@ int auto_segments(const lasp::Plan &p, Pass pass) {
     const int64_t chains = (int64_t)p.B * p.H;
     const bool two_per_cu = p.dtype == LASP_F32 ? pass == kForward || p.D == 64 : pass == kForward && (p.dk == 64 || p.dv == 64);
     const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
-    int want = (int)((target + (two_per_cu && pass == kForward ? chains / 2 : 0)) / chains);
+    int64_t round = two_per_cu && pass == kForward ? chains / 2 : 0;
+    // Three workgroups of the d=64 forward walk fit a CU. With a decay per token, which keeps them longer at the tables, the
+    // count is rounded up: 100 heads x 8000 tokens, five / six segments 152 / 142 us.
+    if (p.dtype == LASP_BF16 && p.D == 64 && p.token && pass == kForward) round = chains - 1;
+    int want = (int)((target + round) / chains);
+    // Backward by tiles at d=64, two workgroups a CU: 48 heads x 5056 tokens, 5 / 6 / 10 segments 79 / 90 / 67 us,
+    // 100 x 5056, 2 / 3 / 5 174 / 169 / 140; past 32 segments the scan costs more (8 x 5056, 32 / 64 28.3 / 31.1).
+    if (p.dtype == LASP_BF16 && p.D == 64 && pass == kBackward && p.cache_tiles == 1) {
+        want = (int)(kTargetWorkgroupsLatencyBound / chains);
+        if (want > 32) want = 32;
+    }
     if (want > p.ntiles) want = p.ntiles;
     return want < 1 ? 1 : want;
 }
@@ -69,15 +79,21 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     p->ntiles = (s->N + p->tile - 1) / p->tile;
     int want = s->segments;
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
-    if (want == 0) want = auto_segments(*p, pass);
-    const bool pairs = p->dtype == LASP_BF16;   // tiles are walked in pairs
+    const bool two_byte = p->dtype == LASP_BF16;   // tiles are walked in pairs, or one by one
+    const int64_t chains = (int64_t)s->B * s->H;
     p->token = token;
     p->norm = norm;
-    const int fwd_auto = auto_segments(*p, kForward);
-    p->cache_tiles = pairs ? 2 : (p->ntiles + fwd_auto - 1) / fwd_auto;
-    p->ragged = s->N % (pairs ? 2 * p->tile : p->tile) != 0;
+    if (two_byte) {
+        p->cache_tiles = lasp::cache_every_tile(p->ntiles, chains, p->D) ? 1 : 2;
+    } else {
+        const int fwd_auto = auto_segments(*p, kForward);
+        p->cache_tiles = (p->ntiles + fwd_auto - 1) / fwd_auto;
+    }
+    if (want == 0) want = auto_segments(*p, pass);
+    p->ragged = s->N % (two_byte && pass == kBackward ? 2 * p->tile : p->tile) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
-    if (pairs) p->tiles_per_seg += p->tiles_per_seg & 1;   // segments start on cached tiles
+    if (two_byte)
+        p->tiles_per_seg = lasp::segment_tiles(p->tiles_per_seg, p->ntiles, chains, p->D, p->cache_tiles == 1, pass == kBackward);
     p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
     return LASP_OK;
 }

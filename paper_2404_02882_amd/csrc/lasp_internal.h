@@ -19,9 +19,10 @@ struct Plan {
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
     int cache_tiles;    // the state cache holds the state every cache_tiles-th tile starts from, whatever `segments` a
-                        // call asks for: bfloat16 2 (the backward walk takes tiles in pairs), float the segments of
-                        // the forward pass at segments = 0 (where the walk that produces dQ starts)
-    bool ragged;        // the last tile is short, or (bfloat16) the last pair of tiles has only one
+                        // call asks for: bfloat16 2 (the backward walk takes tiles in pairs) or 1 (one by one, see
+                        // cache_every_tile), float the segments of the forward pass at segments = 0 (where the walk
+                        // that produces dQ starts)
+    bool ragged;        // the last tile is short, or (bfloat16, backward) the last pair of tiles has only one
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)

@@ -8,6 +8,33 @@ namespace lasp {
 // up to which the bfloat16 forward walk takes eight waves a workgroup.
 constexpr int kOnePerCu = 256;
 
+// Whether the bfloat16 state cache holds the state of every tile, not of every second one, and the backward walk takes its
+// tiles one by one (D: the larger dimension). Pairs halve the cache's bytes; but a sequence of an odd number of tiles has a
+// pair of one, and cannot be cut below two tiles, which keeps a short sequence of few heads waiting; and at d=64, where a
+// state is small, the walk by tiles leaves room for a second workgroup on its CU. Step by tiles / in pairs: d=128 2 heads x
+// 448 tokens 34.3 / 42.3 us, 8 x 1088 (136 workgroups) 49.1 / 51.5, with a decay per token 16 x 448 46.8 / 53.8; d=64
+// 16 x 5056 63.0 / 71.5, 100 x 8000 317 / 419, with a decay per token 362 / 562. The backward walk alone, d=128, from where
+// one tile a segment no longer pays: 8 x 21 tiles 30.5 / 29.8, 16 x 16 34.9 / 32.6.
+inline bool cache_every_tile(int ntiles, long long chains, int D) {
+    return ntiles % 2 != 0 && (D == 64 || chains * ntiles <= kOnePerCu * 9 / 16);
+}
+
+// Tiles per segment of a bfloat16 pass that was asked for `want`: whole pairs where the cache has pairs. By tiles the
+// backward pass takes what it was asked for. The forward walk, whose chain is shorter, takes single tiles up to 72 workgroups
+// (2 heads x 3 tiles 13.8 us / in pairs 15.2, 2 x 9 17.1 / 18.7, 4 x 17 19.9 / 20.5, 8 x 11 20.6 / 20.4), but not from five
+// to eight tiles, where pairs make at most four segments and need no scan (16 x 7 21.1 / 18.0, 8 x 5 18.3 / 16.4); and
+// other odd numbers at d=64 while three workgroups share a CU (16 heads x 79 tiles, three / four 27.0 / 29.3, 32 x 79,
+// five / six 35.0 / 37.7).
+inline int segment_tiles(int want, int ntiles, long long chains, int D, bool every_tile, bool backward) {
+    if (want % 2 == 0) return want;
+    bool keep = every_tile;
+    if (!backward) {
+        const long long workgroups = chains * ((ntiles + want - 1) / want);
+        keep = keep && (want == 1 ? workgroups <= 72 && (ntiles <= 4 || ntiles > 8) : D == 64 && workgroups <= 3 * kOnePerCu);
+    }
+    return keep ? want : want + 1;
+}
+
 // Blocks of tiles per chain for `chains` independent rows of `ntiles` tiles where `slots` workgroups are resident at
 // once. Two counts come into question, the share of the slots rounded down and up: the launch takes as many rounds as
 // its workgroups fill the slots, each as long as the tiles of a block. The shorter is taken, and if both are as long the

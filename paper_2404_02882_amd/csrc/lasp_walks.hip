@@ -350,16 +350,17 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     typename TokenDecay<T, CT>::LogG lgreg = {};
     if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t0 * CT, nvalid(t0));
 
-    // State cache: the state KV_{t-1} that tile `t` starts from, rows a, columns c. bfloat16: every second tile. Float:
-    // every cache_tiles-th, where the kDq walk starts; these are the segments' starts unless the caller chose the segments.
+    // State cache: the state KV_{t-1} that tile `t` starts from, rows a, columns c. bfloat16: every second tile, or every
+    // tile (cache_tiles 2 or 1). Float: every cache_tiles-th, where the kDq walk starts; these are the segments' starts unless the caller chose the segments.
     [[maybe_unused]] int slot = 0;
     if constexpr (sizeof(T) == 4 && !DQ) {
         if (cache) slot = (t0 + cache_tiles - 1) / cache_tiles;   // the next to be written
     }
     auto to_cache = [&](int t) __attribute__((always_inline)) {
         if constexpr (sizeof(T) == 2) {
-            if (cache && t % 2 == 0)
-                cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * WK * WV, st, sStage + w * 32 * 36, w);
+            const int half = cache_tiles - 1;
+            if (cache && (t & half) == 0)
+                cache_store<D, WK, WV>(ln, cache + ((size_t)chain * ((ntiles + half) >> half) + (t >> half)) * WK * WV, st, sStage + w * 32 * 36, w);
         } else if constexpr (!DQ) {
             if (cache && t == slot * cache_tiles) {
                 const int slots = (ntiles + cache_tiles - 1) / cache_tiles;
@@ -544,7 +545,7 @@ struct Fwd8Smem {
 template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, Role ROLE = kOutputs>
 __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                 const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
-                                                T *__restrict__ cache, const float *__restrict__ scratch,
+                                                T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
                                                 int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps) {
@@ -595,8 +596,9 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     auto to_cache = [&](int t) __attribute__((always_inline)) {
-        if (cache && t % 2 == 0)
-            cache_store<D, D, D, HB>(ln, cache + ((size_t)chain * ((ntiles + 1) / 2) + t / 2) * D * D + a0 * D, st, stage, w);
+        const int half = cache_tiles - 1;
+        if (cache && (t & half) == 0)
+            cache_store<D, D, D, HB>(ln, cache + ((size_t)chain * ((ntiles + half) >> half) + (t >> half)) * D * D + a0 * D, st, stage, w);
     };
     to_cache(t0);
     if constexpr (RAGGED && !TOKEN) {
@@ -908,20 +910,23 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
 //     one tile early. Per pair: six barriers, 9 tile loads, one cache-tile load.
 // An odd tile count leaves the last pair without its O tile: nothing of it is
 // read, its phase is skipped and the E tile is the one that may be short.
+// BY_TILES: the cache holds every tile's state (cache_every_tile), the tiles are
+// walked one by one, each as an E tile: four input tiles in LDS, three barriers.
 // ---------------------------------------------------------------------------
-template <typename T, int CT, int D>
+template <typename T, int CT, int D, bool BY_TILES = false>
 struct Bwd8pSmem {
     static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
     static constexpr size_t TILE = (size_t)CT * LDD * sizeof(T);
-    static constexpr size_t P_OFF = 6 * TILE;
-    static constexpr size_t C_OFF = P_OFF + 3 * (size_t)CT * LDP * sizeof(T);   // S, dS and the cross tile dS(O x E)
+    static constexpr size_t P_OFF = (BY_TILES ? 4 : 6) * TILE;
+    static constexpr size_t C_OFF = P_OFF + (BY_TILES ? 2 : 3) * (size_t)CT * LDP * sizeof(T);   // S, dS and the cross tile dS(O x E)
     static constexpr size_t PW_OFF = C_OFF + (size_t)D * LDD * sizeof(T);
     // decay tables of the O tile and of the E tile, then one row of per-token partial sums per wave
-    static constexpr size_t TOTAL = PW_OFF + (6 * CT + 4 + 8 * CT) * sizeof(float);
+    static constexpr int TABLES = (BY_TILES ? 1 : 2) * 3 * CT;
+    static constexpr size_t TOTAL = PW_OFF + (TABLES + 4 + 8 * CT) * sizeof(float);
 };
 
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, bool BY_TILES = false>
 __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const T *__restrict__ K,
                                                   const T *__restrict__ V, const T *__restrict__ dO,
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
@@ -933,8 +938,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
     using E = WalkElem<T>;
     using F = typename E::frag;
-    using SM = Bwd8pSmem<T, CT, D>;
+    using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
     static_assert(CT == 64, "two 32-token blocks per tile");
+    static_assert(RAGGED || !BY_TILES, "by tiles: an odd number of them");
     constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
                   NKD = D / E::KSTEP, SPB = 32 / E::KSTEP;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -942,8 +948,8 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     T *sdO = sVO + CT * LDD;       // dO of the tile being processed
     T *sKO = sdO + CT * LDD;       // K of the O tile
     T *sQ = sKO + CT * LDD;        // Q of the tile being processed
-    T *sVE = sQ + CT * LDD;        // V of the E tile
-    T *sKE = sVE + CT * LDD;       // K of the E tile
+    T *sVE = BY_TILES ? sVO : sQ + CT * LDD;    // V of the E tile
+    T *sKE = BY_TILES ? sKO : sVE + CT * LDD;   // K of the E tile
     T *sS = (T *)(smem + SM::P_OFF);
     T *sDS = sS + CT * LDP;
     T *sDX = sDS + CT * LDP;       // masked dS between the O tile's queries and the E tile's keys
@@ -951,8 +957,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     float *pw = (float *)(smem + SM::PW_OFF);
 
     const int chain = blockIdx.y, seg = blockIdx.x;
-    const int t0 = seg * tiles_per_seg;                                  // even
-    const int t1 = (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;   // even: the last pair may lack its O tile
+    const int t0 = seg * tiles_per_seg;                                  // even, unless by tiles
+    // even: the last pair may lack its O tile
+    const int t1 = BY_TILES ? min(t0 + tiles_per_seg, ntiles) : (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;
     auto nvalid = [&](int t) { return RAGGED ? max(min(CT, ntok - t * CT), 0) : CT; };  // rows of tile `t` that exist
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW;    // feature block of this wave's outputs
@@ -965,12 +972,12 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
     TileMover<T, CT, D, NT> mvO, moX, mkO, mqX, mvE, mkE;   // moX / mqX carry dO, Q of the O tile, then of the E tile
     TileMover<T, D, D, NT> mc;                               // cached state at the start of the E tile
-    const T *ctile = cache + (size_t)chain * ((ntiles + 1) / 2) * WK * WV;   // [WK][WV] per slot
+    const T *ctile = cache + (size_t)chain * (BY_TILES ? ntiles : (ntiles + 1) / 2) * WK * WV;   // [WK][WV] per slot
     // With a decay per token (`decay` = log g, [chain][token]) the O and the E tile have their own
     // tables; with one lambda per head both names refer to the same table.
     const auto decO = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     const auto decE = [&] {
-        if constexpr (TOKEN) return TokenDecay<T, CT>(pw + 3 * CT);
+        if constexpr (TOKEN && !BY_TILES) return TokenDecay<T, CT>(pw + 3 * CT);
         else return decO;
     }();
     // weight key j of the E tile carries at query i of the O tile, and the E tile's entering state at query i
@@ -986,7 +993,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     const float *lg = decay + (size_t)chain * ntok;
     typename TokenDecay<T, CT>::LogG lgO = {}, lgE = {};
     // per-token decay: r_t = q_t.dq_t - k_t.dk_t, one partial row per wave, summed and written per tile
-    float *rs = pw + 6 * CT + 4;
+    float *rs = pw + SM::TABLES + 4;
     auto flush_r = [&](int tile) {
         if (threadIdx.x < CT) {
             float r = 0.0f;
@@ -1025,7 +1032,17 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         load_pair_kv(tE);
         load_pair_rest(tE);
     };
-    load_pair(t1 - 2);
+    [[maybe_unused]] auto load_tile = [&](int t, int n) {   // by tiles
+        mvE.template load_w<WV>(V + voff(t), n);
+        mkE.template load_w<WK>(K + koff(t), n);
+        moX.template load_w<WV>(dO + voff(t), n);
+        mqX.template load_w<WK>(Q + koff(t), n);
+        mc.template load_w<WV>(ctile + (size_t)t * WK * WV, WK);
+        if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
+        if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
+    };
+    if constexpr (BY_TILES) load_tile(t1 - 1, nvalid(t1 - 1));
+    else load_pair(t1 - 2);
 
     const T *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
     const T *sUA = rg ? sdO : sQ;    // state-update A operand: [token][feature of the state rows]
@@ -1232,7 +1249,30 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         }
     };
 
-    for (int tE = t1 - 2; tE >= t0; tE -= 2) {
+    if constexpr (BY_TILES) {
+        for (int t = t1 - 1; t >= t0; --t) {
+            __syncthreads();  // previous tile fully consumed
+            ln = fresh_lane();
+            if constexpr (TOKEN) {
+                if (t + 1 < t1) flush_r(t + 1);
+                decE.fill(lgE);
+            }
+            if constexpr (NORM) mnX.apply(moX);
+            mvE.store(sVE, LDD);
+            moX.store(sdO, LDD);
+            mkE.store(sKE, LDD);
+            mqX.store(sQ, LDD);
+            mc.store(sC, LDD);
+            __syncthreads();
+            ln = fresh_lane();
+            if (t > t0) load_tile(t - 1, CT);   // (only the sub-sequence's last tile is short)
+            scores(decE, sVE, sKE);
+            __syncthreads();
+            ln = fresh_lane();
+            products(decE, sVE, sKE, t, nvalid(t), false);
+        }
+    }
+    for (int tE = BY_TILES ? t0 - 1 : t1 - 2; tE >= t0; tE -= 2) {
         __syncthreads();  // previous pair fully consumed
         ln = fresh_lane();
         if constexpr (TOKEN) {
@@ -1357,9 +1397,14 @@ struct Bwd8pFam {   // eight waves, one cached state per pair of tiles
     template <bool TK, bool RG, bool NM>
     static constexpr auto fn = k_bwd8p<T, CT, D, TK, RG, NM, WK, WV>;
 };
+template <typename T, int CT, int D, int WK, int WV>
+struct Bwd8tFam {   // one cached state per tile; an odd tile count is ragged
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, true>;
+};
 
 // The local pass only sums over its segment, so its tile need not be the walk's:
-// bfloat16 segments (always an even number of 64-token tiles) are read 128 tokens
+// bfloat16 segments of an even number of 64-token tiles are read 128 tokens
 // at a time (half the barriers, twice the bytes in flight per workgroup), unless
 // the Norm prologue (a third tile in registers) or key and value dimensions that
 // differ ask for the walk's tile.
@@ -1368,7 +1413,7 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
                             const T *yn, const float *rstd, hipStream_t s) {
     const dim3 grid(p.nseg - 1, p.B * p.H), block(D * 2);
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
-        if (!(BWD && p.norm))
+        if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0)
             return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D>>(p), grid, block, Smem<T, 128, D>::local, s, x, y,
                                  decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
                                  (const T *)nullptr, (const float *)nullptr);
@@ -1415,7 +1460,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         if ((int64_t)p.nseg * p.B * p.H <= kOnePerCu) {
             const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
             if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
-                                  (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, (const float *)a.scratch,
+                                  (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles, (const float *)a.scratch,
                                   a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
                                   a.rstd_out, a.eps);
                 e != hipSuccess)
@@ -1479,7 +1524,10 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     const dim3 grid(p.nseg, chains), block(D * 4);
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
-        e = launch_kernel(by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block, Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+        static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
+        const bool by_tiles = p.cache_tiles == 1;
+        e = launch_kernel(by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV>>(p) : by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block,
+                          by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                           (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
                           (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H,
                           p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd);

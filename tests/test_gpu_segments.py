@@ -56,3 +56,33 @@ def test_forward_and_backward_cut_differently(gpu, oracle, dtype, tile, D, Dv, t
         emax, efro = harness.rel_errors(got[name].float().cpu().numpy(), r)
         print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
         assert np.isfinite(emax) and emax <= TOL[dtype] and efro <= TOL[dtype], name
+
+
+# (tokens, segments): the backward walk's segments of an odd number of 64-token tiles begin and end inside a pair
+@pytest.mark.parametrize("N,segments", [(64 * 7, 7), (64 * 7, 3), (64 * 3, 0), (64 * 5 + 1, 6), (64 * 6 - 1, 2), (64 * 9, 2), (64, 1), (65, 2)])
+@pytest.mark.parametrize("D,Dv,kv_heads", [(64, 64, 0), (128, 128, 0), (128, 128, 2), (64, 128, 0), (128, 64, 0)])
+@pytest.mark.parametrize("token,norm", [(False, False), (True, False), (False, True), (True, True)])
+def test_odd_segments(gpu, oracle, N, segments, D, Dv, kv_heads, token, norm):
+    harness, lasp, si = gpu
+    cfg = si.Config("odd", B=1, H=4, N=N, D=D, chunk=64, dtype="bf16", seed=8500 + N + D, token_decay=token, Dv=Dv)
+    inp = si.make_inputs(cfg, with_states=True)
+    print(f"case N={N} segments={segments} {D}x{Dv} kv_heads={kv_heads} token={token} norm={norm}", flush=True)
+    G = 4 // kv_heads if kv_heads else 1
+    inp.k, inp.v = inp.k[:, ::G].copy(), inp.v[:, ::G].copy()
+    k, v = oracle.group_expand(inp.k, G), oracle.group_expand(inp.v, G)
+    decay = None if token else inp.decay
+    eps = 1e-5 if norm else None
+    got = harness.run_gpu(inp, segments=segments, norm_eps=eps)
+    o, kvo = oracle.dims_fwd_brute(inp.q, k, v, decay, inp.kv_in, log_g=inp.log_g)
+    dout = inp.dout
+    if norm:
+        o, rstd = oracle.norm_fwd(o, eps)
+        dout = oracle.norm_bwd(inp.dout, o, rstd)
+    g = oracle.dims_bwd_brute(inp.q, k, v, dout, decay, inp.kv_in, inp.dkv_out, log_g=inp.log_g)
+    ref = dict(out=o, kv_out=kvo, dq=g[0], dk=oracle.group_reduce(g[1], G), dv=oracle.group_reduce(g[2], G), dkv_in=g[-1])
+    if token:
+        ref["dlog_g"] = g[3]
+    for name, r in ref.items():
+        emax, efro = harness.rel_errors(got[name], r)
+        print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
+        assert np.isfinite(emax) and emax <= TOL["bf16"] and efro <= TOL["bf16"], name

@@ -66,3 +66,20 @@ def test_forward_workgroups_stay_within_the_cus(dims):
             assert chains * n <= 256, (chains, N, n)
             # (segments are whole pairs of tiles of one length, so up to half of the share may be lost to rounding)
             assert chains * n >= min(128, chains * (N // 128) // 2), (chains, N, n)
+
+
+def test_state_cache_of_odd_tile_counts():
+    """bfloat16: a state per tile for odd tile counts of short sequences and of d=64, a state per pair otherwise; the
+    segments of a short odd sequence are single tiles, whose states the scratch holds."""
+    from paper_2404_02882_amd import lasp
+
+    def slots(H, N, D, **kw):
+        s = lasp.make_shape(1, H, N, D, 64, "bf16", **kw)
+        return lasp.state_cache_bytes(s) / (H * D * (kw.get("Dv") or D) * 2)
+
+    assert [slots(2, N, 128) for N in (448, 447, 385, 384, 512)] == [7, 7, 7, 3, 4]
+    assert slots(2, 448, 64, Dv=128) == 7 and slots(16, 64 * 9, 128) == 9      # 144 workgroups
+    assert slots(16, 64 * 11, 128) == 6 and slots(32, 5000, 128) == 40
+    assert slots(16, 5000, 64) == 79 and slots(16, 5056, 64) == 79 and slots(16, 5120, 64) == 40
+    assert slots(2, 448, 128, segments=3) == 7                                 # not a matter of the segments
+    assert lasp.scratch_bytes(lasp.make_shape(1, 2, 448, 128, 64, "bf16")) == 2 * 7 * 128 * 128 * 4
