@@ -161,8 +161,18 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
             auto weigh = [&](const typename E::frag &f, int ks) { return BWD ? dec.weigh_upto(ln, f, ks) : dec.template weigh_after<true>(ln, f, ks); };
             if constexpr (E::PLANES == 3) {
                 typename E::frag yd[NKS];
+                unsigned lows = 0;
+                auto weigh_all = [&](auto edge) __attribute__((always_inline)) {
+                    constexpr bool EDGE = decltype(edge)::value;
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) yd[ks] = weigh(E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w), ks);
+                    for (int ks = 0; ks < NKS; ++ks) {
+                        const typename E::frag y = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
+                        if constexpr (BWD) yd[ks] = dec.template weigh_upto<EDGE>(ln, y, ks, &lows);
+                        else yd[ks] = dec.template weigh_after<true, EDGE>(ln, y, ks, &lows);
+                    }
+                };
+                weigh_all(std::false_type{});
+                if (E::edge(lows)) weigh_all(std::true_type{});
                 add_tile(yd);
                 continue;
             }
