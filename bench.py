@@ -26,7 +26,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 MFMA rate
 
 # kernel name fragments of the rows of profiles/<config>_fwd_bwd_kernels.md that hold the HBM traffic per launch
-PROFILE_ROW = {"fwd_walk": "k_fwd<", "bwd_walk": "k_bwd", "fwd_local": ("k_local<", ", false, "), "bwd_local": ("k_local<", ", true, "),
+# (the first of several that is found; the local passes are told apart by their template arguments)
+PROFILE_ROW = {"fwd_walk": ("k_fwd<", "k_fwd8<"), "bwd_walk": "k_bwd", "fwd_local": "k_local<", "bwd_local": "k_local<",
                "bwd_apply": "backward (3 products)", "fwd_apply": "forward (1 product)", "state_reduce": "k_bidir_reduce<"}
 
 
@@ -38,7 +39,7 @@ def traffic_from_profile(config, kernel):
     path = os.path.join(ROOT, "profiles", f"{config}_fwd_bwd_kernels.md")
     if not os.path.exists(path):
         return None, None
-    want = PROFILE_ROW.get(kernel)
+    want = PROFILE_ROW.get(kernel, ())
     want = (want,) if isinstance(want, str) else want
     in_table = False
     for line in open(path):
@@ -53,7 +54,7 @@ def traffic_from_profile(config, kernel):
             m = re.match(r"`lasp::k_local<[^,]+, \d+, \d+, (true|false)", name)
             if not m or (m.group(1) == "true") != (kernel == "bwd_local"):
                 continue
-        elif not all(w in name for w in want) or "k_bwd" in want[0] and "k_bidir" in name:
+        elif not any(w in name for w in want):
             continue
         try:
             return int((float(cells[2]) + float(cells[4])) * 2**20), os.path.relpath(path, ROOT)

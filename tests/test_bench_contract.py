@@ -4,6 +4,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -49,6 +51,30 @@ def test_traffic_is_read_from_the_committed_profiles():
     assert 1792 * 16 * 32768 < got < 1.3 * 1792 * 16 * 32768
     assert bench.traffic_from_profile("c3", "fwd_local")[0] != bench.traffic_from_profile("c3", "bwd_local")[0]
     assert bench.traffic_from_profile("no_such_config", "bwd_walk") == (None, None)
+
+
+def test_traffic_of_either_forward_walk(tmp_path, monkeypatch):
+    """The forward walk runs as k_fwd or, in eight waves, as k_fwd8: the traffic is that of the one in the profile."""
+    sys.path.insert(0, ROOT)
+    import bench
+    for kernel in ("k_fwd", "k_fwd8"):
+        root = tmp_path / kernel
+        (root / "profiles").mkdir(parents=True)
+        (root / "profiles" / "x_fwd_bwd_kernels.md").write_text(
+            "## HBM traffic per launch\n| kernel | a | b | c | d |\n|---|---|---|---|---|\n"
+            "| `lasp::k_bwd8p<unsigned short, 64>` | 1.0 | 7.0 | 1.0 | 8.0 |\n"
+            f"| `lasp::{kernel}<unsigned short, 64>` | 1.0 | 2.0 | 1.0 | 3.0 |\n")
+        monkeypatch.setattr(bench, "ROOT", str(root))
+        assert bench.traffic_from_profile("x", "fwd_walk")[0] == 5 * 2**20, kernel
+        assert bench.traffic_from_profile("x", "bwd_walk")[0] == 15 * 2**20, kernel
+
+
+@pytest.mark.parametrize("config,kernels", [("c2", 4), ("c3", 4), ("c4", 4), ("g3", 4), ("n3", 4), ("m3", 4)])
+def test_every_committed_profile_serves_every_kernel(config, kernels):
+    sys.path.insert(0, ROOT)
+    import bench
+    got = [bench.traffic_from_profile(config, k)[0] for k in ("fwd_local", "fwd_walk", "bwd_local", "bwd_walk")]
+    assert len([x for x in got if x]) == kernels, got
 
 
 def test_head_groups_slice_every_tensor_with_a_head_axis():
