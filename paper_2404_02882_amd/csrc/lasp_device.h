@@ -287,7 +287,7 @@ struct WalkElem<float> {
     }
     // Whether a pair whose last parts (of any number of splits, or-ed) are `lows` may hold such values: true for these,
     // and for lows of 2 and more (x from 2^17 on), where it costs the second split but changes nothing.
-    static DEVI bool edge(unsigned lows) { return __builtin_expect(__builtin_amdgcn_ballot_w64(lows & 0x40004000u) != 0, 0); }
+    static DEVI bool edge(unsigned lows) { return __builtin_amdgcn_ballot_w64(lows & 0x40004000u) != 0; }
     static DEVI void split2_edge(float x0, float x1, unsigned (&s)[3]) {
         typedef __attribute__((ext_vector_type(2))) float f32x2;
         typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -330,7 +330,7 @@ struct WalkElem<float> {
         if (lows) return split<EDGE>(x, *lows);
         unsigned own = 0;
         frag f = split<false>(x, own);
-        if (edge(own)) f = split<true>(x, own);
+        if (__builtin_expect(edge(own), 0)) f = split<true>(x, own);
         return f;
     }
     static DEVI f32x8 join(const frag &s) {
@@ -497,7 +497,7 @@ struct TileMover {
             }
         };
         put(std::false_type{});
-        if (WalkElem<float>::edge(lows)) put(std::true_type{});
+        if (__builtin_expect(WalkElem<float>::edge(lows), 0)) put(std::true_type{});
     }
 };
 
@@ -925,8 +925,10 @@ DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *bounda
 }
 
 // Float data: the product of the state with fragments load(i), contracted over its rows in accumulator order. `lows` tells
-// the caller whether to take it again with EDGE; a walk asks once a tile, for everything that it split itself: a step of
-// 16 heads x 8192 tokens, d=128, takes 485 us so, 494 asked at every fragment, 473 without the question.
+// the caller whether to take it again with EDGE; a walk asks once a tile, for everything that it split itself. A step of
+// 16 heads x 8192 tokens, d=128, takes 469 us so and 463 without the question (asked at every fragment 494 against 468);
+// 128 x 1000 at d=64 195 and 189. The branches are marked as rare where they stand, or the second products lie in the
+// loop's way: 473 and 198.
 template <typename E, bool EDGE, int DB, typename Load>
 DEVI f32x16 state_product(const f32x16 (&st)[DB], unsigned &lows, Load load) {
     f32x16 acc = {0};
@@ -980,7 +982,7 @@ DEVI void store_masked_scores(const Lane &ln, bf16_t *sP, const f32x16 &acc, int
             }
         };
         put(std::false_type{});
-        if (WalkElem<T>::edge(lows)) put(std::true_type{});
+        if (__builtin_expect(WalkElem<T>::edge(lows), 0)) put(std::true_type{});
     }
 }
 

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                     }
                 };
                 weigh_all(std::false_type{});
-                if (E::edge(lows)) weigh_all(std::true_type{});
+                if (__builtin_expect(E::edge(lows), 0)) weigh_all(std::true_type{});
                 add_tile(yd);
                 continue;
             }
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
                 for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<!RAGGED, EDGE>(ln, vf[ks], ks, &lows);
             };
             inter_and_weigh(std::false_type{});
-            if (E::edge(lows)) inter_and_weigh(std::true_type{});
+            if (__builtin_expect(E::edge(lows), 0)) inter_and_weigh(std::true_type{});
             decay_and_add<E>(ln, st, lamC, sK, LDD, vf);
         } else {
             load_vf();
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
                 for (int ks = 0; ks < NKS; ++ks) x2[ks] = dec.template weigh_upto<EDGE>(ln, x2[ks], ks, &lows);
             };
             inter_and_weigh(std::false_type{});
-            if (E::edge(lows)) inter_and_weigh(std::true_type{});
+            if (__builtin_expect(E::edge(lows), 0)) inter_and_weigh(std::true_type{});
             // dKV <- lambda^CT dKV + (Lambda Q)^T dO, in this group's orientation
             decay_and_add<E>(ln, st, dec.whole(nv), sUA, LDD, x2);
         }
