@@ -24,7 +24,7 @@ struct Plan {
                         // that produces dQ starts)
     bool ragged;        // the last tile is short, or (bfloat16, backward) the last pair of tiles has only one
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
-    bool norm;          // output rows are normalised (forward epilogue, backward prologue); token == false
+    bool norm;          // output rows are normalised (forward epilogue, backward prologue)
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
 };
 
@@ -35,11 +35,11 @@ struct FwdArgs {
     void *out;
     float *kv_out;
     void *cache;          // may be null
-    float *scratch;       // [B*H][nseg][D][D]
+    float *scratch;       // [B*H][nseg][d_k][d_v]
     float *seglog;        // per-token decay only: [B*H][nseg], log2 of the decay over each segment
     float *rstd_out;      // norm only: [B][H][N]
     float eps;            // norm only
-    bool states_only;     // rebuild the state cache only: q, out, rstd_out are not touched (kv_out still is)
+    bool states_only;     // rebuild the state cache only: q, out, rstd_out are not touched, kv_out may be null
 };
 
 struct BwdArgs {
@@ -79,7 +79,7 @@ struct KernelEvents {
 hipError_t allow_dynamic_lds(const void *kernel, size_t bytes);
 
 // The library's own scratch for lasp_fwd_noalloc: a file-scope device array of kStaticScratchBytes
-// (32 MiB: 512 float [128][128] segment states, the automatic plan of 16 heads). static_scratch() returns
+// (32 MiB: 512 float [128][128] segment states; an automatic bfloat16 plan of up to 256 heads takes half of it). static_scratch() returns
 // its address on the current device (resolved once per device).
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 hipError_t static_scratch(void **ptr);

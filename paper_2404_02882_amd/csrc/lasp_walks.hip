@@ -28,7 +28,8 @@
 // (Alg. 2) folded onto one GPU; there are no atomics, so results are
 // bit-reproducible.
 //
-// Wave tiling. A workgroup has D/32 waves; wave w owns the 32-wide column block
+// Wave tiling. A workgroup has D/32 waves, or two groups of as many (k_fwd8 and
+// the backward walks); wave w of a group owns the 32-wide column block
 // w of every [.][D] output tile and of the state, so the state tile it holds in
 // MFMA accumulator layout can be fed back as the B operand of the next product
 // without leaving registers (the contraction index is permuted identically on
@@ -713,12 +714,12 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
 //
 // k_bwdkv (float data) produces dK, dV and the dKV update only; dQ, which needs no
 // dKV but the forward states, is a forward walk of its own (k_fwd, kDq) from one
-// kept state per segment. A float state per 32-token tile would be as many bytes as
-// Q, K, V and O together, written by the forward pass and read here (the cache this
-// replaces: 268 MB each way at 16 heads x 8192 tokens, d=128; that step 667 -> 439 us
-// with this, the operand split of WalkElem and 512 forward workgroups, of it backward
-// 488 -> 318). Both walks are bound by the split's vector instructions and the matrix
-// instructions, which a wave issues one after the other (1250 and 120 a tile).
+// kept state per automatic segment. A float state per 32-token tile would be as many
+// bytes as Q, K, V and O together, written by the forward pass and read here (268 MB
+// each way at 16 heads x 8192 tokens, d=128; that step, 682 us with such a cache and
+// fp32 matrix instructions, takes 469 with this, the operand split of WalkElem and 512
+// forward workgroups). Both walks are bound by the split's vector instructions and the
+// matrix instructions, which a wave issues one after the other (about 1300 and 120 a tile).
 // Workgroups of 2 * D/32 waves. Two groups of waves keep dKV in registers in the
 // orientation their product needs, so nothing is exchanged:
 //   group 0 holds dKV[a][c in w] (rows a) and produces dV (dV_inter contracts a),
@@ -894,7 +895,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
 
 // ---------------------------------------------------------------------------
 // k_bwd8p: the backward walk for bfloat16 tiles of 64 tokens, one workgroup of
-// 2 * D/32 waves per CU. Same mathematics as k_bwd, different residency:
+// 2 * D/32 waves per CU:
 //   - every input tile, the masked score tiles and the cached state live in LDS
 //     at once;
 //   - the waves form two groups that each keep dKV in registers in the

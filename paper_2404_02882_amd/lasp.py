@@ -320,7 +320,7 @@ def lasp_bidir_bwd(shape: Shape, k, v, dout, kv, dkv, dq, dk, dv, stream=None) -
 
 
 class Workspace:
-    """Device buffers one (shape) needs besides the tensors: per-tile state cache and scratch."""
+    """Device buffers one (shape) needs besides the tensors: state cache and scratch."""
 
     def __init__(self, shape: Shape, device="cuda", with_cache=True):
         self.shape = shape

@@ -4,7 +4,7 @@ A sequence of N tokens is held as T shards of N/T tokens, each a contiguous
 [B,H,N/T,D] tensor (what one rank of the paper holds). Forward runs the shards
 in order and hands kv_out of one to the next as kv_in (Alg. 2: Recv KV from
 rank i-1, Send KV to rank i+1); backward runs them in reverse and hands dkv_in
-of one to the previous as dkv_out (Alg. 3). Every shard keeps the per-tile
+of one to the previous as dkv_out (Alg. 3). Every shard keeps the
 state cache its forward call filled until its backward call has used it.
 All buffers are allocated once, up front; the calls only enqueue kernels.
 """

@@ -69,7 +69,8 @@ def test_sizes_and_plan(L):
     assert 1 <= L.num_segments(r) <= 3
     bad = L.make_shape(1, 1, 128, 96, 64, "bf16")
     assert L.tile_tokens(bad) == 0 and L.scratch_bytes(bad) == 0 and L.state_cache_bytes(bad) == 0
-    # a length that is not a multiple of the tile: one more (short) tile, and scratch for the synthesised log g
+    # a length that is not a multiple of the tile: one more (short) tile; its reported scratch is larger
+    # (two values per token beside the states: the size callers have been told, although one lambda per head needs none)
     rag = L.make_shape(1, 2, 64 * 3 + 5, 64, 64, "bf16")
     full = L.make_shape(1, 2, 64 * 4, 64, 64, "bf16")
     assert L.state_cache_bytes(rag) == L.state_cache_bytes(full)
@@ -231,7 +232,7 @@ def test_norm_rejects_before_launch(L):
     assert call(*a) == 5
     a = list(ok_args); a[8] = out                    # rstd aliases out
     assert call(*a) == 6
-    # a length that is not a multiple of the tile is a valid shape; it needs more scratch (log g is synthesised)
+    # a length that is not a multiple of the tile is a valid shape; its reported scratch is larger
     ragged = L.make_shape(1, 1, 100, 64, 64, "bf16")
     assert L.check_shape(ragged) == 0 and L.scratch_bytes(ragged) > sb
     a = list(ok_args); a[0] = ctypes.byref(ragged)

@@ -1,6 +1,5 @@
 """Sub-sequence lengths that are not a multiple of the kernel tile (a short last tile), through the
-C-ABI against the brute-force oracle: the per-token-decay entry points handle it natively; with one
-lambda per head the library runs the same kernels on log g = log(lambda). Tolerances 1e-4 / 2e-2."""
+C-ABI against the brute-force oracle, with a decay per token and with one lambda per head. Tolerances 1e-4 / 2e-2."""
 import sys
 
 import numpy as np
@@ -35,8 +34,8 @@ CASES = [
     # dtype, D, N, segments
     ("f32", 64, 1, 0), ("f32", 64, 33, 0), ("f32", 128, 32 * 5 + 7, 3),
     ("bf16", 64, 5, 0), ("bf16", 64, 63, 0), ("bf16", 64, 65, 2), ("bf16", 128, 100, 0),
-    ("bf16", 128, 64 * 5 + 17, 3),      # odd tile count: one cached state per tile
-    ("bf16", 128, 64 * 7 + 63, 2),      # even tile count: pair cache, 128-token local pass with a short last step
+    ("bf16", 128, 64 * 5 + 17, 3),      # even tile count, the last one short
+    ("bf16", 128, 64 * 7 + 63, 2),      # the same, one token short: 128-token local pass with a short last step
     ("bf16", 64, 128 * 3 + 1, 4),
 ]
 

@@ -30,7 +30,7 @@ CASES = [
     ("bf16", 64, 64 * 6, 2, 0, False),
     ("bf16", 128, 64 * 12, 1, 4, False),     # even tile count: one cached state per pair of tiles
     ("bf16", 128, 64 * 5, 1, 2, False),      # odd tile count
-    ("bf16", 128, 64 * 9 + 21, 3, 0, False), # short last tiles (log g synthesised)
+    ("bf16", 128, 64 * 9 + 21, 3, 0, False), # short last tiles
     ("f32", 128, 32 * 6, 2, 2, True),
     ("bf16", 128, 64 * 8, 2, 0, True),
     ("bf16", 64, 64 * 5 + 3, 1, 2, True),

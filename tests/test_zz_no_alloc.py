@@ -57,7 +57,7 @@ def test_two_calls_in_a_row_second_smaller(gpu):
     run_pair(gpu, 2, 4, 64 * 24, 128, 128, "bf16", seed=4101, segments=6)
     run_pair(gpu, 1, 2, 64 * 6, 64, 64, "bf16", seed=4102, segments=3)
     run_pair(gpu, 1, 2, 32 * 9, 64, 64, "f32", seed=4103, segments=0)
-    # a length that is not a multiple of the tile (scratch then also holds the synthesised log decay)
+    # a length that is not a multiple of the tile (the reported scratch is larger then)
     run_pair(gpu, 1, 3, 64 * 5 + 17, 128, 128, "bf16", seed=4104, segments=2)
 
 
