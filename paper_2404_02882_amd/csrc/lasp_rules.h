@@ -20,17 +20,17 @@ inline bool cache_every_tile(int ntiles, long long chains, int D) {
 }
 
 // Tiles per segment of a bfloat16 pass that was asked for `want`: whole pairs where the cache has pairs. By tiles the
-// backward pass takes what it was asked for. The forward walk, whose chain is shorter, takes single tiles up to 72 workgroups
-// (2 heads x 3 tiles 13.8 us / in pairs 15.2, 2 x 9 17.1 / 18.7, 4 x 17 19.9 / 20.5, 8 x 11 20.6 / 20.4), but not from five
-// to eight tiles, where pairs make at most four segments and need no scan (16 x 7 21.1 / 18.0, 8 x 5 18.3 / 16.4); and
-// other odd numbers at d=64 while three workgroups share a CU (16 heads x 79 tiles, three / four 27.0 / 29.3, 32 x 79,
-// five / six 35.0 / 37.7).
+// backward pass takes what it was asked for. The forward walk, whose chain is shorter, takes single tiles up to 88 workgroups
+// (d=128, 2 heads x 3 tiles 13.8 us / in pairs 15.2, 2 x 9 17.1 / 18.7, 4 x 17 19.9 / 20.5, 8 x 11 20.6 / 20.4 and with a
+// decay per token 20.4 / 21.6, 16 x 9 23.0 / 22.2) or, at d=64, 208 (16 x 13 15.9 / 16.8), but not from five to eight tiles,
+// where pairs make at most four segments and need no scan (16 x 7 21.1 / 18.0, 8 x 5 18.3 / 16.4); and other odd numbers at
+// d=64 while three workgroups share a CU (16 heads x 79 tiles, three / four 27.0 / 29.3, 32 x 79, five / six 35.0 / 37.7).
 inline int segment_tiles(int want, int ntiles, long long chains, int D, bool every_tile, bool backward) {
     if (want % 2 == 0) return want;
     bool keep = every_tile;
     if (!backward) {
         const long long workgroups = chains * ((ntiles + want - 1) / want);
-        keep = keep && (want == 1 ? workgroups <= 72 && (ntiles <= 4 || ntiles > 8) : D == 64 && workgroups <= 3 * kOnePerCu);
+        keep = keep && (want == 1 ? workgroups <= (D == 64 ? 208 : 88) && (ntiles <= 4 || ntiles > 8) : D == 64 && workgroups <= 3 * kOnePerCu);
     }
     return keep ? want : want + 1;
 }
