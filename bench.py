@@ -254,7 +254,8 @@ def main():
     peak_mem = torch.cuda.max_memory_allocated()
 
     # ---- roofline of the dominant kernel (largest share of the step) ----
-    tok_heads_per_launch = B * (H // args.head_groups) * (N // T)
+    # (a launch takes several sub-sequences where that fills the device: nf launches of `steps` passes over all tokens)
+    tok_heads_per_launch = B * H * N * args.steps // nf
     esz = 2 if cfg.dtype == "bf16" else 4
     per_launch_ms = {"fwd_local": kernel_ms["fwd"][0] / nf, "fwd_scan": kernel_ms["fwd"][1] / nf,
                      "fwd_walk": kernel_ms["fwd"][2] / nf, "bwd_local": kernel_ms["bwd"][0] / nb_calls,

@@ -298,6 +298,45 @@ int lasp_gated_bwd_norm(const lasp_shape *shape, const void *q, const void *k, c
                         float *dkv_in, void *scratch, size_t scratch_bytes, void *hip_stream);
 
 /*
+ * ---- A whole sequence -------------------------------------------------------
+ * The loop over the T sub-sequences of a sequence (the paper's ring of ranks on one
+ * device) as one call: what T calls of lasp_fwd (lasp_bwd, lasp_gated_*, *_norm)
+ * compute that hand kv_out on as the next kv_in (dkv_in as the previous dkv_out),
+ * every sub-sequence with the same shape and with buffers of its own (arrays of T
+ * device pointers, themselves in host memory, not kept). Several sub-sequences go
+ * through a launch together where that fills the device and their buffers do not
+ * overlap; sums are then taken in another order than call by call.
+ *
+ *   decay      one pointer (lambda [H], shared), or with token != 0 T pointers (log g).
+ *   rstd       NULL = outputs are not normalised (eps, and out in lasp_seq_bwd, are
+ *              then not looked at).
+ *   kv         T + 1 states. kv[t + 1] is the state after sub-sequence t. Forward:
+ *              kv[0] receives a copy of kv_in (it may be kv_in; it is not touched when
+ *              kv_in is NULL = zeros). Backward: as the forward call left them, kv[0]
+ *              NULL = zeros; read where the states are rebuilt, and with a decay per
+ *              token.
+ *   dkv        T + 1 gradients: dkv[t] is the one w.r.t. kv[t]; dkv[T] receives a copy
+ *              of dkv_out (it may be dkv_out; it is not touched when that is NULL).
+ *   state_cache  NULL, or a NULL first pointer, = none: kept (forward), the states are
+ *              rebuilt (backward). A cache of lasp_seq_fwd serves lasp_seq_bwd of the
+ *              same shape and T.
+ *   scratch    lasp_seq_scratch_bytes() bytes (recompute: for sequences that keep no
+ *              cache; those launch several sub-sequences together only while their
+ *              caches, which then lie in the scratch, take at most 64 MiB).
+ */
+size_t lasp_seq_scratch_bytes(const lasp_shape *shape, int32_t T, int32_t token, int32_t recompute);
+int lasp_seq_fwd(const lasp_shape *shape, int32_t T, const void *const *q, const void *const *k,
+                 const void *const *v, const float *kv_in, const float *const *decay, int32_t token,
+                 float eps, void *const *out, float *const *rstd, float *const *kv,
+                 void *const *state_cache, void *scratch, size_t scratch_bytes, void *hip_stream);
+int lasp_seq_bwd(const lasp_shape *shape, int32_t T, const void *const *q, const void *const *k,
+                 const void *const *v, const void *const *out, const float *const *rstd,
+                 const void *const *dout, const float *const *kv, const float *dkv_out,
+                 const float *const *decay, int32_t token, const void *const *state_cache,
+                 void *const *dq, void *const *dk, void *const *dv, float *const *dlog_g,
+                 float *const *dkv, void *scratch, size_t scratch_bytes, void *hip_stream);
+
+/*
  * ---- Bidirectional (unmasked) attention ---------------------------------------
  * Without the causal mask the attention of Sec. 3.1 is O = (Q K^T) V, which
  * associativity turns into the right-product form O = Q (K^T V) of Eq. (3)

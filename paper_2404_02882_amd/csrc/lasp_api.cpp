@@ -3,8 +3,10 @@
 #include "../../include/lasp.h"
 #include "../../include/lasp_profile.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <initializer_list>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -43,9 +45,9 @@ bool valid_dims(const lasp_shape *s) {
     return true;
 }
 
-// Segments per head of a pass when the caller leaves the choice to the library.
-int auto_segments(const lasp::Plan &p, Pass pass) {
-    const int64_t chains = (int64_t)p.B * p.H;
+// Segments per head of a pass when the caller leaves the choice to the library. chains: heads times the sub-sequences that
+// go through one launch.
+int auto_segments(const lasp::Plan &p, Pass pass, int64_t chains) {
     const bool two_per_cu = p.dtype == LASP_F32 ? pass == kForward || p.D == 64 : pass == kForward && (p.dk == 64 || p.dv == 64);
     const int target = two_per_cu ? kTargetWorkgroupsLatencyBound : kTargetWorkgroups;
     int64_t round = two_per_cu && pass == kForward ? chains / 2 : 0;
@@ -63,7 +65,8 @@ int auto_segments(const lasp::Plan &p, Pass pass) {
     return want < 1 ? 1 : want;
 }
 
-int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false, bool norm = false) {
+// group: sub-sequences that a launch takes (at most)
+int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false, bool norm = false, int group = 1) {
     if (!s) return LASP_ERR_NULL;
     if (s->dtype != LASP_F32 && s->dtype != LASP_BF16) return LASP_ERR_DTYPE;
     if (!valid_dims(s)) return LASP_ERR_SHAPE;
@@ -80,16 +83,17 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     int want = s->segments;
     if (want < 0 || want > p->ntiles) return LASP_ERR_SHAPE;
     const bool two_byte = p->dtype == LASP_BF16;   // tiles are walked in pairs, or one by one
-    const int64_t chains = (int64_t)s->B * s->H;
+    const int64_t chains = (int64_t)s->B * s->H * group;
+    p->shards = 1;
     p->token = token;
     p->norm = norm;
-    if (two_byte) {
-        p->cache_tiles = lasp::cache_every_tile(p->ntiles, chains, p->D) ? 1 : 2;
+    if (two_byte) {   // (whatever the group: the layout of a sub-sequence's cache does not depend on the others)
+        p->cache_tiles = lasp::cache_every_tile(p->ntiles, (int64_t)s->B * s->H, p->D) ? 1 : 2;
     } else {
-        const int fwd_auto = auto_segments(*p, kForward);
+        const int fwd_auto = auto_segments(*p, kForward, chains);
         p->cache_tiles = (p->ntiles + fwd_auto - 1) / fwd_auto;
     }
-    if (want == 0) want = auto_segments(*p, pass);
+    if (want == 0) want = auto_segments(*p, pass, chains);
     p->ragged = s->N % (two_byte && pass == kBackward ? 2 * p->tile : p->tile) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
     if (two_byte)
@@ -113,25 +117,30 @@ struct ScratchLayout {
     size_t states, seglog, rtok, dk_part, dv_part, total;  // byte offsets of the regions (states = 0), total size
 };
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
-bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l) {
+size_t rtok_bytes(const lasp::Plan &p) { return round256((size_t)p.B * p.H * p.N * sizeof(float)); }
+bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l, int group = 1) {
     lasp::Plan f, b;
-    if (make_plan(shape, kForward, &f, token) != LASP_OK || make_plan(shape, kBackward, &b, token) != LASP_OK) return false;
-    const size_t nseg = f.nseg > b.nseg ? f.nseg : b.nseg;  // one buffer serves both passes
-    const size_t chains = (size_t)f.B * f.H;
+    const size_t chains = (size_t)(shape ? shape->B : 0) * (shape ? shape->H : 0);
+    size_t nseg = 0;   // of all sub-sequences of a launch; one buffer serves both passes, and launches of one sub-sequence
+    for (int n : {1, group}) {
+        if (make_plan(shape, kForward, &f, token, false, n) != LASP_OK || make_plan(shape, kBackward, &b, token, false, n) != LASP_OK)
+            return false;
+        nseg = std::max<size_t>(nseg, n * std::max(f.nseg, b.nseg));
+    }
     l->states = 0;
     l->seglog = round256(chains * nseg * f.dk * f.dv * sizeof(float));   // segment states, [d_k][d_v] floats each
     l->rtok = l->seglog;
     size_t end = l->seglog;
     const bool ragged = f.N % f.tile != 0;
     if (f.token || ragged) {
-        const size_t per_token = round256(chains * (size_t)f.N * sizeof(float));
+        const size_t per_token = rtok_bytes(f);   // of one sub-sequence
         l->rtok = l->seglog + round256(chains * nseg * sizeof(float));
-        end = l->rtok + (f.token ? 1 : 2) * per_token;
+        end = l->rtok + (f.token ? group * per_token : 2 * per_token);
     }
     l->dk_part = l->dv_part = end;
     if (f.kvdiv > 1) {
-        l->dv_part = l->dk_part + round256(chains * (size_t)f.N * f.dk * elem_bytes(f.dtype));
-        end = l->dv_part + round256(chains * (size_t)f.N * f.dv * elem_bytes(f.dtype));
+        l->dv_part = l->dk_part + round256(group * chains * f.N * f.dk * elem_bytes(f.dtype));
+        end = l->dv_part + round256(group * chains * f.N * f.dv * elem_bytes(f.dtype));
     }
     l->total = end;
     return true;
@@ -161,7 +170,7 @@ bool overlap(Span a, Span b) {
 
 // Outputs must not overlap inputs or each other, and the kernels move data in 16-byte pieces.
 // NULL (an absent optional buffer) passes both checks.
-int check_buffers(const std::vector<Span> &ins, const std::vector<Span> &outs) {
+int check_buffers(std::initializer_list<Span> ins, std::initializer_list<Span> outs) {
     for (const Span &x : ins)
         if ((uintptr_t)x.p % 16 != 0) return LASP_ERR_ALIGN;
     for (const Span &x : outs)
@@ -175,60 +184,210 @@ int check_buffers(const std::vector<Span> &ins, const std::vector<Span> &outs) {
     return LASP_OK;
 }
 
-// One forward call of any flavour: `token` selects the decay model (decay = lambda [H] or log g
-// [B][H][N]), `norm` the fused output normalisation (eps, rstd).
+// Whether sub-sequences can share a launch: no output of one may touch another's buffers (in a loop over them that is the
+// caller's affair: the later call reads what the earlier one wrote, or writes over it).
+class Together {
+    struct Item {
+        const char *begin, *end;
+        bool out;
+    };
+    std::vector<Item> items;
+
+public:
+    void in(const void *p, size_t n) {
+        if (p) items.push_back({(const char *)p, (const char *)p + n, false});
+    }
+    void out(const void *p, size_t n) {
+        if (p) items.push_back({(const char *)p, (const char *)p + n, true});
+    }
+    bool disjoint() {
+        std::sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.begin < b.begin; });
+        const char *any_end = nullptr, *out_end = nullptr;   // ends of what has begun so far
+        for (const Item &x : items) {
+            if (x.begin < out_end || (x.out && x.begin < any_end)) return false;
+            any_end = std::max(any_end, x.end);
+            if (x.out) out_end = std::max(out_end, x.end);
+        }
+        return true;
+    }
+};
+
+template <typename P>
+const P at(const P *list, int t) { return list ? list[t] : nullptr; }
+// distances of list[first + i] from list[first], for the `n` sub-sequences of a launch
+template <typename P>
+lasp::Offsets offsets(const P *list, int first, int n) {
+    lasp::Offsets o{};
+    if (list)
+        for (int i = 1; i < n; ++i) o.at[i] = (const char *)list[first + i] - (const char *)list[first];
+    return o;
+}
+lasp::Offsets strides(size_t bytes) {
+    lasp::Offsets o{};
+    for (int i = 1; i < lasp::kMaxShards; ++i) o.at[i] = (long long)(i * bytes);
+    return o;
+}
+
+// Sub-sequences of a T-part sequence that go through one launch. Every launch of one sub-sequence leaves the device idle
+// at both ends and needs segments of its own to fill it; several together are cut into fewer segments (whose states are
+// that much less to move) and scanned once, at the price of a local pass over each but one. As many as still leave about as
+// many workgroups as a launch of one has: more would go through in several rounds, and read more in the local pass.
+// Step one by one / together, us: 16 heads x 1024 tokens x 4, d=64, in a graph 149 / 64; 32 heads x 4096 x 2 with four K/V
+// heads 314 / 261; 16 x 32768 x 8 3890 / 3658. (The longer kernel arguments cost every launch 0.1 - 0.2 us of host time.)
+int shards_per_launch(const lasp_shape *s, int T, bool token) {
+    if (T < 2 || s->segments != 0) return 1;
+    const int64_t chains = (int64_t)s->B * s->H;
+    auto workgroups = [&](Pass pass, int group) {
+        lasp::Plan p;
+        return make_plan(s, pass, &p, token, false, group) == LASP_OK ? chains * group * p.nseg : 0;
+    };
+    const int64_t most = std::min<int64_t>(std::min(T, lasp::kMaxShards), lasp::kOnePerCu / chains);
+    for (int n = (int)most; n > 1; --n) {
+        const int launches = (T + n - 1) / n, group = (T + launches - 1) / launches;   // of about one size
+        if (10 * workgroups(kForward, group) >= 9 * workgroups(kForward, 1) && 10 * workgroups(kBackward, group) >= 9 * workgroups(kBackward, 1))
+            return group;
+    }
+    return 1;
+}
+// The same for a sequence whose backward pass rebuilds the states: the caches of a launch's sub-sequences lie in its
+// scratch, which is there to save memory.
+constexpr size_t kRebuiltCacheLimit = (size_t)64 << 20;
+int shards_per_launch(const lasp_shape *s, int T, bool token, bool recompute) {
+    int group = shards_per_launch(s, T, token);
+    if (recompute && group > 1 && group * cache_bytes(s, token) > kRebuiltCacheLimit) group = 1;
+    return group;
+}
+
+// One forward call of any flavour, over T sub-sequences of one shape (T = 1: a plain call): `token` selects the decay model
+// (decay = lambda [H], one for all, or log g [B][H][N] of each), `norm` the fused output normalisation (eps, rstd). kv_out[t]
+// is what sub-sequence t leaves and t + 1 starts from.
 struct FwdCall {
     const lasp_shape *shape;
-    const void *q, *k, *v;
-    const float *kv_in, *decay;
+    int T, group;
+    const void *const *q, *const *k, *const *v;
+    const float *kv_in;
+    float *kv_copy;   // receives kv_in; may be NULL
+    const float *const *decay;
     bool token, norm;
     float eps;
-    void *out;
-    float *rstd, *kv_out;
-    void *cache, *scratch;
+    void *const *out;
+    float *const *rstd, *const *kv_out;
+    void *const *cache;
+    void *scratch;
     size_t scratch_bytes;
     void *stream;
 };
 
+// The plan of a launch of one sub-sequence of a sequence that goes in groups: its cache is that of the group's.
+int single_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, const lasp::Plan &of_group) {
+    const int rc = make_plan(s, pass, p, of_group.token, of_group.norm);
+    p->cache_tiles = of_group.cache_tiles;
+    return rc;
+}
+
 int run_fwd_call(const FwdCall &c) {
-    lasp::Plan p;
-    int rc = make_plan(c.shape, kForward, &p, c.token, c.norm);
-    if (rc != LASP_OK) return rc;
-    if (!c.q || !c.k || !c.v || !c.decay || !c.out || !c.kv_out || (c.norm && !c.rstd)) return LASP_ERR_NULL;
+    lasp::Plan p, one;
+    int rc = make_plan(c.shape, kForward, &p, c.token, c.norm, c.group);
+    if (rc != LASP_OK || (rc = single_plan(c.shape, kForward, &one, p)) != LASP_OK) return rc;
+    for (int t = 0; t < c.T; ++t)
+        if (!c.q[t] || !c.k[t] || !c.v[t] || !c.decay[c.token ? t : 0] || !c.out[t] || !c.kv_out[t] || (c.norm && !at(c.rstd, t)))
+            return LASP_ERR_NULL;
     if (c.norm && (!std::isfinite(c.eps) || c.eps < 0.0f)) return LASP_ERR_SHAPE;
     ScratchLayout l;
-    scratch_layout(c.shape, c.token, &l);
+    scratch_layout(c.shape, c.token, &l, c.group);
     if (!c.scratch || c.scratch_bytes < l.total) return LASP_ERR_WORKSPACE;
 
     const size_t esz = elem_bytes(p.dtype);
     const size_t qb = (size_t)p.B * p.H * p.N * p.dk * esz, ob = (size_t)p.B * p.H * p.N * p.dv * esz;   // q / out
     const size_t sb = (size_t)p.B * p.H * p.dk * p.dv * sizeof(float);
     const size_t gb = (size_t)p.B * p.H * p.N * sizeof(float);
-    rc = check_buffers({{c.q, qb}, {c.k, qb / p.kvdiv}, {c.v, ob / p.kvdiv}, {c.kv_in, sb},
-                        {c.decay, c.token ? gb : p.H * sizeof(float)}},
-                       {{c.out, ob}, {c.rstd, gb}, {c.kv_out, sb}, {c.cache, cache_bytes(c.shape, c.token)},
-                        {c.scratch, l.total}});
-    if (rc != LASP_OK) return rc;
-
+    const size_t cb = c.cache ? cache_bytes(c.shape, c.token) : 0, db = c.token ? gb : p.H * sizeof(float);
     hipStream_t stream = (hipStream_t)c.stream;
+    // kv_in goes to kv_copy with the walk that starts from it, unless it lies in what the call writes
+    const float *kv_in = c.kv_in;
+    float *kv_copy = kv_in == c.kv_copy ? nullptr : c.kv_copy;
+    if (kv_in && kv_copy) {
+        const Span in{kv_in, sb};
+        bool apart = (uintptr_t)kv_in % 16 == 0 && !overlap(in, {kv_copy, sb}) && !overlap(in, {c.scratch, l.total});
+        for (int t = 0; t < c.T && apart; ++t)
+            apart = !overlap(in, {c.out[t], ob}) && !overlap(in, {at(c.rstd, t), gb}) && !overlap(in, {c.kv_out[t], sb}) && !overlap(in, {at(c.cache, t), cb});
+        if (!apart) {
+            if (hipMemcpyAsync(kv_copy, kv_in, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
+            kv_in = kv_copy;
+            kv_copy = nullptr;
+        }
+    } else {
+        kv_copy = nullptr;
+    }
+    for (int t = 0; t < c.T; ++t) {
+        rc = check_buffers({{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {t ? c.kv_out[t - 1] : kv_in, sb}, {c.decay[c.token ? t : 0], db}},
+                           {{c.out[t], ob}, {at(c.rstd, t), gb}, {c.kv_out[t], sb}, {at(c.cache, t), cb}, {c.scratch, l.total}, {t ? nullptr : kv_copy, sb}});
+        if (rc != LASP_OK) return rc;
+    }
+
     char *scr = (char *)c.scratch;
-    const lasp::FwdArgs a{c.q, c.k, c.v, c.kv_in, c.decay, c.out, c.kv_out, c.cache, (float *)scr,
-                    p.token ? (float *)(scr + l.seglog) : nullptr, c.rstd, c.eps, false};
-    return lasp::launch_fwd(p, a, stream, next_slot(0)) == hipSuccess ? LASP_OK : LASP_ERR_HIP;
+    auto launch = [&](int first, int n) {
+        lasp::Plan use = n > 1 ? p : one;
+        use.shards = n;
+        lasp::FwdArgs a{c.q[first], c.k[first], c.v[first], first ? c.kv_out[first - 1] : kv_in, c.decay[c.token ? first : 0], c.out[first],
+                        c.kv_out[first], at(c.cache, first), (float *)scr, p.token ? (float *)(scr + l.seglog) : nullptr, at(c.rstd, first),
+                        c.eps, false, first ? nullptr : kv_copy, {}};
+        if (n > 1) {
+            a.sh.q = offsets(c.q, first, n);
+            a.sh.k = offsets(c.k, first, n);
+            a.sh.v = offsets(c.v, first, n);
+            if (c.token) a.sh.decay = offsets(c.decay, first, n);
+            a.sh.out = offsets(c.out, first, n);
+            a.sh.rstd = offsets(c.rstd, first, n);
+            a.sh.kv_out = offsets(c.kv_out, first, n);
+            a.sh.cache = offsets(c.cache, first, n);
+        }
+        return lasp::launch_fwd(use, a, stream, next_slot(0)) == hipSuccess;
+    };
+    for (int first = 0; first < c.T; first += c.group) {
+        const int n = std::min(c.group, c.T - first);
+        if (n > 1) {
+            Together all;
+            all.in(first ? c.kv_out[first - 1] : kv_in, sb);
+            all.in(c.token ? nullptr : c.decay[0], db);
+            for (int t = first; t < first + n; ++t) {
+                all.in(c.q[t], qb);
+                all.in(c.k[t], qb / p.kvdiv);
+                all.in(c.v[t], ob / p.kvdiv);
+                all.in(c.token ? c.decay[t] : nullptr, db);
+                all.out(c.out[t], ob);
+                all.out(at(c.rstd, t), gb);
+                all.out(c.kv_out[t], sb);
+                all.out(at(c.cache, t), cb);
+            }
+            if (!all.disjoint()) {
+                for (int t = first; t < first + n; ++t)
+                    if (!launch(t, 1)) return LASP_ERR_HIP;
+                continue;
+            }
+        }
+        if (!launch(first, n)) return LASP_ERR_HIP;
+    }
+    return LASP_OK;
 }
 
-// One backward call of any flavour. `yn`, `rstd`: norm only; `kv_out`, `dlog_g`: per-token decay only.
+// One backward call of any flavour, over T sub-sequences of one shape. `yn`, `rstd`: norm only; `kv_out`, `dlog_g`: per-token
+// decay only. kv_in[t] (the state sub-sequence t started from; NULL = zeros) is used only where it has no cache: the states are then rebuilt from
+// it. dkv_in[t] is what sub-sequence t leaves and t - 1 receives from the right.
 struct BwdCall {
     const lasp_shape *shape;
-    const void *q, *k, *v, *dout;
-    const float *kv_in;     // used only when cache is NULL (the states are then rebuilt from it); NULL = zeros
-    const float *dkv_out, *decay;
+    int T, group;
+    const void *const *q, *const *k, *const *v, *const *dout;
+    const float *const *kv_in;
+    const float *dkv_out;
+    float *dkv_copy;   // receives dkv_out; may be NULL
+    const float *const *decay;
     bool token, norm;
-    const void *yn;
-    const float *rstd, *kv_out;
-    const void *cache;
-    void *dq, *dk, *dv;
-    float *dlog_g, *dkv_in;
+    const void *const *yn;
+    const float *const *rstd, *const *kv_out;
+    const void *const *cache;
+    void *const *dq, *const *dk, *const *dv;
+    float *const *dlog_g, *const *dkv_in;
     void *scratch;
     size_t scratch_bytes;
     void *stream;
@@ -236,63 +395,163 @@ struct BwdCall {
 
 // Without a state cache the backward pass rebuilds the states first (Sec. 3.4: recomputation instead of
 // caching): the forward pass reduced to its states writes them into the tail of the scratch buffer.
-size_t recompute_scratch(const lasp_shape *shape, bool token) {
+size_t recompute_scratch(const lasp_shape *shape, bool token, int group = 1) {
     ScratchLayout l;
-    if (!scratch_layout(shape, token, &l)) return 0;
-    return round256(l.total) + cache_bytes(shape, token);
+    if (!scratch_layout(shape, token, &l, group)) return 0;
+    return round256(l.total) + group * cache_bytes(shape, token);
 }
 
 int run_bwd_call(const BwdCall &c) {
-    lasp::Plan p;
-    int rc = make_plan(c.shape, kBackward, &p, c.token, c.norm);
-    if (rc != LASP_OK) return rc;
-    if (!c.q || !c.k || !c.v || !c.dout || !c.decay || !c.dq || !c.dk || !c.dv || !c.dkv_in)
-        return LASP_ERR_NULL;
-    if (c.norm && (!c.yn || !c.rstd)) return LASP_ERR_NULL;
-    if (c.token && (!c.dlog_g || (c.dkv_out && !c.kv_out))) return LASP_ERR_NULL;
+    lasp::Plan p, one;
+    int rc = make_plan(c.shape, kBackward, &p, c.token, c.norm, c.group);
+    if (rc != LASP_OK || (rc = single_plan(c.shape, kBackward, &one, p)) != LASP_OK) return rc;
+    const bool rebuild = !c.cache || c.cache[0] == nullptr;
+    for (int t = 0; t < c.T; ++t) {
+        if (!c.q[t] || !c.k[t] || !c.v[t] || !c.dout[t] || !c.decay[c.token ? t : 0] || !c.dq[t] || !c.dk[t] || !c.dv[t] || !c.dkv_in[t])
+            return LASP_ERR_NULL;
+        if (c.norm && (!at(c.yn, t) || !at(c.rstd, t))) return LASP_ERR_NULL;
+        if (c.token && (!at(c.dlog_g, t) || ((c.dkv_out || t + 1 < c.T) && !at(c.kv_out, t)))) return LASP_ERR_NULL;
+        if (!rebuild && !c.cache[t]) return LASP_ERR_NULL;
+    }
     ScratchLayout l;
-    scratch_layout(c.shape, c.token, &l);
-    const bool rebuild = c.cache == nullptr;
+    scratch_layout(c.shape, c.token, &l, c.group);
     const size_t cb = cache_bytes(c.shape, c.token);
-    const size_t need = rebuild ? round256(l.total) + cb : l.total;
+    const size_t need = rebuild ? round256(l.total) + c.group * cb : l.total;
     if (!c.scratch || c.scratch_bytes < need) return LASP_ERR_WORKSPACE;
     char *scr = (char *)c.scratch;
-    const void *cache = rebuild ? scr + round256(l.total) : c.cache;
 
     const size_t esz = elem_bytes(p.dtype);
     const size_t qb = (size_t)p.B * p.H * p.N * p.dk * esz, ob = (size_t)p.B * p.H * p.N * p.dv * esz;   // q / out
     const size_t sb = (size_t)p.B * p.H * p.dk * p.dv * sizeof(float);
-    const size_t gb = (size_t)p.B * p.H * p.N * sizeof(float);
-    rc = check_buffers({{c.q, qb}, {c.k, qb / p.kvdiv}, {c.v, ob / p.kvdiv}, {c.dout, ob}, {c.dkv_out, sb}, {c.kv_out, sb},
-                        {rebuild ? c.kv_in : nullptr, sb}, {c.yn, ob}, {c.rstd, gb}, {c.decay, c.token ? gb : p.H * sizeof(float)},
-                        {c.cache, cb}},
-                       {{c.dq, qb}, {c.dk, qb / p.kvdiv}, {c.dv, ob / p.kvdiv}, {c.dlog_g, gb}, {c.dkv_in, sb},
-                        {c.scratch, need}});
-    if (rc != LASP_OK) return rc;
-
+    const size_t gb = (size_t)p.B * p.H * p.N * sizeof(float), db = c.token ? gb : p.H * sizeof(float);
     hipStream_t stream = (hipStream_t)c.stream;
-    lasp::Plan f;   // the forward pass's own plan (its segment count)
-    if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm); rc != LASP_OK) return rc;
-    if (rebuild && p.dtype == LASP_F32 && f.tiles_per_seg == f.cache_tiles) {
-        cache = nullptr;   // the segments' start states, which launch_bwd rebuilds in the states' region, are the cache
-    } else if (rebuild) {   // states only, into the scratch tail
-        const lasp::FwdArgs fa{nullptr, c.k, c.v, c.kv_in, c.decay, nullptr, nullptr, (void *)cache, (float *)scr,
-                               f.token ? (float *)(scr + l.seglog) : nullptr, nullptr, 0.0f, true};
-        if (lasp::launch_fwd(f, fa, stream, nullptr) != hipSuccess) return LASP_ERR_HIP;
+    // dkv_out goes to dkv_copy with the walk that starts from it, unless it lies in what the call writes
+    const float *dkv_out = c.dkv_out;
+    float *dkv_copy = dkv_out == c.dkv_copy ? nullptr : c.dkv_copy;
+    if (dkv_out && dkv_copy) {
+        const Span in{dkv_out, sb};
+        bool apart = (uintptr_t)dkv_out % 16 == 0 && !overlap(in, {dkv_copy, sb}) && !overlap(in, {c.scratch, need});
+        for (int t = 0; t < c.T && apart; ++t)
+            apart = !overlap(in, {c.dq[t], qb}) && !overlap(in, {c.dk[t], qb / p.kvdiv}) && !overlap(in, {c.dv[t], ob / p.kvdiv}) &&
+                    !overlap(in, {at(c.dlog_g, t), gb}) && !overlap(in, {c.dkv_in[t], sb});
+        if (!apart) {
+            if (hipMemcpyAsync(dkv_copy, dkv_out, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
+            dkv_out = dkv_copy;
+            dkv_copy = nullptr;
+        }
+    } else {
+        dkv_copy = nullptr;
     }
-    lasp_shape cut = *c.shape;   // dQ of float data: the segments whose start states the cache holds
+    for (int t = 0; t < c.T; ++t) {
+        rc = check_buffers({{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.dout[t], ob}, {t + 1 < c.T ? c.dkv_in[t + 1] : dkv_out, sb},
+                            {at(c.kv_out, t), sb}, {rebuild ? at(c.kv_in, t) : nullptr, sb}, {at(c.yn, t), ob}, {at(c.rstd, t), gb},
+                            {c.decay[c.token ? t : 0], db}, {at(c.cache, t), cb}},
+                           {{c.dq[t], qb}, {c.dk[t], qb / p.kvdiv}, {c.dv[t], ob / p.kvdiv}, {at(c.dlog_g, t), gb}, {c.dkv_in[t], sb},
+                            {c.scratch, need}, {t + 1 < c.T ? nullptr : dkv_copy, sb}});
+        if (rc != LASP_OK) return rc;
+    }
+
+    lasp::Plan f, f1, g;   // the forward pass's own plans (its segment count), and that of the cached states: dQ of float data
+    if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm, c.group); rc != LASP_OK) return rc;
+    if (rc = single_plan(c.shape, kForward, &f1, f); rc != LASP_OK) return rc;
+    lasp_shape cut = *c.shape;
     cut.segments = 0;
-    if (rc = make_plan(&cut, kForward, &f, c.token, c.norm); rc != LASP_OK) return rc;
-    lasp::BwdArgs a{c.q, c.k, c.v, c.dout, c.dkv_out, c.decay, cache, c.dq, c.dk, c.dv, c.dkv_in, (float *)scr,
-                    &f, c.kv_in, c.kv_out, c.dlog_g, p.token ? (float *)(scr + l.seglog) : nullptr,
-                    p.token ? (float *)(scr + l.rtok) : nullptr, c.yn, c.rstd, nullptr, nullptr};
-    if (p.kvdiv > 1) {   // the kernels write dK, dV per query head; launch_bwd sums each group into the outputs
-        a.dk_out = c.dk;
-        a.dv_out = c.dv;
-        a.dk = scr + l.dk_part;
-        a.dv = scr + l.dv_part;
+    if (rc = make_plan(&cut, kForward, &g, c.token, c.norm, c.group); rc != LASP_OK) return rc;
+    auto launch = [&](int first, int n) {
+        const int last = first + n - 1;
+        lasp::Plan use = n > 1 ? p : one, use_f = n > 1 ? f : f1;
+        use.shards = use_f.shards = g.shards = n;
+        lasp::Shards sh{};
+        if (n > 1) {
+            sh.q = offsets(c.q, first, n);
+            sh.k = offsets(c.k, first, n);
+            sh.v = offsets(c.v, first, n);
+            sh.dout = offsets(c.dout, first, n);
+            if (c.token) sh.decay = offsets(c.decay, first, n);
+            sh.dq = offsets(c.dq, first, n);
+            sh.dk = offsets(c.dk, first, n);
+            sh.dv = offsets(c.dv, first, n);
+            sh.dkv_in = offsets(c.dkv_in, first, n);
+            sh.yn = offsets(c.yn, first, n);
+            sh.rstd = offsets(c.rstd, first, n);
+            sh.rtok = strides(rtok_bytes(p));
+            sh.cache = rebuild ? strides(cb) : offsets(c.cache, first, n);
+        }
+        const void *cache = rebuild ? scr + round256(l.total) : c.cache[first];
+        const float *kv_in = at(c.kv_in, first);
+        if (rebuild && p.dtype == LASP_F32 && use_f.tiles_per_seg == use_f.cache_tiles) {
+            cache = nullptr;   // the segments' start states, which launch_bwd rebuilds in the states' region, are the cache
+        } else if (rebuild) {   // states only, into the scratch tail
+            lasp::FwdArgs fa{nullptr, c.k[first], c.v[first], kv_in, c.decay[c.token ? first : 0], nullptr, nullptr, (void *)cache, (float *)scr,
+                             f.token ? (float *)(scr + l.seglog) : nullptr, nullptr, 0.0f, true, nullptr, sh};
+            if (lasp::launch_fwd(use_f, fa, stream, nullptr) != hipSuccess) return false;
+        }
+        lasp::BwdArgs a{c.q[first], c.k[first], c.v[first], c.dout[first], last + 1 < c.T ? c.dkv_in[last + 1] : dkv_out, c.decay[c.token ? first : 0],
+                        cache, c.dq[first], c.dk[first], c.dv[first], c.dkv_in[first], (float *)scr, &g, kv_in, {},
+                        p.token ? (float *)(scr + l.seglog) : nullptr, p.token ? (float *)(scr + l.rtok) : nullptr, at(c.yn, first),
+                        at(c.rstd, first), {}, last + 1 < c.T ? nullptr : dkv_copy, sh};
+        for (int i = 0; i < n && c.token; ++i) {
+            a.dlg.kv_out[i] = at(c.kv_out, first + i);
+            a.dlg.dkv_out[i] = first + i + 1 < c.T ? c.dkv_in[first + i + 1] : dkv_out;
+            a.dlg.dlog_g[i] = c.dlog_g[first + i];
+        }
+        if (p.kvdiv > 1) {   // the kernels write dK, dV per query head; launch_bwd sums each group into the outputs
+            for (int i = 0; i < n; ++i) {
+                a.group.dk[i] = c.dk[first + i];
+                a.group.dv[i] = c.dv[first + i];
+            }
+            a.dk = scr + l.dk_part;
+            a.dv = scr + l.dv_part;
+            a.sh.dk = strides(qb);
+            a.sh.dv = strides(ob);
+        }
+        return lasp::launch_bwd(use, a, stream, next_slot(1)) == hipSuccess;
+    };
+    for (int end = c.T; end > 0;) {   // from the right, groups that begin where the forward pass's did
+        const int first = (end - 1) / c.group * c.group;
+        if (end - first > 1) {
+            Together all;
+            all.in(end < c.T ? c.dkv_in[end] : dkv_out, sb);
+            all.in(c.token ? nullptr : c.decay[0], db);
+            if (rebuild) all.in(at(c.kv_in, first), sb);
+            for (int t = first; t < end; ++t) {
+                all.in(c.q[t], qb);
+                all.in(c.k[t], qb / p.kvdiv);
+                all.in(c.v[t], ob / p.kvdiv);
+                all.in(c.dout[t], ob);
+                all.in(c.token ? c.decay[t] : nullptr, db);
+                all.in(at(c.kv_out, t), sb);
+                all.in(at(c.yn, t), ob);
+                all.in(at(c.rstd, t), gb);
+                all.in(at(c.cache, t), cb);
+                all.out(c.dq[t], qb);
+                all.out(c.dk[t], qb / p.kvdiv);
+                all.out(c.dv[t], ob / p.kvdiv);
+                all.out(at(c.dlog_g, t), gb);
+                all.out(c.dkv_in[t], sb);
+            }
+            if (!all.disjoint()) {
+                for (; end - first > 1; --end)
+                    if (!launch(end - 1, 1)) return LASP_ERR_HIP;
+            }
+        }
+        if (!launch(first, end - first)) return LASP_ERR_HIP;
+        end = first;
     }
-    return lasp::launch_bwd(p, a, stream, next_slot(1)) == hipSuccess ? LASP_OK : LASP_ERR_HIP;
+    return LASP_OK;
+}
+
+// Calls of one sub-sequence.
+int fwd_one(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *kv_in, const float *decay, bool token, bool norm,
+            float eps, void *out, float *rstd, float *kv_out, void *cache, void *scratch, size_t scratch_bytes, void *stream) {
+    return run_fwd_call({shape, 1, 1, &q, &k, &v, kv_in, nullptr, &decay, token, norm, eps, &out, &rstd, &kv_out, &cache, scratch,
+                         scratch_bytes, stream});
+}
+int bwd_one(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *dout, const float *kv_in, const float *dkv_out,
+            const float *decay, bool token, bool norm, const void *yn, const float *rstd, const float *kv_out, const void *cache, void *dq,
+            void *dk, void *dv, float *dlog_g, float *dkv_in, void *scratch, size_t scratch_bytes, void *stream) {
+    return run_bwd_call({shape, 1, 1, &q, &k, &v, &dout, &kv_in, dkv_out, nullptr, &decay, token, norm, &yn, &rstd, &kv_out, &cache, &dq, &dk,
+                         &dv, &dlog_g, &dkv_in, scratch, scratch_bytes, stream});
 }
 
 // Bidirectional path: shape rules of the causal path, own K/V head per query head only.
@@ -414,9 +673,7 @@ int lasp_check_log_decay(const float *log_g_host, int64_t n) {
 int lasp_fwd(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *kv_in,
              const float *decay, void *out, float *kv_out, void *state_cache, void *scratch,
              size_t scratch_bytes, void *hip_stream) {
-    FwdCall c{shape, q, k, v, kv_in, decay, false, false, 0.0f, out, nullptr, kv_out, state_cache, scratch, scratch_bytes,
-              hip_stream};
-    return run_fwd_call(c);
+    return fwd_one(shape, q, k, v, kv_in, decay, false, false, 0.0f, out, nullptr, kv_out, state_cache, scratch, scratch_bytes, hip_stream);
 }
 
 int lasp_fwd_noalloc(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *kv_in,
@@ -427,9 +684,7 @@ int lasp_fwd_noalloc(const lasp_shape *shape, const void *q, const void *k, cons
     if (l.total > lasp::kStaticScratchBytes) return LASP_ERR_WORKSPACE;   // beyond the library's own scratch
     void *scr = nullptr;
     if (lasp::static_scratch(&scr) != hipSuccess) return LASP_ERR_HIP;
-    FwdCall c{shape, q, k, v, kv_in, decay, false, false, 0.0f, out, nullptr, kv_out, state_cache, scr,
-              lasp::kStaticScratchBytes, hip_stream};
-    return run_fwd_call(c);
+    return fwd_one(shape, q, k, v, kv_in, decay, false, false, 0.0f, out, nullptr, kv_out, state_cache, scr, lasp::kStaticScratchBytes, hip_stream);
 }
 
 size_t lasp_noalloc_scratch_limit(void) { return lasp::kStaticScratchBytes; }
@@ -440,60 +695,79 @@ size_t lasp_gated_bwd_recompute_scratch_bytes(const lasp_shape *shape) { return 
 int lasp_bwd(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *dout,
              const float *kv_in, const float *dkv_out, const float *decay, const void *state_cache, void *dq, void *dk,
              void *dv, float *dkv_in, void *scratch, size_t scratch_bytes, void *hip_stream) {
-    BwdCall c{shape, q, k, v, dout, kv_in, dkv_out, decay, false, false, nullptr, nullptr, nullptr, state_cache, dq, dk, dv,
-              nullptr, dkv_in, scratch, scratch_bytes, hip_stream};
-    return run_bwd_call(c);
+    return bwd_one(shape, q, k, v, dout, kv_in, dkv_out, decay, false, false, nullptr, nullptr, nullptr, state_cache, dq, dk, dv, nullptr, dkv_in, scratch,
+                   scratch_bytes, hip_stream);
 }
 
 int lasp_gated_fwd(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *log_g,
                    const float *kv_in, void *out, float *kv_out, void *state_cache, void *scratch,
                    size_t scratch_bytes, void *hip_stream) {
-    FwdCall c{shape, q, k, v, kv_in, log_g, true, false, 0.0f, out, nullptr, kv_out, state_cache, scratch, scratch_bytes,
-              hip_stream};
-    return run_fwd_call(c);
+    return fwd_one(shape, q, k, v, kv_in, log_g, true, false, 0.0f, out, nullptr, kv_out, state_cache, scratch, scratch_bytes, hip_stream);
 }
 
 int lasp_gated_bwd(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *dout,
                    const float *log_g, const float *kv_in, const float *kv_out, const float *dkv_out,
                    const void *state_cache, void *dq, void *dk, void *dv, float *dlog_g, float *dkv_in, void *scratch,
                    size_t scratch_bytes, void *hip_stream) {
-    BwdCall c{shape, q, k, v, dout, kv_in, dkv_out, log_g, true, false, nullptr, nullptr, kv_out, state_cache, dq, dk, dv,
-              dlog_g, dkv_in, scratch, scratch_bytes, hip_stream};
-    return run_bwd_call(c);
+    return bwd_one(shape, q, k, v, dout, kv_in, dkv_out, log_g, true, false, nullptr, nullptr, kv_out, state_cache, dq, dk, dv, dlog_g, dkv_in, scratch,
+                   scratch_bytes, hip_stream);
 }
 
 int lasp_fwd_norm(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *kv_in,
                   const float *decay, float eps, void *out, float *rstd, float *kv_out, void *state_cache,
                   void *scratch, size_t scratch_bytes, void *hip_stream) {
-    FwdCall c{shape, q, k, v, kv_in, decay, false, true, eps, out, rstd, kv_out, state_cache, scratch, scratch_bytes,
-              hip_stream};
-    return run_fwd_call(c);
+    return fwd_one(shape, q, k, v, kv_in, decay, false, true, eps, out, rstd, kv_out, state_cache, scratch, scratch_bytes, hip_stream);
 }
 
 int lasp_bwd_norm(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *out,
                   const float *rstd, const void *dout, const float *kv_in, const float *dkv_out, const float *decay,
                   const void *state_cache, void *dq, void *dk, void *dv, float *dkv_in, void *scratch,
                   size_t scratch_bytes, void *hip_stream) {
-    BwdCall c{shape, q, k, v, dout, kv_in, dkv_out, decay, false, true, out, rstd, nullptr, state_cache, dq, dk, dv,
-              nullptr, dkv_in, scratch, scratch_bytes, hip_stream};
-    return run_bwd_call(c);
+    return bwd_one(shape, q, k, v, dout, kv_in, dkv_out, decay, false, true, out, rstd, nullptr, state_cache, dq, dk, dv, nullptr, dkv_in, scratch,
+                   scratch_bytes, hip_stream);
 }
 
 int lasp_gated_fwd_norm(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *log_g,
                         const float *kv_in, float eps, void *out, float *rstd, float *kv_out, void *state_cache,
                         void *scratch, size_t scratch_bytes, void *hip_stream) {
-    FwdCall c{shape, q, k, v, kv_in, log_g, true, true, eps, out, rstd, kv_out, state_cache, scratch, scratch_bytes,
-              hip_stream};
-    return run_fwd_call(c);
+    return fwd_one(shape, q, k, v, kv_in, log_g, true, true, eps, out, rstd, kv_out, state_cache, scratch, scratch_bytes, hip_stream);
 }
 
 int lasp_gated_bwd_norm(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *out,
                         const float *rstd, const void *dout, const float *log_g, const float *kv_in, const float *kv_out,
                         const float *dkv_out, const void *state_cache, void *dq, void *dk, void *dv,
                         float *dlog_g, float *dkv_in, void *scratch, size_t scratch_bytes, void *hip_stream) {
-    BwdCall c{shape, q, k, v, dout, kv_in, dkv_out, log_g, true, true, out, rstd, kv_out, state_cache, dq, dk, dv,
-              dlog_g, dkv_in, scratch, scratch_bytes, hip_stream};
-    return run_bwd_call(c);
+    return bwd_one(shape, q, k, v, dout, kv_in, dkv_out, log_g, true, true, out, rstd, kv_out, state_cache, dq, dk, dv, dlog_g, dkv_in, scratch,
+                   scratch_bytes, hip_stream);
+}
+
+size_t lasp_seq_scratch_bytes(const lasp_shape *shape, int32_t T, int32_t token, int32_t recompute) {
+    if (lasp_check_shape(shape) != LASP_OK || T < 1) return 0;
+    ScratchLayout l;
+    scratch_layout(shape, token != 0, &l, shards_per_launch(shape, T, token != 0));
+    return recompute ? std::max(l.total, recompute_scratch(shape, token != 0, shards_per_launch(shape, T, token != 0, true))) : l.total;
+}
+
+int lasp_seq_fwd(const lasp_shape *shape, int32_t T, const void *const *q, const void *const *k, const void *const *v, const float *kv_in,
+                 const float *const *decay, int32_t token, float eps, void *const *out, float *const *rstd, float *const *kv,
+                 void *const *state_cache, void *scratch, size_t scratch_bytes, void *hip_stream) {
+    if (int rc = lasp_check_shape(shape); rc != LASP_OK) return rc;
+    if (T < 1) return LASP_ERR_SHAPE;
+    if (!q || !k || !v || !decay || !out || !kv) return LASP_ERR_NULL;
+    return run_fwd_call({shape, T, shards_per_launch(shape, T, token != 0), q, k, v, kv_in, kv[0], decay, token != 0, rstd != nullptr, eps, out,
+                         rstd, kv + 1, state_cache, scratch, scratch_bytes, hip_stream});
+}
+
+int lasp_seq_bwd(const lasp_shape *shape, int32_t T, const void *const *q, const void *const *k, const void *const *v, const void *const *out,
+                 const float *const *rstd, const void *const *dout, const float *const *kv, const float *dkv_out, const float *const *decay,
+                 int32_t token, const void *const *state_cache, void *const *dq, void *const *dk, void *const *dv, float *const *dlog_g,
+                 float *const *dkv, void *scratch, size_t scratch_bytes, void *hip_stream) {
+    if (int rc = lasp_check_shape(shape); rc != LASP_OK) return rc;
+    if (T < 1) return LASP_ERR_SHAPE;
+    if (!q || !k || !v || !dout || !decay || !kv || !dq || !dk || !dv || !dkv) return LASP_ERR_NULL;
+    const int group = shards_per_launch(shape, T, token != 0, !state_cache || !state_cache[0]);
+    return run_bwd_call({shape, T, group, q, k, v, dout, kv, dkv_out, dkv[T], decay, token != 0, rstd != nullptr, rstd ? out : nullptr, rstd,
+                         token ? kv + 1 : nullptr, state_cache, dq, dk, dv, token ? dlog_g : nullptr, dkv, scratch, scratch_bytes, hip_stream});
 }
 
 size_t lasp_bidir_scratch_bytes(const lasp_shape *shape) {

@@ -9,6 +9,8 @@
 
 #include <type_traits>
 
+#include "lasp_internal.h"
+
 namespace lasp {
 
 typedef unsigned short bf16_t;  // storage type of bfloat16 data
@@ -464,6 +466,16 @@ struct TileMover {
                 r[i] = col_ok && row0 + i * (NT / VPR) < nrows ? gload<u32x4, STREAM>(g + i * (NT / VPR) * W, lo) : u32x4{0, 0, 0, 0};
         }
     }
+    // Rows < skip are not touched in memory and read as zero: the first tile of a run of tokens that is cut into tiles
+    // from its end.
+    template <int W>
+    DEVI void load_tail_w(const T *g, int skip) {
+        const int row0 = threadIdx.x / VPR, chunk = threadIdx.x % VPR;
+        const unsigned lo = (row0 * W + chunk * EPV) * sizeof(T);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            r[i] = chunk * EPV < W && row0 + i * (NT / VPR) >= skip ? gload<u32x4, STREAM>(g + i * (NT / VPR) * W, lo) : u32x4{0, 0, 0, 0};
+    }
     DEVI void store(T *s, int ld) const {
         if (sizeof(T) == 2 && ld == kSwzLd) {
             static_assert(sizeof(T) != 2 || COLS != 128 || (NT / VPR) % 16 == 0, "row step must keep row % 16");
@@ -879,46 +891,62 @@ DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[BLK], float *g, int w
         for (int i = 0; i < 16; ++i) gstore<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo, st[ab][i]);
 }
 
+// A pointer into the first sub-sequence of a launch, moved to the same place of sub-sequence `shard`.
+template <typename P>
+DEVI P *at_shard(P *p, const Offsets &o, int shard) { return (P *)((char *)p + o.at[shard]); }
+
 // Decay over whole segments, for carrying a state across them: one lambda per head (`full` tokens' worth for every
-// segment but the last, `last` for that), or with a decay per token 2^seglog[j], written by the local pass.
+// segment but the last of a sub-sequence, `last` for that), or with a decay per token 2^seglog[j], written by the local
+// pass. nseg: segments per sub-sequence, nslots: of all that the launch takes.
 template <bool TOKEN>
 struct SegDecay {
     float full = 0.0f, last = 0.0f;
     const float *seglog;
-    int nseg;
-    DEVI SegDecay(const float *decay, const float *seglog_all, int chain, int H, int nseg_, int seg_tokens, int ntok)
-        : seglog(TOKEN ? seglog_all + (size_t)chain * nseg_ : nullptr), nseg(nseg_) {
+    DEVI SegDecay(const float *decay, const float *seglog_all, int chain, int H, int nseg, int nslots, int seg_tokens, int ntok)
+        : seglog(TOKEN ? seglog_all + (size_t)chain * nslots : nullptr) {
         if constexpr (!TOKEN) {
             full = (float)pow_n(decay[chain % H], seg_tokens);
             last = (float)pow_n(decay[chain % H], ntok - (nseg - 1) * seg_tokens);
         }
     }
-    DEVI float operator()(int j) const {
+    DEVI float operator()(int j, bool shard_end) const {
         if constexpr (TOKEN) return exp2f(seglog[j]);
-        else return j == nseg - 1 ? last : full;
+        else return shard_end ? last : full;
+    }
+};
+// Whether the segments met on a walk over all of a launch's, from either end, are the last of their sub-sequence.
+template <bool BWD>
+struct ShardEnds {
+    int nseg, left;
+    DEVI explicit ShardEnds(int nseg_) : nseg(nseg_), left(BWD ? 1 : nseg_) {}
+    DEVI bool next() {
+        const bool end = --left == 0;
+        if (end) left = nseg;
+        return end;
     }
 };
 
-// The state segment `seg` starts from, in a walk's registers. Either k_scan has already put it into the segment's
-// slot of `states` (the chain's segment states), or (CARRY) the slots still hold the local states and the walk
-// carries the boundary state over the segments before its own itself, in the scan's order and arithmetic
-// (forward: segments 0 .. seg - 1, backward: nseg - 1 .. seg + 1): a few more reads, one launch less.
+// The state slot `slot` of a launch (its segments, over all sub-sequences) starts from, in a walk's registers. Either
+// k_scan has already put it into `states` (the chain's segment states), or (CARRY) the slots still hold the local states
+// and the walk carries the boundary state over the segments before its own itself, in the scan's order and arithmetic
+// (forward: slots 0 .. slot - 1, backward: nslots - 1 .. slot + 1): a few more reads, one launch less.
 // load(st, slot) loads a state in the orientation the wave keeps it in.
 template <bool BWD, bool TOKEN, int DB, typename Load>
-DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int seg,
-                      int nseg, int slot_elems, Load load) {
+DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int slot,
+                      int nseg, int nslots, int slot_elems, Load load) {
     if (boundary) {
         load(st, boundary);
     } else {
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] = f32x16{0};
     }
-    const int steps = BWD ? nseg - 1 - seg : seg;
+    const int steps = BWD ? nslots - 1 - slot : slot;
+    ShardEnds<BWD> ends(nseg);
     for (int n = 0; n < steps; ++n) {
-        const int j = BWD ? nseg - 1 - n : n;
+        const int j = BWD ? nslots - 1 - n : n;
         f32x16 local[DB];
         load(local, states + (size_t)j * slot_elems);
-        const float f = factor(j);
+        const float f = factor(j, ends.next());
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] = f * st[ab] + local[ab];
     }

@@ -16,6 +16,7 @@ struct Plan {
     int dtype;          // 0 = float, 1 = bfloat16
     int tile;           // tokens per kernel tile (CT)
     int ntiles;         // ceil(N / tile); only the last tile may be short
+    int shards;         // sub-sequences that go through one launch, cut alike (N, ntiles, nseg, ...: of one of them)
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
     int cache_tiles;    // the state cache holds the state every cache_tiles-th tile starts from, whatever `segments` a
@@ -28,23 +29,56 @@ struct Plan {
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
 };
 
+// Sub-sequences of one shape, each with buffers of its own, can go through the kernels in one launch (blockIdx.z), the
+// segments of all of them scanned together. A kernel gets the pointers of the first and, per tensor, the distance in bytes to
+// the others'. (Four at most: kernel arguments cost the host time, a launch with all distances of eight 1 us.)
+constexpr int kMaxShards = 4;
+struct Offsets {
+    long long at[kMaxShards];
+};
+struct Shards {
+    Offsets q, k, v, dout, decay, cache, out, rstd, kv_out, dq, dk, dv, dkv_in, yn, rtok;   // (decay: log g only)
+};
+// What each kernel needs of it (the forward walk as kDq: dO, V, K as q, k, v, dQ as out, Q as kv_out).
+struct LocalShards {
+    Offsets x, y, decay, yn, rstd;
+};
+struct FwdShards {
+    Offsets q, k, v, decay, cache, out, rstd, kv_out, yn, rtok;
+};
+struct BwdShards {
+    Offsets q, k, v, dout, decay, cache, dq, dk, dv, dkv_in, yn, rstd, rtok;
+};
+
 struct FwdArgs {
     const void *q, *k, *v;
-    const float *kv_in;   // may be null (zeros)
+    const float *kv_in;   // entering the first sub-sequence; may be null (zeros)
     const float *decay;   // lambda [H], or log g [B][H][N] with per-token decay
     void *out;
     float *kv_out;
     void *cache;          // may be null
-    float *scratch;       // [B*H][nseg][d_k][d_v]
-    float *seglog;        // per-token decay only: [B*H][nseg], log2 of the decay over each segment
+    float *scratch;       // [B*H][shards * nseg][d_k][d_v]
+    float *seglog;        // per-token decay only: [B*H][shards * nseg], log2 of the decay over each segment
     float *rstd_out;      // norm only: [B][H][N]
     float eps;            // norm only
     bool states_only;     // rebuild the state cache only: q, out, rstd_out are not touched, kv_out may be null
+    float *kv_copy;       // where kv_in is copied to, may be null
+    Shards sh;
 };
 
+// Per sub-sequence of a launch, for the gradient of the per-token decay: the state the forward pass returned, the gradient
+// that comes in from the right (null where it is zero), and the result [B][H][N].
+struct DlogArgs {
+    const float *kv_out[kMaxShards], *dkv_out[kMaxShards];
+    float *dlog_g[kMaxShards];
+};
+// Per sub-sequence, with grouped K/V heads: dk, dv [B][kv_heads][N][D].
+struct GroupOut {
+    void *dk[kMaxShards], *dv[kMaxShards];
+};
 struct BwdArgs {
     const void *q, *k, *v, *dout;
-    const float *dkv_out; // may be null (zeros)
+    const float *dkv_out; // entering the last sub-sequence from the right; may be null (zeros)
     const float *decay;
     const void *cache;
     void *dq, *dk, *dv;
@@ -55,16 +89,17 @@ struct BwdArgs {
     const Plan *fwd;
     const float *kv_in;
     // per-token decay only
-    const float *kv_out;  // state the forward pass returned (needed when dkv_out is given)
-    float *dlog_g;        // [B][H][N]
-    float *seglog;        // [B*H][nseg]
-    float *rtok;          // [B*H][N] scratch: q_t.dq_t - k_t.dk_t
+    DlogArgs dlg;
+    float *seglog;        // [B*H][shards * nseg]
+    float *rtok;          // [shards] blocks (sh.rtok) of [B*H][N], scratch: q_t.dq_t - k_t.dk_t
     // norm only: `dout` is the gradient w.r.t. the normalised output
     const void *yn;       // the normalised output the forward pass wrote
     const float *rstd;    // [B][H][N], from the forward pass
     // grouped K/V heads only (kvdiv > 1): dk, dv above are per-query-head buffers in scratch,
-    // summed over each group into these [B][kv_heads][N][D] outputs
-    void *dk_out, *dv_out;
+    // summed over each group into these
+    GroupOut group;
+    float *dkv_copy;      // where dkv_out is copied to, may be null
+    Shards sh;
 };
 
 // Optional event recorder: when non-null, launch_* records ev[0] before the
@@ -91,8 +126,8 @@ int tile_tokens(int dtype, int chunk, int D);
 hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boundary, const float *decay, const float *seglog,
                        hipStream_t s);
 hipError_t launch_dlg(const Plan &p, const BwdArgs &a, hipStream_t s);
-// out[K/V head] = sum of part[its query heads], rows of `width` elements
-hipError_t launch_group_sum(const Plan &p, const void *part, void *out, int width, hipStream_t s);
+// dk, dv [K/V head] = sum of the parts of its query heads
+hipError_t launch_group_sum(const Plan &p, const BwdArgs &a, hipStream_t s);
 
 // The passes for one data type and one (d_k, d_v), each in a translation unit of its own (lasp_walks.hip).
 #define LASP_PASSES(NAME)                                                                         \

@@ -20,30 +20,32 @@ namespace lasp {
 template <bool BWD, bool TOKEN>
 __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const float *__restrict__ boundary,
                                               const float *__restrict__ decay, const float *__restrict__ seglog,
-                                              int H, int DD, int nseg, int seg_tokens, int ntok) {
+                                              int H, int DD, int nseg, int nslots, int seg_tokens, int ntok) {
     const int chain = blockIdx.y;
     const int e = (blockIdx.x * blockDim.x + threadIdx.x) * 4;  // four consecutive state elements per thread
     if (e >= DD) return;
-    const SegDecay<TOKEN> seg_decay(decay, seglog, chain, H, nseg, seg_tokens, ntok);
+    const SegDecay<TOKEN> seg_decay(decay, seglog, chain, H, nseg, nslots, seg_tokens, ntok);
     // The caller's state and the segment states share one layout, [d_k][d_v] (DD = d_k * d_v elements).
     f32x4 carry = {0, 0, 0, 0};
     if (boundary) carry = *(const f32x4 *)(boundary + (size_t)chain * DD + e);
-    float *s = scratch + (size_t)chain * nseg * DD + e;
+    float *s = scratch + (size_t)chain * nslots * DD + e;
+    ShardEnds<BWD> ends(nseg);
     constexpr int U = 8;  // segments whose local states are fetched together (independent loads)
-    for (int n0 = 0; n0 < nseg; n0 += U) {
+    for (int n0 = 0; n0 < nslots; n0 += U) {
         f32x4 local[U];
         float factor[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int n = n0 + u, j = BWD ? nseg - 1 - n : n;
-            const bool has_local = n < nseg && (BWD ? (j > 0) : (j < nseg - 1));
+            const int n = n0 + u, j = BWD ? nslots - 1 - n : n;
+            const bool has_local = n < nslots && (BWD ? (j > 0) : (j < nslots - 1));
             local[u] = has_local ? *(const f32x4 *)(s + (size_t)j * DD) : f32x4{0, 0, 0, 0};
-            factor[u] = !TOKEN || has_local ? seg_decay(j) : 0.0f;
+            const bool end = ends.next();
+            factor[u] = !TOKEN || has_local ? seg_decay(j, end) : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int n = n0 + u, j = BWD ? nseg - 1 - n : n;
-            if (n < nseg) {
+            const int n = n0 + u, j = BWD ? nslots - 1 - n : n;
+            if (n < nslots) {
                 *(f32x4 *)(s + (size_t)j * DD) = carry;
                 carry = factor[u] * carry + local[u];
             }
@@ -56,7 +58,8 @@ hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boun
     const int DD = p.dk * p.dv;   // states hold the real rows and columns only
     const dim3 grid((DD / 4 + 255) / 256, p.B * p.H);
     const auto kernel = bwd ? (p.token ? k_scan<true, true> : k_scan<true, false>) : (p.token ? k_scan<false, true> : k_scan<false, false>);
-    kernel<<<grid, dim3(256), 0, s>>>(states, boundary, p.token ? nullptr : decay, seglog, p.H, DD, p.nseg, p.tiles_per_seg * p.tile, p.N);
+    kernel<<<grid, dim3(256), 0, s>>>(states, boundary, p.token ? nullptr : decay, seglog, p.H, DD, p.nseg, p.shards * p.nseg,
+                                      p.tiles_per_seg * p.tile, p.N);
     return hipGetLastError();
 }
 
@@ -83,10 +86,12 @@ DEVI double block_sum(double x, double *sh) {  // sum over the 256 threads, retu
     return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-__global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, const float *__restrict__ kv_out,
-                                             const float *__restrict__ dkv_out, float *__restrict__ dlg, int N, int DD) {
+__global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, Offsets shards, DlogArgs args, int N, int DD) {
     __shared__ double sh[4];
-    const int chain = blockIdx.y, tid = threadIdx.x;
+    const int chain = blockIdx.y, tid = threadIdx.x, shard = blockIdx.z;
+    const float *kv_out = args.kv_out[shard], *dkv_out = args.dkv_out[shard];
+    float *dlg = args.dlog_g[shard];
+    rtok = at_shard(rtok, shards, shard);
     const int s0 = blockIdx.x * kDlgBlock;  // first token of this block
     const float *r = rtok + (size_t)chain * N;
     double behind = 0.0;
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, con
 }
 
 hipError_t launch_dlg(const Plan &p, const BwdArgs &a, hipStream_t s) {
-    k_dlg<<<dim3((p.N + kDlgBlock - 1) / kDlgBlock, p.B * p.H), dim3(256), 0, s>>>(a.rtok, a.kv_out, a.dkv_out, a.dlog_g, p.N, p.dk * p.dv);
+    k_dlg<<<dim3((p.N + kDlgBlock - 1) / kDlgBlock, p.B * p.H, p.shards), dim3(256), 0, s>>>(a.rtok, a.sh.rtok, a.dlg, p.N, p.dk * p.dv);
     return hipGetLastError();
 }
 
@@ -154,10 +159,13 @@ hipError_t launch_dlg(const Plan &p, const BwdArgs &a, hipStream_t s) {
 // each, independent) add in quadrature, so the sum stays well inside the 2e-2 bound also for
 // multi-query attention (tested with 16 query heads per K/V head).
 template <typename T>
-__global__ __launch_bounds__(256) void k_group_sum(const T *__restrict__ part, T *__restrict__ out, int kvdiv, size_t per_head) {
-    const size_t kvchain = blockIdx.y;
-    const T *src = part + kvchain * kvdiv * per_head;
-    T *dst = out + kvchain * per_head;
+__global__ __launch_bounds__(256) void k_group_sum(const T *__restrict__ dk_part, const T *__restrict__ dv_part, GroupOut out, int kvdiv,
+                                                   size_t dk_head, size_t dv_head) {
+    const int shard = blockIdx.z >> 1;
+    const bool values = blockIdx.z & 1;
+    const size_t kvchain = blockIdx.y, per_head = values ? dv_head : dk_head;
+    const T *src = (values ? dv_part : dk_part) + (shard * gridDim.y + kvchain) * kvdiv * per_head;
+    T *dst = (T *)(values ? out.dv[shard] : out.dk[shard]) + kvchain * per_head;
     for (size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; e < per_head; e += (size_t)gridDim.x * 256 * 4) {
         float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int g = 0; g < kvdiv; ++g)
@@ -167,17 +175,18 @@ __global__ __launch_bounds__(256) void k_group_sum(const T *__restrict__ part, T
     }
 }
 template <typename T>
-static hipError_t run_group_sum(const Plan &p, const void *part, void *out, int width, hipStream_t s) {
-    const size_t per_head = (size_t)p.N * width;
+static hipError_t run_group_sum(const Plan &p, const BwdArgs &a, hipStream_t s) {
+    const size_t dk_head = (size_t)p.N * p.dk, dv_head = (size_t)p.N * p.dv;
     const int kvchains = p.B * (p.H / p.kvdiv);
-    size_t blocks = (per_head / 4 + 255) / 256;
+    size_t blocks = ((dk_head > dv_head ? dk_head : dv_head) / 4 + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    k_group_sum<T><<<dim3((unsigned)blocks, kvchains), dim3(256), 0, s>>>((const T *)part, (T *)out, p.kvdiv, per_head);
+    k_group_sum<T><<<dim3((unsigned)blocks, kvchains, 2 * p.shards), dim3(256), 0, s>>>((const T *)a.dk, (const T *)a.dv, a.group, p.kvdiv,
+                                                                                     dk_head, dv_head);
     return hipGetLastError();
 }
 
-hipError_t launch_group_sum(const Plan &p, const void *part, void *out, int width, hipStream_t s) {
-    return p.dtype == 0 ? run_group_sum<float>(p, part, out, width, s) : run_group_sum<bf16_t>(p, part, out, width, s);
+hipError_t launch_group_sum(const Plan &p, const BwdArgs &a, hipStream_t s) {
+    return p.dtype == 0 ? run_group_sum<float>(p, a, s) : run_group_sum<bf16_t>(p, a, s);
 }
 
 // Scratch of the entry point that allocates nothing (lasp_fwd_noalloc): the segment states live in this
@@ -227,7 +236,7 @@ constexpr int kStepTokens = 12;
 template <typename T, int DK, bool TOKEN>
 __global__ __launch_bounds__(256) void k_step(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                               const float *__restrict__ kv_in, const float *__restrict__ decay, T *__restrict__ O,
-                                              float *__restrict__ kv_out, int H, int ntok, int dv, int kvdiv) {
+                                              float *__restrict__ kv_out, float *__restrict__ kv_copy, int H, int ntok, int dv, int kvdiv) {
     constexpr int R = DK / 32;
     __shared__ float sq[kStepTokens][DK], sk[kStepTokens][DK];
     __shared__ __attribute__((aligned(16))) float sv[kStepTokens][32], red[kStepTokens][4][32];
@@ -239,6 +248,10 @@ __global__ __launch_bounds__(256) void k_step(const T *__restrict__ Q, const T *
 #pragma unroll
     for (int r = 0; r < R; ++r)
         st[r] = kv_in ? *(const f32x4 *)(kv_in + ((size_t)chain * DK + row + 32 * r) * dv + c0 + col) : f32x4{0, 0, 0, 0};
+    if (kv_copy) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) *(f32x4 *)(kv_copy + ((size_t)chain * DK + row + 32 * r) * dv + c0 + col) = st[r];
+    }
     for (int i = tid; i < ntok * DK; i += 256) {
         sq[i / DK][i % DK] = Elem<T>::ld1(Q + (size_t)chain * ntok * DK + i);
         sk[i / DK][i % DK] = Elem<T>::ld1(K + (size_t)kvchain * ntok * DK + i);
@@ -278,7 +291,7 @@ static hipError_t run_step(const Plan &p, const FwdArgs &a, hipStream_t s, const
     if (ke)
         for (int i = 0; i < 3; ++i) (void)hipEventRecord(ke->ev[i], s);
     kernel<<<dim3(p.dv / 32, p.B * p.H), dim3(256), 0, s>>>((const T *)a.q, (const T *)a.k, (const T *)a.v, a.kv_in, a.decay, (T *)a.out,
-                                                          a.kv_out, p.H, p.N, p.dv, p.kvdiv);
+                                                          a.kv_out, a.kv_copy, p.H, p.N, p.dv, p.kvdiv);
     if (ke) (void)hipEventRecord(ke->ev[3], s);
     return hipGetLastError();
 }
@@ -290,7 +303,7 @@ static Fn by_shape(const Plan &p, Fn f64, Fn f128, Fn f64_128, Fn f128_64, Fn b6
     return p.dtype == 0 ? (p.D == 64 ? f64 : f128) : (p.D == 64 ? b64 : b128);
 }
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t stream, const KernelEvents *ke) {
-    if (p.N <= kStepTokens && !a.cache && !p.norm) return p.dtype == 0 ? run_step<float>(p, a, stream, ke) : run_step<bf16_t>(p, a, stream, ke);
+    if (p.N <= kStepTokens && !a.cache && !p.norm && p.shards == 1) return p.dtype == 0 ? run_step<float>(p, a, stream, ke) : run_step<bf16_t>(p, a, stream, ke);
     return by_shape(p, fwd_f32_64, fwd_f32_128, fwd_f32_64_128, fwd_f32_128_64, fwd_bf16_64, fwd_bf16_128, fwd_bf16_64_128,
                     fwd_bf16_128_64)(p, a, stream, ke);
 }

@@ -75,9 +75,9 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM = false, int WX = D, int WY = D>
 __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
-                                                  float *__restrict__ seglog, int H, int ntiles, int nseg,
-                                                  int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn = nullptr,
-                                                  const float *__restrict__ rstd = nullptr) {
+                                                  float *__restrict__ seglog, int H, int ntiles, int nseg, int nslots,
+                                                  int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn,
+                                                  const float *__restrict__ rstd, LocalShards sh) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
     using E = WalkElem<T>;
     constexpr int NT = D * 2, LDD = walk_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
@@ -86,12 +86,22 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     bf16_t *sY = sX + TILE;
     float *pw = (float *)(sY + TILE);
 
-    const int chain = blockIdx.y;
-    const int seg = BWD ? blockIdx.x + 1 : blockIdx.x;
+    const int chain = blockIdx.y, shard = blockIdx.z;
+    const int seg = blockIdx.x + (BWD && nslots == nseg ? 1 : 0), slot = shard * nseg + seg;
+    if (slot == (BWD ? 0 : nslots - 1)) return;   // no other segment starts from the last one's state (of several sub-sequences: the grid has it)
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
+    if (shard) {
+        X = at_shard(X, sh.x, shard);
+        Y = at_shard(Y, sh.y, shard);
+        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
+        if constexpr (NORM) {
+            yn = at_shard(yn, sh.yn, shard);
+            rstd = at_shard(rstd, sh.rstd, shard);
+        }
+    }
     if (!BWD) {  // forward: X, Y are K, V
         X += kv_shift(chain, H, kvdiv, ntok, WX);
         Y += kv_shift(chain, H, kvdiv, ntok, WY);
@@ -101,15 +111,25 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     const int ntl = t1 - t0;
     auto tile_of = [&](int n) { return BWD ? t1 - 1 - n : t0 + n; };
     // the first tile is requested before anything else so that its latency covers the set-up
-    // rows of tile `t` that exist: the last tile of a sub-sequence may be short. (The forward pass never sums
-    // over the last segment; the backward weights run from the segment's start, which a short end leaves alone.)
+    // rows of tile `t` that exist: the last tile of a sub-sequence may be short
     auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
+    // One lambda per head, forward: the weights run from the segment's end, so where a sub-sequence ends inside a tile its
+    // last segment is cut into tiles from the end, and the first of them is the one that lacks rows (END_CUT).
+    constexpr bool END_CUT = RAGGED && !BWD && !TOKEN;
+    const int gap = END_CUT ? t1 * CT - min(t1 * CT, ntok) : 0;   // rows the first tile lacks
     TileMover<T, CT, D, NT, true> mx, my;   // streaming (non-temporal) loads
     NormTile<T, CT, D, NT, WY> mn;   // the normalised output has the rows of Y (= dY)
     const float *rstd_c = rstd + (size_t)chain * ntok;
     if constexpr (!TOKEN) {   // (the per-token-decay path walks the tiles in the other order)
-        mx.template load_w<WX>(X + xoff(tile_of(0)), nvalid(tile_of(0)));
-        my.template load_w<WY>(Y + yoff(tile_of(0)), nvalid(tile_of(0)));
+        if constexpr (END_CUT) {
+            X -= gap * WX;
+            Y -= gap * WY;
+            mx.template load_tail_w<WX>(X + xoff(t0), gap);
+            my.template load_tail_w<WY>(Y + yoff(t0), gap);
+        } else {
+            mx.template load_w<WX>(X + xoff(tile_of(0)), nvalid(tile_of(0)));
+            my.template load_w<WY>(Y + yoff(tile_of(0)), nvalid(tile_of(0)));
+        }
         if constexpr (NORM) mn.load(yn + yoff(tile_of(0)), rstd_c + (size_t)tile_of(0) * CT, nvalid(tile_of(0)));
     }
     f32x16 st[DB];
@@ -196,7 +216,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                 });
         }
         // log2 of the product of g over the segment, for the scan
-        if (threadIdx.x == 0) seglog[(size_t)chain * nseg + seg] = base;
+        if (threadIdx.x == 0) seglog[(size_t)chain * nslots + slot] = base;
     } else {
     const float lam = decay[chain % H];
     fill_pow_table<CT>(pw, lam);
@@ -214,7 +234,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
         else my.store(sY, LDD);
         __syncthreads();
         if (n + 1 < ntl) {
-            // (tiles of this loop are requested after the segment's last one: never the short one)
+            // (never the tile that lacks rows, which was requested first)
             mx.template load_w<WX>(X + xoff(tile_of(n + 1)), CT);
             my.template load_w<WY>(Y + yoff(tile_of(n + 1)), CT);
             if constexpr (NORM) mn.load(yn + yoff(tile_of(n + 1)), rstd_c + (size_t)tile_of(n + 1) * CT);
@@ -269,7 +289,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] += low[ab];
     }
-    state_store_w<D, WX, WY>(ln, st, scratch + ((size_t)chain * nseg + seg) * WX * WY, w);
+    state_store_w<D, WX, WY>(ln, st, scratch + ((size_t)chain * nslots + slot) * WX * WY, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -309,9 +329,10 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
-                                                int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
+                                                int H, int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
-                                                const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok) {
+                                                const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok,
+                                                float *__restrict__ kv_copy, FwdShards sh) {
     using E = WalkElem<T>;
     constexpr bool STATES = ROLE == kStates, DQ = ROLE == kDq;
     constexpr int NT = D * 2, LDD = walk_ld<T, D>(), LDP = fwd_ldp<T, CT>(), DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
@@ -324,11 +345,34 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     bf16_t *sStage = sP + walk_tile<T>(CT, LDP);   // cache stores, bfloat16
     float *pw = (float *)(sStage + fwd_stage<T, D>());
 
-    const int chain = blockIdx.y, seg = blockIdx.x;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
+    if (shard) {
+        Q = at_shard(Q, sh.q, shard);
+        K = at_shard(K, sh.k, shard);
+        V = at_shard(V, sh.v, shard);
+        O = at_shard(O, sh.out, shard);
+        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
+        if constexpr (DQ) {
+            if constexpr (NORM) {
+                yn = at_shard(yn, sh.yn, shard);
+                rstd = at_shard(rstd, sh.rstd, shard);
+            }
+            if constexpr (TOKEN) {
+                q_rows = at_shard(q_rows, sh.kv_out, shard);
+                rtok = at_shard(rtok, sh.rtok, shard);
+            }
+            if (carry < 0) scratch = at_shard(scratch, sh.cache, shard);
+        } else {
+            kv_out = at_shard(kv_out, sh.kv_out, shard);
+            cache = at_shard(cache, sh.cache, shard);
+            if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
+        }
+    }
     // requests first (tile, then start state), table arithmetic while they fly
     K += kv_shift(chain, H, kvdiv, ntok, WK);   // K, V of this chain's K/V head
     V += kv_shift(chain, H, kvdiv, ntok, WV);
@@ -346,15 +390,17 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     if constexpr (DQ && NORM) mn.load(yn + koff(t0), rstd_c + (size_t)t0 * CT, nvalid(t0));
     f32x16 st[DB];
     {
-        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        // kDq, carry < 0: the states are those that the forward pass kept, a buffer per sub-sequence
+        const bool kept = DQ && carry < 0;
+        const float *states = scratch + (size_t)chain * (kept ? nseg : nslots) * WK * WV;
         auto load = [&](f32x16(&s)[DB], const float *g) {
             if constexpr (DQ) state_load_t_w<D, WV, WK>(ln, s, g, w);   // stored [d_k][d_v] = [WV][WK]
             else state_load_w<D, WK, WV>(ln, s, g, w);
         };
-        if (carry)
+        if (carry > 0)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
-        else load(st, states + (size_t)seg * WK * WV);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+        else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
@@ -380,6 +426,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         }
     };
     to_cache(t0);
+    if (!DQ && kv_copy && slot0 == 0) state_store_w<D, WK, WV>(ln, st, kv_copy + (size_t)chain * WK * WV, w);
     if constexpr (RAGGED && !TOKEN) {
         __syncthreads();   // the power table
         dec.set_end(nvalid(t0));
@@ -530,7 +577,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             for (int ib = 0; ib < NB; ++ib) store_out_tile_t<T, D, WV>(ln, o, acc[ib], 32 * ib, w, nvalid(t));
         }
     }
-    if (seg == nseg - 1 && kv_out) state_store_w<D, WK, WV>(ln, st, kv_out + (size_t)chain * WK * WV, w);
+    if (!DQ && seg == nseg - 1 && kv_out) state_store_w<D, WK, WV>(ln, st, kv_out + (size_t)chain * WK * WV, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -558,8 +605,8 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
                                                 const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
-                                                int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
-                                                float *__restrict__ rstd_out, float eps) {
+                                                int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
+                                                float *__restrict__ rstd_out, float eps, float *__restrict__ kv_copy, FwdShards sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = Fwd8Smem<T, CT, D>;
@@ -574,9 +621,20 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     float *sX = (float *)(smem + SM::X_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
+    if (shard) {
+        Q = at_shard(Q, sh.q, shard);
+        K = at_shard(K, sh.k, shard);
+        V = at_shard(V, sh.v, shard);
+        O = at_shard(O, sh.out, shard);
+        kv_out = at_shard(kv_out, sh.kv_out, shard);
+        cache = at_shard(cache, sh.cache, shard);
+        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
+        if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
+    }
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW, g = w8 / NW;   // value-feature block; row half of the state and token block of the output
     const int a0 = 64 * g;                // first state row of this wave
@@ -598,12 +656,12 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     request(t0);
     f32x16 st[HB];   // st[ab][i] = KV[a0 + 32 ab + acc_row(i)][32 w + r]
     {
-        const float *states = scratch + (size_t)chain * nseg * D * D;
+        const float *states = scratch + (size_t)chain * nslots * D * D;
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, D * D, load);
-        else load(st, states + (size_t)seg * D * D);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, D * D, load);
+        else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     auto to_cache = [&](int t) __attribute__((always_inline)) {
@@ -612,6 +670,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
             cache_store<D, D, D, HB>(ln, cache + ((size_t)chain * ((ntiles + half) >> half) + (t >> half)) * D * D + a0 * D, st, stage, w);
     };
     to_cache(t0);
+    if (kv_copy && slot0 == 0) state_store_w<D, D, D, HB>(ln, st, kv_copy + (size_t)chain * D * D + a0 * D, w);
     if constexpr (RAGGED && !TOKEN) {
         __syncthreads();   // the power table
         dec.set_end(nvalid(t0));
@@ -745,8 +804,9 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
                                                  const T *__restrict__ dO, const float *__restrict__ decay, T *__restrict__ dK,
                                                  T *__restrict__ dV, float *__restrict__ dkv_in, const float *__restrict__ scratch,
                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
-                                                 float *__restrict__ rtok, int H, int ntiles, int nseg, int tiles_per_seg, int ntok,
-                                                 int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd) {
+                                                 float *__restrict__ rtok, int H, int ntiles, int nseg, int nslots, int tiles_per_seg,
+                                                 int ntok, int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd,
+                                                 float *__restrict__ dkv_copy, BwdShards sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = BwdkvSmem<T, CT, D>;
@@ -762,9 +822,27 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     bf16_t *sDS = sS + SM::PTILE;
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
+    if (shard) {
+        Q = at_shard(Q, sh.q, shard);
+        K = at_shard(K, sh.k, shard);
+        V = at_shard(V, sh.v, shard);
+        dO = at_shard(dO, sh.dout, shard);
+        dK = at_shard(dK, sh.dk, shard);
+        dV = at_shard(dV, sh.dv, shard);
+        dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
+        if constexpr (TOKEN) {
+            decay = at_shard(decay, sh.decay, shard);
+            rtok = at_shard(rtok, sh.rtok, shard);
+        }
+        if constexpr (NORM) {
+            yn = at_shard(yn, sh.yn, shard);
+            rstd = at_shard(rstd, sh.rstd, shard);
+        }
+    }
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW;    // feature block of this wave's output
     const int rg = w8 / NW;   // group: 0 produces dV, 1 produces dK
@@ -810,15 +888,16 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
     f32x16 st[DB];
     {
-        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        const float *states = scratch + (size_t)chain * nslots * WK * WV;
         auto load = [&](f32x16(&s)[DB], const float *g) {
             if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
-        else load(st, states + (size_t)seg * WK * WV);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+        else load(st, states + (size_t)slot0 * WK * WV);
+        if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
 
     for (int t = t1 - 1; t >= t0; --t) {
@@ -945,8 +1024,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   float *__restrict__ dkv_in, const float *__restrict__ scratch,
                                                   const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                   float *__restrict__ rtok,
-                                                  int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
-                                                  const T *__restrict__ yn = nullptr, const float *__restrict__ rstd = nullptr) {
+                                                  int H, int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
+                                                  const T *__restrict__ yn, const float *__restrict__ rstd, float *__restrict__ dkv_copy,
+                                                  BwdShards sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
@@ -967,7 +1047,27 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     T *sC = (T *)(smem + SM::C_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
+    if (shard) {
+        Q = at_shard(Q, sh.q, shard);
+        K = at_shard(K, sh.k, shard);
+        V = at_shard(V, sh.v, shard);
+        dO = at_shard(dO, sh.dout, shard);
+        dK = at_shard(dK, sh.dk, shard);
+        dV = at_shard(dV, sh.dv, shard);
+        dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
+        if constexpr (TOKEN) {
+            decay = at_shard(decay, sh.decay, shard);
+            rtok = at_shard(rtok, sh.rtok, shard);
+        }
+        if constexpr (NORM) {
+            yn = at_shard(yn, sh.yn, shard);
+            rstd = at_shard(rstd, sh.rstd, shard);
+        }
+        dQ = at_shard(dQ, sh.dq, shard);
+        cache = at_shard(cache, sh.cache, shard);
+    }
     const int t0 = seg * tiles_per_seg;                                  // even, unless by tiles
     // even: the last pair may lack its O tile
     const int t1 = BY_TILES ? min(t0 + tiles_per_seg, ntiles) : (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;
@@ -1063,15 +1163,16 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
     f32x16 st[DB];
     {
-        const float *states = scratch + (size_t)chain * nseg * WK * WV;
+        const float *states = scratch + (size_t)chain * nslots * WK * WV;
         auto load = [&](f32x16(&s)[DB], const float *g) {
             if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, tiles_per_seg * CT, ntok), seg, nseg, WK * WV, load);
-        else load(st, states + (size_t)seg * WK * WV);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+        else load(st, states + (size_t)slot0 * WK * WV);
+        if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
 
     // masked score tiles of the tile whose V, K are at pV, pK (dO, Q in sdO, sQ): one 32x32 block per wave
@@ -1376,7 +1477,7 @@ static auto by_model(const Plan &p) {
 template <typename T, int CT, int D, bool BWD, bool WITH_NORM, int WX, int WY>
 struct LocalFam {   // the Norm prologue exists in the backward pass only
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG && (BWD || TK), NM && BWD && WITH_NORM, WX, WY>;
+    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG, NM && BWD && WITH_NORM, WX, WY>;
 };
 template <typename T, int CT, int D, int WK, int WV>
 struct FwdFam {
@@ -1418,19 +1519,25 @@ struct Bwd8tFam {   // one cached state per tile; an odd tile count is ragged
 // bfloat16 segments of an even number of 64-token tiles are read 128 tokens
 // at a time (half the barriers, twice the bytes in flight per workgroup), unless
 // the Norm prologue (a third tile in registers) or key and value dimensions that
-// differ ask for the walk's tile.
+// differ ask for the walk's tile. The forward pass of one sub-sequence never sums over the segment with the short end.
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
-                            const T *yn, const float *rstd, hipStream_t s) {
-    const dim3 grid(p.nseg - 1, p.B * p.H), block(D * 2);
+                            const T *yn, const float *rstd, const Shards &all, hipStream_t s) {
+    const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.decay, all.yn, all.rstd};
+    const dim3 grid(p.shards > 1 ? p.nseg : p.nseg - 1, p.B * p.H, p.shards), block(D * 2);
+    const int nslots = p.shards * p.nseg;
+    Plan q = p;
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
-        if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0)
-            return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D>>(p), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                 decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
-                                 (const T *)nullptr, (const float *)nullptr);
+        if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0) {
+            if (!BWD) q.ragged = p.shards > 1 && p.N % 128 != 0;
+            return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
+                                 decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, nslots, p.tiles_per_seg / 2, p.N, p.kvdiv,
+                                 (const T *)nullptr, (const float *)nullptr, sh);
+        }
     }
-    return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV>>(p), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
-                         scratch, seglog, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd);
+    if (!BWD) q.ragged = p.shards > 1 && p.N % CT != 0;
+    return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
+                         scratch, seglog, p.H, p.ntiles, p.nseg, nslots, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, sh);
 }
 
 // Whether the walk carries the boundary state over the segments before its own itself (start_state) instead of
@@ -1438,14 +1545,14 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
 // first tile (a state's loads, one after the other), the scan 3 - 11 us and a launch. bf16 d=128 forward / backward:
 // 128 heads x 1024 tokens (2 segments) 63.9 / 88.2 -> 56.8 / 79.2 us, 64 x 8192 (4) 195.4 / 302.4 -> 188.0 / 301.9,
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
-static bool walk_carries(const Plan &p) { return p.nseg <= 4; }
+static bool walk_carries(const Plan &p) { return p.shards * p.nseg <= 4; }
 
 // Local pass and scan of the forward states over K, V; `carry`: the scan is left to the walk.
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_states(const Plan &p, const void *k, const void *v, const float *kv_in, const float *decay, float *scratch,
-                             float *seglog, bool carry, hipStream_t s, const KernelEvents *ke) {
-    if (p.nseg > 1) {
-        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, s);
+                             float *seglog, bool carry, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
+    if (p.shards * p.nseg > 1) {
+        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1458,9 +1565,10 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     const bool carry = walk_carries(p);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
-    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, ke); e != hipSuccess) return e;
+    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, a.sh, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
+    const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.decay, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}, {}};
     if constexpr (sizeof(T) == 2 && WK == 128 && WV == 128) {
         static_assert(Fwd8Smem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         // Up to 256 workgroups a CU has one, and four waves leave each SIMD only one; from 257 on two workgroups of
@@ -1468,12 +1576,12 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         // Forward, k_fwd / k_fwd8, us: 256 workgroups, 128 heads x 8192 tokens 309.0 / 300.1, x 4000 165.0 / 156.4,
         // x 8192 with a decay per token 357.6 / 315.2; 512 workgroups, 512 heads x 2048 221.7 / 235.7, x 2000
         // 231.3 / 238.8, x 2048 with a decay per token 223.0 / 253.3.
-        if ((int64_t)p.nseg * p.B * p.H <= kOnePerCu) {
+        if ((int64_t)p.shards * p.nseg * p.B * p.H <= kOnePerCu) {
             const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
-            if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
+            if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                   (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles, (const float *)a.scratch,
-                                  a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv,
-                                  a.rstd_out, a.eps);
+                                  a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N,
+                                  p.kvdiv, a.rstd_out, a.eps, a.kv_copy, sh);
                 e != hipSuccess)
                 return e;
             if (ke) (void)hipEventRecord(ke->ev[3], s);
@@ -1481,11 +1589,11 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         }
     }
     const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
-    if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
+    if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                           (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
                           p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
-                          p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
-                          (const T *)nullptr, (float *)nullptr);
+                          p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
+                          (const T *)nullptr, (float *)nullptr, a.kv_copy, sh);
         e != hipSuccess)
         return e;
     if (ke) (void)hipEventRecord(ke->ev[3], s);
@@ -1497,16 +1605,18 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
     const Plan &f = *a.fwd;   // a segment per cached state
-    const bool carry = !a.cache && walk_carries(f);
+    const int carry = a.cache ? -1 : walk_carries(f);   // -1: a state per segment of every sub-sequence, in its own buffer
     if (!a.cache) {
-        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, s, nullptr); e != hipSuccess)
+        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry != 0, a.sh, s, nullptr);
+            e != hipSuccess)
             return e;
     }
-    return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H), dim3(D * 2), Smem<T, CT, D>::fwd, s,
+    return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                          (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr, f.cache_tiles,
-                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry,
-                         f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
-                         (const T *)a.q, a.rtok);
+                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, carry,
+                         f.H, f.ntiles, f.nseg, f.shards * f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
+                         (const T *)a.q, a.rtok, (float *)nullptr,
+                         FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.decay, a.sh.cache, a.sh.dq, a.sh.rstd, a.sh.q, a.sh.yn, a.sh.rtok});
 }
 
 template <typename T, int CT, int D, int WK = D, int WV = D>
@@ -1520,9 +1630,9 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
             if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
         }
     }
-    if (p.nseg > 1) {
+    if (p.shards * p.nseg > 1) {
         if (e = run_local<T, CT, D, true, WK, WV>(p, (const T *)a.q, (const T *)a.dout, a.decay, a.scratch, a.seglog, (const T *)a.yn,
-                                          a.rstd, s);
+                                          a.rstd, a.sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1532,7 +1642,8 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     }
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     // The walks: bfloat16 in one kernel with one cached state per pair of tiles; float dQ and dK, dV apart.
-    const dim3 grid(p.nseg, chains), block(D * 4);
+    const dim3 grid(p.nseg, chains, p.shards), block(D * 4);
+    const BwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.dout, a.sh.decay, a.sh.cache, a.sh.dq, a.sh.dk, a.sh.dv, a.sh.dkv_in, a.sh.yn, a.sh.rstd, a.sh.rtok};
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
@@ -1541,7 +1652,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
                           by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                           (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
                           (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H,
-                          p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd);
+                          p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
     } else {
         static_assert(BwdkvSmem<T, CT, D>::TOTAL <= 163840 / (D == 128 ? 1 : 2), "LDS of one gfx950 CU for the workgroups meant to share it");
         if (a.cache) {
@@ -1550,15 +1661,14 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
         e = launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                           (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
                           (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H, p.ntiles, p.nseg,
-                          p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd);
+                          p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
     }
     if (e != hipSuccess) return e;
     if (p.kvdiv > 1) {
-        if (e = launch_group_sum(p, a.dk, a.dk_out, p.dk, s); e != hipSuccess) return e;
-        if (e = launch_group_sum(p, a.dv, a.dv_out, p.dv, s); e != hipSuccess) return e;
+        if (e = launch_group_sum(p, a, s); e != hipSuccess) return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[3], s);
-    if (p.token && a.dlog_g) return launch_dlg(p, a, s);
+    if (p.token) return launch_dlg(p, a, s);
     return hipGetLastError();
 }
 

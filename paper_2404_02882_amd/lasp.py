@@ -84,6 +84,12 @@ def _bind(handle):
     handle.lasp_gated_fwd_norm.restype = ctypes.c_int
     handle.lasp_gated_bwd_norm.argtypes = [_sp] + [_vp] * 17 + [_sz, _vp]
     handle.lasp_gated_bwd_norm.restype = ctypes.c_int
+    handle.lasp_seq_scratch_bytes.argtypes = [_sp] + [ctypes.c_int32] * 3
+    handle.lasp_seq_scratch_bytes.restype = _sz
+    handle.lasp_seq_fwd.argtypes = [_sp, ctypes.c_int32] + [_vp] * 5 + [ctypes.c_int32, ctypes.c_float] + [_vp] * 5 + [_sz, _vp]
+    handle.lasp_seq_fwd.restype = ctypes.c_int
+    handle.lasp_seq_bwd.argtypes = [_sp, ctypes.c_int32] + [_vp] * 9 + [ctypes.c_int32] + [_vp] * 7 + [_sz, _vp]
+    handle.lasp_seq_bwd.restype = ctypes.c_int
     handle.lasp_bidir_scratch_bytes.argtypes = [_sp]
     handle.lasp_bidir_scratch_bytes.restype = _sz
     handle.lasp_bidir_state.argtypes = [_sp, _vp, _vp, _vp, ctypes.c_int32, _vp, _sz, _vp]
@@ -289,6 +295,55 @@ def lasp_gated_bwd_norm(shape: Shape, q, k, v, out, rstd, dout, log_g, kv_in, kv
                                  _ptr(dv), _ptr(dlog_g), _ptr(dkv_in), _ptr(scratch), nbytes, _stream(stream))
     if rc != 0:
         raise LaspError(rc, "lasp_gated_bwd_norm")
+
+
+def seq_scratch_bytes(shape: Shape, T: int, token: bool, recompute: bool) -> int:
+    return int(lib.lasp_seq_scratch_bytes(ctypes.byref(shape), int(T), int(token), int(recompute)))
+
+
+def _tables(*lists):
+    """Addresses of the first n tensors of every (list, n) in one host array: (the array, which the caller keeps until its
+    call has returned, the address of each list's part of it; None for a list that is None)."""
+    flat, first = [], []
+    for tensors, n in lists:
+        if tensors is None:
+            first.append(None)
+            continue
+        first.append(8 * len(flat))
+        for t in range(n):
+            t = tensors[t]
+            if t is None:
+                flat.append(0)
+            elif t.is_contiguous():
+                flat.append(t.data_ptr())
+            else:
+                raise ValueError("tensors handed to the library must be contiguous")
+    table = (ctypes.c_size_t * len(flat))(*flat)
+    base = ctypes.addressof(table)
+    return table, [None if n is None else base + n for n in first]
+
+
+def lasp_seq_fwd(shape: Shape, T, q, k, v, kv_in, decay, token, eps, out, rstd, kv, state_cache, scratch, stream=None) -> None:
+    """Enqueue the forward pass of T sub-sequences (lists of T tensors, kv of T + 1; decay: a tensor, or a list of T with
+    `token`; rstd None = outputs not normalised); raises LaspError on a non-zero status."""
+    keep, (q, k, v, decay, out, rstd, kv, state_cache) = _tables(
+        (q, T), (k, T), (v, T), (decay, T) if token else ([decay], 1), (out, T), (rstd, T), (kv, T + 1), (state_cache, T))
+    rc = lib.lasp_seq_fwd(ctypes.byref(shape), T, q, k, v, _ptr(kv_in), decay, token, eps, out, rstd, kv, state_cache, _ptr(scratch),
+                          scratch.numel() * scratch.element_size(), _stream(stream))
+    if rc != 0:
+        raise LaspError(rc, "lasp_seq_fwd")
+
+
+def lasp_seq_bwd(shape: Shape, T, q, k, v, out, rstd, dout, kv, dkv_out, decay, token, state_cache, dq, dk, dv, dlog_g, dkv, scratch,
+                 stream=None) -> None:
+    """Enqueue the backward pass of T sub-sequences; raises LaspError on a non-zero status."""
+    keep, (q, k, v, out, rstd, dout, kv, decay, state_cache, dq, dk, dv, dlog_g, dkv) = _tables(
+        (q, T), (k, T), (v, T), (out, T), (rstd, T), (dout, T), (kv, T + 1), (decay, T) if token else ([decay], 1), (state_cache, T),
+        (dq, T), (dk, T), (dv, T), (dlog_g, T), (dkv, T + 1))
+    rc = lib.lasp_seq_bwd(ctypes.byref(shape), T, q, k, v, out, rstd, dout, kv, _ptr(dkv_out), decay, token, state_cache, dq, dk, dv,
+                          dlog_g, dkv, _ptr(scratch), scratch.numel() * scratch.element_size(), _stream(stream))
+    if rc != 0:
+        raise LaspError(rc, "lasp_seq_bwd")
 
 
 def bidir_scratch_bytes(shape: Shape) -> int:
