@@ -426,6 +426,9 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         }
     };
     to_cache(t0);
+    if constexpr (E::PLANES == 3 && !STATES) {
+        if (w == D / 32 - 1) clear_upper_scores<LDP>(ln, sP);
+    }
     if (!DQ && kv_copy && slot0 == 0) state_store_w<D, WK, WV>(ln, st, kv_copy + (size_t)chain * WK * WV, w);
     if constexpr (RAGGED && !TOKEN) {
         __syncthreads();   // the power table
@@ -900,6 +903,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
 
+    if (w8 < 2) clear_upper_scores<LDP>(ln, w8 ? sDS : sS);
     for (int t = t1 - 1; t >= t0; --t) {
         __syncthreads();  // previous tile fully consumed
         ln = fresh_lane();
@@ -915,16 +919,12 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             if (t < t1 - 1) flush_r(t + 1);
         }
         if (t > t0) request(t - 1, CT);
-        // masked scores: one wave S^T = K Q^T, one on another SIMD dS^T = V dO^T
-        auto score = [&](const bf16_t *sA, const bf16_t *sB, bf16_t *dst, auto steps) __attribute__((always_inline)) {
-            f32x16 acc = {0};
-            pipelined_flat<decltype(steps)::value, 1>(
-                [&](int k) { return FragPair<F>{E::ld_kc(ln, sA, LDD, 0, k * E::KSTEP), E::ld_kc(ln, sB, LDD, 0, k * E::KSTEP)}; },
-                [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); });
-            store_masked_scores<T, LDP>(ln, dst, acc, 0, 0, dec);
-        };
-        if (w8 == 0) score(sK, sQ, sS, std::integral_constant<int, WK / E::KSTEP>{});
-        else if (w8 == NW + 1) score(sV, sdO, sDS, std::integral_constant<int, WV / E::KSTEP>{});
+        // masked scores S^T = K Q^T and dS^T = V dO^T (over the real key and value features), a 16x16 block at a time
+        for (int blk = w8; blk < 2 * kScoreBlocks16; blk += 2 * NW) {
+            const int b = blk % kScoreBlocks16, jb = score_jb16(b), ib = score_ib16(b);
+            if (blk < kScoreBlocks16) score_block16<LDD, LDP, WK>(ln, sS, sK, sQ, jb, ib, dec);
+            else score_block16<LDD, LDP, WV>(ln, sDS, sV, sdO, jb, ib, dec);
+        }
         ln = fresh_lane();
 
         const int nv = nvalid(t);
