@@ -94,11 +94,15 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
         p->cache_tiles = (p->ntiles + fwd_auto - 1) / fwd_auto;
     }
     if (want == 0) want = auto_segments(*p, pass, chains);
+    const bool alone = s->segments == 0 && group == 1;   // a launch of one sub-sequence, cut as the library likes
     p->ragged = s->N % (two_byte && pass == kBackward ? 2 * p->tile : p->tile) != 0;
     p->tiles_per_seg = (p->ntiles + want - 1) / want;
     if (two_byte)
-        p->tiles_per_seg = lasp::segment_tiles(p->tiles_per_seg, p->ntiles, chains, p->D, p->cache_tiles == 1, pass == kBackward);
+        p->tiles_per_seg = lasp::segment_tiles(p->tiles_per_seg, p->ntiles, chains, p->D, p->cache_tiles == 1, pass == kBackward, alone);
     p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
+    // (the backward walk in pairs has no room for it: with it in, its loop comes out 2 - 4 % slower)
+    p->own_states = alone && p->nseg > 1 && lasp::own_states((p->nseg - 1) * p->tiles_per_seg, two_byte) &&
+                    (!two_byte || pass == kForward || p->tiles_per_seg == 1 || p->cache_tiles == 1);
     return LASP_OK;
 }
 

@@ -27,6 +27,7 @@ struct Plan {
     bool token;         // per-token decay: `decay` of the argument structs is log g, [B][H][N]
     bool norm;          // output rows are normalised (forward epilogue, backward prologue)
     int kvdiv;          // query heads per K/V head (1 = every query head has its own)
+    bool own_states;    // every workgroup of a walk computes its segment's start state itself: no local pass, no scan, no scratch
 };
 
 // Sub-sequences of one shape, each with buffers of its own, can go through the kernels in one launch (blockIdx.z), the

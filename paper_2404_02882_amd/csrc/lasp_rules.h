@@ -8,6 +8,15 @@ namespace lasp {
 // up to which the bfloat16 forward walk takes eight waves a workgroup.
 constexpr int kOnePerCu = 256;
 
+// Whether the workgroups of a walk compute their segments' start states themselves, `tiles` being what the last of them has
+// in front of it (the first, backward, behind it): no local pass, no scan, one launch a pass. A tile taken through the state
+// alone costs about 1.3 us (bfloat16, 64 tokens) or 3.5 us (float, 32), the local pass and its launch 6 - 9 us and a scan or
+// the states carried over 5 more. Steps without / with, d=128: bfloat16 2 heads x 128 tokens 23.4 / 18.5 us, 16 x 256
+// 38.0 / 24.9, 32 x 384 46.2 / 31.8, 2 x 512 42.3 / 33.8, 64 x 512 60.1 / 53.4; 16 x 768 51.7 / 51.9, 2 x 768 35.0 / 45.1;
+// float 16 x 128 60.3 / 48.8, 2 x 256 51.4 / 67.9.
+constexpr int kShortTiles = 8;
+inline bool own_states(int tiles, bool two_byte) { return tiles < (two_byte ? kShortTiles : 4); }
+
 // Whether the bfloat16 state cache holds the state of every tile, not of every second one, and the backward walk takes its
 // tiles one by one (D: the larger dimension). Pairs halve the cache's bytes; but a sequence of an odd number of tiles has a
 // pair of one, and cannot be cut below two tiles, which keeps a short sequence of few heads waiting; and at d=64, where a
@@ -25,7 +34,11 @@ inline bool cache_every_tile(int ntiles, long long chains, int D) {
 // decay per token 20.4 / 21.6, 16 x 9 23.0 / 22.2) or, at d=64, 208 (16 x 13 15.9 / 16.8), but not from five to eight tiles,
 // where pairs make at most four segments and need no scan (16 x 7 21.1 / 18.0, 8 x 5 18.3 / 16.4); and other odd numbers at
 // d=64 while three workgroups share a CU (16 heads x 79 tiles, three / four 27.0 / 29.3, 32 x 79, five / six 35.0 / 37.7).
-inline int segment_tiles(int want, int ntiles, long long chains, int D, bool every_tile, bool backward) {
+// Both passes take single tiles, whatever the cache holds, where a short sequence goes through alone (own_states): steps with
+// pairs / single tiles in the forward pass 16 x 384 33.6 / 30.7 us, 32 x 256 29.4 / 27.3, in the backward pass too 25.8 / 24.9
+// (16 x 256), 41.1 / 36.9 (16 x 512); beside other sub-sequences, which are scanned together, pairs (4 x 16 x 512 46.1 / 49.6).
+inline int segment_tiles(int want, int ntiles, long long chains, int D, bool every_tile, bool backward, bool alone) {
+    if (alone && ntiles <= kShortTiles && chains * ntiles <= kOnePerCu) return 1;
     if (want % 2 == 0) return want;
     bool keep = every_tile;
     if (!backward) {

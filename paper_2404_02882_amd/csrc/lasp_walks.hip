@@ -18,6 +18,8 @@
 //                tile). Backward: k_bwd8p for bfloat16 (one cached state per
 //                pair of tiles); float: dQ by k_fwd over dO, V, K, then k_bwdkv
 //                for dK and dV.
+// Short sequences need only step 3: with few tiles in front of it a workgroup
+// takes the state through them itself (Start kOwn, own_states in lasp_rules.h).
 // Every kernel is instantiated for a decay model (lasp_device.h): one lambda
 // per head, or a decay per token (general recurrent form of App. A.4), which
 // adds k_dlg for the gradient of the log decay; optionally with the output
@@ -51,6 +53,10 @@ DEVI ptrdiff_t kv_shift(int chain, int H, int kvdiv, int ntok, int width) {
     const int kvchain = (chain / H) * (H / kvdiv) + (chain % H) / kvdiv;
     return (ptrdiff_t)(kvchain - chain) * ntok * width;
 }
+// Where a walk takes its segment's start state from: a state that the forward pass kept (float dQ), its slot as k_scan left
+// it, the boundary state carried over the local states of the segments before (start_state), or the boundary state taken
+// through the tiles of those segments by the workgroup itself, which needs no local pass and no scratch.
+enum Start { kKept = -1, kScanned = 0, kCarried = 1, kOwn = 2 };
 // First element of tile `t` (CT tokens) of a chain in a token tensor whose rows hold `width` elements.
 DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
     return ((size_t)chain * ntok + (size_t)t * CT) * width;
@@ -382,16 +388,27 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
     static_assert(!STATES || !NORM, "the states do not depend on the Norm");
     TileMover<T, CT, D, NT> mq, mk, mv;
-    if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t0), nvalid(t0));
-    mk.template load_w<WK>(K + koff(t0), nvalid(t0));
-    mv.template load_w<WV>(V + voff(t0), nvalid(t0));
     NormTile<T, CT, D, NT, WK> mn;   // kDq only
     const float *rstd_c = rstd + (size_t)chain * ntok;
-    if constexpr (DQ && NORM) mn.load(yn + koff(t0), rstd_c + (size_t)t0 * CT, nvalid(t0));
+    const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
+    typename TokenDecay<T, CT>::LogG lgreg = {};
+    auto request_kv = [&](int t) __attribute__((always_inline)) {
+        mk.template load_w<WK>(K + koff(t), nvalid(t));
+        mv.template load_w<WV>(V + voff(t), nvalid(t));
+        if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
+    };
+    auto request = [&](int t) __attribute__((always_inline)) {
+        if constexpr (DQ && NORM) mn.load(yn + koff(t), rstd_c + (size_t)t * CT, nvalid(t));
+        if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t), nvalid(t));
+        request_kv(t);
+    };
+    const int own = carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    if (own) request_kv(0);
+    else request(t0);
     f32x16 st[DB];
     {
         // kDq, carry < 0: the states are those that the forward pass kept, a buffer per sub-sequence
-        const bool kept = DQ && carry < 0;
+        const bool kept = DQ && carry == kKept;
         const float *states = scratch + (size_t)chain * (kept ? nseg : nslots) * WK * WV;
         auto load = [&](f32x16(&s)[DB], const float *g) {
             if constexpr (DQ) state_load_t_w<D, WV, WK>(ln, s, g, w);   // stored [d_k][d_v] = [WV][WK]
@@ -399,13 +416,48 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         };
         if (carry > 0)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
-    const float *lg = decay + (size_t)chain * ntok;  // per-token decay: `decay` is log g, [chain][token]
-    typename TokenDecay<T, CT>::LogG lgreg = {};
-    if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t0 * CT, nvalid(t0));
+    typename E::frag vf[NKS];
+    auto load_vf = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) vf[ks] = E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w);
+    };
+    for (int t = 0; t < own; ++t) {   // the state alone (all of these tiles are whole)
+        __syncthreads();
+        mk.store(sK, LDD);
+        mv.store(sV, LDD);
+        if constexpr (TOKEN) dec.fill(lgreg);
+        __syncthreads();
+        if (t + 1 < own) request_kv(t + 1);
+        else request(t0);
+        ln = fresh_lane();
+        const float lamC = dec.whole(CT);
+        if constexpr (E::PLANES == 3) {
+            unsigned lows = 0;
+            auto weigh = [&](auto edge) __attribute__((always_inline)) {
+                load_vf();
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<true, decltype(edge)::value>(ln, vf[ks], ks, &lows);
+            };
+            weigh(std::false_type{});
+            if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});
+            decay_and_add<E>(ln, st, lamC, sK, LDD, vf);
+        } else {
+            load_vf();
+#pragma unroll
+            for (int ab = 0; ab < DB; ++ab) st[ab] *= lamC;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                const typename E::frag vd = dec.template weigh_after<true>(ln, vf[ks], ks);
+#pragma unroll
+                for (int ab = 0; ab < DB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, 32 * ab), vd, st[ab]);
+            }
+        }
+    }
+    if (own) __syncthreads();
 
     // State cache: the state KV_{t-1} that tile `t` starts from, rows a, columns c. bfloat16: every second tile, or every
     // tile (cache_tiles 2 or 1). Float: every cache_tiles-th, where the kDq walk starts; these are the segments' starts unless the caller chose the segments.
@@ -449,13 +501,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             if (t > t0 && nvalid(t) < CT) dec.set_end(nvalid(t));
         }
         __syncthreads();
-        if (t + 1 < t1) {
-            if constexpr (DQ && NORM) mn.load(yn + koff(t + 1), rstd_c + (size_t)(t + 1) * CT, nvalid(t + 1));
-            if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t + 1), nvalid(t + 1));
-            mk.template load_w<WK>(K + koff(t + 1), nvalid(t + 1));
-            mv.template load_w<WV>(V + voff(t + 1), nvalid(t + 1));
-            if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)(t + 1) * CT, nvalid(t + 1));
-        }
+        if (t + 1 < t1) request(t + 1);
         // Output tiles are accumulated transposed: OT[c][i], c in this wave's column block.
         f32x16 acc[NB];
         if constexpr (!STATES) {
@@ -482,11 +528,6 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         }
         // V of this wave's columns, for the state update and, behind the barrier, for P V
         ln = fresh_lane();
-        typename E::frag vf[NKS];
-        auto load_vf = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) vf[ks] = E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w);
-        };
         // state update: KV <- lambda^CT KV + (diag{lambda^(CT-1-j)} K)^T V, weight applied to the V fragments
         const float lamC = dec.whole(nvalid(t));
         if constexpr (E::PLANES == 3) {
@@ -650,23 +691,48 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     TileMover<T, CT, D, NT> mq, mk, mv;
     const float *lg = decay + (size_t)chain * ntok;
     typename TokenDecay<T, CT>::LogG lgreg = {};
-    auto request = [&](int t) __attribute__((always_inline)) {
-        if constexpr (!STATES) mq.load(Q + off(t), nvalid(t));
+    auto request_kv = [&](int t) __attribute__((always_inline)) {
         mk.load(K + off(t), nvalid(t));
         mv.load(V + off(t), nvalid(t));
         if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
     };
-    request(t0);
+    auto request = [&](int t) __attribute__((always_inline)) {
+        if constexpr (!STATES) mq.load(Q + off(t), nvalid(t));
+        request_kv(t);
+    };
+    const int own = carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    if (own) request_kv(0);
+    else request(t0);
     f32x16 st[HB];   // st[ab][i] = KV[a0 + 32 ab + acc_row(i)][32 w + r]
     {
         const float *states = scratch + (size_t)chain * nslots * D * D;
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, D * D, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
         else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
+    for (int t = 0; t < own; ++t) {   // the state alone (all of these tiles are whole)
+        __syncthreads();
+        mk.store(sK, LDD);
+        mv.store(sV, LDD);
+        if constexpr (TOKEN) dec.fill(lgreg);
+        __syncthreads();
+        if (t + 1 < own) request_kv(t + 1);
+        else request(t0);
+        ln = fresh_lane();
+        const float lamC = dec.whole(CT);
+#pragma unroll
+        for (int ab = 0; ab < HB; ++ab) st[ab] *= lamC;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            const F vd = dec.template weigh_after<true>(ln, E::ld_ks(ln, sV, LDD, ks * E::KSTEP, 32 * w), ks);
+#pragma unroll
+            for (int ab = 0; ab < HB; ++ab) st[ab] = E::mfma(E::ld_ks(ln, sK, LDD, ks * E::KSTEP, a0 + 32 * ab), vd, st[ab]);
+        }
+    }
+    if (own) __syncthreads();
     auto to_cache = [&](int t) __attribute__((always_inline)) {
         const int half = cache_tiles - 1;
         if (cache && (t & half) == 0)
@@ -871,7 +937,16 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         if constexpr (NORM) mn.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
         if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
     };
-    request(t1 - 1, nvalid(t1 - 1));
+    // what the state alone needs, of the tiles behind this segment that the workgroup takes it through
+    auto request_qdo = [&](int t) __attribute__((always_inline)) {
+        mo.template load_w<WV>(dO + voff(t), nvalid(t));
+        mq.template load_w<WK>(Q + koff(t), nvalid(t));
+        if constexpr (NORM) mn.load(yn + voff(t), rstd_c + (size_t)t * CT, nvalid(t));
+        if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
+    };
+    const int own = carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
+    if (own) request_qdo(ntiles - 1);
+    else request(t1 - 1, nvalid(t1 - 1));
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     float *rs = pw + 3 * CT + 4;   // one row of k.dk sums per wave of group 1
     auto flush_r = [&](int tile) {
@@ -898,9 +973,32 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
+    }
+    for (int t = ntiles - 1; t >= ntiles - own; --t) {
+        __syncthreads();
+        if constexpr (NORM) mn.apply(mo);
+        mo.store(sdO, LDD);
+        mq.store(sQ, LDD);
+        if constexpr (TOKEN) dec.fill(lgreg);
+        __syncthreads();
+        if (t > t1) request_qdo(t - 1);
+        else request(t1 - 1, CT);
+        ln = fresh_lane();
+        if (own_block) {
+            F x2[NKS];
+            unsigned lows = 0;
+            auto weigh = [&](auto edge) __attribute__((always_inline)) {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    x2[ks] = dec.template weigh_upto<decltype(edge)::value>(ln, E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w), ks, &lows);
+            };
+            weigh(std::false_type{});
+            if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});
+            decay_and_add<E>(ln, st, dec.whole(nvalid(t)), sUA, LDD, x2);
+        }
     }
 
     if (w8 < 2) clear_upper_scores<LDP>(ln, w8 ? sDS : sS);
@@ -1000,9 +1098,15 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
 //     one tile early. Per pair: six barriers, 9 tile loads, one cache-tile load.
 // An odd tile count leaves the last pair without its O tile: nothing of it is
 // read, its phase is skipped and the E tile is the one that may be short.
-// BY_TILES: the cache holds every tile's state (cache_every_tile), the tiles are
+// kTiles: the cache holds every tile's state (cache_every_tile), the tiles are
 // walked one by one, each as an E tile: four input tiles in LDS, three barriers.
+// kHalves: a state per pair, but a workgroup takes one tile of it, as E or as O tile
+// (short sequences, whose few workgroups leave CUs idle and are bound by the length
+// of a workgroup's chain: 16 heads x 256 tokens, step 38.0 -> 24.9 us together with
+// the start states computed by the workgroups). One copy of the products in either
+// role, so that less code is fetched for a single tile.
 // ---------------------------------------------------------------------------
+enum BwdWalk { kPairs, kTiles, kHalves };
 template <typename T, int CT, int D, bool BY_TILES = false>
 struct Bwd8pSmem {
     static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
@@ -1016,7 +1120,7 @@ struct Bwd8pSmem {
 };
 
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, bool BY_TILES = false>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, BwdWalk MODE = kPairs>
 __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const T *__restrict__ K,
                                                   const T *__restrict__ V, const T *__restrict__ dO,
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
@@ -1029,9 +1133,10 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   BwdShards sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
+    constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves;
     using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
     static_assert(CT == 64, "two 32-token blocks per tile");
-    static_assert(RAGGED || !BY_TILES, "by tiles: an odd number of them");
+    static_assert(RAGGED || MODE == kPairs, "one by one: one instance for any number of tiles and any length of the last");
     constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
                   NKD = D / E::KSTEP, SPB = 32 / E::KSTEP;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1068,9 +1173,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         dQ = at_shard(dQ, sh.dq, shard);
         cache = at_shard(cache, sh.cache, shard);
     }
-    const int t0 = seg * tiles_per_seg;                                  // even, unless by tiles
+    const int t0 = seg * tiles_per_seg;                                  // pairs: even
     // even: the last pair may lack its O tile
-    const int t1 = BY_TILES ? min(t0 + tiles_per_seg, ntiles) : (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;
+    const int t1 = MODE != kPairs ? min(t0 + tiles_per_seg, ntiles) : (min(t0 + tiles_per_seg, ntiles) + (RAGGED ? 1 : 0)) & ~1;
     auto nvalid = [&](int t) { return RAGGED ? max(min(CT, ntok - t * CT), 0) : CT; };  // rows of tile `t` that exist
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW;    // feature block of this wave's outputs
@@ -1152,8 +1257,36 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
         if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
     };
-    if constexpr (BY_TILES) load_tile(t1 - 1, nvalid(t1 - 1));
-    else load_pair(t1 - 2);
+    [[maybe_unused]] auto load_half = [&](int t) __attribute__((always_inline)) {   // halves
+        const int tE = t & ~1, n = nvalid(t);
+        if (t & 1) {
+            mvO.template load_w<WV>(V + voff(t), n);
+            mkO.template load_w<WK>(K + koff(t), n);
+            if constexpr (TOKEN) lgO = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
+        }
+        mvE.template load_w<WV>(V + voff(tE), nvalid(tE));
+        mkE.template load_w<WK>(K + koff(tE), nvalid(tE));
+        mc.template load_w<WV>(ctile + (size_t)(tE / 2) * WK * WV, WK);
+        if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
+        if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)tE * CT, nvalid(tE));
+        moX.template load_w<WV>(dO + voff(t), n);
+        mqX.template load_w<WK>(Q + koff(t), n);
+    };
+    auto load_first = [&]() __attribute__((always_inline)) {
+        if constexpr (BY_TILES) load_tile(t1 - 1, nvalid(t1 - 1));
+        else if constexpr (HALVES) load_half(t0);
+        else load_pair(t1 - 2);
+    };
+    // what the state alone needs, of the tiles behind this segment that the workgroup takes it through
+    auto load_qdo = [&](int t) __attribute__((always_inline)) {
+        moX.template load_w<WV>(dO + voff(t), nvalid(t));
+        mqX.template load_w<WK>(Q + koff(t), nvalid(t));
+        if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, nvalid(t));
+        if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
+    };
+    const int own = MODE != kPairs && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
+    if (MODE != kPairs && own) load_qdo(ntiles - 1);
+    else load_first();
 
     const T *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
     const T *sUA = rg ? sdO : sQ;    // state-update A operand: [token][feature of the state rows]
@@ -1170,7 +1303,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), slot0, nseg, nslots, WK * WV, load);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), MODE != kPairs && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1254,6 +1387,40 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     // keys span both blocks, group 1 the first).
     constexpr int KB = WK / 32, VB = WV / 32;
     const bool own_block = WK == WV || (rg ? w < KB : w < VB);   // this wave's dK / dV block exists
+    auto update = [&](const auto &dec, int nrows) __attribute__((always_inline)) {
+        if (own_block) {   // state update in this group's orientation
+            const float lamC = dec.whole(nrows);
+#pragma unroll
+            for (int blk = 0; blk < DB; ++blk) st[blk] *= lamC;
+            struct Step { F b; F a[DB]; };
+            pipelined<NKS>(
+                [&](int ks) {
+                    Step f;
+                    f.b = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
+#pragma unroll
+                    for (int blk = 0; blk < DB; ++blk) f.a[blk] = E::ld_ks(ln, sUA, LDD, ks * E::KSTEP, 32 * blk);
+                    return f;
+                },
+                [&](int ks, const Step &f) {
+                    const F bs = dec.weigh_upto(ln, f.b, ks);
+#pragma unroll
+                    for (int blk = 0; blk < DB; ++blk) st[blk] = E::mfma(f.a[blk], bs, st[blk]);
+                });
+        }
+    };
+    if constexpr (MODE != kPairs)
+    for (int t = ntiles - 1; t >= ntiles - own; --t) {
+        __syncthreads();
+        if constexpr (NORM) mnX.apply(moX);
+        moX.store(sdO, LDD);
+        mqX.store(sQ, LDD);
+        if constexpr (TOKEN) decE.fill(lgE);
+        __syncthreads();
+        if (t > t1) load_qdo(t - 1);
+        else load_first();
+        ln = fresh_lane();
+        update(decE, nvalid(t));
+    }
     constexpr bool DQ_BY_IDLE = WK < WV && !(TOKEN && NORM);   // (that one combination would run out of registers)
     auto products = [&](const auto &dec, const T *pV, const T *pK, int t, int nrows, bool cross) {
         const T *sX1 = rg ? pV : pK;  // inter operand: token rows, features contracted with the state
@@ -1340,25 +1507,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                 if (ln.h == 0) rs[w8 * CT + 32 * jb + ln.r] = rq[jb];
         }
         ln = fresh_lane();
-        if (own_block) {   // state update in this group's orientation
-            const float lamC = dec.whole(nrows);
-#pragma unroll
-            for (int blk = 0; blk < DB; ++blk) st[blk] *= lamC;
-            struct Step { F b; F a[DB]; };
-            pipelined<NKS>(
-                [&](int ks) {
-                    Step f;
-                    f.b = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
-#pragma unroll
-                    for (int blk = 0; blk < DB; ++blk) f.a[blk] = E::ld_ks(ln, sUA, LDD, ks * E::KSTEP, 32 * blk);
-                    return f;
-                },
-                [&](int ks, const Step &f) {
-                    const F bs = dec.weigh_upto(ln, f.b, ks);
-#pragma unroll
-                    for (int blk = 0; blk < DB; ++blk) st[blk] = E::mfma(f.a[blk], bs, st[blk]);
-                });
-        }
+        update(dec, nrows);
     };
 
     if constexpr (BY_TILES) {
@@ -1384,7 +1533,38 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             products(decE, sVE, sKE, t, nvalid(t), false);
         }
     }
-    for (int tE = BY_TILES ? t0 - 1 : t1 - 2; tE >= t0; tE -= 2) {
+    if constexpr (HALVES) {
+        const bool odd = t0 & 1;
+        const auto dec = [&] {
+            if constexpr (TOKEN) return TokenDecay<T, CT>(odd ? pw : pw + 3 * CT);
+            else return decO;
+        }();
+        const T *pV = odd ? sVO : sVE, *pK = odd ? sKO : sKE;
+        __syncthreads();
+        ln = fresh_lane();
+        if constexpr (TOKEN) {
+            if (odd) decO.fill(lgO);
+            decE.fill(lgE);
+        }
+        if constexpr (NORM) mnX.apply(moX);
+        if (odd) {
+            mvO.store(sVO, LDD);
+            mkO.store(sKO, LDD);
+        }
+        moX.store(sdO, LDD);
+        mqX.store(sQ, LDD);
+        mvE.store(sVE, LDD);
+        mkE.store(sKE, LDD);
+        mc.store(sC, LDD);
+        __syncthreads();
+        ln = fresh_lane();
+        scores(dec, pV, pK);
+        if (odd) cross_scores();
+        __syncthreads();
+        ln = fresh_lane();
+        products(dec, pV, pK, t0, nvalid(t0), odd);
+    }
+    for (int tE = MODE != kPairs ? t0 - 1 : t1 - 2; tE >= t0; tE -= 2) {
         __syncthreads();  // previous pair fully consumed
         ln = fresh_lane();
         if constexpr (TOKEN) {
@@ -1512,7 +1692,12 @@ struct Bwd8pFam {   // eight waves, one cached state per pair of tiles
 template <typename T, int CT, int D, int WK, int WV>
 struct Bwd8tFam {   // one cached state per tile; an odd tile count is ragged
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, true>;
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kTiles>;
+};
+template <typename T, int CT, int D, int WK, int WV>
+struct Bwd8hFam {   // one cached state per pair of tiles, a workgroup per tile
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kHalves>;
 };
 
 // The local pass only sums over its segment, so its tile need not be the walk's:
@@ -1545,27 +1730,27 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
 // first tile (a state's loads, one after the other), the scan 3 - 11 us and a launch. bf16 d=128 forward / backward:
 // 128 heads x 1024 tokens (2 segments) 63.9 / 88.2 -> 56.8 / 79.2 us, 64 x 8192 (4) 195.4 / 302.4 -> 188.0 / 301.9,
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
-static bool walk_carries(const Plan &p) { return p.shards * p.nseg <= 4; }
+static Start walk_start(const Plan &p) { return p.own_states ? kOwn : p.shards * p.nseg <= 4 ? kCarried : kScanned; }
 
-// Local pass and scan of the forward states over K, V; `carry`: the scan is left to the walk.
+// Local pass and scan of the forward states over K, V, as far as the walk's start asks for them.
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_states(const Plan &p, const void *k, const void *v, const float *kv_in, const float *decay, float *scratch,
-                             float *seglog, bool carry, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
-    if (p.shards * p.nseg > 1) {
+                             float *seglog, Start start, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
+    if (start != kOwn && p.shards * p.nseg > 1) {
         if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, sh, s);
             e != hipSuccess)
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
-    return carry ? hipSuccess : launch_scan(p, false, scratch, kv_in, decay, seglog, s);
+    return start != kScanned ? hipSuccess : launch_scan(p, false, scratch, kv_in, decay, seglog, s);
 }
 
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
-    const bool carry = walk_carries(p);
+    const Start start = walk_start(p);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
-    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry, a.sh, s, ke); e != hipSuccess) return e;
+    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
     const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.decay, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}, {}};
@@ -1580,7 +1765,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
             const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
             if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                   (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles, (const float *)a.scratch,
-                                  a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N,
+                                  a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N,
                                   p.kvdiv, a.rstd_out, a.eps, a.kv_copy, sh);
                 e != hipSuccess)
                 return e;
@@ -1591,7 +1776,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
     if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                           (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                          p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)carry, p.H, p.ntiles, p.nseg,
+                          p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
                           p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
                           (const T *)nullptr, (float *)nullptr, a.kv_copy, sh);
         e != hipSuccess)
@@ -1605,15 +1790,15 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
     const Plan &f = *a.fwd;   // a segment per cached state
-    const int carry = a.cache ? -1 : walk_carries(f);   // -1: a state per segment of every sub-sequence, in its own buffer
+    const Start start = a.cache ? kKept : walk_start(f);   // kKept: a state per segment of every sub-sequence, in its own buffer
     if (!a.cache) {
-        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, carry != 0, a.sh, s, nullptr);
+        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, nullptr);
             e != hipSuccess)
             return e;
     }
     return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
                          (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr, f.cache_tiles,
-                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, carry,
+                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start,
                          f.H, f.ntiles, f.nseg, f.shards * f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
                          (const T *)a.q, a.rtok, (float *)nullptr,
                          FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.decay, a.sh.cache, a.sh.dq, a.sh.rstd, a.sh.q, a.sh.yn, a.sh.rtok});
@@ -1622,7 +1807,7 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const int chains = p.B * p.H;
-    const bool carry = walk_carries(p);
+    const Start start = walk_start(p);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
     if constexpr (sizeof(T) == 4) {
@@ -1630,14 +1815,14 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
             if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
         }
     }
-    if (p.shards * p.nseg > 1) {
+    if (start != kOwn && p.shards * p.nseg > 1) {
         if (e = run_local<T, CT, D, true, WK, WV>(p, (const T *)a.q, (const T *)a.dout, a.decay, a.scratch, a.seglog, (const T *)a.yn,
                                           a.rstd, a.sh, s);
             e != hipSuccess)
             return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[1], s);
-    if (!carry) {
+    if (start == kScanned) {
         if (e = launch_scan(p, true, a.scratch, a.dkv_out, a.decay, a.seglog, s); e != hipSuccess) return e;
     }
     if (ke) (void)hipEventRecord(ke->ev[2], s);
@@ -1647,11 +1832,12 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
-        const bool by_tiles = p.cache_tiles == 1;
-        e = launch_kernel(by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV>>(p) : by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block,
+        const bool by_tiles = p.cache_tiles == 1, halves = !by_tiles && p.tiles_per_seg == 1;
+        e = launch_kernel(by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV>>(p) : halves ? by_model<Bwd8hFam<T, CT, D, WK, WV>>(p)
+                                                                                      : by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block,
                           by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                           (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
-                          (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H,
+                          (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
                           p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
     } else {
         static_assert(BwdkvSmem<T, CT, D>::TOTAL <= 163840 / (D == 128 ? 1 : 2), "LDS of one gfx950 CU for the workgroups meant to share it");
@@ -1660,7 +1846,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
         }
         e = launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                           (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)carry, a.rtok, p.H, p.ntiles, p.nseg,
+                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
                           p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
     }
     if (e != hipSuccess) return e;

@@ -1,0 +1,38 @@
+"""Short sequences that go through alone: every workgroup takes the state through the tiles before (backward: after) its own,
+and the backward walk takes single tiles of a state cache that holds one state per pair. Lengths around the tiles and around
+the longest that goes this way, odd and even tile counts, one more head than there are CUs for, against the brute-force
+oracle at the tolerances of the other parity tests (1e-4 / 2e-2)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+CASES = [("bf16", 128, 2, N) for N in (64, 65, 128, 129, 200, 256, 511, 512, 513)] + \
+        [("bf16", 64, 3, N) for N in (127, 192, 320, 512)] + [("bf16", 128, 33, 512), ("bf16", 128, 86, 192)] + \
+        [("f32", D, 2, N) for D in (64, 128) for N in (32, 33, 97, 128, 129)]
+
+
+@pytest.mark.parametrize("token", [False, True])
+@pytest.mark.parametrize("dtype,D,H,N", CASES)
+def test_short_alone(oracle, dtype, D, H, N, token):
+    from paper_2404_02882_amd import harness
+    from paper_2404_02882_amd import synth_inputs as si
+    print(f"case short dtype={dtype} D={D} H={H} N={N} token={token}", flush=True)
+    inp = si.make_inputs(si.Config("short", B=1, H=H, N=N, D=D, chunk=64, dtype=dtype, seed=N + H, token_decay=token), with_states=True)
+    rng = np.random.default_rng(N)
+    if token:
+        inp.log_g = np.log(rng.uniform(0.9, 1.0, (1, H, N))).astype(np.float32)
+        o, kvo = oracle.gated_fwd_brute(inp.q, inp.k, inp.v, inp.log_g, inp.kv_in)
+        dq, dk, dv, dlg, gin = oracle.gated_bwd_brute(inp.q, inp.k, inp.v, inp.dout, inp.log_g, inp.kv_in, inp.dkv_out)
+        ref = dict(out=o, kv_out=kvo, dq=dq, dk=dk, dv=dv, dlog_g=dlg, dkv_in=gin)
+    else:
+        inp.decay = rng.uniform(0.95, 1.0, H).astype(np.float32)
+        o, kvo = oracle.fwd_brute(inp.q, inp.k, inp.v, inp.decay, inp.kv_in)
+        dq, dk, dv, gin = oracle.bwd_brute(inp.q, inp.k, inp.v, inp.dout, inp.decay, inp.kv_in, inp.dkv_out)
+        ref = dict(out=o, kv_out=kvo, dq=dq, dk=dk, dv=dv, dkv_in=gin)
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    for recompute in (False, True):
+        got = harness.run_gpu(inp, recompute=recompute)
+        for name, r in ref.items():
+            emax, efro = harness.rel_errors(got[name], r)
+            assert np.isfinite(emax) and emax <= tol and efro <= tol, (recompute, name, emax, efro)
