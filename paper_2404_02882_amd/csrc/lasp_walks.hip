@@ -444,7 +444,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             };
             weigh(std::false_type{});
             if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});
-            decay_and_add<E>(ln, st, lamC, sK, LDD, vf);
+            decay_and_add<E, true>(ln, st, lamC, sK, LDD, vf);
         } else {
             load_vf();
 #pragma unroll
@@ -997,7 +997,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             };
             weigh(std::false_type{});
             if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});
-            decay_and_add<E>(ln, st, dec.whole(nvalid(t)), sUA, LDD, x2);
+            decay_and_add<E, true>(ln, st, dec.whole(nvalid(t)), sUA, LDD, x2);
         }
     }
 
