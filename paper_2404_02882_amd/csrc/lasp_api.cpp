@@ -130,7 +130,7 @@ bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l, int g
     lasp::Plan f, b;
     const size_t chains = (size_t)(shape ? shape->B : 0) * (shape ? shape->H : 0);
     size_t nseg = 0;   // of all sub-sequences of a launch; one buffer serves both passes, and launches of one sub-sequence
-    for (int n : {1, group}) {
+    for (int n = group; n >= 1; n = n > 1 ? 1 : 0) {
         if (make_plan(shape, kForward, &f, token, false, n) != LASP_OK || make_plan(shape, kBackward, &b, token, false, n) != LASP_OK)
             return false;
         nseg = std::max<size_t>(nseg, n * std::max(f.nseg, b.nseg));
@@ -296,7 +296,9 @@ int single_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, const lasp::Plan 
 int run_fwd_call(const FwdCall &c) {
     lasp::Plan p, one;
     int rc = make_plan(c.shape, kForward, &p, c.token, c.norm, c.group);
-    if (rc != LASP_OK || (rc = single_plan(c.shape, kForward, &one, p)) != LASP_OK) return rc;
+    if (rc != LASP_OK) return rc;
+    if (c.group == 1) one = p;
+    else if (rc = single_plan(c.shape, kForward, &one, p); rc != LASP_OK) return rc;
     for (int t = 0; t < c.T; ++t)
         if (!c.q[t] || !c.k[t] || !c.v[t] || !c.decay[c.token ? t : 0] || !c.out[t] || !c.kv_out[t] || (c.norm && !at(c.rstd, t)))
             return LASP_ERR_NULL;
@@ -412,7 +414,9 @@ size_t recompute_scratch(const lasp_shape *shape, bool token, int group = 1) {
 int run_bwd_call(const BwdCall &c) {
     lasp::Plan p, one;
     int rc = make_plan(c.shape, kBackward, &p, c.token, c.norm, c.group);
-    if (rc != LASP_OK || (rc = single_plan(c.shape, kBackward, &one, p)) != LASP_OK) return rc;
+    if (rc != LASP_OK) return rc;
+    if (c.group == 1) one = p;
+    else if (rc = single_plan(c.shape, kBackward, &one, p); rc != LASP_OK) return rc;
     const bool rebuild = !c.cache || c.cache[0] == nullptr;
     for (int t = 0; t < c.T; ++t) {
         if (!c.q[t] || !c.k[t] || !c.v[t] || !c.dout[t] || !c.decay[c.token ? t : 0] || !c.dq[t] || !c.dk[t] || !c.dv[t] || !c.dkv_in[t])
@@ -459,12 +463,18 @@ int run_bwd_call(const BwdCall &c) {
         if (rc != LASP_OK) return rc;
     }
 
-    lasp::Plan f, f1, g;   // the forward pass's own plans (its segment count), and that of the cached states: dQ of float data
-    if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm, c.group); rc != LASP_OK) return rc;
-    if (rc = single_plan(c.shape, kForward, &f1, f); rc != LASP_OK) return rc;
-    lasp_shape cut = *c.shape;
-    cut.segments = 0;
-    if (rc = make_plan(&cut, kForward, &g, c.token, c.norm, c.group); rc != LASP_OK) return rc;
+    // the forward pass's own plans (its segment count: only where the states are rebuilt), and that of the cached states: dQ of
+    // float data
+    lasp::Plan f{}, f1{}, g{};
+    if (rebuild) {
+        if (rc = make_plan(c.shape, kForward, &f, c.token, c.norm, c.group); rc != LASP_OK) return rc;
+        if (rc = single_plan(c.shape, kForward, &f1, f); rc != LASP_OK) return rc;
+    }
+    if (p.dtype == LASP_F32) {
+        lasp_shape cut = *c.shape;
+        cut.segments = 0;
+        if (rc = make_plan(&cut, kForward, &g, c.token, c.norm, c.group); rc != LASP_OK) return rc;
+    }
     auto launch = [&](int first, int n) {
         const int last = first + n - 1;
         lasp::Plan use = n > 1 ? p : one, use_f = n > 1 ? f : f1;

@@ -925,7 +925,7 @@ struct SegDecay {
         : seglog(TOKEN ? seglog_all + (size_t)chain * nslots : nullptr) {
         if constexpr (!TOKEN) {
             full = (float)pow_n(decay[chain % H], seg_tokens);
-            last = (float)pow_n(decay[chain % H], ntok - (nseg - 1) * seg_tokens);
+            last = ntok == nseg * seg_tokens ? full : (float)pow_n(decay[chain % H], ntok - (nseg - 1) * seg_tokens);
         }
     }
     DEVI float operator()(int j, bool shard_end) const {
