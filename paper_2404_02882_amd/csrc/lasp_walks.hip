@@ -1725,8 +1725,9 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
                          scratch, seglog, p.H, p.ntiles, p.nseg, nslots, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, sh);
 }
 
-// Whether the walk carries the boundary state over the segments before its own itself (start_state) instead of
-// a scan kernel filling every segment's slot. Each segment carried over costs the walk 1.3 - 1.8 us before its
+// Where the walk's start states come from: own_states (lasp_rules.h) where the plan says so; else, up to four segments, the
+// walk carries the boundary state over the local states before its own (start_state) instead of a scan kernel filling
+// every segment's slot. Each segment carried over costs the walk 1.3 - 1.8 us before its
 // first tile (a state's loads, one after the other), the scan 3 - 11 us and a launch. bf16 d=128 forward / backward:
 // 128 heads x 1024 tokens (2 segments) 63.9 / 88.2 -> 56.8 / 79.2 us, 64 x 8192 (4) 195.4 / 302.4 -> 188.0 / 301.9,
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
