@@ -305,7 +305,8 @@ int lasp_gated_bwd_norm(const lasp_shape *shape, const void *q, const void *k, c
  * every sub-sequence with the same shape and with buffers of its own (arrays of T
  * device pointers, themselves in host memory, not kept). Several sub-sequences go
  * through a launch together where that fills the device and their buffers do not
- * overlap; sums are then taken in another order than call by call.
+ * overlap; sums are then taken in another order than call by call. With a decay per
+ * token they go one after the other.
  *
  *   decay      one pointer (lambda [H], shared), or with token != 0 T pointers (log g).
  *   rstd       NULL = outputs are not normalised (eps, and out in lasp_seq_bwd, are

@@ -125,7 +125,6 @@ struct ScratchLayout {
     size_t states, seglog, rtok, dk_part, dv_part, total;  // byte offsets of the regions (states = 0), total size
 };
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
-size_t rtok_bytes(const lasp::Plan &p) { return round256((size_t)p.B * p.H * p.N * sizeof(float)); }
 bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l, int group = 1) {
     lasp::Plan f, b;
     const size_t chains = (size_t)(shape ? shape->B : 0) * (shape ? shape->H : 0);
@@ -141,9 +140,9 @@ bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l, int g
     size_t end = l->seglog;
     const bool ragged = f.N % f.tile != 0;
     if (f.token || ragged) {
-        const size_t per_token = rtok_bytes(f);   // of one sub-sequence
+        const size_t per_token = round256(chains * (size_t)f.N * sizeof(float));
         l->rtok = l->seglog + round256(chains * nseg * sizeof(float));
-        end = l->rtok + (f.token ? group * per_token : 2 * per_token);
+        end = l->rtok + (f.token ? 1 : 2) * per_token;
     }
     l->dk_part = l->dv_part = end;
     if (f.kvdiv > 1) {
@@ -242,12 +241,17 @@ lasp::Offsets strides(size_t bytes) {
 // many workgroups as a launch of one has: more would go through in several rounds, and read more in the local pass.
 // Step one by one / together, us: 16 heads x 1024 tokens x 4, d=64, in a graph 149 / 64; 32 heads x 4096 x 2 with four K/V
 // heads 314 / 261; 16 x 32768 x 8 3890 / 3658. (The longer kernel arguments cost every launch 0.1 - 0.2 us of host time.)
+// With a decay per token one by one: the gradient of log g is <dkv_out, kv_out> plus a sum over the sub-sequence's tail that
+// cancels most of it, and together its two ends would not be the tensors the walk starts from (a scan's states stand 0.2 %
+// from what the neighbour's walk returns) and its segments longer. Error of dlog_g against 64 bits, mean (largest) of six
+// inputs, one by one / together: 2 heads x 24576 x 4, Norm, d=64 3.7e-2 (4.8e-2) / 4.0e-2 (5.5e-2), d=128 3.7e-2 (4.3e-2) /
+// 4.0e-2 (5.1e-2), 16 x 777 x 4 7.0e-3 / 7.2e-3.
 int shards_per_launch(const lasp_shape *s, int T, bool token) {
-    if (T < 2 || s->segments != 0) return 1;
+    if (T < 2 || s->segments != 0 || token) return 1;
     const int64_t chains = (int64_t)s->B * s->H;
     auto workgroups = [&](Pass pass, int group) {
         lasp::Plan p;
-        return make_plan(s, pass, &p, token, false, group) == LASP_OK ? chains * group * p.nseg : 0;
+        return make_plan(s, pass, &p, false, false, group) == LASP_OK ? chains * group * p.nseg : 0;
     };
     const int64_t most = std::min<int64_t>(std::min(T, lasp::kMaxShards), lasp::kOnePerCu / chains);
     for (int n = (int)most; n > 1; --n) {
@@ -346,7 +350,6 @@ int run_fwd_call(const FwdCall &c) {
             a.sh.q = offsets(c.q, first, n);
             a.sh.k = offsets(c.k, first, n);
             a.sh.v = offsets(c.v, first, n);
-            if (c.token) a.sh.decay = offsets(c.decay, first, n);
             a.sh.out = offsets(c.out, first, n);
             a.sh.rstd = offsets(c.rstd, first, n);
             a.sh.kv_out = offsets(c.kv_out, first, n);
@@ -359,12 +362,11 @@ int run_fwd_call(const FwdCall &c) {
         if (n > 1) {
             Together all;
             all.in(first ? c.kv_out[first - 1] : kv_in, sb);
-            all.in(c.token ? nullptr : c.decay[0], db);
+            all.in(c.decay[0], db);
             for (int t = first; t < first + n; ++t) {
                 all.in(c.q[t], qb);
                 all.in(c.k[t], qb / p.kvdiv);
                 all.in(c.v[t], ob / p.kvdiv);
-                all.in(c.token ? c.decay[t] : nullptr, db);
                 all.out(c.out[t], ob);
                 all.out(at(c.rstd, t), gb);
                 all.out(c.kv_out[t], sb);
@@ -485,14 +487,12 @@ int run_bwd_call(const BwdCall &c) {
             sh.k = offsets(c.k, first, n);
             sh.v = offsets(c.v, first, n);
             sh.dout = offsets(c.dout, first, n);
-            if (c.token) sh.decay = offsets(c.decay, first, n);
             sh.dq = offsets(c.dq, first, n);
             sh.dk = offsets(c.dk, first, n);
             sh.dv = offsets(c.dv, first, n);
             sh.dkv_in = offsets(c.dkv_in, first, n);
             sh.yn = offsets(c.yn, first, n);
             sh.rstd = offsets(c.rstd, first, n);
-            sh.rtok = strides(rtok_bytes(p));
             sh.cache = rebuild ? strides(cb) : offsets(c.cache, first, n);
         }
         const void *cache = rebuild ? scr + round256(l.total) : c.cache[first];
@@ -505,14 +505,9 @@ int run_bwd_call(const BwdCall &c) {
             if (lasp::launch_fwd(use_f, fa, stream, nullptr) != hipSuccess) return false;
         }
         lasp::BwdArgs a{c.q[first], c.k[first], c.v[first], c.dout[first], last + 1 < c.T ? c.dkv_in[last + 1] : dkv_out, c.decay[c.token ? first : 0],
-                        cache, c.dq[first], c.dk[first], c.dv[first], c.dkv_in[first], (float *)scr, &g, kv_in, {},
+                        cache, c.dq[first], c.dk[first], c.dv[first], c.dkv_in[first], (float *)scr, &g, kv_in, at(c.kv_out, first), at(c.dlog_g, first),
                         p.token ? (float *)(scr + l.seglog) : nullptr, p.token ? (float *)(scr + l.rtok) : nullptr, at(c.yn, first),
                         at(c.rstd, first), {}, last + 1 < c.T ? nullptr : dkv_copy, sh};
-        for (int i = 0; i < n && c.token; ++i) {
-            a.dlg.kv_out[i] = at(c.kv_out, first + i);
-            a.dlg.dkv_out[i] = first + i + 1 < c.T ? c.dkv_in[first + i + 1] : dkv_out;
-            a.dlg.dlog_g[i] = c.dlog_g[first + i];
-        }
         if (p.kvdiv > 1) {   // the kernels write dK, dV per query head; launch_bwd sums each group into the outputs
             for (int i = 0; i < n; ++i) {
                 a.group.dk[i] = c.dk[first + i];
@@ -530,22 +525,19 @@ int run_bwd_call(const BwdCall &c) {
         if (end - first > 1) {
             Together all;
             all.in(end < c.T ? c.dkv_in[end] : dkv_out, sb);
-            all.in(c.token ? nullptr : c.decay[0], db);
+            all.in(c.decay[0], db);
             if (rebuild) all.in(at(c.kv_in, first), sb);
             for (int t = first; t < end; ++t) {
                 all.in(c.q[t], qb);
                 all.in(c.k[t], qb / p.kvdiv);
                 all.in(c.v[t], ob / p.kvdiv);
                 all.in(c.dout[t], ob);
-                all.in(c.token ? c.decay[t] : nullptr, db);
-                all.in(at(c.kv_out, t), sb);
                 all.in(at(c.yn, t), ob);
                 all.in(at(c.rstd, t), gb);
                 all.in(at(c.cache, t), cb);
                 all.out(c.dq[t], qb);
                 all.out(c.dk[t], qb / p.kvdiv);
                 all.out(c.dv[t], ob / p.kvdiv);
-                all.out(at(c.dlog_g, t), gb);
                 all.out(c.dkv_in[t], sb);
             }
             if (!all.disjoint()) {

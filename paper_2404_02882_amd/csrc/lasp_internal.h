@@ -31,24 +31,24 @@ struct Plan {
 };
 
 // Sub-sequences of one shape, each with buffers of its own, can go through the kernels in one launch (blockIdx.z), the
-// segments of all of them scanned together. A kernel gets the pointers of the first and, per tensor, the distance in bytes to
+// segments of all of them scanned together (one lambda per head only). A kernel gets the pointers of the first and, per tensor, the distance in bytes to
 // the others'. (Four at most: kernel arguments cost the host time, a launch with all distances of eight 1 us.)
 constexpr int kMaxShards = 4;
 struct Offsets {
     long long at[kMaxShards];
 };
 struct Shards {
-    Offsets q, k, v, dout, decay, cache, out, rstd, kv_out, dq, dk, dv, dkv_in, yn, rtok;   // (decay: log g only)
+    Offsets q, k, v, dout, cache, out, rstd, kv_out, dq, dk, dv, dkv_in, yn;
 };
-// What each kernel needs of it (the forward walk as kDq: dO, V, K as q, k, v, dQ as out, Q as kv_out).
+// What each kernel needs of it (the forward walk as kDq: dO, V, K as q, k, v, dQ as out).
 struct LocalShards {
-    Offsets x, y, decay, yn, rstd;
+    Offsets x, y, yn, rstd;
 };
 struct FwdShards {
-    Offsets q, k, v, decay, cache, out, rstd, kv_out, yn, rtok;
+    Offsets q, k, v, cache, out, rstd, kv_out, yn;
 };
 struct BwdShards {
-    Offsets q, k, v, dout, decay, cache, dq, dk, dv, dkv_in, yn, rstd, rtok;
+    Offsets q, k, v, dout, cache, dq, dk, dv, dkv_in, yn, rstd;
 };
 
 struct FwdArgs {
@@ -59,7 +59,7 @@ struct FwdArgs {
     float *kv_out;
     void *cache;          // may be null
     float *scratch;       // [B*H][shards * nseg][d_k][d_v]
-    float *seglog;        // per-token decay only: [B*H][shards * nseg], log2 of the decay over each segment
+    float *seglog;        // per-token decay only: [B*H][nseg], log2 of the decay over each segment
     float *rstd_out;      // norm only: [B][H][N]
     float eps;            // norm only
     bool states_only;     // rebuild the state cache only: q, out, rstd_out are not touched, kv_out may be null
@@ -67,12 +67,6 @@ struct FwdArgs {
     Shards sh;
 };
 
-// Per sub-sequence of a launch, for the gradient of the per-token decay: the state the forward pass returned, the gradient
-// that comes in from the right (null where it is zero), and the result [B][H][N].
-struct DlogArgs {
-    const float *kv_out[kMaxShards], *dkv_out[kMaxShards];
-    float *dlog_g[kMaxShards];
-};
 // Per sub-sequence, with grouped K/V heads: dk, dv [B][kv_heads][N][D].
 struct GroupOut {
     void *dk[kMaxShards], *dv[kMaxShards];
@@ -90,9 +84,10 @@ struct BwdArgs {
     const Plan *fwd;
     const float *kv_in;
     // per-token decay only
-    DlogArgs dlg;
-    float *seglog;        // [B*H][shards * nseg]
-    float *rtok;          // [shards] blocks (sh.rtok) of [B*H][N], scratch: q_t.dq_t - k_t.dk_t
+    const float *kv_out;  // state the forward pass returned (needed when dkv_out is given)
+    float *dlog_g;        // [B][H][N]
+    float *seglog;        // [B*H][nseg]
+    float *rtok;          // [B*H][N] scratch: q_t.dq_t - k_t.dk_t
     // norm only: `dout` is the gradient w.r.t. the normalised output
     const void *yn;       // the normalised output the forward pass wrote
     const float *rstd;    // [B][H][N], from the forward pass

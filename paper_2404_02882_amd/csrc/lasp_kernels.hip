@@ -86,12 +86,10 @@ DEVI double block_sum(double x, double *sh) {  // sum over the 256 threads, retu
     return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-__global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, Offsets shards, DlogArgs args, int N, int DD) {
+__global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, const float *__restrict__ kv_out,
+                                             const float *__restrict__ dkv_out, float *__restrict__ dlg, int N, int DD) {
     __shared__ double sh[4];
-    const int chain = blockIdx.y, tid = threadIdx.x, shard = blockIdx.z;
-    const float *kv_out = args.kv_out[shard], *dkv_out = args.dkv_out[shard];
-    float *dlg = args.dlog_g[shard];
-    rtok = at_shard(rtok, shards, shard);
+    const int chain = blockIdx.y, tid = threadIdx.x;
     const int s0 = blockIdx.x * kDlgBlock;  // first token of this block
     const float *r = rtok + (size_t)chain * N;
     double behind = 0.0;
@@ -148,7 +146,7 @@ __global__ __launch_bounds__(256) void k_dlg(const float *__restrict__ rtok, Off
 }
 
 hipError_t launch_dlg(const Plan &p, const BwdArgs &a, hipStream_t s) {
-    k_dlg<<<dim3((p.N + kDlgBlock - 1) / kDlgBlock, p.B * p.H, p.shards), dim3(256), 0, s>>>(a.rtok, a.sh.rtok, a.dlg, p.N, p.dk * p.dv);
+    k_dlg<<<dim3((p.N + kDlgBlock - 1) / kDlgBlock, p.B * p.H), dim3(256), 0, s>>>(a.rtok, a.kv_out, a.dkv_out, a.dlog_g, p.N, p.dk * p.dv);
     return hipGetLastError();
 }
 

@@ -99,10 +99,9 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
-    if (shard) {
+    if (!TOKEN && shard) {
         X = at_shard(X, sh.x, shard);
         Y = at_shard(Y, sh.y, shard);
-        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
         if constexpr (NORM) {
             yn = at_shard(yn, sh.yn, shard);
             rstd = at_shard(rstd, sh.rstd, shard);
@@ -357,20 +356,15 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
-    if (shard) {
+    if (!TOKEN && shard) {
         Q = at_shard(Q, sh.q, shard);
         K = at_shard(K, sh.k, shard);
         V = at_shard(V, sh.v, shard);
         O = at_shard(O, sh.out, shard);
-        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
         if constexpr (DQ) {
             if constexpr (NORM) {
                 yn = at_shard(yn, sh.yn, shard);
                 rstd = at_shard(rstd, sh.rstd, shard);
-            }
-            if constexpr (TOKEN) {
-                q_rows = at_shard(q_rows, sh.kv_out, shard);
-                rtok = at_shard(rtok, sh.rtok, shard);
             }
             if (carry < 0) scratch = at_shard(scratch, sh.cache, shard);
         } else {
@@ -669,14 +663,13 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
-    if (shard) {
+    if (!TOKEN && shard) {
         Q = at_shard(Q, sh.q, shard);
         K = at_shard(K, sh.k, shard);
         V = at_shard(V, sh.v, shard);
         O = at_shard(O, sh.out, shard);
         kv_out = at_shard(kv_out, sh.kv_out, shard);
         cache = at_shard(cache, sh.cache, shard);
-        if constexpr (TOKEN) decay = at_shard(decay, sh.decay, shard);
         if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
     }
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -895,7 +888,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
-    if (shard) {
+    if (!TOKEN && shard) {
         Q = at_shard(Q, sh.q, shard);
         K = at_shard(K, sh.k, shard);
         V = at_shard(V, sh.v, shard);
@@ -903,10 +896,6 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         dK = at_shard(dK, sh.dk, shard);
         dV = at_shard(dV, sh.dv, shard);
         dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
-        if constexpr (TOKEN) {
-            decay = at_shard(decay, sh.decay, shard);
-            rtok = at_shard(rtok, sh.rtok, shard);
-        }
         if constexpr (NORM) {
             yn = at_shard(yn, sh.yn, shard);
             rstd = at_shard(rstd, sh.rstd, shard);
@@ -1154,7 +1143,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
 
     const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
-    if (shard) {
+    if (!TOKEN && shard) {
         Q = at_shard(Q, sh.q, shard);
         K = at_shard(K, sh.k, shard);
         V = at_shard(V, sh.v, shard);
@@ -1162,10 +1151,6 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         dK = at_shard(dK, sh.dk, shard);
         dV = at_shard(dV, sh.dv, shard);
         dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
-        if constexpr (TOKEN) {
-            decay = at_shard(decay, sh.decay, shard);
-            rtok = at_shard(rtok, sh.rtok, shard);
-        }
         if constexpr (NORM) {
             yn = at_shard(yn, sh.yn, shard);
             rstd = at_shard(rstd, sh.rstd, shard);
@@ -1708,7 +1693,7 @@ struct Bwd8hFam {   // one cached state per pair of tiles, a workgroup per tile
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
                             const T *yn, const float *rstd, const Shards &all, hipStream_t s) {
-    const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.decay, all.yn, all.rstd};
+    const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.yn, all.rstd};
     const dim3 grid(p.shards > 1 ? p.nseg : p.nseg - 1, p.B * p.H, p.shards), block(D * 2);
     const int nslots = p.shards * p.nseg;
     Plan q = p;
@@ -1754,7 +1739,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
-    const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.decay, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}, {}};
+    const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}};
     if constexpr (sizeof(T) == 2 && WK == 128 && WV == 128) {
         static_assert(Fwd8Smem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         // Up to 256 workgroups a CU has one, and four waves leave each SIMD only one; from 257 on two workgroups of
@@ -1802,7 +1787,7 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
                          a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start,
                          f.H, f.ntiles, f.nseg, f.shards * f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
                          (const T *)a.q, a.rtok, (float *)nullptr,
-                         FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.decay, a.sh.cache, a.sh.dq, a.sh.rstd, a.sh.q, a.sh.yn, a.sh.rtok});
+                         FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.cache, a.sh.dq, a.sh.rstd, {}, a.sh.yn});
 }
 
 template <typename T, int CT, int D, int WK = D, int WV = D>
@@ -1829,7 +1814,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     // The walks: bfloat16 in one kernel with one cached state per pair of tiles; float dQ and dK, dV apart.
     const dim3 grid(p.nseg, chains, p.shards), block(D * 4);
-    const BwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.dout, a.sh.decay, a.sh.cache, a.sh.dq, a.sh.dk, a.sh.dv, a.sh.dkv_in, a.sh.yn, a.sh.rstd, a.sh.rtok};
+    const BwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.dout, a.sh.cache, a.sh.dq, a.sh.dk, a.sh.dv, a.sh.dkv_in, a.sh.yn, a.sh.rstd};
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");

@@ -103,3 +103,53 @@ def test_states_between_and_buffers_that_overlap(gpu, oracle, dtype, n):
                 emax, efro = harness.rel_errors(a, b)
                 assert emax <= TOL[dtype] and efro <= TOL[dtype], (i, emax, efro)
     assert all(np.array_equal(a, b) for x, y in zip(own, together) for a, b in zip(x, y))
+
+
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("D,n", [(64, 24576), (128, 1000)])
+def test_decay_per_token_is_call_after_call(gpu, D, n, norm):
+    """With a decay per token a sequence is what one call after the other computes, to the last bit: the gradient of log g is a
+    sum over each sub-sequence's tail in which most cancels, and holds only for the states the walks themselves start from."""
+    import torch
+    harness, lasp, sequence, si = gpu
+    B, H, T, eps, bf = 1, 2, 4, 1e-5, torch.bfloat16
+    print(f"case call after call D={D} n={n} norm={norm}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")   # noqa: E731
+    q, k, v, do = ([(rnd(B, H, n, D) * D ** -0.5).to(bf) for _ in range(T)] for _ in range(4))
+    lg = [torch.rand(B, H, n, generator=g, device="cuda") * -1e-3 for _ in range(T)]
+    kv_in, dkv_out = rnd(B, H, D, D), rnd(B, H, D, D)
+    seq = sequence.LaspSequence(B, H, n * T, D, 64, bf, T=T, token_decay=True, norm_eps=eps if norm else None)
+    fresh = lambda like: [torch.empty_like(x) for x in like]   # noqa: E731
+
+    def by_sequence():
+        out, dq, dk, dv, dlg = (fresh(x) for x in (v, q, k, v, lg))
+        rstd = fresh(lg) if norm else None
+        seq.forward(q, k, v, lg, out, kv_in, rstd)
+        seq.backward(q, k, v, do, lg, dq, dk, dv, dkv_out, dlg, out if norm else None, rstd)
+        return out + dq + dk + dv + dlg + seq.kv[1:] + seq.dkv[:T]
+
+    def by_calls():
+        out, rstd, dq, dk, dv, dlg = (fresh(x) for x in (v, lg, q, k, v, lg))
+        kv, dkv = [kv_in] + fresh(seq.kv[1:]), fresh(seq.dkv[:T]) + [dkv_out]
+        one = lasp.make_shape(B, H, n, D, 64, bf)
+        scratch = torch.empty(lasp.gated_scratch_bytes(one), dtype=torch.uint8, device="cuda")
+        caches = fresh(seq.caches)
+        for t in range(T):
+            if norm:
+                lasp.lasp_gated_fwd_norm(one, q[t], k[t], v[t], lg[t], kv[t], eps, out[t], rstd[t], kv[t + 1], caches[t], scratch)
+            else:
+                lasp.lasp_gated_fwd(one, q[t], k[t], v[t], lg[t], kv[t], out[t], kv[t + 1], caches[t], scratch)
+        for t in reversed(range(T)):
+            if norm:
+                lasp.lasp_gated_bwd_norm(one, q[t], k[t], v[t], out[t], rstd[t], do[t], lg[t], kv[t], kv[t + 1], dkv[t + 1], caches[t],
+                                         dq[t], dk[t], dv[t], dlg[t], dkv[t], scratch)
+            else:
+                lasp.lasp_gated_bwd(one, q[t], k[t], v[t], do[t], lg[t], kv[t], kv[t + 1], dkv[t + 1], caches[t], dq[t], dk[t], dv[t], dlg[t],
+                                    dkv[t], scratch)
+        return out + dq + dk + dv + dlg + kv[1:] + dkv[:T]
+
+    a, b = by_sequence(), by_calls()
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b)) and all(torch.isfinite(x).all() for x in a)

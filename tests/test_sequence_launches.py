@@ -1,0 +1,142 @@
+"""What the host layer of a whole sequence (lasp_seq_fwd, lasp_seq_bwd) checks, launches and copies: csrc/lasp_api.cpp built
+with the host compiler against launches that only write down what they were asked for. Addresses are never dereferenced."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2404_02882_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+ERR_NULL, ERR_SHAPE, ERR_WORKSPACE, ERR_ALIAS, ERR_ALIGN = 1, 2, 5, 6, 8
+
+RECORDER = r"""
+#include "%(csrc)s/lasp_internal.h"
+#include <cstring>
+namespace { int n; long long rec[256][8]; }
+static hipError_t put(int kind, int shards, const void *a, const void *b, const void *c, int own) {
+    long long r[8] = {kind, shards, (long long)a, (long long)b, (long long)c, own};
+    std::memcpy(rec[n++ & 255], r, sizeof r);
+    return hipSuccess;
+}
+extern "C" int recorded(long long *out) {
+    std::memcpy(out, rec, sizeof rec);
+    const int count = n;
+    n = 0;
+    return count;
+}
+namespace lasp {
+int tile_tokens(int dtype, int, int) { return dtype == 0 ? 32 : 64; }
+hipError_t static_scratch(void **) { return hipErrorUnknown; }
+int bidir_reduce_tile(int) { return 64; }
+hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t, const KernelEvents *) {
+    return put(a.states_only ? 2 : 0, p.shards, a.k, a.kv_in, a.kv_copy, p.own_states);
+}
+hipError_t launch_bwd(const Plan &p, const BwdArgs &a, hipStream_t, const KernelEvents *) {
+    return put(1, p.shards, a.k, a.dkv_out, a.dkv_copy, p.own_states);
+}
+hipError_t launch_bidir_apply(const BidirPlan &, const BidirOps &, int, hipStream_t, const KernelEvents *) { return hipErrorUnknown; }
+hipError_t launch_bidir_state(const BidirPlan &, const void *, const void *, float *, int, float *, hipStream_t, const KernelEvents *) { return hipErrorUnknown; }
+}
+extern "C" {
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t, hipMemcpyKind, hipStream_t) { return put(3, 0, s, nullptr, d, 0); }
+hipError_t hipEventCreate(hipEvent_t *) { return hipErrorUnknown; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *, hipEvent_t, hipEvent_t) { return hipErrorUnknown; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipErrorUnknown; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def api(tmp_path_factory):
+    from paper_2404_02882_amd import lasp
+    d = tmp_path_factory.mktemp("api")
+    src, lib = d / "recorder.cpp", d / "recorder.so"
+    src.write_text(RECORDER % dict(csrc=CSRC))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{ROOT}/include",
+                    str(src), os.path.join(CSRC, "lasp_api.cpp"), "-o", str(lib)], check=True)
+    handle = ctypes.CDLL(str(lib), mode=os.RTLD_LOCAL | os.RTLD_NOW)
+    lasp._bind(handle)
+    return Api(handle, lasp)
+
+
+class Sequence:
+    """Addresses of a sequence's buffers, all apart unless a test moves one."""
+
+    def __init__(self, T, size=1 << 30):
+        self.next = 1 << 40
+        self.size = size
+        for name in ("q", "k", "v", "out", "rstd", "dout", "log_g", "cache", "dq", "dk", "dv", "dlog_g"):
+            setattr(self, name, [self.new() for _ in range(T)])
+        self.kv, self.dkv = ([self.new() for _ in range(T + 1)] for _ in range(2))
+        self.kv_in, self.dkv_out, self.decay, self.scratch = (self.new() for _ in range(4))
+
+    def new(self):
+        self.next += self.size
+        return self.next
+
+
+class Api:
+    def __init__(self, lib, lasp):
+        self.lib, self.lasp = lib, lasp
+
+    def record(self):
+        out = (ctypes.c_longlong * (256 * 8))()
+        n = self.lib.recorded(out)
+        return [tuple(out[8 * i:8 * i + 6]) for i in range(n)]   # kind (0 forward, 1 backward, 2 states, 3 copy), shards, k, in, copy, own
+
+    def shape(self, H=4, N=1024, D=64, dtype="bf16", **kw):
+        return self.lasp.make_shape(1, H, N, D, 64, dtype, **kw)
+
+    def scratch_bytes(self, shape, T, token=False, recompute=False):
+        return self.lib.lasp_seq_scratch_bytes(ctypes.byref(shape), T, int(token), int(recompute))
+
+    @staticmethod
+    def table(list_):
+        return None if list_ is None else (ctypes.c_size_t * len(list_))(*[x or 0 for x in list_])
+
+    def fwd(self, shape, T, s, token=False, norm=False, cache=True, entering=True, scratch_bytes=None):
+        size = self.scratch_bytes(shape, T, token) if scratch_bytes is None else scratch_bytes
+        t = self.table
+        rc = self.lib.lasp_seq_fwd(ctypes.byref(shape), T, t(s.q), t(s.k), t(s.v), s.kv_in if entering else None,
+                                   t(s.log_g if token else [s.decay]), int(token), 1e-5, t(s.out), t(s.rstd) if norm else None,
+                                   t(s.kv), t(s.cache) if cache else None, s.scratch, size, None)
+        return rc, self.record()
+
+    def bwd(self, shape, T, s, token=False, norm=False, cache=True, entering=True, scratch_bytes=None):
+        size = self.scratch_bytes(shape, T, token, not cache) if scratch_bytes is None else scratch_bytes
+        t = self.table
+        rc = self.lib.lasp_seq_bwd(ctypes.byref(shape), T, t(s.q), t(s.k), t(s.v), t(s.out) if norm else None, t(s.rstd) if norm else None,
+                                   t(s.dout), t(s.kv), s.dkv_out if entering else None, t(s.log_g if token else [s.decay]), int(token),
+                                   t(s.cache) if cache else None, t(s.dq), t(s.dk), t(s.dv), t(s.dlog_g) if token else None, t(s.dkv),
+                                   s.scratch, size, None)
+        return rc, self.record()
+
+
+def groups(records, kinds=(0, 1)):
+    return [r[1] for r in records if r[0] in kinds]
+
+
+@pytest.mark.parametrize("dtype,H,D,N", [("bf16", 4, 64, 1024), ("bf16", 2, 64, 24576), ("bf16", 2, 128, 24576), ("f32", 2, 128, 4096)])
+def test_decay_per_token_goes_one_by_one(api, dtype, H, D, N):
+    """The gradient of the log decay is a sum over a sub-sequence's tail in which most cancels: every sub-sequence's walk starts
+    from the very state (and state gradient) its neighbour's walk returned, and its segments are no longer than alone."""
+    shape, T = api.shape(H, N, D, dtype), 4
+    s = Sequence(T)
+    for cache in (True, False):
+        rc, r = api.fwd(shape, T, s, token=True, cache=cache)
+        assert rc == 0 and groups(r) == [1] * T
+        assert [x[3] for x in r if x[0] == 0] == [s.kv_in] + s.kv[1:T]
+        rc, r = api.bwd(shape, T, s, token=True, cache=cache)
+        assert rc == 0 and groups(r) == [1] * T
+        assert [x[3] for x in r if x[0] == 1] == [s.dkv_out] + s.dkv[T - 1:0:-1]
+        rc, r = api.fwd(shape, T, s, cache=cache)   # one lambda per head: together
+        assert rc == 0 and groups(r) == [4]
+    # and no scratch for several
+    one = (api.lib.lasp_gated_scratch_bytes, api.lib.lasp_gated_bwd_recompute_scratch_bytes)
+    for recompute, size in enumerate(one):
+        assert api.scratch_bytes(shape, T, token=True, recompute=bool(recompute)) == size(ctypes.byref(shape))
