@@ -319,8 +319,8 @@ int lasp_gated_bwd_norm(const lasp_shape *shape, const void *q, const void *k, c
  *   dkv        T + 1 gradients: dkv[t] is the one w.r.t. kv[t]; dkv[T] receives a copy
  *              of dkv_out (it may be dkv_out; it is not touched when that is NULL).
  *   state_cache  NULL, or a NULL first pointer, = none: kept (forward), the states are
- *              rebuilt (backward). A cache of lasp_seq_fwd serves lasp_seq_bwd of the
- *              same shape and T.
+ *              rebuilt (backward); else every sub-sequence has one. A cache of
+ *              lasp_seq_fwd serves lasp_seq_bwd of the same shape and T.
  *   scratch    lasp_seq_scratch_bytes() bytes (recompute: for sequences that keep no
  *              cache; those launch several sub-sequences together only while their
  *              caches, which then lie in the scratch, take at most 64 MiB).

@@ -272,7 +272,7 @@ int shards_per_launch(const lasp_shape *s, int T, bool token, bool recompute) {
 
 // One forward call of any flavour, over T sub-sequences of one shape (T = 1: a plain call): `token` selects the decay model
 // (decay = lambda [H], one for all, or log g [B][H][N] of each), `norm` the fused output normalisation (eps, rstd). kv_out[t]
-// is what sub-sequence t leaves and t + 1 starts from.
+// is what sub-sequence t leaves and t + 1 starts from. cache: NULL, or one of every sub-sequence.
 struct FwdCall {
     const lasp_shape *shape;
     int T, group;
@@ -304,7 +304,8 @@ int run_fwd_call(const FwdCall &c) {
     if (c.group == 1) one = p;
     else if (rc = single_plan(c.shape, kForward, &one, p); rc != LASP_OK) return rc;
     for (int t = 0; t < c.T; ++t)
-        if (!c.q[t] || !c.k[t] || !c.v[t] || !c.decay[c.token ? t : 0] || !c.out[t] || !c.kv_out[t] || (c.norm && !at(c.rstd, t)))
+        if (!c.q[t] || !c.k[t] || !c.v[t] || !c.decay[c.token ? t : 0] || !c.out[t] || !c.kv_out[t] || (c.norm && !at(c.rstd, t)) ||
+            (c.cache && !c.cache[t]))
             return LASP_ERR_NULL;
     if (c.norm && (!std::isfinite(c.eps) || c.eps < 0.0f)) return LASP_ERR_SHAPE;
     ScratchLayout l;
@@ -419,7 +420,7 @@ int run_bwd_call(const BwdCall &c) {
     if (rc != LASP_OK) return rc;
     if (c.group == 1) one = p;
     else if (rc = single_plan(c.shape, kBackward, &one, p); rc != LASP_OK) return rc;
-    const bool rebuild = !c.cache || c.cache[0] == nullptr;
+    const bool rebuild = !c.cache;
     for (int t = 0; t < c.T; ++t) {
         if (!c.q[t] || !c.k[t] || !c.v[t] || !c.dout[t] || !c.decay[c.token ? t : 0] || !c.dq[t] || !c.dk[t] || !c.dv[t] || !c.dkv_in[t])
             return LASP_ERR_NULL;
@@ -554,13 +555,13 @@ int run_bwd_call(const BwdCall &c) {
 // Calls of one sub-sequence.
 int fwd_one(const lasp_shape *shape, const void *q, const void *k, const void *v, const float *kv_in, const float *decay, bool token, bool norm,
             float eps, void *out, float *rstd, float *kv_out, void *cache, void *scratch, size_t scratch_bytes, void *stream) {
-    return run_fwd_call({shape, 1, 1, &q, &k, &v, kv_in, nullptr, &decay, token, norm, eps, &out, &rstd, &kv_out, &cache, scratch,
-                         scratch_bytes, stream});
+    return run_fwd_call({shape, 1, 1, &q, &k, &v, kv_in, nullptr, &decay, token, norm, eps, &out, &rstd, &kv_out, cache ? &cache : nullptr,
+                         scratch, scratch_bytes, stream});
 }
 int bwd_one(const lasp_shape *shape, const void *q, const void *k, const void *v, const void *dout, const float *kv_in, const float *dkv_out,
             const float *decay, bool token, bool norm, const void *yn, const float *rstd, const float *kv_out, const void *cache, void *dq,
             void *dk, void *dv, float *dlog_g, float *dkv_in, void *scratch, size_t scratch_bytes, void *stream) {
-    return run_bwd_call({shape, 1, 1, &q, &k, &v, &dout, &kv_in, dkv_out, nullptr, &decay, token, norm, &yn, &rstd, &kv_out, &cache, &dq, &dk,
+    return run_bwd_call({shape, 1, 1, &q, &k, &v, &dout, &kv_in, dkv_out, nullptr, &decay, token, norm, &yn, &rstd, &kv_out, cache ? &cache : nullptr, &dq, &dk,
                          &dv, &dlog_g, &dkv_in, scratch, scratch_bytes, stream});
 }
 
@@ -765,7 +766,7 @@ int lasp_seq_fwd(const lasp_shape *shape, int32_t T, const void *const *q, const
     if (T < 1) return LASP_ERR_SHAPE;
     if (!q || !k || !v || !decay || !out || !kv) return LASP_ERR_NULL;
     return run_fwd_call({shape, T, shards_per_launch(shape, T, token != 0), q, k, v, kv_in, kv[0], decay, token != 0, rstd != nullptr, eps, out,
-                         rstd, kv + 1, state_cache, scratch, scratch_bytes, hip_stream});
+                         rstd, kv + 1, state_cache && state_cache[0] ? state_cache : nullptr, scratch, scratch_bytes, hip_stream});
 }
 
 int lasp_seq_bwd(const lasp_shape *shape, int32_t T, const void *const *q, const void *const *k, const void *const *v, const void *const *out,
@@ -775,9 +776,10 @@ int lasp_seq_bwd(const lasp_shape *shape, int32_t T, const void *const *q, const
     if (int rc = lasp_check_shape(shape); rc != LASP_OK) return rc;
     if (T < 1) return LASP_ERR_SHAPE;
     if (!q || !k || !v || !dout || !decay || !kv || !dq || !dk || !dv || !dkv) return LASP_ERR_NULL;
-    const int group = shards_per_launch(shape, T, token != 0, !state_cache || !state_cache[0]);
+    const void *const *caches = state_cache && state_cache[0] ? state_cache : nullptr;
+    const int group = shards_per_launch(shape, T, token != 0, !caches);
     return run_bwd_call({shape, T, group, q, k, v, dout, kv, dkv_out, dkv[T], decay, token != 0, rstd != nullptr, rstd ? out : nullptr, rstd,
-                         token ? kv + 1 : nullptr, state_cache, dq, dk, dv, token ? dlog_g : nullptr, dkv, scratch, scratch_bytes, hip_stream});
+                         token ? kv + 1 : nullptr, caches, dq, dk, dv, token ? dlog_g : nullptr, dkv, scratch, scratch_bytes, hip_stream});
 }
 
 size_t lasp_bidir_scratch_bytes(const lasp_shape *shape) {

@@ -140,3 +140,22 @@ def test_decay_per_token_goes_one_by_one(api, dtype, H, D, N):
     one = (api.lib.lasp_gated_scratch_bytes, api.lib.lasp_gated_bwd_recompute_scratch_bytes)
     for recompute, size in enumerate(one):
         assert api.scratch_bytes(shape, T, token=True, recompute=bool(recompute)) == size(ctypes.byref(shape))
+
+
+def test_caches_are_all_there_or_none(api):
+    """A NULL first pointer = no cache; a NULL among the others is refused in both passes before anything is launched (the
+    distance to it would send a shared launch to address 0)."""
+    T, shape = 4, api.shape()
+    for at in (1, 2, 3):
+        s = Sequence(T)
+        s.cache[at] = None
+        assert api.fwd(shape, T, s) == (ERR_NULL, [])
+        assert api.bwd(shape, T, s) == (ERR_NULL, [])
+    s = Sequence(T)
+    s.cache[0] = None   # the others are not looked at
+    rc, r = api.fwd(shape, T, s)
+    assert rc == 0 and groups(r) == [4]
+    rc, r = api.bwd(shape, T, s)   # states rebuilt: more scratch
+    assert (rc, r) == (ERR_WORKSPACE, [])
+    rc, r = api.bwd(shape, T, s, scratch_bytes=api.scratch_bytes(shape, T, recompute=True))
+    assert rc == 0 and groups(r, (1, 2)) == [4, 4]
