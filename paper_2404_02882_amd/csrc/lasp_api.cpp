@@ -426,7 +426,7 @@ int run_bwd_call(const BwdCall &c) {
             return LASP_ERR_NULL;
         if (c.norm && (!at(c.yn, t) || !at(c.rstd, t))) return LASP_ERR_NULL;
         if (c.token && (!at(c.dlog_g, t) || ((c.dkv_out || t + 1 < c.T) && !at(c.kv_out, t)))) return LASP_ERR_NULL;
-        if (!rebuild && !c.cache[t]) return LASP_ERR_NULL;
+        if (rebuild ? t > 0 && !at(c.kv_in, t) : !c.cache[t]) return LASP_ERR_NULL;
     }
     ScratchLayout l;
     scratch_layout(c.shape, c.token, &l, c.group);

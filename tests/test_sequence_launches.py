@@ -159,3 +159,14 @@ def test_caches_are_all_there_or_none(api):
     assert (rc, r) == (ERR_WORKSPACE, [])
     rc, r = api.bwd(shape, T, s, scratch_bytes=api.scratch_bytes(shape, T, recompute=True))
     assert rc == 0 and groups(r, (1, 2)) == [4, 4]
+
+
+def test_states_between_are_needed_where_they_are_rebuilt(api):
+    """Only the state in front of the first sub-sequence may be absent (zeros)."""
+    T, shape = 3, api.shape(segments=1)
+    s = Sequence(T)
+    s.kv[0] = None
+    assert api.bwd(shape, T, s, cache=False)[0] == 0 and api.bwd(shape, T, s)[0] == 0
+    s.kv[1] = None
+    assert api.bwd(shape, T, s, cache=False) == (ERR_NULL, [])
+    assert api.bwd(shape, T, s)[0] == 0   # with caches they are not read
