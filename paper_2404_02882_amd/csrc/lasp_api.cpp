@@ -175,6 +175,12 @@ bool overlap(Span a, Span b) {
     return x && y && x < y + b.n && y < x + a.n;
 }
 
+bool overlap_any(Span a, std::initializer_list<Span> others) {
+    for (const Span &x : others)
+        if (overlap(a, x)) return true;
+    return false;
+}
+
 // Outputs must not overlap inputs or each other, and the kernels move data in 16-byte pieces.
 // NULL (an absent optional buffer) passes both checks.
 int check_buffers(std::initializer_list<Span> ins, std::initializer_list<Span> outs) {
@@ -338,6 +344,8 @@ int run_fwd_call(const FwdCall &c) {
         rc = check_buffers({{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {t ? c.kv_out[t - 1] : kv_in, sb}, {c.decay[c.token ? t : 0], db}},
                            {{c.out[t], ob}, {at(c.rstd, t), gb}, {c.kv_out[t], sb}, {at(c.cache, t), cb}, {c.scratch, l.total}, {t ? nullptr : kv_copy, sb}});
         if (rc != LASP_OK) return rc;
+        if (overlap_any({kv_copy, sb}, {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.decay[c.token ? t : 0], db}}))
+            return LASP_ERR_ALIAS;
     }
 
     char *scr = (char *)c.scratch;
@@ -364,6 +372,7 @@ int run_fwd_call(const FwdCall &c) {
             Together all;
             all.in(first ? c.kv_out[first - 1] : kv_in, sb);
             all.in(c.decay[0], db);
+            all.out(first ? nullptr : kv_copy, sb);
             for (int t = first; t < first + n; ++t) {
                 all.in(c.q[t], qb);
                 all.in(c.k[t], qb / p.kvdiv);
@@ -464,6 +473,10 @@ int run_bwd_call(const BwdCall &c) {
                            {{c.dq[t], qb}, {c.dk[t], qb / p.kvdiv}, {c.dv[t], ob / p.kvdiv}, {at(c.dlog_g, t), gb}, {c.dkv_in[t], sb},
                             {c.scratch, need}, {t + 1 < c.T ? nullptr : dkv_copy, sb}});
         if (rc != LASP_OK) return rc;
+        if (overlap_any({dkv_copy, sb}, {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.dout[t], ob}, {at(c.kv_out, t), sb},
+                                         {rebuild ? at(c.kv_in, t) : nullptr, sb}, {at(c.yn, t), ob}, {at(c.rstd, t), gb},
+                                         {c.decay[c.token ? t : 0], db}, {at(c.cache, t), cb}}))
+            return LASP_ERR_ALIAS;
     }
 
     // the forward pass's own plans (its segment count: only where the states are rebuilt), and that of the cached states: dQ of
@@ -527,6 +540,7 @@ int run_bwd_call(const BwdCall &c) {
             Together all;
             all.in(end < c.T ? c.dkv_in[end] : dkv_out, sb);
             all.in(c.decay[0], db);
+            all.out(end < c.T ? nullptr : dkv_copy, sb);
             if (rebuild) all.in(at(c.kv_in, first), sb);
             for (int t = first; t < end; ++t) {
                 all.in(c.q[t], qb);

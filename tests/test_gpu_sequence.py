@@ -153,3 +153,35 @@ def test_decay_per_token_is_call_after_call(gpu, D, n, norm):
     a, b = by_sequence(), by_calls()
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(a, b)) and all(torch.isfinite(x).all() for x in a)
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 256), ("f32", 100)])
+def test_states_in_turn(gpu, dtype, n):
+    """Two states written in turn (kv[0] = kv[2], kv[1] = kv[3]): the copy of the entering state goes to memory that the second
+    sub-sequence writes, so the sequence goes one by one, to the last bit like sub-sequences with states of their own."""
+    import torch
+    harness, lasp, sequence, si = gpu
+    B, H, D, T = 1, 3, 64, 3
+    inp = si.make_inputs(si.Config("turn", B=B, H=H, N=n * T, D=D, chunk=64, dtype=dtype, seed=78), with_states=True)
+    q, k, v, do = (harness.shards(x, T, dtype) for x in (inp.q, inp.k, inp.v, inp.dout))
+    decay, kv_in, dkv_out = (torch.from_numpy(x).cuda() for x in (inp.decay, inp.kv_in, inp.dkv_out))
+    fresh = lambda like: [torch.empty_like(x) for x in like]   # noqa: E731
+
+    def run(in_turn):
+        seq = sequence.LaspSequence(B, H, n * T, D, 64, harness.TORCH_DTYPE[dtype], T=T)
+        out, dq, dk, dv = (fresh(x) for x in (v, q, k, v))
+        if in_turn:
+            for states in (seq.kv, seq.dkv):
+                states[2:] = states[:2]
+            seq.forward(q, k, v, decay, out, kv_in)
+            seq.backward(q, k, v, do, decay, dq, dk, dv, dkv_out)
+        else:
+            one, entering, leaving = lasp.make_shape(B, H, n, D, 64, harness.TORCH_DTYPE[dtype]), [kv_in] + seq.kv[1:], seq.dkv[:T] + [dkv_out]
+            for t in range(T):
+                lasp.lasp_fwd(one, q[t], k[t], v[t], entering[t], decay, out[t], seq.kv[t + 1], seq.caches[t], seq.scratch)
+            for t in reversed(range(T)):
+                lasp.lasp_bwd(one, q[t], k[t], v[t], do[t], None, leaving[t + 1], decay, seq.caches[t], dq[t], dk[t], dv[t], seq.dkv[t], seq.scratch)
+        torch.cuda.synchronize()
+        return out + dq + dk + dv + [seq.kv[T], seq.dkv[0]]
+
+    assert all(torch.equal(a, b) for a, b in zip(run(True), run(False)))

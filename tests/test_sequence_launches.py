@@ -170,3 +170,44 @@ def test_states_between_are_needed_where_they_are_rebuilt(api):
     s.kv[1] = None
     assert api.bwd(shape, T, s, cache=False) == (ERR_NULL, [])
     assert api.bwd(shape, T, s)[0] == 0   # with caches they are not read
+
+
+def test_copy_of_the_entering_state_among_other_sub_sequences_buffers(api):
+    """kv[0] (dkv[T]) is written by the first (last) sub-sequence's walk. On what another one reads it is refused, on what
+    another one writes the sequence goes one by one, in whose order the later write stays; the other groups stay together."""
+    T, shape = 6, api.shape()
+    for buf in ("q", "k", "v"):
+        for t in range(T):
+            s = Sequence(T)
+            s.kv[0] = getattr(s, buf)[t]
+            assert api.fwd(shape, T, s) == (ERR_ALIAS, []), (buf, t)
+            assert api.fwd(shape, T, s, entering=False)[0] == 0   # not written then
+    s = Sequence(T)
+    s.kv[0] = s.decay
+    assert api.fwd(shape, T, s) == (ERR_ALIAS, [])
+    for buf in ("q", "k", "v", "dout", "cache", "out", "rstd"):
+        for t in range(T):
+            s = Sequence(T)
+            s.dkv[T] = getattr(s, buf)[t]
+            assert api.bwd(shape, T, s, norm=True) == (ERR_ALIAS, []), (buf, t)
+    s = Sequence(T)
+    s.dkv[T] = s.kv[0]   # read where the states are rebuilt
+    assert api.bwd(shape, T, s, cache=False) == (ERR_ALIAS, [])
+    assert api.bwd(shape, T, s)[0] == 0
+    group = 3
+    assert groups(api.fwd(shape, T, Sequence(T))[1]) == [group] * 2 == groups(api.bwd(shape, T, Sequence(T))[1])
+    for buf, t in [("out", 1), ("out", 2), ("cache", 1), ("rstd", 2), ("kv", 2), ("kv", 3)]:   # kv[0] = kv[2]: states in turn
+        s = Sequence(T)
+        s.kv[0] = getattr(s, buf)[t]
+        rc, r = api.fwd(shape, T, s, norm=True)
+        assert rc == 0 and groups(r) == [1, 1, 1, 3], (buf, t)
+        assert [x[4] for x in r] == [s.kv[0], 0, 0, 0]
+    for buf, t in [("dq", 4), ("dk", 3), ("dv", 4), ("dkv", 4), ("dkv", 3)]:
+        s = Sequence(T)
+        s.dkv[T] = getattr(s, buf)[t]
+        rc, r = api.bwd(shape, T, s)
+        assert rc == 0 and groups(r) == [1, 1, 1, 3], (buf, t)
+        assert [x[4] for x in r] == [s.dkv[T], 0, 0, 0]
+    s = Sequence(T)
+    s.kv[0] = s.out[4]   # a group after the one that writes it
+    assert groups(api.fwd(shape, T, s)[1]) == [3, 3]
