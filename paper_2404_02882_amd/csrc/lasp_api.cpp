@@ -327,13 +327,15 @@ int run_fwd_call(const FwdCall &c) {
     // kv_in goes to kv_copy with the walk that starts from it, unless it lies in what the call writes
     const float *kv_in = c.kv_in;
     float *kv_copy = kv_in == c.kv_copy ? nullptr : c.kv_copy;
+    bool copy_first = false;
     if (kv_in && kv_copy) {
         const Span in{kv_in, sb};
         bool apart = (uintptr_t)kv_in % 16 == 0 && !overlap(in, {kv_copy, sb}) && !overlap(in, {c.scratch, l.total});
         for (int t = 0; t < c.T && apart; ++t)
             apart = !overlap(in, {c.out[t], ob}) && !overlap(in, {at(c.rstd, t), gb}) && !overlap(in, {c.kv_out[t], sb}) && !overlap(in, {at(c.cache, t), cb});
         if (!apart) {
-            if (hipMemcpyAsync(kv_copy, kv_in, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
+            if (overlap(in, {kv_copy, sb})) return LASP_ERR_ALIAS;
+            copy_first = true;
             kv_in = kv_copy;
             kv_copy = nullptr;
         }
@@ -344,9 +346,10 @@ int run_fwd_call(const FwdCall &c) {
         rc = check_buffers({{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {t ? c.kv_out[t - 1] : kv_in, sb}, {c.decay[c.token ? t : 0], db}},
                            {{c.out[t], ob}, {at(c.rstd, t), gb}, {c.kv_out[t], sb}, {at(c.cache, t), cb}, {c.scratch, l.total}, {t ? nullptr : kv_copy, sb}});
         if (rc != LASP_OK) return rc;
-        if (overlap_any({kv_copy, sb}, {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.decay[c.token ? t : 0], db}}))
+        if (overlap_any({copy_first ? c.kv_copy : kv_copy, sb}, {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.decay[c.token ? t : 0], db}}))
             return LASP_ERR_ALIAS;
     }
+    if (copy_first && hipMemcpyAsync(c.kv_copy, c.kv_in, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
 
     char *scr = (char *)c.scratch;
     auto launch = [&](int first, int n) {
@@ -452,6 +455,7 @@ int run_bwd_call(const BwdCall &c) {
     // dkv_out goes to dkv_copy with the walk that starts from it, unless it lies in what the call writes
     const float *dkv_out = c.dkv_out;
     float *dkv_copy = dkv_out == c.dkv_copy ? nullptr : c.dkv_copy;
+    bool copy_first = false;
     if (dkv_out && dkv_copy) {
         const Span in{dkv_out, sb};
         bool apart = (uintptr_t)dkv_out % 16 == 0 && !overlap(in, {dkv_copy, sb}) && !overlap(in, {c.scratch, need});
@@ -459,7 +463,8 @@ int run_bwd_call(const BwdCall &c) {
             apart = !overlap(in, {c.dq[t], qb}) && !overlap(in, {c.dk[t], qb / p.kvdiv}) && !overlap(in, {c.dv[t], ob / p.kvdiv}) &&
                     !overlap(in, {at(c.dlog_g, t), gb}) && !overlap(in, {c.dkv_in[t], sb});
         if (!apart) {
-            if (hipMemcpyAsync(dkv_copy, dkv_out, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
+            if (overlap(in, {dkv_copy, sb})) return LASP_ERR_ALIAS;
+            copy_first = true;
             dkv_out = dkv_copy;
             dkv_copy = nullptr;
         }
@@ -473,9 +478,10 @@ int run_bwd_call(const BwdCall &c) {
                            {{c.dq[t], qb}, {c.dk[t], qb / p.kvdiv}, {c.dv[t], ob / p.kvdiv}, {at(c.dlog_g, t), gb}, {c.dkv_in[t], sb},
                             {c.scratch, need}, {t + 1 < c.T ? nullptr : dkv_copy, sb}});
         if (rc != LASP_OK) return rc;
-        if (overlap_any({dkv_copy, sb}, {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.dout[t], ob}, {at(c.kv_out, t), sb},
-                                         {rebuild ? at(c.kv_in, t) : nullptr, sb}, {at(c.yn, t), ob}, {at(c.rstd, t), gb},
-                                         {c.decay[c.token ? t : 0], db}, {at(c.cache, t), cb}}))
+        if (overlap_any({copy_first ? c.dkv_copy : dkv_copy, sb},
+                        {{c.q[t], qb}, {c.k[t], qb / p.kvdiv}, {c.v[t], ob / p.kvdiv}, {c.dout[t], ob}, {at(c.kv_out, t), sb},
+                         {rebuild ? at(c.kv_in, t) : nullptr, sb}, {at(c.yn, t), ob}, {at(c.rstd, t), gb},
+                         {c.decay[c.token ? t : 0], db}, {at(c.cache, t), cb}}))
             return LASP_ERR_ALIAS;
     }
 
@@ -491,6 +497,7 @@ int run_bwd_call(const BwdCall &c) {
         cut.segments = 0;
         if (rc = make_plan(&cut, kForward, &g, c.token, c.norm, c.group); rc != LASP_OK) return rc;
     }
+    if (copy_first && hipMemcpyAsync(c.dkv_copy, c.dkv_out, sb, hipMemcpyDeviceToDevice, stream) != hipSuccess) return LASP_ERR_HIP;
     auto launch = [&](int first, int n) {
         const int last = first + n - 1;
         lasp::Plan use = n > 1 ? p : one, use_f = n > 1 ? f : f1;

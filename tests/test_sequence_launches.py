@@ -211,3 +211,35 @@ def test_copy_of_the_entering_state_among_other_sub_sequences_buffers(api):
     s = Sequence(T)
     s.kv[0] = s.out[4]   # a group after the one that writes it
     assert groups(api.fwd(shape, T, s)[1]) == [3, 3]
+
+
+def test_refused_calls_copy_nothing(api):
+    """An entering state that lies in what the call writes is copied first, but only by a call that passes its checks; a state
+    that overlaps its own copy in part is refused."""
+    T, shape = 3, api.shape()
+    state = 4 * 64 * 64 * 4
+    for copied, place in (("fwd", lambda s: setattr(s, "kv_in", s.kv[T])), ("bwd", lambda s: setattr(s, "dkv_out", s.dkv[0])),
+                          ("fwd", lambda s: setattr(s, "kv_in", s.kv_in + 4)), ("bwd", lambda s: setattr(s, "dkv_out", s.dkv_out + 4))):
+        s = Sequence(T)
+        place(s)
+        src, dst = (s.kv_in, s.kv[0]) if copied == "fwd" else (s.dkv_out, s.dkv[T])
+        rc, r = getattr(api, copied)(shape, T, s)
+        assert rc == 0 and r[0][0] == 3 and (r[0][2], r[0][4]) == (src, dst)
+        assert r[1][3] == dst and groups(r) == [3] and [x[4] for x in r[1:]] == [0]
+        s.q[2] += 8
+        assert getattr(api, copied)(shape, T, s) == (ERR_ALIGN, [])
+        s.q[2] = s.out[2] if copied == "fwd" else s.dq[2]
+        assert getattr(api, copied)(shape, T, s) == (ERR_ALIAS, [])
+    for call in (api.fwd, api.bwd):   # nor onto what another sub-sequence reads
+        s = Sequence(T)
+        s.kv_in, s.dkv_out, s.kv[0], s.dkv[T] = s.kv_in + 4, s.dkv_out + 4, s.q[1], s.q[1]
+        assert call(shape, T, s) == (ERR_ALIAS, [])
+    for off in (16, state - 16, -16):
+        s = Sequence(T)
+        s.kv[0], s.dkv[T] = s.kv_in + off, s.dkv_out + off
+        assert api.fwd(shape, T, s) == (ERR_ALIAS, []) == api.bwd(shape, T, s)
+    s = Sequence(T)
+    s.kv[0], s.dkv[T] = s.kv_in, s.dkv_out   # in place already
+    for call in (api.fwd, api.bwd):
+        rc, r = call(shape, T, s)
+        assert rc == 0 and groups(r) == [3] and [x[0] for x in r].count(3) == 0 and r[0][4] == 0
