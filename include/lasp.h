@@ -131,7 +131,8 @@ size_t lasp_state_cache_bytes(const lasp_shape *shape);
 
 /*
  * Bytes of scratch both lasp_fwd and lasp_bwd need: one float [D][Dv] state per
- * head per segment. Contents are overwritten by every call. 0 on an invalid shape.
+ * head per segment. Contents are overwritten by every call (short sequences go through
+ * without; their size is that of pairs of tiles as segments). 0 on an invalid shape.
  */
 size_t lasp_scratch_bytes(const lasp_shape *shape);
 

@@ -100,13 +100,19 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     if (want == 0) want = auto_segments(*p, pass, chains);
     const bool alone = s->segments == 0 && group == 1;   // a launch of one sub-sequence, cut as the library likes
     p->ragged = s->N % (two_byte && pass == kBackward ? 2 * p->tile : p->tile) != 0;
-    p->tiles_per_seg = (p->ntiles + want - 1) / want;
-    if (two_byte)
-        p->tiles_per_seg = lasp::segment_tiles(p->tiles_per_seg, p->ntiles, chains, p->D, p->cache_tiles == 1, pass == kBackward, alone);
-    p->nseg = (p->ntiles + p->tiles_per_seg - 1) / p->tiles_per_seg;  // every segment non-empty
+    auto segments = [&](int tiles) { return (p->ntiles + tiles - 1) / tiles; };   // every segment non-empty
+    const int share = segments(want);
+    auto tiles = [&](bool single) {
+        return two_byte ? lasp::segment_tiles(share, p->ntiles, chains, p->D, p->cache_tiles == 1, pass == kBackward, single) : share;
+    };
+    p->tiles_per_seg = tiles(alone);
+    p->nseg = segments(p->tiles_per_seg);
     // (the backward walk in pairs has no room for it: with it in, its loop comes out 2 - 4 % slower)
     p->own_states = alone && p->nseg > 1 && lasp::own_states((p->nseg - 1) * p->tiles_per_seg, two_byte) &&
                     (!two_byte || pass == kForward || p->tiles_per_seg == 1 || p->cache_tiles == 1);
+    // The scratch is that of the cut without the rule for short sequences that go through alone: where that makes more
+    // segments, the workgroups compute their own start states and no scratch is touched.
+    p->scratch_segs = segments(tiles(false));
     return LASP_OK;
 }
 
@@ -132,7 +138,7 @@ bool scratch_layout(const lasp_shape *shape, bool token, ScratchLayout *l, int g
     for (int n = group; n >= 1; n = n > 1 ? 1 : 0) {
         if (make_plan(shape, kForward, &f, token, false, n) != LASP_OK || make_plan(shape, kBackward, &b, token, false, n) != LASP_OK)
             return false;
-        nseg = std::max<size_t>(nseg, n * std::max(f.nseg, b.nseg));
+        nseg = std::max<size_t>(nseg, n * std::max(f.scratch_segs, b.scratch_segs));
     }
     l->states = 0;
     l->seglog = round256(chains * nseg * f.dk * f.dv * sizeof(float));   // segment states, [d_k][d_v] floats each

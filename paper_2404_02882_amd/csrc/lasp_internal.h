@@ -19,6 +19,7 @@ struct Plan {
     int shards;         // sub-sequences that go through one launch, cut alike (N, ntiles, nseg, ...: of one of them)
     int nseg;           // segments per head (S)
     int tiles_per_seg;  // ceil(ntiles / nseg); the last segment may be shorter
+    int scratch_segs;   // segments whose states the scratch has room for (>= nseg, unless own_states)
     int cache_tiles;    // the state cache holds the state every cache_tiles-th tile starts from, whatever `segments` a
                         // call asks for: bfloat16 2 (the backward walk takes tiles in pairs) or 1 (one by one, see
                         // cache_every_tile), float the segments of the forward pass at segments = 0 (where the walk

@@ -83,3 +83,17 @@ def test_state_cache_of_odd_tile_counts():
     assert slots(16, 5000, 64) == 79 and slots(16, 5056, 64) == 79 and slots(16, 5120, 64) == 40
     assert slots(2, 448, 128, segments=3) == 7                                 # not a matter of the segments
     assert lasp.scratch_bytes(lasp.make_shape(1, 2, 448, 128, 64, "bf16")) == 2 * 7 * 128 * 128 * 4
+
+
+def test_short_sequences_scratch():
+    """Passes whose workgroups compute their start states themselves use no scratch; the size stays that of the cut they had
+    with scanned states (pairs of tiles for even counts), so that buffers of that size still serve."""
+    from paper_2404_02882_amd import lasp
+
+    def segments(H, N, D=128, dtype="bf16", **kw):
+        s = lasp.make_shape(1, H, N, D, 64, dtype, **kw)
+        return lasp.scratch_bytes(s) / (H * D * D * 4)
+
+    assert [segments(2, N) for N in (64, 128, 256, 384, 512, 448, 576, 640)] == [1, 1, 2, 3, 4, 7, 9, 5]
+    assert [segments(2, N, 64) for N in (128, 256, 512)] == [1, 2, 4]
+    assert [segments(2, N, dtype="f32") for N in (32, 64, 128, 256)] == [1, 2, 4, 8]

@@ -15,8 +15,8 @@ RECORDER = r"""
 #include "%(csrc)s/lasp_internal.h"
 #include <cstring>
 namespace { int n; long long rec[256][8]; }
-static hipError_t put(int kind, int shards, const void *a, const void *b, const void *c, int own) {
-    long long r[8] = {kind, shards, (long long)a, (long long)b, (long long)c, own};
+static hipError_t put(int kind, int shards, const void *a, const void *b, const void *c, const lasp::Plan *p = nullptr) {
+    long long r[8] = {kind, shards, (long long)a, (long long)b, (long long)c, p && p->own_states, p ? p->nseg : 0, p ? p->scratch_segs : 0};
     std::memcpy(rec[n++ & 255], r, sizeof r);
     return hipSuccess;
 }
@@ -31,16 +31,16 @@ int tile_tokens(int dtype, int, int) { return dtype == 0 ? 32 : 64; }
 hipError_t static_scratch(void **) { return hipErrorUnknown; }
 int bidir_reduce_tile(int) { return 64; }
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t, const KernelEvents *) {
-    return put(a.states_only ? 2 : 0, p.shards, a.k, a.kv_in, a.kv_copy, p.own_states);
+    return put(a.states_only ? 2 : 0, p.shards, a.k, a.kv_in, a.kv_copy, &p);
 }
 hipError_t launch_bwd(const Plan &p, const BwdArgs &a, hipStream_t, const KernelEvents *) {
-    return put(1, p.shards, a.k, a.dkv_out, a.dkv_copy, p.own_states);
+    return put(1, p.shards, a.k, a.dkv_out, a.dkv_copy, &p);
 }
 hipError_t launch_bidir_apply(const BidirPlan &, const BidirOps &, int, hipStream_t, const KernelEvents *) { return hipErrorUnknown; }
 hipError_t launch_bidir_state(const BidirPlan &, const void *, const void *, float *, int, float *, hipStream_t, const KernelEvents *) { return hipErrorUnknown; }
 }
 extern "C" {
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t, hipMemcpyKind, hipStream_t) { return put(3, 0, s, nullptr, d, 0); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t, hipMemcpyKind, hipStream_t) { return put(3, 0, s, nullptr, d); }
 hipError_t hipEventCreate(hipEvent_t *) { return hipErrorUnknown; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *, hipEvent_t, hipEvent_t) { return hipErrorUnknown; }
@@ -87,7 +87,8 @@ class Api:
     def record(self):
         out = (ctypes.c_longlong * (256 * 8))()
         n = self.lib.recorded(out)
-        return [tuple(out[8 * i:8 * i + 6]) for i in range(n)]   # kind (0 forward, 1 backward, 2 states, 3 copy), shards, k, in, copy, own
+        return [tuple(out[8 * i:8 * i + 8]) for i in range(n)]   # kind (0 forward, 1 backward, 2 states, 3 copy), shards, k, in,
+                                                                  # copy, own start states, segments, segments in the scratch
 
     def shape(self, H=4, N=1024, D=64, dtype="bf16", **kw):
         return self.lasp.make_shape(1, H, N, D, 64, dtype, **kw)
@@ -243,3 +244,19 @@ def test_refused_calls_copy_nothing(api):
     for call in (api.fwd, api.bwd):
         rc, r = call(shape, T, s)
         assert rc == 0 and groups(r) == [3] and [x[0] for x in r].count(3) == 0 and r[0][4] == 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_segments_fit_the_scratch(api, dtype, D):
+    """Every pass that goes through its segments' states in the scratch finds room for them there."""
+    for H in (1, 2, 16, 32, 86, 128, 300):
+        for N in (1, 64, 65, 128, 191, 192, 256, 448, 500, 512, 513, 640, 1000, 5000):
+            for token in (False, True):
+                for T in (1, 3):
+                    shape, s = api.shape(H, N, D, dtype), Sequence(T)
+                    records = api.fwd(shape, T, s, token)[1] + api.bwd(shape, T, s, token)[1] + api.bwd(shape, T, s, token, cache=False)[1]
+                    assert len(records) >= 3
+                    for r in records:
+                        assert r[5] or r[6] <= r[7], (H, N, token, T, r)
+                        assert not r[5] or r[1] == 1
