@@ -258,6 +258,9 @@ lasp::Offsets strides(size_t bytes) {
 // from what the neighbour's walk returns) and its segments longer. Error of dlog_g against 64 bits, mean (largest) of six
 // inputs, one by one / together: 2 heads x 24576 x 4, Norm, d=64 3.7e-2 (4.8e-2) / 4.0e-2 (5.5e-2), d=128 3.7e-2 (4.3e-2) /
 // 4.0e-2 (5.1e-2), 16 x 777 x 4 7.0e-3 / 7.2e-3.
+// With grouped K/V heads the parts of dK, dV of all of them lie in the scratch at once: bounded, since a sequence long enough
+// to fill the memory has little to gain (the last figure), and one by one it needs no more than a call.
+constexpr size_t kPartsLimit = (size_t)1 << 30;
 int shards_per_launch(const lasp_shape *s, int T, bool token) {
     if (T < 2 || s->segments != 0 || token) return 1;
     const int64_t chains = (int64_t)s->B * s->H;
@@ -265,9 +268,12 @@ int shards_per_launch(const lasp_shape *s, int T, bool token) {
         lasp::Plan p;
         return make_plan(s, pass, &p, false, false, group) == LASP_OK ? chains * group * p.nseg : 0;
     };
+    const bool grouped = s->kv_heads > 0 && s->kv_heads < s->H;
+    const size_t parts = grouped ? (size_t)chains * s->N * (s->D + (s->Dv ? s->Dv : s->D)) * elem_bytes(s->dtype) : 0;
     const int64_t most = std::min<int64_t>(std::min(T, lasp::kMaxShards), lasp::kOnePerCu / chains);
     for (int n = (int)most; n > 1; --n) {
         const int launches = (T + n - 1) / n, group = (T + launches - 1) / launches;   // of about one size
+        if (group * parts > kPartsLimit) continue;
         if (10 * workgroups(kForward, group) >= 9 * workgroups(kForward, 1) && 10 * workgroups(kBackward, group) >= 9 * workgroups(kBackward, 1))
             return group;
     }

@@ -260,3 +260,18 @@ def test_segments_fit_the_scratch(api, dtype, D):
                     for r in records:
                         assert r[5] or r[6] <= r[7], (H, N, token, T, r)
                         assert not r[5] or r[1] == 1
+
+
+def test_parts_of_grouped_heads_stay_bounded(api):
+    """Grouped K/V heads: dK, dV parts of every sub-sequence of a launch lie in the scratch at once, up to 1 GiB."""
+    T, H = 4, 16
+    for N, sizes in ((4096, [4]), (32768, [4]), (32832, [2, 2]), (65536, [2, 2]), (65600, [1] * 4), (262144, [1] * 4)):
+        shape = api.shape(H, N, 128, kv_heads=4)
+        rc, r = api.bwd(shape, T, Sequence(T))
+        assert rc == 0 and groups(r) == sizes, N
+        one = api.lib.lasp_scratch_bytes(ctypes.byref(shape))
+        assert api.scratch_bytes(shape, T) <= one + (1 << 30)
+        if len(sizes) == T:
+            assert api.scratch_bytes(shape, T) == one
+    plain = api.shape(H, 65536, 128)
+    assert groups(api.bwd(plain, T, Sequence(T))[1]) == [4]   # no parts
