@@ -736,6 +736,11 @@ struct FixedDecay {
     DEVI typename WalkElem<T>::frag weigh_upto(const Lane &ln, typename WalkElem<T>::frag f, int ks, unsigned *lows = nullptr) const {
         return lasp::weigh_upto<T, CT, EDGE>(ln, f, ks, pw, geo, lows);
     }
+    // with every weight from the table, rounded once (the products of weigh_upto's factors are rounded twice)
+    template <bool EDGE = false>
+    DEVI typename WalkElem<T>::frag weigh_upto_once(const Lane &ln, typename WalkElem<T>::frag f, int ks, unsigned *lows = nullptr) const {
+        return WalkElem<T>::template scale_tab<EDGE>(ln, f, pw + 1, ks * WalkElem<T>::KSTEP, lows);
+    }
 };
 
 constexpr float kLog2e = 1.44269504088896340736f;
@@ -832,6 +837,10 @@ struct TokenDecay {
     template <bool EDGE = false>
     DEVI typename WalkElem<T>::frag weigh_upto(const Lane &ln, typename WalkElem<T>::frag f, int ks, unsigned *lows = nullptr) const {
         return WalkElem<T>::template scale_tab<EDGE>(ln, f, wu, ks * WalkElem<T>::KSTEP, lows);
+    }
+    template <bool EDGE = false>
+    DEVI typename WalkElem<T>::frag weigh_upto_once(const Lane &ln, typename WalkElem<T>::frag f, int ks, unsigned *lows = nullptr) const {
+        return weigh_upto<EDGE>(ln, f, ks, lows);
     }
 };
 template <bool TOKEN, typename T, int CT>
@@ -988,7 +997,8 @@ DEVI f32x16 state_product(const f32x16 (&st)[DB], unsigned &lows, Load load) {
 // Float data: st[blk] = decay st[blk] + sum over a tile's tokens of A[token][32 blk + .] b[token][.], with A in LDS and
 // b (both contraction steps) in registers. The tile's sum is built from zero, so the running state is rounded once
 // a tile and the addition rides on the multiplication. APART: the small terms are summed apart, as the local pass does it,
-// where this stands in its place (kv_out of 8 heads x 128 tokens 8.9e-8 off without, 7.6e-8 with, 7.4e-8 by the local pass).
+// where this stands in its place; with weights rounded once the states are then to the last bit the scanned ones (kv_out of 8
+// heads x 128 tokens, d=128: 8.9e-8 off with the small terms in the sum, 7.6e-8 apart, 7.38e-8 with the weights too).
 template <typename E, bool APART = false, int DB, int NKS>
 DEVI void decay_and_add(const Lane &ln, f32x16 (&st)[DB], float decay, const bf16_t *sA, int ld, const typename E::frag (&b)[NKS]) {
     f32x16 sum, low;

@@ -424,6 +424,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         mk.store(sK, LDD);
         mv.store(sV, LDD);
         if constexpr (TOKEN) dec.fill(lgreg);
+        else if constexpr (E::PLANES == 3) dec.set_end(CT);   // float: weights rounded once, like the local pass's
         __syncthreads();
         if (t + 1 < own) request_kv(t + 1);
         else request(t0);
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             auto weigh = [&](auto edge) __attribute__((always_inline)) {
                 load_vf();
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<true, decltype(edge)::value>(ln, vf[ks], ks, &lows);
+                for (int ks = 0; ks < NKS; ++ks) vf[ks] = dec.template weigh_after<false, decltype(edge)::value>(ln, vf[ks], ks, &lows);
             };
             weigh(std::false_type{});
             if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});
@@ -982,7 +983,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             auto weigh = [&](auto edge) __attribute__((always_inline)) {
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks)
-                    x2[ks] = dec.template weigh_upto<decltype(edge)::value>(ln, E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w), ks, &lows);
+                    x2[ks] = dec.template weigh_upto_once<decltype(edge)::value>(ln, E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w), ks, &lows);
             };
             weigh(std::false_type{});
             if (__builtin_expect(E::edge(lows), 0)) weigh(std::true_type{});

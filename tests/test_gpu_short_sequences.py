@@ -36,3 +36,20 @@ def test_short_alone(oracle, dtype, D, H, N, token):
         for name, r in ref.items():
             emax, efro = harness.rel_errors(got[name], r)
             assert np.isfinite(emax) and emax <= tol and efro <= tol, (recompute, name, emax, efro)
+
+
+@pytest.mark.parametrize("D,Dv", [(64, 64), (128, 128), (64, 128), (128, 64)])
+@pytest.mark.parametrize("N", [64, 97, 100, 128])
+def test_float_start_states_are_the_scanned_ones(N, D, Dv):
+    """Float, one lambda per head: the states that workgroups compute themselves are to the last bit those of a local pass and
+    a scan over as many segments (segments = tiles)."""
+    from paper_2404_02882_amd import harness
+    from paper_2404_02882_amd import synth_inputs as si
+    print(f"case own start states N={N} {D}x{Dv}", flush=True)
+    inp = si.make_inputs(si.Config("own", B=1, H=8, N=N, D=D, chunk=64, dtype="f32", seed=N + Dv, Dv=Dv), with_states=True)
+    inp.decay = np.random.default_rng(N).uniform(0.95, 1.0, 8).astype(np.float32)
+    got = [harness.run_gpu(inp, segments=s) for s in (0, -(-N // 32))]
+    for name in ("out", "kv_out", "dq", "dv", "dkv_in"):
+        assert np.array_equal(got[0][name], got[1][name]), name
+    # (the waves that make dK keep the state the other way round and weigh q instead of dO: two roundings of 2^-24 a product apart)
+    assert max(harness.rel_errors(got[0]["dk"], got[1]["dk"])) <= 1e-6
