@@ -252,7 +252,7 @@ lasp::Offsets strides(size_t bytes) {
 // that much less to move) and scanned once, at the price of a local pass over each but one. As many as still leave about as
 // many workgroups as a launch of one has: more would go through in several rounds, and read more in the local pass.
 // Step one by one / together, us: 16 heads x 1024 tokens x 4, d=64, in a graph 149 / 64; 32 heads x 4096 x 2 with four K/V
-// heads 314 / 261; 16 x 32768 x 8 3890 / 3658. (The longer kernel arguments cost every launch 0.1 - 0.2 us of host time.)
+// heads 314 / 261; 16 x 32768 x 8 3890 / 3658.
 // With a decay per token one by one: the gradient of log g is <dkv_out, kv_out> plus a sum over the sub-sequence's tail that
 // cancels most of it, and together its two ends would not be the tensors the walk starts from (a scan's states stand 0.2 %
 // from what the neighbour's walk returns) and its segments longer. Error of dlog_g against 64 bits, mean (largest) of six

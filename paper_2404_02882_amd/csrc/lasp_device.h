@@ -919,6 +919,9 @@ DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[BLK], float *g, int w
         for (int i = 0; i < 16; ++i) gstore<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo, st[ab][i]);
 }
 
+// Whether a kernel serves launches that several sub-sequences share (SH: their distances), or launches of one (Alone).
+template <typename SH>
+constexpr bool is_shared = !std::is_same_v<SH, Alone>;
 // A pointer into the first sub-sequence of a launch, moved to the same place of sub-sequence `shard`.
 template <typename P>
 DEVI P *at_shard(P *p, const Offsets &o, int shard) { return (P *)((char *)p + o.at[shard]); }

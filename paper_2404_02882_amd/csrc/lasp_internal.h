@@ -42,6 +42,7 @@ struct Shards {
     Offsets q, k, v, dout, cache, out, rstd, kv_out, dq, dk, dv, dkv_in, yn;
 };
 // What each kernel needs of it (the forward walk as kDq: dO, V, K as q, k, v, dQ as out).
+struct Alone {};   // a launch of one sub-sequence: nothing
 struct LocalShards {
     Offsets x, y, yn, rstd;
 };

@@ -78,12 +78,12 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 // it every row count is CT and known at compile time.
 // WX, WY: elements per row of X and Y in memory (<= D; narrower rows are zero-padded on their way to LDS,
 // which serves key and value dimensions that differ).
-template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM = false, int WX = D, int WY = D>
+template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM, int WX, int WY, typename SH>
 __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
-                                                  float *__restrict__ seglog, int H, int ntiles, int nseg, int nslots,
+                                                  float *__restrict__ seglog, int H, int ntiles, int nseg,
                                                   int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn,
-                                                  const float *__restrict__ rstd, LocalShards sh) {
+                                                  const float *__restrict__ rstd, SH sh) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
     using E = WalkElem<T>;
     constexpr int NT = D * 2, LDD = walk_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
@@ -92,19 +92,22 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     bf16_t *sY = sX + TILE;
     float *pw = (float *)(sY + TILE);
 
-    const int chain = blockIdx.y, shard = blockIdx.z;
-    const int seg = blockIdx.x + (BWD && nslots == nseg ? 1 : 0), slot = shard * nseg + seg;
-    if (slot == (BWD ? 0 : nslots - 1)) return;   // no other segment starts from the last one's state (of several sub-sequences: the grid has it)
+    constexpr bool SHARED = is_shared<SH>;
+    const int chain = blockIdx.y, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
+    const int seg = blockIdx.x + (BWD && !SHARED ? 1 : 0), slot = shard * nseg + seg;
+    if (SHARED && slot == (BWD ? 0 : nslots - 1)) return;   // no other segment starts from the last one's state (of several sub-sequences: the grid has it)
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
-    if (!TOKEN && shard) {
-        X = at_shard(X, sh.x, shard);
-        Y = at_shard(Y, sh.y, shard);
-        if constexpr (NORM) {
-            yn = at_shard(yn, sh.yn, shard);
-            rstd = at_shard(rstd, sh.rstd, shard);
+    if constexpr (SHARED) {
+        if (shard) {
+            X = at_shard(X, sh.x, shard);
+            Y = at_shard(Y, sh.y, shard);
+            if constexpr (NORM) {
+                yn = at_shard(yn, sh.yn, shard);
+                rstd = at_shard(rstd, sh.rstd, shard);
+            }
         }
     }
     if (!BWD) {  // forward: X, Y are K, V
@@ -120,7 +123,8 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     auto nvalid = [&](int t) { return RAGGED ? min(CT, ntok - t * CT) : CT; };
     // One lambda per head, forward: the weights run from the segment's end, so where a sub-sequence ends inside a tile its
     // last segment is cut into tiles from the end, and the first of them is the one that lacks rows (END_CUT).
-    constexpr bool END_CUT = RAGGED && !BWD && !TOKEN;
+    constexpr bool END_CUT = RAGGED && !BWD;
+    static_assert(!END_CUT || (SHARED && !TOKEN), "alone, the forward pass does not sum over its last segment");
     const int gap = END_CUT ? t1 * CT - min(t1 * CT, ntok) : 0;   // rows the first tile lacks
     TileMover<T, CT, D, NT, true> mx, my;   // streaming (non-temporal) loads
     NormTile<T, CT, D, NT, WY> mn;   // the normalised output has the rows of Y (= dY)
@@ -328,16 +332,16 @@ template <typename T, int CT>
 constexpr int fwd_ldp() { return sizeof(T) == 4 ? CT : CT + WalkElem<T>::PAD; }
 template <typename T, int D>
 constexpr int fwd_stage() { return sizeof(T) == 4 ? 0 : D * 36; }
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, Role ROLE = kOutputs>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, int WK, int WV, Role ROLE, typename SH>
 __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq && (TOKEN || NORM)) ? 1 : 2) void k_fwd(const T *__restrict__ Q, const T *__restrict__ K,
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
-                                                int H, int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
+                                                int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
                                                 const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok,
-                                                float *__restrict__ kv_copy, FwdShards sh) {
+                                                float *__restrict__ kv_copy, SH sh) {
     using E = WalkElem<T>;
     constexpr bool STATES = ROLE == kStates, DQ = ROLE == kDq;
     constexpr int NT = D * 2, LDD = walk_ld<T, D>(), LDP = fwd_ldp<T, CT>(), DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
@@ -350,27 +354,30 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     bf16_t *sStage = sP + walk_tile<T>(CT, LDP);   // cache stores, bfloat16
     float *pw = (float *)(sStage + fwd_stage<T, D>());
 
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    constexpr bool SHARED = is_shared<SH>;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
-    if (!TOKEN && shard) {
-        Q = at_shard(Q, sh.q, shard);
-        K = at_shard(K, sh.k, shard);
-        V = at_shard(V, sh.v, shard);
-        O = at_shard(O, sh.out, shard);
-        if constexpr (DQ) {
-            if constexpr (NORM) {
-                yn = at_shard(yn, sh.yn, shard);
-                rstd = at_shard(rstd, sh.rstd, shard);
+    if constexpr (SHARED) {
+        if (shard) {
+            Q = at_shard(Q, sh.q, shard);
+            K = at_shard(K, sh.k, shard);
+            V = at_shard(V, sh.v, shard);
+            O = at_shard(O, sh.out, shard);
+            if constexpr (DQ) {
+                if constexpr (NORM) {
+                    yn = at_shard(yn, sh.yn, shard);
+                    rstd = at_shard(rstd, sh.rstd, shard);
+                }
+                if (carry < 0) scratch = at_shard(scratch, sh.cache, shard);
+            } else {
+                kv_out = at_shard(kv_out, sh.kv_out, shard);
+                cache = at_shard(cache, sh.cache, shard);
+                if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
             }
-            if (carry < 0) scratch = at_shard(scratch, sh.cache, shard);
-        } else {
-            kv_out = at_shard(kv_out, sh.kv_out, shard);
-            cache = at_shard(cache, sh.cache, shard);
-            if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
         }
     }
     // requests first (tile, then start state), table arithmetic while they fly
@@ -396,7 +403,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t), nvalid(t));
         request_kv(t);
     };
-    const int own = carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    const int own = !SHARED && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
     if (own) request_kv(0);
     else request(t0);
     f32x16 st[DB];
@@ -410,7 +417,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         };
         if (carry > 0)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -639,13 +646,13 @@ struct Fwd8Smem {
     static constexpr size_t PW_OFF = X_OFF + 8 * 1024 * sizeof(float);
     static constexpr size_t TOTAL = PW_OFF + table_floats<CT>() * sizeof(float);
 };
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, Role ROLE = kOutputs>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, Role ROLE, typename SH>
 __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                 const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
                                                 const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
-                                                int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
-                                                float *__restrict__ rstd_out, float eps, float *__restrict__ kv_copy, FwdShards sh) {
+                                                int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
+                                                float *__restrict__ rstd_out, float eps, float *__restrict__ kv_copy, SH sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = Fwd8Smem<T, CT, D>;
@@ -660,18 +667,21 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     float *sX = (float *)(smem + SM::X_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    constexpr bool SHARED = is_shared<SH>;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
-    if (!TOKEN && shard) {
-        Q = at_shard(Q, sh.q, shard);
-        K = at_shard(K, sh.k, shard);
-        V = at_shard(V, sh.v, shard);
-        O = at_shard(O, sh.out, shard);
-        kv_out = at_shard(kv_out, sh.kv_out, shard);
-        cache = at_shard(cache, sh.cache, shard);
-        if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
+    if constexpr (SHARED) {
+        if (shard) {
+            Q = at_shard(Q, sh.q, shard);
+            K = at_shard(K, sh.k, shard);
+            V = at_shard(V, sh.v, shard);
+            O = at_shard(O, sh.out, shard);
+            kv_out = at_shard(kv_out, sh.kv_out, shard);
+            cache = at_shard(cache, sh.cache, shard);
+            if constexpr (NORM) rstd_out = at_shard(rstd_out, sh.rstd, shard);
+        }
     }
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = w8 % NW, g = w8 / NW;   // value-feature block; row half of the state and token block of the output
@@ -694,7 +704,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         if constexpr (!STATES) mq.load(Q + off(t), nvalid(t));
         request_kv(t);
     };
-    const int own = carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    const int own = !SHARED && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
     if (own) request_kv(0);
     else request(t0);
     f32x16 st[HB];   // st[ab][i] = KV[a0 + 32 ab + acc_row(i)][32 w + r]
@@ -703,7 +713,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
         else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -862,14 +872,14 @@ struct BwdkvSmem {
     static constexpr size_t TOTAL = PW_OFF + table_floats<CT>() * sizeof(float);
 };
 
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, int WK, int WV, typename SH>
 __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                  const T *__restrict__ dO, const float *__restrict__ decay, T *__restrict__ dK,
                                                  T *__restrict__ dV, float *__restrict__ dkv_in, const float *__restrict__ scratch,
                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
-                                                 float *__restrict__ rtok, int H, int ntiles, int nseg, int nslots, int tiles_per_seg,
+                                                 float *__restrict__ rtok, int H, int ntiles, int nseg, int tiles_per_seg,
                                                  int ntok, int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd,
-                                                 float *__restrict__ dkv_copy, BwdShards sh) {
+                                                 float *__restrict__ dkv_copy, SH sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
     using SM = BwdkvSmem<T, CT, D>;
@@ -885,21 +895,24 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     bf16_t *sDS = sS + SM::PTILE;
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    constexpr bool SHARED = is_shared<SH>;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
-    if (!TOKEN && shard) {
-        Q = at_shard(Q, sh.q, shard);
-        K = at_shard(K, sh.k, shard);
-        V = at_shard(V, sh.v, shard);
-        dO = at_shard(dO, sh.dout, shard);
-        dK = at_shard(dK, sh.dk, shard);
-        dV = at_shard(dV, sh.dv, shard);
-        dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
-        if constexpr (NORM) {
-            yn = at_shard(yn, sh.yn, shard);
-            rstd = at_shard(rstd, sh.rstd, shard);
+    if constexpr (SHARED) {
+        if (shard) {
+            Q = at_shard(Q, sh.q, shard);
+            K = at_shard(K, sh.k, shard);
+            V = at_shard(V, sh.v, shard);
+            dO = at_shard(dO, sh.dout, shard);
+            dK = at_shard(dK, sh.dk, shard);
+            dV = at_shard(dV, sh.dv, shard);
+            dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
+            if constexpr (NORM) {
+                yn = at_shard(yn, sh.yn, shard);
+                rstd = at_shard(rstd, sh.rstd, shard);
+            }
         }
     }
     const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -934,7 +947,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         if constexpr (NORM) mn.load(yn + voff(t), rstd_c + (size_t)t * CT, nvalid(t));
         if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
     };
-    const int own = carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
+    const int own = !SHARED && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
     if (own) request_qdo(ntiles - 1);
     else request(t1 - 1, nvalid(t1 - 1));
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -963,7 +976,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1110,7 +1123,7 @@ struct Bwd8pSmem {
 };
 
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
-template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM = false, int WK = D, int WV = D, BwdWalk MODE = kPairs>
+template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, int WK, int WV, BwdWalk MODE, typename SH>
 __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const T *__restrict__ K,
                                                   const T *__restrict__ V, const T *__restrict__ dO,
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
@@ -1118,12 +1131,12 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   float *__restrict__ dkv_in, const float *__restrict__ scratch,
                                                   const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                   float *__restrict__ rtok,
-                                                  int H, int ntiles, int nseg, int nslots, int tiles_per_seg, int ntok, int kvdiv,
+                                                  int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                   const T *__restrict__ yn, const float *__restrict__ rstd, float *__restrict__ dkv_copy,
-                                                  BwdShards sh) {
+                                                  SH sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
-    constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves;
+    constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves, OWN = MODE != kPairs && !is_shared<SH>;
     using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
     static_assert(CT == 64, "two 32-token blocks per tile");
     static_assert(RAGGED || MODE == kPairs, "one by one: one instance for any number of tiles and any length of the last");
@@ -1142,22 +1155,25 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     T *sC = (T *)(smem + SM::C_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = blockIdx.z;
+    constexpr bool SHARED = is_shared<SH>;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
-    if (!TOKEN && shard) {
-        Q = at_shard(Q, sh.q, shard);
-        K = at_shard(K, sh.k, shard);
-        V = at_shard(V, sh.v, shard);
-        dO = at_shard(dO, sh.dout, shard);
-        dK = at_shard(dK, sh.dk, shard);
-        dV = at_shard(dV, sh.dv, shard);
-        dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
-        if constexpr (NORM) {
-            yn = at_shard(yn, sh.yn, shard);
-            rstd = at_shard(rstd, sh.rstd, shard);
+    if constexpr (SHARED) {
+        if (shard) {
+            Q = at_shard(Q, sh.q, shard);
+            K = at_shard(K, sh.k, shard);
+            V = at_shard(V, sh.v, shard);
+            dO = at_shard(dO, sh.dout, shard);
+            dK = at_shard(dK, sh.dk, shard);
+            dV = at_shard(dV, sh.dv, shard);
+            dkv_in = at_shard(dkv_in, sh.dkv_in, shard);
+            if constexpr (NORM) {
+                yn = at_shard(yn, sh.yn, shard);
+                rstd = at_shard(rstd, sh.rstd, shard);
+            }
+            dQ = at_shard(dQ, sh.dq, shard);
+            cache = at_shard(cache, sh.cache, shard);
         }
-        dQ = at_shard(dQ, sh.dq, shard);
-        cache = at_shard(cache, sh.cache, shard);
     }
     const int t0 = seg * tiles_per_seg;                                  // pairs: even
     // even: the last pair may lack its O tile
@@ -1270,8 +1286,8 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, nvalid(t));
         if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
     };
-    const int own = MODE != kPairs && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
-    if (MODE != kPairs && own) load_qdo(ntiles - 1);
+    const int own = OWN && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
+    if (OWN && own) load_qdo(ntiles - 1);
     else load_first();
 
     const T *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
@@ -1289,7 +1305,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), MODE != kPairs && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1394,7 +1410,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                 });
         }
     };
-    if constexpr (MODE != kPairs)
+    if constexpr (OWN)
     for (int t = ntiles - 1; t >= ntiles - own; --t) {
         __syncthreads();
         if constexpr (NORM) mnX.apply(moX);
@@ -1634,56 +1650,67 @@ static auto by_edges(const Plan &p) {
     return p.ragged ? (p.norm ? Fam::template fn<TK, true, true> : Fam::template fn<TK, true, false>)
                     : (p.norm ? Fam::template fn<TK, false, true> : Fam::template fn<TK, false, false>);
 }
+// (launches that several sub-sequences share know one lambda per head only)
 template <typename Fam>
 static auto by_model(const Plan &p) {
-    return p.token ? by_edges<Fam, true>(p) : by_edges<Fam, false>(p);
+    if constexpr (Fam::kShared) return by_edges<Fam, false>(p);
+    else return p.token ? by_edges<Fam, true>(p) : by_edges<Fam, false>(p);
 }
+// go(sh) with the distances of a launch's sub-sequences, or with Alone for a launch of one: those are kernels of their own,
+// whose arguments do not hold the distances (128 - 350 bytes a launch, 0.1 - 0.2 us: three launches of a float forward pass
+// over 2 heads x 256 tokens, d=64, through the Python binding 14.59 us with the distances, 13.97 without).
+template <typename SH, typename Go>
+static hipError_t by_shards(const Plan &p, const SH &sh, Go go) { return p.shards > 1 ? go(sh) : go(Alone{}); }
 
 // Kernel families by decay model and Norm (see by_model).
-template <typename T, int CT, int D, bool BWD, bool WITH_NORM, int WX, int WY>
-struct LocalFam {   // the Norm prologue exists in the backward pass only
+template <typename SH>
+struct Family {
+    static constexpr bool kShared = is_shared<SH>;
+};
+template <typename T, int CT, int D, bool BWD, bool WITH_NORM, int WX, int WY, typename SH>
+struct LocalFam : Family<SH> {   // the Norm prologue exists in the backward pass only; alone the forward pass never sums over a short end
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG, NM && BWD && WITH_NORM, WX, WY>;
+    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG && (BWD || is_shared<SH>), NM && BWD && WITH_NORM, WX, WY, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct FwdFam : Family<SH> {
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WK, WV, kOutputs, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct StatesFam : Family<SH> {  // the forward walk reduced to the states (no Norm: the states do not depend on it)
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, kStates, SH>;
+};
+template <typename T, int CT, int D, Role ROLE, typename SH>
+struct Fwd8Fam : Family<SH> {
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd8<T, CT, D, TK, RG, NM && ROLE == kOutputs, ROLE, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct DqFam : Family<SH> {      // dQ as a forward walk over dO, V, K
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WV, WK, kDq, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct BwdkvFam : Family<SH> {
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwdkv<T, CT, D, TK, RG, NM, WK, WV, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct Bwd8pFam : Family<SH> {   // eight waves, one cached state per pair of tiles
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, RG, NM, WK, WV, kPairs, SH>;
+};
+template <typename T, int CT, int D, int WK, int WV, typename SH>
+struct Bwd8tFam : Family<SH> {   // one cached state per tile; an odd tile count is ragged
+    template <bool TK, bool RG, bool NM>
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kTiles, SH>;
 };
 template <typename T, int CT, int D, int WK, int WV>
-struct FwdFam {
+struct Bwd8hFam : Family<Alone> {   // one cached state per pair of tiles, a workgroup per tile
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WK, WV>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct StatesFam {  // the forward walk reduced to the states (no Norm: the states do not depend on it)
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, false, WK, WV, kStates>;
-};
-template <typename T, int CT, int D, Role ROLE>
-struct Fwd8Fam {
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_fwd8<T, CT, D, TK, RG, NM && ROLE == kOutputs, ROLE>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct DqFam {      // dQ as a forward walk over dO, V, K
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_fwd<T, CT, D, TK, RG, NM, WV, WK, kDq>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct BwdkvFam {
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwdkv<T, CT, D, TK, RG, NM, WK, WV>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct Bwd8pFam {   // eight waves, one cached state per pair of tiles
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, RG, NM, WK, WV>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct Bwd8tFam {   // one cached state per tile; an odd tile count is ragged
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kTiles>;
-};
-template <typename T, int CT, int D, int WK, int WV>
-struct Bwd8hFam {   // one cached state per pair of tiles, a workgroup per tile
-    template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kHalves>;
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kHalves, Alone>;
 };
 
 // The local pass only sums over its segment, so its tile need not be the walk's:
@@ -1696,19 +1723,21 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
                             const T *yn, const float *rstd, const Shards &all, hipStream_t s) {
     const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.yn, all.rstd};
     const dim3 grid(p.shards > 1 ? p.nseg : p.nseg - 1, p.B * p.H, p.shards), block(D * 2);
-    const int nslots = p.shards * p.nseg;
     Plan q = p;
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
         if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0) {
-            if (!BWD) q.ragged = p.shards > 1 && p.N % 128 != 0;
-            return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                 decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, nslots, p.tiles_per_seg / 2, p.N, p.kvdiv,
-                                 (const T *)nullptr, (const float *)nullptr, sh);
+            if (!BWD) q.ragged = p.N % 128 != 0;
+            return by_shards(p, sh, [&](auto of) {
+                return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D, decltype(of)>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
+                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
+                                     (const T *)nullptr, (const float *)nullptr, of);
+            });
         }
     }
-    if (!BWD) q.ragged = p.shards > 1 && p.N % CT != 0;
-    return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
-                         scratch, seglog, p.H, p.ntiles, p.nseg, nslots, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, sh);
+    return by_shards(p, sh, [&](auto of) {
+        return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV, decltype(of)>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
+                             scratch, seglog, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, of);
+    });
 }
 
 // Where the walk's start states come from: own_states (lasp_rules.h) where the plan says so; else, up to four segments, the
@@ -1741,6 +1770,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
     const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}};
+    const dim3 grid(p.nseg, p.B * p.H, p.shards);
     if constexpr (sizeof(T) == 2 && WK == 128 && WV == 128) {
         static_assert(Fwd8Smem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         // Up to 256 workgroups a CU has one, and four waves leave each SIMD only one; from 257 on two workgroups of
@@ -1749,25 +1779,29 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         // x 8192 with a decay per token 357.6 / 315.2; 512 workgroups, 512 heads x 2048 221.7 / 235.7, x 2000
         // 231.3 / 238.8, x 2048 with a decay per token 223.0 / 253.3.
         if ((int64_t)p.shards * p.nseg * p.B * p.H <= kOnePerCu) {
-            const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs>>(p);
-            if (e = launch_kernel(walk8, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
-                                  (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles, (const float *)a.scratch,
-                                  a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N,
-                                  p.kvdiv, a.rstd_out, a.eps, a.kv_copy, sh);
-                e != hipSuccess)
-                return e;
+            e = by_shards(p, sh, [&](auto of) {
+                using SH = decltype(of);
+                const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates, SH>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs, SH>>(p);
+                return launch_kernel(walk8, grid, dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                                     (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles,
+                                     (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
+                                     p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, a.kv_copy, of);
+            });
+            if (e != hipSuccess) return e;
             if (ke) (void)hipEventRecord(ke->ev[3], s);
             return hipGetLastError();
         }
     }
-    const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV>>(p) : by_model<FwdFam<T, CT, D, WK, WV>>(p);
-    if (e = launch_kernel(walk, dim3(p.nseg, p.B * p.H, p.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
-                          (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                          p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
-                          p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
-                          (const T *)nullptr, (float *)nullptr, a.kv_copy, sh);
-        e != hipSuccess)
-        return e;
+    e = by_shards(p, sh, [&](auto of) {
+        using SH = decltype(of);
+        const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV, SH>>(p) : by_model<FwdFam<T, CT, D, WK, WV, SH>>(p);
+        return launch_kernel(walk, grid, dim3(D * 2), Smem<T, CT, D>::fwd, s,
+                             (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
+                             p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
+                             p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
+                             (const T *)nullptr, (float *)nullptr, a.kv_copy, of);
+    });
+    if (e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[3], s);
     return hipGetLastError();
 }
@@ -1783,12 +1817,13 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
             e != hipSuccess)
             return e;
     }
-    return launch_kernel(by_model<DqFam<T, CT, D, WK, WV>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd, s,
-                         (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr, f.cache_tiles,
-                         a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start,
-                         f.H, f.ntiles, f.nseg, f.shards * f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
-                         (const T *)a.q, a.rtok, (float *)nullptr,
-                         FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.cache, a.sh.dq, a.sh.rstd, {}, a.sh.yn});
+    return by_shards(f, FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.cache, a.sh.dq, a.sh.rstd, {}, a.sh.yn}, [&](auto of) {
+        return launch_kernel(by_model<DqFam<T, CT, D, WK, WV, decltype(of)>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd,
+                             s, (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
+                             f.cache_tiles, a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog,
+                             (int)start, f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
+                             (const T *)a.q, a.rtok, (float *)nullptr, of);
+    });
 }
 
 template <typename T, int CT, int D, int WK = D, int WV = D>
@@ -1819,22 +1854,29 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
-        const bool by_tiles = p.cache_tiles == 1, halves = !by_tiles && p.tiles_per_seg == 1;
-        e = launch_kernel(by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV>>(p) : halves ? by_model<Bwd8hFam<T, CT, D, WK, WV>>(p)
-                                                                                      : by_model<Bwd8pFam<T, CT, D, WK, WV>>(p), grid, block,
-                          by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
-                          (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
-                          (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
-                          p.ntiles, p.nseg, p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
+        const bool by_tiles = p.cache_tiles == 1;
+        e = by_shards(p, sh, [&](auto of) {
+            using SH = decltype(of);
+            auto walk = by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV, SH>>(p) : by_model<Bwd8pFam<T, CT, D, WK, WV, SH>>(p);
+            if constexpr (!is_shared<SH>) {
+                if (!by_tiles && p.tiles_per_seg == 1) walk = by_model<Bwd8hFam<T, CT, D, WK, WV>>(p);
+            }
+            return launch_kernel(walk, grid, block, by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                                 (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
+                                 (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
+                                 p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
+        });
     } else {
         static_assert(BwdkvSmem<T, CT, D>::TOTAL <= 163840 / (D == 128 ? 1 : 2), "LDS of one gfx950 CU for the workgroups meant to share it");
         if (a.cache) {
             if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
         }
-        e = launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
-                          (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                          (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
-                          p.shards * p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, sh);
+        e = by_shards(p, sh, [&](auto of) {
+            return launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV, decltype(of)>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+                                 (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
+                                 (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
+                                 p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
+        });
     }
     if (e != hipSuccess) return e;
     if (p.kvdiv > 1) {
