@@ -919,9 +919,12 @@ DEVI void state_store_w(const Lane &ln, const f32x16 (&st)[BLK], float *g, int w
         for (int i = 0; i < 16; ++i) gstore<float>(g + (32 * ab + 8 * (i >> 2) + (i & 3)) * WV, lo, st[ab][i]);
 }
 
-// Whether a kernel serves launches that several sub-sequences share (SH: their distances), or launches of one (Alone).
+// Whether a kernel serves launches that several sub-sequences share (SH: their distances), or launches of one (Alone,
+// AloneOwn), and whether its workgroups can compute their start states (AloneOwn).
 template <typename SH>
-constexpr bool is_shared = !std::is_same_v<SH, Alone>;
+constexpr bool is_own = std::is_same_v<SH, AloneOwn>;
+template <typename SH>
+constexpr bool is_shared = !std::is_same_v<SH, Alone> && !is_own<SH>;
 // A pointer into the first sub-sequence of a launch, moved to the same place of sub-sequence `shard`.
 template <typename P>
 DEVI P *at_shard(P *p, const Offsets &o, int shard) { return (P *)((char *)p + o.at[shard]); }

@@ -42,7 +42,8 @@ struct Shards {
     Offsets q, k, v, dout, cache, out, rstd, kv_out, dq, dk, dv, dkv_in, yn;
 };
 // What each kernel needs of it (the forward walk as kDq: dO, V, K as q, k, v, dQ as out).
-struct Alone {};   // a launch of one sub-sequence: nothing
+struct Alone {};      // a launch of one sub-sequence: nothing
+struct AloneOwn {};   // nor one whose workgroups compute their own start states
 struct LocalShards {
     Offsets x, y, yn, rstd;
 };

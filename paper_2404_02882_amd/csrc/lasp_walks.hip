@@ -354,7 +354,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     bf16_t *sStage = sP + walk_tile<T>(CT, LDP);   // cache stores, bfloat16
     float *pw = (float *)(sStage + fwd_stage<T, D>());
 
-    constexpr bool SHARED = is_shared<SH>;
+    constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
     const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         if constexpr (!STATES) mq.template load_w<WK>(Q + koff(t), nvalid(t));
         request_kv(t);
     };
-    const int own = !SHARED && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    const int own = OWN && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
     if (own) request_kv(0);
     else request(t0);
     f32x16 st[DB];
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
         };
         if (carry > 0)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     float *sX = (float *)(smem + SM::X_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    constexpr bool SHARED = is_shared<SH>;
+    constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
     const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         if constexpr (!STATES) mq.load(Q + off(t), nvalid(t));
         request_kv(t);
     };
-    const int own = !SHARED && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
+    const int own = OWN && carry == kOwn ? t0 : 0;   // tiles before this segment that the workgroup takes the state through
     if (own) request_kv(0);
     else request(t0);
     f32x16 st[HB];   // st[ab][i] = KV[a0 + 32 ab + acc_row(i)][32 w + r]
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
             start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
+                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
         else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -895,7 +895,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     bf16_t *sDS = sS + SM::PTILE;
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    constexpr bool SHARED = is_shared<SH>;
+    constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
     const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         if constexpr (NORM) mn.load(yn + voff(t), rstd_c + (size_t)t * CT, nvalid(t));
         if constexpr (TOKEN) lgreg = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, nvalid(t));
     };
-    const int own = !SHARED && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
+    const int own = OWN && carry == kOwn ? ntiles - t1 : 0;   // tiles behind this segment that the workgroup takes the state through
     if (own) request_qdo(ntiles - 1);
     else request(t1 - 1, nvalid(t1 - 1));
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -976,7 +976,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
         };
         if (carry)
             start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), !SHARED && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
+                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1136,9 +1136,10 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   SH sh) {
     using E = WalkElem<T>;
     using F = typename E::frag;
-    constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves, OWN = MODE != kPairs && !is_shared<SH>;
+    constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves;
     using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
     static_assert(CT == 64, "two 32-token blocks per tile");
+    static_assert(!is_own<SH> || MODE != kPairs, "in pairs: from states in the scratch");
     static_assert(RAGGED || MODE == kPairs, "one by one: one instance for any number of tiles and any length of the last");
     constexpr int NT = D * 4, NW = D / 32, LDD = SM::LDD, LDP = SM::LDP, DB = D / 32, NB = CT / 32, NKS = CT / E::KSTEP,
                   NKD = D / E::KSTEP, SPB = 32 / E::KSTEP;
@@ -1155,7 +1156,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     T *sC = (T *)(smem + SM::C_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
-    constexpr bool SHARED = is_shared<SH>;
+    constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
     const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     if constexpr (SHARED) {
@@ -1661,6 +1662,10 @@ static auto by_model(const Plan &p) {
 // over 2 heads x 256 tokens, d=64, through the Python binding 14.59 us with the distances, 13.97 without).
 template <typename SH, typename Go>
 static hipError_t by_shards(const Plan &p, const SH &sh, Go go) { return p.shards > 1 ? go(sh) : go(Alone{}); }
+// The walks also with AloneOwn, where the workgroups compute their start states: with the loop that does it in every walk the
+// forward one at d=64 takes longer, 16 heads x 710 tokens 8.8 -> 9.3 us, 32 x 8448 with a decay per token 48.0 -> 49.1.
+template <typename SH, typename Go>
+static hipError_t by_start(const Plan &p, Start start, const SH &sh, Go go) { return start == kOwn ? go(AloneOwn{}) : by_shards(p, sh, go); }
 
 // Kernel families by decay model and Norm (see by_model).
 template <typename SH>
@@ -1708,9 +1713,9 @@ struct Bwd8tFam : Family<SH> {   // one cached state per tile; an odd tile count
     static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kTiles, SH>;
 };
 template <typename T, int CT, int D, int WK, int WV>
-struct Bwd8hFam : Family<Alone> {   // one cached state per pair of tiles, a workgroup per tile
+struct Bwd8hFam : Family<AloneOwn> {   // one cached state per pair of tiles, a workgroup per tile
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kHalves, Alone>;
+    static constexpr auto fn = k_bwd8p<T, CT, D, TK, true, NM, WK, WV, kHalves, AloneOwn>;
 };
 
 // The local pass only sums over its segment, so its tile need not be the walk's:
@@ -1779,7 +1784,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         // x 8192 with a decay per token 357.6 / 315.2; 512 workgroups, 512 heads x 2048 221.7 / 235.7, x 2000
         // 231.3 / 238.8, x 2048 with a decay per token 223.0 / 253.3.
         if ((int64_t)p.shards * p.nseg * p.B * p.H <= kOnePerCu) {
-            e = by_shards(p, sh, [&](auto of) {
+            e = by_start(p, start, sh, [&](auto of) {
                 using SH = decltype(of);
                 const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates, SH>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs, SH>>(p);
                 return launch_kernel(walk8, grid, dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
@@ -1792,7 +1797,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
             return hipGetLastError();
         }
     }
-    e = by_shards(p, sh, [&](auto of) {
+    e = by_start(p, start, sh, [&](auto of) {
         using SH = decltype(of);
         const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV, SH>>(p) : by_model<FwdFam<T, CT, D, WK, WV, SH>>(p);
         return launch_kernel(walk, grid, dim3(D * 2), Smem<T, CT, D>::fwd, s,
@@ -1817,7 +1822,7 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
             e != hipSuccess)
             return e;
     }
-    return by_shards(f, FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.cache, a.sh.dq, a.sh.rstd, {}, a.sh.yn}, [&](auto of) {
+    return by_start(f, start, FwdShards{a.sh.dout, a.sh.v, a.sh.k, a.sh.cache, a.sh.dq, a.sh.rstd, {}, a.sh.yn}, [&](auto of) {
         return launch_kernel(by_model<DqFam<T, CT, D, WK, WV, decltype(of)>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd,
                              s, (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
                              f.cache_tiles, a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog,
@@ -1855,23 +1860,25 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
         static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
         const bool by_tiles = p.cache_tiles == 1;
-        e = by_shards(p, sh, [&](auto of) {
+        auto go = [&](auto of) {
             using SH = decltype(of);
-            auto walk = by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV, SH>>(p) : by_model<Bwd8pFam<T, CT, D, WK, WV, SH>>(p);
-            if constexpr (!is_shared<SH>) {
-                if (!by_tiles && p.tiles_per_seg == 1) walk = by_model<Bwd8hFam<T, CT, D, WK, WV>>(p);
-            }
+            const auto walk = by_tiles ? by_model<Bwd8tFam<T, CT, D, WK, WV, SH>>(p) : [&] {
+                if constexpr (is_own<SH>) return by_model<Bwd8hFam<T, CT, D, WK, WV>>(p);
+                else return by_model<Bwd8pFam<T, CT, D, WK, WV, SH>>(p);
+            }();
             return launch_kernel(walk, grid, block, by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
                                  (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
                                  p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
-        });
+        };
+        // (single tiles of pairs: also a sequence of one tile, whose workgroups have no tile behind them)
+        e = !by_tiles && p.tiles_per_seg == 1 ? go(AloneOwn{}) : by_start(p, start, sh, go);
     } else {
         static_assert(BwdkvSmem<T, CT, D>::TOTAL <= 163840 / (D == 128 ? 1 : 2), "LDS of one gfx950 CU for the workgroups meant to share it");
         if (a.cache) {
             if (e = run_dq<T, CT, D, WK, WV>(a, s); e != hipSuccess) return e;
         }
-        e = by_shards(p, sh, [&](auto of) {
+        e = by_start(p, start, sh, [&](auto of) {
             return launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV, decltype(of)>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
                                  (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
