@@ -31,14 +31,25 @@ PROFILE_ROW = {"fwd_walk": ("k_fwd<", "k_fwd8<"), "bwd_walk": "k_bwd", "fwd_loca
                "bwd_apply": "backward (3 products)", "fwd_apply": "forward (1 product)", "state_reduce": "k_bidir_reduce<"}
 
 
-def traffic_from_profile(config, kernel):
+def tokens_of_a_launch(B, H, N, steps, launches):
+    """Token-heads that one of `launches` launches of a kernel takes when `steps` steps pass over B x H x N of them. (The two
+    passes differ: sub-sequences that share a launch in one may go one by one in the other.)"""
+    return B * H * N * steps / launches
+
+
+def traffic_from_profile(config, kernel, launches=None):
     """HBM bytes one launch of `kernel` moves, read from the committed rocprofv3 summary of this config
     (table 'HBM traffic per launch': read MiB + written MiB, already scaled by the plain-copy calibration).
-    Returns (bytes, path) or (None, None) when the summary or the row is missing."""
+    Returns (bytes, path) or (None, None) when the summary or the row is missing, or when the summary is of another number
+    of launches a pass than `launches` (None = any)."""
     import re
     path = os.path.join(ROOT, "profiles", f"{config}_fwd_bwd_kernels.md")
     if not os.path.exists(path):
         return None, None
+    if launches is not None:
+        profiled = re.search(r"\((\d+) (?:sub-sequence call\(s\)|launch\(es\)) per pass\)", open(path).read())
+        if not profiled or int(profiled.group(1)) != launches:
+            return None, None
     want = PROFILE_ROW.get(kernel, ())
     want = (want,) if isinstance(want, str) else want
     in_table = False
@@ -254,8 +265,7 @@ def main():
     peak_mem = torch.cuda.max_memory_allocated()
 
     # ---- roofline of the dominant kernel (largest share of the step) ----
-    # (a launch takes several sub-sequences where that fills the device: nf launches of `steps` passes over all tokens)
-    tok_heads_per_launch = B * H * N * args.steps // nf
+    launches = {"fwd": nf, "bwd": nb_calls}   # of `steps` passes: one takes several sub-sequences where that fills the device
     esz = 2 if cfg.dtype == "bf16" else 4
     per_launch_ms = {"fwd_local": kernel_ms["fwd"][0] / nf, "fwd_scan": kernel_ms["fwd"][1] / nf,
                      "fwd_walk": kernel_ms["fwd"][2] / nf, "bwd_local": kernel_ms["bwd"][0] / nb_calls,
@@ -272,10 +282,11 @@ def main():
                  "bwd_walk": (4 * dk_ + 3 * dv_) * esz + gb + nb,
                  "fwd_local": (dk_ + dv_) * esz + gb, "bwd_local": (dk_ + dv_) * esz + gb + nb}
     dominant = max(("fwd_walk", "bwd_walk", "fwd_local", "bwd_local"), key=lambda n: per_launch_ms[n])
-    dom_bytes = alg_bytes[dominant] * tok_heads_per_launch
+    dom_launches = launches[dominant[:3]]
+    dom_bytes = int(alg_bytes[dominant] * tokens_of_a_launch(B, H, N, args.steps, dom_launches))
     achieved = dom_bytes / (per_launch_ms[dominant] * 1e-3) / 1e9
-    as_profiled = args.segments == 0 and args.sub_sequences == 0 and args.head_groups == 1   # the committed summaries' launch shape
-    traffic, traffic_src = traffic_from_profile(args.config, dominant) if as_profiled else (None, None)
+    as_profiled = args.segments == 0 and args.sub_sequences == 0 and args.head_groups == 1 and not args.recompute
+    traffic, traffic_src = traffic_from_profile(args.config, dominant, dom_launches // args.steps) if as_profiled else (None, None)
     roofline = {"kernel": dominant, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "traffic_source": traffic_src,

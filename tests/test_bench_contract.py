@@ -69,6 +69,22 @@ def test_traffic_of_either_forward_walk(tmp_path, monkeypatch):
         assert bench.traffic_from_profile("x", "bwd_walk")[0] == 15 * 2**20, kernel
 
 
+def test_launches_of_the_two_passes_are_counted_apart(tmp_path, monkeypatch):
+    """A forward pass in groups beside a backward pass one by one: bytes from each pass's own launches, and traffic only from
+    a summary with as many."""
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.tokens_of_a_launch(1, 16, 262144, 20, 2 * 20) == 16 * 131072      # eight sub-sequences, four a launch
+    assert bench.tokens_of_a_launch(1, 16, 262144, 20, 8 * 20) == 16 * 32768
+    (tmp_path / "profiles").mkdir()
+    row = "## HBM traffic per launch\n| `lasp::k_bwd8p<unsigned short, 64>` | 1.0 | 7.0 | 1.0 | 8.0 |\n"
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    for text in ("(8 sub-sequence call(s) per pass)", "(8 launch(es) per pass)"):
+        (tmp_path / "profiles" / "x_fwd_bwd_kernels.md").write_text(row + f"Sum over the kernels of one step {text}: 1 MiB\n")
+        assert bench.traffic_from_profile("x", "bwd_walk", 8)[0] == bench.traffic_from_profile("x", "bwd_walk")[0] == 15 * 2**20
+        assert bench.traffic_from_profile("x", "bwd_walk", 2) == (None, None)
+
+
 @pytest.mark.parametrize("config,kernels", [("c2", 4), ("c3", 4), ("c4", 4), ("g3", 4), ("n3", 4), ("m3", 4)])
 def test_every_committed_profile_serves_every_kernel(config, kernels):
     sys.path.insert(0, ROOT)
