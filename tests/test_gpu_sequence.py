@@ -30,9 +30,9 @@ CASES = [
 
 @pytest.mark.parametrize("dtype,D,Dv,n,T,kv_heads,token,norm", CASES)
 @pytest.mark.parametrize("recompute", [False, True])
-def test_together(gpu, oracle, dtype, D, Dv, n, T, kv_heads, token, norm, recompute):
+def test_together(gpu, oracle, dtype, D, Dv, n, T, kv_heads, token, norm, recompute, H=4):
     harness, lasp, sequence, si = gpu
-    H, N, G = 4, n * T, 4 // kv_heads if kv_heads else 1
+    N, G = n * T, H // kv_heads if kv_heads else 1
     cfg = si.Config("seq", B=1, H=H, N=N, D=D, chunk=64, dtype=dtype, seed=9100 + n + T, token_decay=token, Dv=Dv)
     inp = si.make_inputs(cfg, with_states=True)
     print(f"case {dtype} {D}x{Dv or D} {T} x {n} kv_heads={kv_heads} token={token} norm={norm} recompute={recompute}", flush=True)
@@ -54,6 +54,19 @@ def test_together(gpu, oracle, dtype, D, Dv, n, T, kv_heads, token, norm, recomp
         emax, efro = harness.rel_errors(got[name], r)
         print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
         assert np.isfinite(emax) and emax <= TOL[dtype] and efro <= TOL[dtype], name
+
+
+# (H, data type, D, Dv, tokens, T): sub-sequences whose last segment is short and has several tiles of the local pass (which cuts
+# it from its end: three of 128 tokens, three of 64 where d_k is not d_v, two of 32), and sequences whose last group is one
+# sub-sequence with a plan of its own (4, 4, 4, 1 and 2, 1)
+LONGER = [(32, "bf16", 128, 0, 1050, 2), (32, "bf16", 128, 64, 1180, 2), (32, "f32", 128, 0, 1000, 2),
+          (4, "bf16", 128, 0, 130, 13), (4, "f32", 64, 0, 40, 13), (100, "bf16", 64, 0, 130, 3)]
+
+
+@pytest.mark.parametrize("H,dtype,D,Dv,n,T", LONGER)
+@pytest.mark.parametrize("recompute", [False, True])
+def test_together_longer_segments_and_one_left_over(gpu, oracle, H, dtype, D, Dv, n, T, recompute):
+    test_together(gpu, oracle, dtype, D, Dv, n, T, 0, False, False, recompute, H)
 
 
 @pytest.mark.parametrize("dtype,n", [("bf16", 200), ("f32", 100)])

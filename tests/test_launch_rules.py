@@ -97,3 +97,34 @@ def test_short_sequences_scratch():
     assert [segments(2, N) for N in (64, 128, 256, 384, 512, 448, 576, 640)] == [1, 1, 2, 3, 4, 7, 9, 5]
     assert [segments(2, N, 64) for N in (128, 256, 512)] == [1, 2, 4]
     assert [segments(2, N, dtype="f32") for N in (32, 64, 128, 256)] == [1, 2, 4, 8]
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("short")
+    src, lib = d / "short.cpp", d / "short.so"
+    src.write_text(f'#include "{ROOT}/paper_2404_02882_amd/csrc/lasp_rules.h"\n'
+                   'extern "C" int tiles(int want, int ntiles, long long chains, int D, int every, int backward, int alone) {\n'
+                   '    return lasp::segment_tiles(want, ntiles, chains, D, every, backward, alone);\n}\n'
+                   'extern "C" int own(int tiles, int two_byte) { return lasp::own_states(tiles, two_byte); }\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    handle = ctypes.CDLL(str(lib))
+    handle.tiles.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong] + [ctypes.c_int] * 4
+    return handle
+
+
+def test_short_sequences_alone(rules):
+    """Single tiles up to eight of them and a workgroup a CU, whatever the cache holds and only alone; own start states where
+    less than eight (float: four) tiles lie in front."""
+    assert [rules.own(t, 1) for t in (1, 7, 8)] == [1, 1, 0] and [rules.own(t, 0) for t in (1, 3, 4)] == [1, 1, 0]
+    for D in (64, 128):
+        for every in (0, 1):
+            for backward in (0, 1):
+                for ntiles in (1, 2, 7, 8):
+                    for want in range(1, ntiles + 1):
+                        assert rules.tiles(want, ntiles, 256 // ntiles, D, every, backward, 1) == 1
+                        beside = rules.tiles(want, ntiles, 256 // ntiles, D, every, backward, 0)
+                        assert rules.tiles(want, ntiles, 256 // ntiles + 1, D, every, backward, 1) == \
+                            rules.tiles(want, ntiles, 256 // ntiles + 1, D, every, backward, 0)
+                        assert beside >= want and (every or beside % 2 == 0)
+                assert rules.tiles(2, 9, 2, D, every, backward, 1) == 2

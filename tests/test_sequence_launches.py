@@ -275,3 +275,70 @@ def test_parts_of_grouped_heads_stay_bounded(api):
             assert api.scratch_bytes(shape, T) == one
     plain = api.shape(H, 65536, 128)
     assert groups(api.bwd(plain, T, Sequence(T))[1]) == [4]   # no parts
+
+
+def test_groups_of_about_one_size_and_what_is_left_over(api):
+    """(The sequences that the GPU tests of shared launches take as ragged, over several tiles, or with one left over.)"""
+    for H, dtype, D, Dv, n, T, sizes in ((32, "bf16", 128, 0, 1050, 2, [2]), (32, "bf16", 128, 64, 1180, 2, [2]), (32, "f32", 128, 0, 1000, 2, [2]),
+                                         (4, "bf16", 128, 0, 130, 13, [4, 4, 4, 1]), (4, "f32", 64, 0, 40, 13, [4, 4, 4, 1]),
+                                         (100, "bf16", 64, 0, 130, 3, [2, 1]), (4, "bf16", 64, 0, 64, 9, [3, 3, 3]), (257, "bf16", 64, 0, 64, 4, [1] * 4)):
+        shape, s = api.shape(H, n, D, dtype, Dv=Dv), Sequence(T)
+        rc, r = api.fwd(shape, T, s)
+        assert rc == 0 and groups(r) == sizes
+        if sizes == [2]:   # ragged last segments of several tiles of the local pass
+            tile, local = (32, 32) if dtype == "f32" else (64, 64 if Dv else 128)
+            tiles = -(-n // tile)
+            per_seg = -(-tiles // r[0][6])
+            per_seg += per_seg % 2 if dtype == "bf16" else 0
+            last = n - (r[0][6] - 1) * per_seg * tile
+            assert last % local and last > local, (H, dtype, last)
+        rc, r = api.bwd(shape, T, s)
+        assert rc == 0 and groups(r) == sizes[::-1]
+        assert [x[5] for x in r if x[1] > 1] == [0] * sum(g > 1 for g in sizes)   # start states from the scratch
+
+
+def test_rejects_before_launch(api):
+    T, shape = 3, api.shape()
+    lib, by = api.lib, ctypes.byref
+    assert api.scratch_bytes(shape, 0) == api.scratch_bytes(shape, -1) == api.scratch_bytes(api.shape(D=96), T) == 0
+    assert api.scratch_bytes(shape, 1) == lib.lasp_scratch_bytes(by(shape))
+    for token in (False, True):
+        for norm in (False, True):
+            need = {"fwd": ["q", "k", "v", "out"], "bwd": ["q", "k", "v", "dout", "dq", "dk", "dv"]}
+            need["fwd"] += ["log_g"] * token + ["rstd"] * norm
+            need["bwd"] += ["log_g", "dlog_g"] * token + ["out", "rstd"] * norm
+            for name, call in (("fwd", api.fwd), ("bwd", api.bwd)):
+                assert call(shape, T, Sequence(T), token, norm)[0] == 0
+                for buf in need[name]:
+                    for t in range(T):
+                        s = Sequence(T)
+                        getattr(s, buf)[t] = None
+                        assert call(shape, T, s, token, norm) == (ERR_NULL, []), (name, buf, t)
+                        s = Sequence(T)
+                        getattr(s, buf)[t] += 4
+                        assert call(shape, T, s, token, norm) == (ERR_ALIGN, []), (name, buf, t)
+                size = api.scratch_bytes(shape, T, token)
+                assert call(shape, T, Sequence(T), token, norm, scratch_bytes=size - 1) == (ERR_WORKSPACE, [])
+                for bad in (0, -2):
+                    s = Sequence(T)
+                    assert (lib.lasp_seq_fwd(by(shape), bad, *[api.table(x) for x in (s.q, s.k, s.v)], s.kv_in, api.table([s.decay]), 0, 0.0, api.table(s.out),
+                                             None, api.table(s.kv), None, s.scratch, size, None) == ERR_SHAPE)
+                for t in range(T):
+                    s = Sequence(T)
+                    (s.out if name == "fwd" else s.dq)[t] = s.q[t]
+                    assert call(shape, T, s, token, norm) == (ERR_ALIAS, [])
+                    s = Sequence(T)
+                    (s.kv if name == "fwd" else s.dkv)[t + (name == "fwd")] = s.scratch
+                    assert call(shape, T, s, token, norm) == (ERR_ALIAS, [])
+    recompute = api.scratch_bytes(shape, T, recompute=True)
+    assert api.bwd(shape, T, Sequence(T), cache=False, scratch_bytes=recompute - 1) == (ERR_WORKSPACE, [])
+    s = Sequence(T)   # whole lists
+    args = [by(shape), T, *[api.table(x) for x in (s.q, s.k, s.v)], s.kv_in, api.table([s.decay]), 0, 0.0, api.table(s.out), None,
+            api.table(s.kv), None, s.scratch, recompute, None]
+    for at in (2, 3, 4, 6, 9, 11):
+        assert lib.lasp_seq_fwd(*args[:at], None, *args[at + 1:]) == ERR_NULL
+    args = [by(shape), T, *[api.table(x) for x in (s.q, s.k, s.v)], None, None, api.table(s.dout), api.table(s.kv), s.dkv_out,
+            api.table([s.decay]), 0, None, *[api.table(x) for x in (s.dq, s.dk, s.dv)], None, api.table(s.dkv), s.scratch, recompute, None]
+    for at in (2, 3, 4, 7, 8, 10, 13, 14, 15, 17):
+        assert lib.lasp_seq_bwd(*args[:at], None, *args[at + 1:]) == ERR_NULL
+    assert api.record() == []
