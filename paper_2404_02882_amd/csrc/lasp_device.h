@@ -948,12 +948,14 @@ struct SegDecay {
         else return shard_end ? last : full;
     }
 };
-// Whether the segments met on a walk over all of a launch's, from either end, are the last of their sub-sequence.
-template <bool BWD>
+// Whether the segments met on a walk over all of a launch's, from either end, are the last of their sub-sequence (SHARED:
+// of several; `j` = the segment's slot).
+template <bool BWD, bool SHARED>
 struct ShardEnds {
     int nseg, left;
     DEVI explicit ShardEnds(int nseg_) : nseg(nseg_), left(BWD ? 1 : nseg_) {}
-    DEVI bool next() {
+    DEVI bool next(int j) {
+        if constexpr (!SHARED) return j == nseg - 1;
         const bool end = --left == 0;
         if (end) left = nseg;
         return end;
@@ -965,7 +967,7 @@ struct ShardEnds {
 // and the walk carries the boundary state over the segments before its own itself, in the scan's order and arithmetic
 // (forward: slots 0 .. slot - 1, backward: nslots - 1 .. slot + 1): a few more reads, one launch less.
 // load(st, slot) loads a state in the orientation the wave keeps it in.
-template <bool BWD, bool TOKEN, int DB, typename Load>
+template <bool BWD, bool SHARED, bool TOKEN, int DB, typename Load>
 DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int slot,
                       int nseg, int nslots, int slot_elems, Load load) {
     if (boundary) {
@@ -975,12 +977,12 @@ DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *bounda
         for (int ab = 0; ab < DB; ++ab) st[ab] = f32x16{0};
     }
     const int steps = BWD ? nslots - 1 - slot : slot;
-    ShardEnds<BWD> ends(nseg);
+    ShardEnds<BWD, SHARED> ends(nseg);
     for (int n = 0; n < steps; ++n) {
         const int j = BWD ? nslots - 1 - n : n;
         f32x16 local[DB];
         load(local, states + (size_t)j * slot_elems);
-        const float f = factor(j, ends.next());
+        const float f = factor(j, ends.next(j));
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] = f * st[ab] + local[ab];
     }

@@ -416,7 +416,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             else state_load_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry > 0)
-            start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
+            start_state<false, SHARED>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
                                SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         const float *states = scratch + (size_t)chain * nslots * D * D;
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
-            start_state<false>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
+            start_state<false, SHARED>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
                                SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
         else load(st, states + (size_t)slot0 * D * D);
     }
@@ -762,7 +762,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         }
         __syncthreads();
         if (t + 1 < t1) request(t + 1);
-        f32x16 own = {0};   // OT[c][i], c in w, i in token block g
+        f32x16 part = {0};   // OT[c][i], c in w, i in token block g
         if constexpr (!STATES) {
             masked_scores<T, CT, D, LDD, LDP, 2 * NW>(ln, sP, sK, sQ, dec, w8);
             // this row half's share of Q KV, both token blocks
@@ -779,7 +779,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
                 }
             // the other group's block to LDS, lane-contiguous
             const f32x16 give = g ? acc[0] : acc[1];
-            own = g ? acc[1] : acc[0];
+            part = g ? acc[1] : acc[0];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *(f32x4 *)(sX + (w8 * 4 + q) * 256 + 4 * ln.id) = f32x4{give[4 * q], give[4 * q + 1], give[4 * q + 2], give[4 * q + 3]};
@@ -807,17 +807,17 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
             for (int q = 0; q < 4; ++q) {
                 const f32x4 x = *(const f32x4 *)(sX + (((1 - g) * NW + w) * 4 + q) * 256 + 4 * ln.id);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) own[4 * q + e] += x[e];
+                for (int e = 0; e < 4; ++e) part[4 * q + e] += x[e];
             }
-            own *= up;
+            part *= up;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
-                if (g == 1 || ks < SPB) own = E::mfma(vf[ks], E::ld_kc(ln, sP, LDP, 32 * g, ks * E::KSTEP), own);
+                if (g == 1 || ks < SPB) part = E::mfma(vf[ks], E::ld_kc(ln, sP, LDP, 32 * g, ks * E::KSTEP), part);
             if constexpr (NORM) {
                 float *red = pw + 3 * CT + 4;
                 float ss = 0.0f;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) ss += own[i] * own[i];
+                for (int i = 0; i < 16; ++i) ss += part[i] * part[i];
                 ss = add_other_half(ss);
                 if (ln.h == 0) red[w * CT + 32 * g + ln.r] = ss;
                 __syncthreads();
@@ -825,11 +825,11 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
 #pragma unroll
                 for (int wv = 0; wv < NW; ++wv) tot += red[wv * CT + 32 * g + ln.r];
                 const float rs = rsqrtf(tot * (1.0f / D) + eps);
-                own *= rs;
+                part *= rs;
                 if (w == 0 && ln.h == 0 && (!RAGGED || 32 * g + ln.r < nvalid(t)))
                     rstd_out[(size_t)chain * ntok + (size_t)t * CT + 32 * g + ln.r] = rs;
             }
-            store_out_tile_t<T, D>(ln, O + off(t), own, 32 * g, w, nvalid(t));
+            store_out_tile_t<T, D>(ln, O + off(t), part, 32 * g, w, nvalid(t));
         }
     }
     if (seg == nseg - 1 && kv_out) state_store_w<D, D, D, HB>(ln, st, kv_out + (size_t)chain * D * D + a0 * D, w);
@@ -975,7 +975,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
-            start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+            start_state<true, SHARED>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
-            start_state<true>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+            start_state<true, SHARED>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
