@@ -37,6 +37,11 @@ def tokens_of_a_launch(B, H, N, steps, launches):
     return B * H * N * steps / launches
 
 
+def dominant_kernel(per_launch_ms, launches):
+    """The kernel with the largest share of the step: its time a launch times the launches of its pass."""
+    return max(("fwd_walk", "bwd_walk", "fwd_local", "bwd_local"), key=lambda n: per_launch_ms[n] * launches[n[:3]])
+
+
 def traffic_from_profile(config, kernel, launches=None):
     """HBM bytes one launch of `kernel` moves, read from the committed rocprofv3 summary of this config
     (table 'HBM traffic per launch': read MiB + written MiB, already scaled by the plain-copy calibration).
@@ -281,7 +286,7 @@ def main():
     alg_bytes = {"fwd_walk": (2 * dk_ + 2 * dv_) * esz + gb + (4 if norm else 0),
                  "bwd_walk": (4 * dk_ + 3 * dv_) * esz + gb + nb,
                  "fwd_local": (dk_ + dv_) * esz + gb, "bwd_local": (dk_ + dv_) * esz + gb + nb}
-    dominant = max(("fwd_walk", "bwd_walk", "fwd_local", "bwd_local"), key=lambda n: per_launch_ms[n])
+    dominant = dominant_kernel(per_launch_ms, launches)
     dom_launches = launches[dominant[:3]]
     dom_bytes = int(alg_bytes[dominant] * tokens_of_a_launch(B, H, N, args.steps, dom_launches))
     achieved = dom_bytes / (per_launch_ms[dominant] * 1e-3) / 1e9

@@ -83,6 +83,10 @@ def test_launches_of_the_two_passes_are_counted_apart(tmp_path, monkeypatch):
         (tmp_path / "profiles" / "x_fwd_bwd_kernels.md").write_text(row + f"Sum over the kernels of one step {text}: 1 MiB\n")
         assert bench.traffic_from_profile("x", "bwd_walk", 8)[0] == bench.traffic_from_profile("x", "bwd_walk")[0] == 15 * 2**20
         assert bench.traffic_from_profile("x", "bwd_walk", 2) == (None, None)
+    # the dominant kernel is that of the step, not of a launch
+    ms = {"fwd_walk": 0.53, "bwd_walk": 0.24, "fwd_local": 0.18, "bwd_local": 0.05}
+    assert bench.dominant_kernel(ms, {"fwd": 2 * 20, "bwd": 8 * 20}) == "bwd_walk"
+    assert bench.dominant_kernel(ms, {"fwd": 2 * 20, "bwd": 2 * 20}) == "fwd_walk"
 
 
 @pytest.mark.parametrize("config,kernels", [("c2", 4), ("c3", 4), ("c4", 4), ("g3", 4), ("n3", 4), ("m3", 4)])
