@@ -120,8 +120,9 @@ class LaspSequence:
 class GraphedStep:
     """One forward + backward pass of a LaspSequence captured in a HIP graph and replayed.
 
-    With short sub-sequences the T-loop is launch-bound (six small kernels per call, 2T calls per
-    step); a graph replays them with one submission. The library allocates nothing and never
+    Short sequences are bound by launches: a pass is up to three kernels for every four sub-sequences
+    (one for a short sequence alone; with a decay per token, or sub-sequences that fill the device, for each),
+    and the calls that enqueue them; a graph replays all with one submission. The library allocates nothing and never
     synchronises, so its calls can be captured as they are. The graph reads and writes the very
     tensors given here: refresh their contents in place between replays. Per-kernel timing
     (lasp_profile_begin) must be off while capturing.
