@@ -929,18 +929,17 @@ constexpr bool is_shared = !std::is_same_v<SH, Alone> && !is_own<SH>;
 template <typename P>
 DEVI P *at_shard(P *p, const Offsets &o, int shard) { return (P *)((char *)p + o.at[shard]); }
 
-// Decay over whole segments, for carrying a state across them: one lambda per head (`full` tokens' worth for every
-// segment but the last of a sub-sequence, `last` for that), or with a decay per token 2^seglog[j], written by the local
-// pass. nseg: segments per sub-sequence, nslots: of all that the launch takes.
+// Decay over whole pieces of segments, for carrying a state across them: one lambda per head (`full` tokens' worth for every
+// piece but the last of a sub-sequence, `last` for that), or with a decay per token 2^seglog[j], written by the local pass.
+// seglog: the chain's first piece; npieces: pieces per sub-sequence.
 template <bool TOKEN>
 struct SegDecay {
     float full = 0.0f, last = 0.0f;
     const float *seglog;
-    DEVI SegDecay(const float *decay, const float *seglog_all, int chain, int H, int nseg, int nslots, int seg_tokens, int ntok)
-        : seglog(TOKEN ? seglog_all + (size_t)chain * nslots : nullptr) {
+    DEVI SegDecay(const float *decay, const float *seglog_chain, int chain, int H, int npieces, int piece_tokens, int ntok) : seglog(seglog_chain) {
         if constexpr (!TOKEN) {
-            full = (float)pow_n(decay[chain % H], seg_tokens);
-            last = ntok == nseg * seg_tokens ? full : (float)pow_n(decay[chain % H], ntok - (nseg - 1) * seg_tokens);
+            full = (float)pow_n(decay[chain % H], piece_tokens);
+            last = ntok == npieces * piece_tokens ? full : (float)pow_n(decay[chain % H], ntok - (npieces - 1) * piece_tokens);
         }
     }
     DEVI float operator()(int j, bool shard_end) const {
@@ -962,31 +961,34 @@ struct ShardEnds {
     }
 };
 
-// The state slot `slot` of a launch (its segments, over all sub-sequences) starts from, in a walk's registers. Either
-// k_scan has already put it into `states` (the chain's segment states), or (CARRY) the slots still hold the local states
-// and the walk carries the boundary state over the segments before its own itself, in the scan's order and arithmetic
-// (forward: slots 0 .. slot - 1, backward: nslots - 1 .. slot + 1): a few more reads, one launch less.
-// load(st, slot) loads a state in the orientation the wave keeps it in.
+// The state a segment starts from, in a walk's registers, where its slot does not hold it already (k_scan): the boundary
+// state carried over the local states of the pieces before it (forward: pieces 0 .. piece - 1, `piece` being its first;
+// backward: npieces - 1 .. piece + 1, its last), in the scan's order and arithmetic: a few more reads, one launch less.
+// `states` is where piece 0 lies (or would), `per_shard` pieces a sub-sequence has; load(st, p) loads a state in the
+// orientation the wave keeps it in.
 template <bool BWD, bool SHARED, bool TOKEN, int DB, typename Load>
-DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int slot,
-                      int nseg, int nslots, int slot_elems, Load load) {
+DEVI void start_state(f32x16 (&st)[DB], const float *states, const float *boundary, const SegDecay<TOKEN> &factor, int piece,
+                      int per_shard, int npieces, int state_elems, Load load) {
     if (boundary) {
         load(st, boundary);
     } else {
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] = f32x16{0};
     }
-    const int steps = BWD ? nslots - 1 - slot : slot;
-    ShardEnds<BWD, SHARED> ends(nseg);
+    const int steps = BWD ? npieces - 1 - piece : piece;
+    ShardEnds<BWD, SHARED> ends(per_shard);
     for (int n = 0; n < steps; ++n) {
-        const int j = BWD ? nslots - 1 - n : n;
+        const int j = BWD ? npieces - 1 - n : n;
         f32x16 local[DB];
-        load(local, states + (size_t)j * slot_elems);
+        load(local, states + (ptrdiff_t)j * state_elems);
         const float f = factor(j, ends.next(j));
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] = f * st[ab] + local[ab];
     }
 }
+// First (forward) or last (backward) piece of segment `seg` of sub-sequence `shard`.
+template <bool BWD>
+DEVI int piece_of(const Pieces &pc, int shard, int seg) { return shard * pc.per_shard + (BWD ? min((seg + 1) * pc.n, pc.per_shard) - 1 : seg * pc.n); }
 
 // Float data: the product of the state with fragments load(i), contracted over its rows in accumulator order. `lows` tells
 // the caller whether to take it again with EDGE; a walk asks once a tile, for everything that it split itself. A step of

@@ -54,6 +54,18 @@ struct BwdShards {
     Offsets q, k, v, dout, cache, dq, dk, dv, dkv_in, yn, rstd;
 };
 
+// The pieces the local pass cuts the segments of a launch into, one workgroup and one state of the scratch each: whole
+// segments, or `n` pieces of each where whole ones would leave most of the device idle (local_pieces in lasp_rules.h). Pieces
+// are numbered over all sub-sequences of the launch.
+struct Pieces {
+    int n;           // pieces per segment
+    int tiles;       // tiles of a piece (the last of a sub-sequence may be shorter)
+    int per_shard;   // pieces of a sub-sequence
+    int first, end;  // the pieces that another segment's state depends on: the local pass sums these
+    int base;        // the piece whose state is the scratch's first (of a chain)
+    int slots;       // states of a chain in the scratch
+};
+
 struct FwdArgs {
     const void *q, *k, *v;
     const float *kv_in;   // entering the first sub-sequence; may be null (zeros)

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
     const int chain = blockIdx.y, nslots = SHARED ? slots : nseg;
     const int e = (blockIdx.x * blockDim.x + threadIdx.x) * 4;  // four consecutive state elements per thread
     if (e >= DD) return;
-    const SegDecay<TOKEN> seg_decay(decay, seglog, chain, H, nseg, nslots, seg_tokens, ntok);
+    const SegDecay<TOKEN> seg_decay(decay, TOKEN ? seglog + (size_t)chain * nslots : nullptr, chain, H, nseg, seg_tokens, ntok);
     // The caller's state and the segment states share one layout, [d_k][d_v] (DD = d_k * d_v elements).
     f32x4 carry = {0, 0, 0, 0};
     if (boundary) carry = *(const f32x4 *)(boundary + (size_t)chain * DD + e);

@@ -48,6 +48,16 @@ inline int segment_tiles(int want, int ntiles, long long chains, int D, bool eve
     return keep ? want : want + 1;
 }
 
+// Pieces that the local pass cuts a segment into. Where two segments (of a sequence, or of two sub-sequences) share a launch,
+// only one of them is summed, and its workgroups are at most half as many as there are CUs: in two pieces they fill them.
+// The walk then carries the boundary state over two pieces instead of one; two states are what the scratch holds anyway.
+// The second state costs the walk 1.3 us, so only from 12 tiles a segment on. Steps of 128 heads, bf16 d=128, one piece / two:
+// x 1024 tokens (8 tiles) 124.7 / 126.5 us, x 1536 181.1 / 177.7, x 2048 234.8 / 227.1, x 8192 880 / 831, x 16384 1737 / 1627 (a
+// local pass 163 -> 100), decay per token x 8192 943 / 907, d=64 x 8192 457 / 441.
+inline int local_pieces(int segments, int tiles_per_seg, long long chains) {
+    return segments == 2 && tiles_per_seg % 2 == 0 && tiles_per_seg >= 12 && chains <= kOnePerCu / 2 ? 2 : 1;
+}
+
 // Blocks of tiles per chain for `chains` independent rows of `ntiles` tiles where `slots` workgroups are resident at
 // once. Two counts come into question, the share of the slots rounded down and up: the launch takes as many rounds as
 // its workgroups fill the slots, each as long as the tiles of a block. The shorter is taken, and if both are as long the

@@ -63,7 +63,7 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 }
 
 // ---------------------------------------------------------------------------
-// k_local: local state of a segment, from zero.
+// k_local: local state of a segment, or of a piece of one (Pieces), from zero.
 //   forward : local = sum_s lambda^(len - s) k_s v_s^T            (X = K, Y = V)
 //   backward: local = sum_s lambda^s q_s do_s^T                    (X = Q, Y = dO)
 // This is the state update of Alg. 2 / the dKV update of Alg. 3 unrolled over the segment's tiles: every
@@ -81,8 +81,8 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM, int WX, int WY, typename SH>
 __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
-                                                  float *__restrict__ seglog, int H, int ntiles, int nseg,
-                                                  int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn,
+                                                  float *__restrict__ seglog, int H, int ntiles, Pieces pc,
+                                                  int ntok, int kvdiv, const T *__restrict__ yn,
                                                   const float *__restrict__ rstd, SH sh) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
     using E = WalkElem<T>;
@@ -93,11 +93,12 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     float *pw = (float *)(sY + TILE);
 
     constexpr bool SHARED = is_shared<SH>;
-    const int chain = blockIdx.y, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
-    const int seg = blockIdx.x + (BWD && !SHARED ? 1 : 0), slot = shard * nseg + seg;
-    if (SHARED && slot == (BWD ? 0 : nslots - 1)) return;   // no other segment starts from the last one's state (of several sub-sequences: the grid has it)
-    const int t0 = seg * tiles_per_seg;
-    const int t1 = min(t0 + tiles_per_seg, ntiles);
+    const int chain = blockIdx.y, shard = SHARED ? blockIdx.z : 0;
+    const int seg = blockIdx.x + (SHARED ? 0 : pc.first), piece = shard * pc.per_shard + seg;
+    if (SHARED && (piece < pc.first || piece >= pc.end)) return;   // (of several sub-sequences: the grid has them all)
+    const size_t slot = (size_t)chain * pc.slots + (piece - pc.base);
+    const int t0 = seg * pc.tiles;
+    const int t1 = min(t0 + pc.tiles, ntiles);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
     Lane ln = fresh_lane();
     if constexpr (SHARED) {
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                 });
         }
         // log2 of the product of g over the segment, for the scan
-        if (threadIdx.x == 0) seglog[(size_t)chain * nslots + slot] = base;
+        if (threadIdx.x == 0) seglog[slot] = base;
     } else {
     const float lam = decay[chain % H];
     fill_pow_table<CT>(pw, lam);
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] += low[ab];
     }
-    state_store_w<D, WX, WY>(ln, st, scratch + ((size_t)chain * nslots + slot) * WX * WY, w);
+    state_store_w<D, WX, WY>(ln, st, scratch + slot * WX * WY, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
-                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, Pieces pc,
                                                 int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
                                                 const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok,
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
     float *pw = (float *)(sStage + fwd_stage<T, D>());
 
     constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, shards = SHARED ? gridDim.z : 1, nslots = shards * nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
@@ -416,8 +417,9 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             else state_load_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry > 0)
-            start_state<false, SHARED>(st, states, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, WK * WV, load);
+            start_state<false, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
+                               SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
+                               OWN && carry == kOwn ? 0 : piece_of<false>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
         else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -650,7 +652,7 @@ template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, Role RO
 __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                 const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
-                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, Pieces pc, int H,
                                                 int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, float *__restrict__ kv_copy, SH sh) {
     using E = WalkElem<T>;
@@ -668,7 +670,7 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     float *pw = (float *)(smem + SM::PW_OFF);
 
     constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, shards = SHARED ? gridDim.z : 1, nslots = shards * nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
@@ -712,8 +714,9 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
         const float *states = scratch + (size_t)chain * nslots * D * D;
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
         if (carry)
-            start_state<false, SHARED>(st, states, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
-                               SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? 0 : slot0, nseg, nslots, D * D, load);
+            start_state<false, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * D * D, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
+                               SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
+                               OWN && carry == kOwn ? 0 : piece_of<false>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, D * D, load);
         else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
@@ -876,7 +879,7 @@ template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, int WK,
 __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                  const T *__restrict__ dO, const float *__restrict__ decay, T *__restrict__ dK,
                                                  T *__restrict__ dV, float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                 const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
+                                                 const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry, Pieces pc,
                                                  float *__restrict__ rtok, int H, int ntiles, int nseg, int tiles_per_seg,
                                                  int ntok, int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd,
                                                  float *__restrict__ dkv_copy, SH sh) {
@@ -896,7 +899,7 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
     float *pw = (float *)(smem + SM::PW_OFF);
 
     constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, shards = SHARED ? gridDim.z : 1, nslots = shards * nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     const int t0 = seg * tiles_per_seg;
     const int t1 = min(t0 + tiles_per_seg, ntiles);
@@ -975,8 +978,9 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
-            start_state<true, SHARED>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
+            start_state<true, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+                              SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
+                              OWN && carry == kOwn ? pc.per_shard * shards - 1 : piece_of<true>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1129,7 +1133,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
                                                   T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
                                                   float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
+                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry, Pieces pc,
                                                   float *__restrict__ rtok,
                                                   int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                   const T *__restrict__ yn, const float *__restrict__ rstd, float *__restrict__ dkv_copy,
@@ -1157,7 +1161,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     float *pw = (float *)(smem + SM::PW_OFF);
 
     constexpr bool SHARED = is_shared<SH>, OWN = is_own<SH>;
-    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, nslots = SHARED ? gridDim.z * nseg : nseg;
+    const int chain = blockIdx.y, seg = blockIdx.x, shard = SHARED ? blockIdx.z : 0, shards = SHARED ? gridDim.z : 1, nslots = shards * nseg;
     const int slot0 = shard * nseg + seg;   // among the segments of all sub-sequences of the launch
     if constexpr (SHARED) {
         if (shard) {
@@ -1305,8 +1309,9 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
         if (carry)
-            start_state<true, SHARED>(st, states, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
-                              SegDecay<TOKEN>(decay, seglog, chain, H, nseg, nslots, tiles_per_seg * CT, ntok), OWN && carry == kOwn ? nslots - 1 : slot0, nseg, nslots, WK * WV, load);
+            start_state<true, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
+                              SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
+                              OWN && carry == kOwn ? pc.per_shard * shards - 1 : piece_of<true>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
         else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
@@ -1725,23 +1730,25 @@ struct Bwd8hFam : Family<AloneOwn> {   // one cached state per pair of tiles, a 
 // differ ask for the walk's tile. The forward pass of one sub-sequence never sums over the segment with the short end.
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
-                            const T *yn, const float *rstd, const Shards &all, hipStream_t s) {
+                            const T *yn, const float *rstd, const Pieces &pc, const Shards &all, hipStream_t s) {
     const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.yn, all.rstd};
-    const dim3 grid(p.shards > 1 ? p.nseg : p.nseg - 1, p.B * p.H, p.shards), block(D * 2);
+    const dim3 grid(p.shards > 1 ? pc.per_shard : pc.end - pc.first, p.B * p.H, p.shards), block(D * 2);
     Plan q = p;
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
-        if (!(BWD && p.norm) && p.tiles_per_seg % 2 == 0) {
+        if (!(BWD && p.norm) && pc.tiles % 2 == 0) {
             if (!BWD) q.ragged = p.N % 128 != 0;
+            Pieces wide = pc;
+            wide.tiles /= 2;
             return by_shards(p, sh, [&](auto of) {
                 return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D, decltype(of)>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, p.nseg, p.tiles_per_seg / 2, p.N, p.kvdiv,
+                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, wide, p.N, p.kvdiv,
                                      (const T *)nullptr, (const float *)nullptr, of);
             });
         }
     }
     return by_shards(p, sh, [&](auto of) {
         return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV, decltype(of)>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
-                             scratch, seglog, p.H, p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, of);
+                             scratch, seglog, p.H, p.ntiles, pc, p.N, p.kvdiv, yn, rstd, of);
     });
 }
 
@@ -1753,12 +1760,25 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
 static Start walk_start(const Plan &p) { return p.own_states ? kOwn : p.shards * p.nseg <= 4 ? kCarried : kScanned; }
 
+static Pieces pieces(const Plan &p, bool bwd) {
+    Pieces c;
+    c.n = local_pieces(p.shards * p.nseg, p.tiles_per_seg, (long long)p.B * p.H);
+    c.tiles = p.tiles_per_seg / c.n;
+    c.per_shard = c.n == 1 ? p.nseg : (p.ntiles + c.tiles - 1) / c.tiles;
+    const int all = p.shards * c.per_shard;
+    c.first = bwd ? c.n : 0;
+    c.end = bwd ? all : (p.shards - 1) * c.per_shard + (p.nseg - 1) * c.n;
+    c.base = c.n > 1 ? c.first : 0;
+    c.slots = c.n > 1 ? c.end - c.first : all;
+    return c;
+}
+
 // Local pass and scan of the forward states over K, V, as far as the walk's start asks for them.
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_states(const Plan &p, const void *k, const void *v, const float *kv_in, const float *decay, float *scratch,
-                             float *seglog, Start start, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
+                             float *seglog, Start start, const Pieces &pc, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
     if (start != kOwn && p.shards * p.nseg > 1) {
-        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, sh, s);
+        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, pc, sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1769,9 +1789,10 @@ static hipError_t run_states(const Plan &p, const void *k, const void *v, const 
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const Start start = walk_start(p);
+    const Pieces pc = pieces(p, false);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
-    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, ke); e != hipSuccess) return e;
+    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, pc, a.sh, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
     const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}};
@@ -1789,7 +1810,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
                 const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates, SH>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs, SH>>(p);
                 return launch_kernel(walk8, grid, dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                      (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles,
-                                     (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
+                                     (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, pc, p.H, p.ntiles, p.nseg,
                                      p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, a.kv_copy, of);
             });
             if (e != hipSuccess) return e;
@@ -1802,7 +1823,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV, SH>>(p) : by_model<FwdFam<T, CT, D, WK, WV, SH>>(p);
         return launch_kernel(walk, grid, dim3(D * 2), Smem<T, CT, D>::fwd, s,
                              (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                             p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
+                             p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, pc, p.H, p.ntiles, p.nseg,
                              p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
                              (const T *)nullptr, (float *)nullptr, a.kv_copy, of);
     });
@@ -1817,8 +1838,9 @@ template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
     const Plan &f = *a.fwd;   // a segment per cached state
     const Start start = a.cache ? kKept : walk_start(f);   // kKept: a state per segment of every sub-sequence, in its own buffer
+    const Pieces pc = pieces(f, false);
     if (!a.cache) {
-        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, nullptr);
+        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, pc, a.sh, s, nullptr);
             e != hipSuccess)
             return e;
     }
@@ -1826,7 +1848,7 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
         return launch_kernel(by_model<DqFam<T, CT, D, WK, WV, decltype(of)>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd,
                              s, (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
                              f.cache_tiles, a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog,
-                             (int)start, f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
+                             (int)start, pc, f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
                              (const T *)a.q, a.rtok, (float *)nullptr, of);
     });
 }
@@ -1835,6 +1857,7 @@ template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const int chains = p.B * p.H;
     const Start start = walk_start(p);
+    const Pieces pc = pieces(p, true);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
     if constexpr (sizeof(T) == 4) {
@@ -1844,7 +1867,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     }
     if (start != kOwn && p.shards * p.nseg > 1) {
         if (e = run_local<T, CT, D, true, WK, WV>(p, (const T *)a.q, (const T *)a.dout, a.decay, a.scratch, a.seglog, (const T *)a.yn,
-                                          a.rstd, a.sh, s);
+                                          a.rstd, pc, a.sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1868,7 +1891,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
             }();
             return launch_kernel(walk, grid, block, by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
-                                 (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
+                                 (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, pc, a.rtok, p.H,
                                  p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
         };
         // (single tiles of pairs: also a sequence of one tile, whose workgroups have no tile behind them)
@@ -1881,7 +1904,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
         e = by_start(p, start, sh, [&](auto of) {
             return launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV, decltype(of)>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                                 (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
+                                 (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, pc, a.rtok, p.H, p.ntiles, p.nseg,
                                  p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
         });
     }

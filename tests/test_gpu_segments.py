@@ -86,3 +86,44 @@ def test_odd_segments(gpu, oracle, N, segments, D, Dv, kv_heads, token, norm):
         emax, efro = harness.rel_errors(got[name], r)
         print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
         assert np.isfinite(emax) and emax <= TOL["bf16"] and efro <= TOL["bf16"], name
+
+
+# Two segments, of which the local pass cuts the one it sums in two pieces (local_pieces, from 12 tiles a segment on): the shortest
+# that is cut, one tile less, pieces of an odd number of 64-token tiles, short last tiles, a last segment of a single piece or
+# little more.
+@pytest.mark.parametrize("dtype,N", [("bf16", 64 * 24), ("bf16", 64 * 22), ("bf16", 64 * 25 + 1), ("bf16", 64 * 23 - 37), ("bf16", 64 * 28),
+                                     ("f32", 32 * 24), ("f32", 32 * 23 + 7), ("f32", 32 * 28 - 1)])
+@pytest.mark.parametrize("D,Dv,token,norm", [(128, 128, False, False), (64, 64, True, False), (64, 128, False, True), (128, 128, True, True)])
+def test_local_pass_in_pieces(gpu, oracle, dtype, N, D, Dv, token, norm):
+    harness, lasp, si = gpu
+    cfg = si.Config("pieces", B=1, H=2, N=N, D=D, chunk=64, dtype=dtype, seed=8700 + N + D, token_decay=token, Dv=Dv)
+    inp = si.make_inputs(cfg, with_states=True)
+    print(f"case {dtype} N={N} {D}x{Dv} token={token} norm={norm}", flush=True)
+    check(harness, oracle, inp, dtype, norm, harness.run_gpu(inp, segments=2, norm_eps=1e-5 if norm else None))
+
+
+# The same in launches that two sub-sequences share, each in one segment (72 heads).
+@pytest.mark.parametrize("dtype,n", [("bf16", 64 * 12), ("bf16", 64 * 13 - 5), ("f32", 32 * 13 - 3)])
+def test_local_pass_in_pieces_of_a_shard(gpu, oracle, dtype, n):
+    harness, lasp, si = gpu
+    cfg = si.Config("pieces", B=1, H=72, N=2 * n, D=64, chunk=64, dtype=dtype, seed=8800 + n)
+    inp = si.make_inputs(cfg, with_states=True)
+    print(f"case {dtype} 2 x {n}", flush=True)
+    check(harness, oracle, inp, dtype, False, harness.run_gpu(inp, T=2))
+
+
+def check(harness, oracle, inp, dtype, norm, got):
+    decay = None if inp.log_g is not None else inp.decay
+    o, kvo = oracle.dims_fwd_brute(inp.q, inp.k, inp.v, decay, inp.kv_in, log_g=inp.log_g)
+    dout = inp.dout
+    if norm:
+        o, rstd = oracle.norm_fwd(o, 1e-5)
+        dout = oracle.norm_bwd(inp.dout, o, rstd)
+    g = oracle.dims_bwd_brute(inp.q, inp.k, inp.v, dout, decay, inp.kv_in, inp.dkv_out, log_g=inp.log_g)
+    ref = dict(out=o, kv_out=kvo, dq=g[0], dk=g[1], dv=g[2], dkv_in=g[-1])
+    if inp.log_g is not None:
+        ref["dlog_g"] = g[3]
+    for name, r in ref.items():
+        emax, efro = harness.rel_errors(got[name], r)
+        print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
+        assert np.isfinite(emax) and emax <= TOL[dtype] and efro <= TOL[dtype], name
