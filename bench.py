@@ -28,7 +28,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 MFMA rate
 # kernel name fragments of the rows of profiles/<config>_fwd_bwd_kernels.md that hold the HBM traffic per launch
 # (the first of several that is found; the local passes are told apart by their template arguments)
 PROFILE_ROW = {"fwd_walk": ("k_fwd<", "k_fwd8<"), "bwd_walk": "k_bwd", "fwd_local": "k_local<", "bwd_local": "k_local<",
-               "bwd_apply": "backward (3 products)", "fwd_apply": "forward (1 product)", "state_reduce": "k_bidir_reduce<"}
+               "bwd_apply": "backward (2 products)", "fwd_apply": "forward (1 product)", "fwd_reduce": "forward (sum)",
+               "bwd_reduce": "backward (sum and dQ)"}
 
 
 def tokens_of_a_launch(B, H, N, steps, launches):
@@ -420,9 +421,9 @@ def copy_reference(args, dev):
 
 
 def bench_bidirectional(args, cfg, dev):
-    """One step = forward + backward of the unmasked attention O = Q (K^T V): per sub-sequence the state
-    reduction on (K, V), then the output product; backward the reduction on (Q, dO), then the three
-    gradient products in one launch."""
+    """One step = forward + backward of the unmasked attention O = Q (K^T V): the state reduction on (K, V), then the
+    output product; backward the reduction on (Q, dO), which produces dQ too, then the products dK, dV in one
+    launch. Up to four sub-sequences share a launch."""
     import numpy as np
     import torch
     from paper_2404_02882_amd import harness, lasp, synth_inputs as si
@@ -462,35 +463,36 @@ def bench_bidirectional(args, cfg, dev):
     for _ in range(args.warmup):
         run()
     if args.eager:
-        lasp.profile_begin(args.steps * 3 * T)
+        lasp.profile_begin(args.steps * 2 * T)
     ms_per_step = timed(run, args.steps)     # the timed region: exactly `steps` steps
     if args.eager:
         kernel_ms, nf, nb = lasp.profile_end()
         eager_ms, graph_ms = ms_per_step, timed(graphed.replay, args.steps)
     else:       # per-kernel HIP events from an eager pass of the same steps (events are not captured in a graph)
-        lasp.profile_begin(args.steps * 3 * T)
+        lasp.profile_begin(args.steps * 2 * T)
         eager_ms = timed(step, args.steps)
         kernel_ms, nf, nb = lasp.profile_end()
         graph_ms = ms_per_step
     tokens_per_s = B * N / (ms_per_step * 1e-3)
 
-    # forward-kind records: 2T state calls and T output calls per step; backward-kind: T calls per step
-    launches = args.steps * T
-    per_launch_ms = {"state_reduce": kernel_ms["fwd"][0] / (2 * launches), "state_sum": kernel_ms["fwd"][1] / (2 * launches),
-                     "fwd_apply": kernel_ms["fwd"][2] / launches, "bwd_apply": kernel_ms["bwd"][2] / launches}
-    assert nf == 3 * launches and nb == launches, (nf, nb)
+    # each pass's records: a reduction and a product launch for every group of sub-sequences
+    launches = nf // 2
+    assert nf == nb and nf % (2 * args.steps) == 0, (nf, nb)
+    per_launch_ms = {"fwd_reduce": kernel_ms["fwd"][0] / launches, "fwd_sum": kernel_ms["fwd"][1] / launches,
+                     "fwd_apply": kernel_ms["fwd"][2] / launches, "bwd_reduce": kernel_ms["bwd"][0] / launches,
+                     "bwd_sum": kernel_ms["bwd"][1] / launches, "bwd_apply": kernel_ms["bwd"][2] / launches}
     esz = 2 if cfg.dtype == "bf16" else 4
-    tok_heads_per_launch = B * H * (N // T)
-    # compulsory HBM bytes per token-head: the reduction reads two tensors; the output product reads q and
-    # writes o; the gradient products read dO, V, K and write dQ, dK, dV
-    alg_bytes = {"state_reduce": 2 * D * esz, "fwd_apply": 2 * D * esz, "bwd_apply": 6 * D * esz}
+    tok_heads_per_launch = tokens_of_a_launch(B, H, N, args.steps, launches)
+    # compulsory HBM bytes per token-head at these sizes: the reductions read two tensors, the backward one writes dQ;
+    # the output product reads q and writes o; the gradient products read V, K and write dK, dV
+    alg_bytes = {"fwd_reduce": 2 * D * esz, "fwd_apply": 2 * D * esz, "bwd_reduce": 3 * D * esz, "bwd_apply": 4 * D * esz}
     dominant = max(alg_bytes, key=lambda n: per_launch_ms[n])
-    dom_bytes = alg_bytes[dominant] * tok_heads_per_launch
+    dom_bytes = int(alg_bytes[dominant] * tok_heads_per_launch)
     achieved = dom_bytes / (per_launch_ms[dominant] * 1e-3) / 1e9
+    traffic, traffic_src = traffic_from_profile(args.config, dominant, launches // args.steps) if args.segments == 0 else (None, None)
     roofline = {"kernel": dominant, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                "traffic": traffic_from_profile(args.config, dominant)[0] if args.segments == 0 else None,
-                "traffic_source": traffic_from_profile(args.config, dominant)[1] if args.segments == 0 else None,
+                "traffic": traffic, "traffic_source": traffic_src,
                 "algorithmic_bytes_per_launch": dom_bytes,
                 "avg_launch_ms": round(per_launch_ms[dominant], 4),
                 "kernel_ms_per_launch": {n: round(x, 4) for n, x in per_launch_ms.items()}}
@@ -525,7 +527,7 @@ def bench_bidirectional(args, cfg, dev):
             "scaling": "weak", "vs_baseline": None, "dtype": cfg.dtype, "data": "synthetic",
             "config": {"workload": f"{cfg.name}: B={B} H={H} N={N} d={D} {cfg.dtype}, T={T} sub-sequence(s), fwd+bwd, "
                                    f"no mask, no decay",
-                       "partial_states_per_head": lasp.bidir_scratch_bytes(seq.shapes[0]) // (B * H * D * D * 4),
+                       "partial_states_per_head": seq.scratch.numel() // (B * H * D * D * 4),
                        "hip_graph": not args.eager, "prewarm_seconds": args.prewarm_seconds},
             "roofline": roofline, "whole_step": extra, "copy_reference": copy, "cpu_baseline": cpu}
     print(json.dumps(line), flush=True)

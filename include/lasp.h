@@ -382,6 +382,21 @@ int lasp_bidir_fwd(const lasp_shape *shape, const void *q, const float *kv, void
 int lasp_bidir_bwd(const lasp_shape *shape, const void *k, const void *v, const void *dout,
                    const float *kv, const float *dkv, void *dq, void *dk, void *dv,
                    void *hip_stream);
+/*
+ * The loops over the T sub-sequences of a sequence as one call each: kv = sum over all of them, then every out
+ * (dkv = sum over all of them, and every dq, dk, dv). shapes: T shapes that differ in N only; the tensors are arrays
+ * of T device pointers, themselves in host memory, not kept. Up to four sub-sequences go through a launch together
+ * (segments = 0; sums are then cut over the tokens of all of them), and dq comes with the sum, which has dO on chip,
+ * where no gradient overlaps an input. scratch: lasp_bidir_seq_scratch_bytes() bytes (0 on invalid shapes).
+ */
+size_t lasp_bidir_seq_scratch_bytes(const lasp_shape *shapes, int32_t T);
+int lasp_bidir_seq_fwd(const lasp_shape *shapes, int32_t T, const void *const *q, const void *const *k,
+                       const void *const *v, float *kv, void *const *out, void *scratch, size_t scratch_bytes,
+                       void *hip_stream);
+int lasp_bidir_seq_bwd(const lasp_shape *shapes, int32_t T, const void *const *q, const void *const *k,
+                       const void *const *v, const void *const *dout, const float *kv, float *dkv,
+                       void *const *dq, void *const *dk, void *const *dv, void *scratch, size_t scratch_bytes,
+                       void *hip_stream);
 
 #ifdef __cplusplus
 }

@@ -6,15 +6,23 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
-#include <initializer_list>
 #include <mutex>
 #include <utility>
 #include <vector>
 
+#include "lasp_checks.h"
 #include "lasp_internal.h"
 #include "lasp_rules.h"
 
 namespace {
+
+using lasp::check_buffers;
+using lasp::elem_bytes;
+using lasp::next_slot;
+using lasp::overlap;
+using lasp::overlap_any;
+using lasp::Span;
+using lasp::Together;
 
 // Segments per head when the caller leaves the choice to the library: about as many workgroups (B*H*segments) as
 // the device has CUs, never more than one segment per tile. A second forward workgroup per CU (512) hides more
@@ -116,8 +124,6 @@ int make_plan(const lasp_shape *s, Pass pass, lasp::Plan *p, bool token = false,
     return LASP_OK;
 }
 
-size_t elem_bytes(int dtype) { return dtype == LASP_F32 ? 4 : 2; }
-
 size_t cache_bytes(const lasp_shape *shape, bool token) {
     lasp::Plan p;
     if (make_plan(shape, kForward, &p, token) != LASP_OK) return 0;
@@ -166,70 +172,6 @@ struct Profiler {
     int used[2] = {0, 0};                       // recorded forward / backward calls
     std::vector<lasp::KernelEvents> slots[2];
 } g_prof;
-
-const lasp::KernelEvents *next_slot(int kind) {
-    if (!g_prof.on || g_prof.used[kind] >= g_prof.cap) return nullptr;
-    return &g_prof.slots[kind][g_prof.used[kind]++];
-}
-
-struct Span {
-    const void *p;
-    size_t n;
-};
-bool overlap(Span a, Span b) {
-    const char *x = (const char *)a.p, *y = (const char *)b.p;
-    return x && y && x < y + b.n && y < x + a.n;
-}
-
-bool overlap_any(Span a, std::initializer_list<Span> others) {
-    for (const Span &x : others)
-        if (overlap(a, x)) return true;
-    return false;
-}
-
-// Outputs must not overlap inputs or each other, and the kernels move data in 16-byte pieces.
-// NULL (an absent optional buffer) passes both checks.
-int check_buffers(std::initializer_list<Span> ins, std::initializer_list<Span> outs) {
-    for (const Span &x : ins)
-        if ((uintptr_t)x.p % 16 != 0) return LASP_ERR_ALIGN;
-    for (const Span &x : outs)
-        if ((uintptr_t)x.p % 16 != 0) return LASP_ERR_ALIGN;
-    for (const Span &o : outs) {
-        for (const Span &i : ins)
-            if (overlap(o, i)) return LASP_ERR_ALIAS;
-        for (const Span &o2 : outs)
-            if (&o != &o2 && overlap(o, o2)) return LASP_ERR_ALIAS;
-    }
-    return LASP_OK;
-}
-
-// Whether sub-sequences can share a launch: no output of one may touch another's buffers (in a loop over them that is the
-// caller's affair: the later call reads what the earlier one wrote, or writes over it).
-class Together {
-    struct Item {
-        const char *begin, *end;
-        bool out;
-    };
-    std::vector<Item> items;
-
-public:
-    void in(const void *p, size_t n) {
-        if (p) items.push_back({(const char *)p, (const char *)p + n, false});
-    }
-    void out(const void *p, size_t n) {
-        if (p) items.push_back({(const char *)p, (const char *)p + n, true});
-    }
-    bool disjoint() {
-        std::sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.begin < b.begin; });
-        const char *any_end = nullptr, *out_end = nullptr;   // ends of what has begun so far
-        for (const Item &x : items) {
-            if (x.begin < out_end || (x.out && x.begin < any_end)) return false;
-            any_end = std::max(any_end, x.end);
-            if (x.out) out_end = std::max(out_end, x.end);
-        }
-        return true;
-    }
-};
 
 template <typename P>
 const P at(const P *list, int t) { return list ? list[t] : nullptr; }
@@ -598,8 +540,17 @@ int bwd_one(const lasp_shape *shape, const void *q, const void *k, const void *v
                          &dv, &dlog_g, &dkv_in, scratch, scratch_bytes, stream});
 }
 
+}  // namespace
+
+namespace lasp {
+
+const KernelEvents *next_slot(int kind) {
+    if (!g_prof.on || g_prof.used[kind] >= g_prof.cap) return nullptr;
+    return &g_prof.slots[kind][g_prof.used[kind]++];
+}
+
 // Bidirectional path: shape rules of the causal path, own K/V head per query head only.
-int make_bidir_plan(const lasp_shape *s, lasp::BidirPlan *p) {
+int make_bidir_plan(const lasp_shape *s, BidirPlan *p) {
     if (!s) return LASP_ERR_NULL;
     if (s->dtype != LASP_F32 && s->dtype != LASP_BF16) return LASP_ERR_DTYPE;
     if (!valid_dims(s)) return LASP_ERR_SHAPE;
@@ -610,13 +561,13 @@ int make_bidir_plan(const lasp_shape *s, lasp::BidirPlan *p) {
     p->N = s->N;
     p->D = s->D;
     p->dtype = s->dtype;
-    const int tile = lasp::bidir_reduce_tile(s->dtype);
+    const int tile = bidir_reduce_tile(s->dtype);
     p->ntiles_r = (s->N + tile - 1) / tile;
     int want = s->segments;
     if (want < 0 || want > p->ntiles_r) return LASP_ERR_SHAPE;
     if (want == 0) {
         const int64_t chains = (int64_t)s->B * s->H;
-        want = (int)((lasp::kBidirTargetSegments + chains - 1) / chains);
+        want = (int)((kBidirTargetSegments + chains - 1) / chains);
         if (want > p->ntiles_r) want = p->ntiles_r;
     }
     p->tiles_per_seg = (p->ntiles_r + want - 1) / want;
@@ -624,11 +575,8 @@ int make_bidir_plan(const lasp_shape *s, lasp::BidirPlan *p) {
     return LASP_OK;
 }
 
-size_t bidir_scratch(const lasp::BidirPlan &p) { return (size_t)p.B * p.H * p.nseg * p.D * p.D * sizeof(float); }
+size_t bidir_scratch(const BidirPlan &p) { return (size_t)p.B * p.H * p.nseg * p.D * p.D * sizeof(float); }
 
-}  // namespace
-
-namespace lasp {
 
 hipError_t allow_dynamic_lds(const void *kernel, size_t bytes) {
     if (bytes <= 65536) return hipSuccess;
@@ -817,19 +765,19 @@ int lasp_seq_bwd(const lasp_shape *shape, int32_t T, const void *const *q, const
 
 size_t lasp_bidir_scratch_bytes(const lasp_shape *shape) {
     lasp::BidirPlan p;
-    return make_bidir_plan(shape, &p) == LASP_OK ? bidir_scratch(p) : 0;
+    return lasp::make_bidir_plan(shape, &p) == LASP_OK ? lasp::bidir_scratch(p) : 0;
 }
 
 int lasp_bidir_state(const lasp_shape *shape, const void *x, const void *y, float *state, int32_t accumulate,
                      void *scratch, size_t scratch_bytes, void *hip_stream) {
     lasp::BidirPlan p;
-    int rc = make_bidir_plan(shape, &p);
+    int rc = lasp::make_bidir_plan(shape, &p);
     if (rc != LASP_OK) return rc;
     if (!x || !y || !state) return LASP_ERR_NULL;
-    if (!scratch || scratch_bytes < bidir_scratch(p)) return LASP_ERR_WORKSPACE;
+    if (!scratch || scratch_bytes < lasp::bidir_scratch(p)) return LASP_ERR_WORKSPACE;
     const size_t tb = (size_t)p.B * p.H * p.N * p.D * elem_bytes(p.dtype);
     const size_t sb = (size_t)p.B * p.H * p.D * p.D * sizeof(float);
-    rc = check_buffers({{x, tb}, {y, tb}}, {{state, sb}, {scratch, bidir_scratch(p)}});
+    rc = check_buffers({{x, tb}, {y, tb}}, {{state, sb}, {scratch, lasp::bidir_scratch(p)}});
     if (rc != LASP_OK) return rc;
     return lasp::launch_bidir_state(p, x, y, state, accumulate != 0, (float *)scratch, (hipStream_t)hip_stream,
                                     next_slot(0)) == hipSuccess ? LASP_OK : LASP_ERR_HIP;
@@ -837,7 +785,7 @@ int lasp_bidir_state(const lasp_shape *shape, const void *x, const void *y, floa
 
 int lasp_bidir_fwd(const lasp_shape *shape, const void *q, const float *kv, void *out, void *hip_stream) {
     lasp::BidirPlan p;
-    int rc = make_bidir_plan(shape, &p);
+    int rc = lasp::make_bidir_plan(shape, &p);
     if (rc != LASP_OK) return rc;
     if (!q || !kv || !out) return LASP_ERR_NULL;
     const size_t tb = (size_t)p.B * p.H * p.N * p.D * elem_bytes(p.dtype);
@@ -851,7 +799,7 @@ int lasp_bidir_fwd(const lasp_shape *shape, const void *q, const float *kv, void
 int lasp_bidir_bwd(const lasp_shape *shape, const void *k, const void *v, const void *dout, const float *kv,
                    const float *dkv, void *dq, void *dk, void *dv, void *hip_stream) {
     lasp::BidirPlan p;
-    int rc = make_bidir_plan(shape, &p);
+    int rc = lasp::make_bidir_plan(shape, &p);
     if (rc != LASP_OK) return rc;
     if (!k || !v || !dout || !kv || !dkv || !dq || !dk || !dv) return LASP_ERR_NULL;
     const size_t tb = (size_t)p.B * p.H * p.N * p.D * elem_bytes(p.dtype);

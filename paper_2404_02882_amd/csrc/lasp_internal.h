@@ -166,13 +166,36 @@ struct BidirOps {
     void *out[3];
     int trans[3];
 };
+// The same over n <= kMaxShards sub-sequences of any lengths (host arrays of n). A sum of the states of all of them:
+struct BidirSums {
+    int n;
+    const int *ntok;
+    const void *const *x, *const *y;
+    float *state;
+    int accumulate;
+    float *part;
+    void *const *dq;    // with y = dO: also dQ = dO kv^T; or null
+    const float *kv;
+};
+// and products of each with the same state.
+struct BidirProducts {
+    int n;
+    const int *ntok;
+    int nops;
+    const void *const *x[3];
+    const float *s[3];
+    void *const *out[3];
+    int trans[3];
+};
 constexpr int kBidirTargetWorkgroups = 512;   // products: two 4-wave workgroups per CU
 constexpr int kBidirTargetSegments = 256;     // reduction: one partial sum per CU (fewer partials to write and add)
 int bidir_reduce_tile(int dtype);
 // events: ev[0]..ev[1] the reduction, ev[1]..ev[2] the sum of the partials
 hipError_t launch_bidir_state(const BidirPlan &p, const void *x, const void *y, float *state, int accumulate, float *part,
                               hipStream_t stream, const KernelEvents *ke);
+hipError_t launch_bidir_sums(const BidirPlan &p, const BidirSums &a, hipStream_t stream, const KernelEvents *ke);
 // events: ev[2]..ev[3] the product kernel
+hipError_t launch_bidir_products(const BidirPlan &p, const BidirProducts &a, hipStream_t stream, const KernelEvents *ke);
 hipError_t launch_bidir_apply(const BidirPlan &p, const BidirOps &ops, int nops, hipStream_t stream, const KernelEvents *ke);
 
 }  // namespace lasp

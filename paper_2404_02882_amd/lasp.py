@@ -104,7 +104,18 @@ def _bind(handle):
     return handle
 
 
-lib = _bind(ctypes.CDLL(LIB_PATH))
+def _bind_bidir_sequence(handle):
+    """The same for the calls of whole bidirectional sequences."""
+    handle.lasp_bidir_seq_scratch_bytes.argtypes = [_sp, ctypes.c_int32]
+    handle.lasp_bidir_seq_scratch_bytes.restype = _sz
+    handle.lasp_bidir_seq_fwd.argtypes = [_sp, ctypes.c_int32] + [_vp] * 6 + [_sz, _vp]
+    handle.lasp_bidir_seq_fwd.restype = ctypes.c_int
+    handle.lasp_bidir_seq_bwd.argtypes = [_sp, ctypes.c_int32] + [_vp] * 10 + [_sz, _vp]
+    handle.lasp_bidir_seq_bwd.restype = ctypes.c_int
+    return handle
+
+
+lib = _bind_bidir_sequence(_bind(ctypes.CDLL(LIB_PATH)))
 
 
 def profile_begin(max_calls: int) -> None:
@@ -372,6 +383,28 @@ def lasp_bidir_bwd(shape: Shape, k, v, dout, kv, dkv, dq, dk, dv, stream=None) -
                             _ptr(dv), _stream(stream))
     if rc != 0:
         raise LaspError(rc, "lasp_bidir_bwd")
+
+
+def bidir_seq_scratch_bytes(shapes, T) -> int:
+    return int(lib.lasp_bidir_seq_scratch_bytes(shapes, T))
+
+
+def lasp_bidir_seq_fwd(shapes, T, q, k, v, kv, out, scratch, stream=None) -> None:
+    """kv = sum over T sub-sequences (shapes: a ctypes array of T, lists of T tensors) of k^T v, every out = q kv; raises
+    LaspError on a non-zero status."""
+    keep, (q, k, v, out) = _tables((q, T), (k, T), (v, T), (out, T))
+    rc = lib.lasp_bidir_seq_fwd(shapes, T, q, k, v, _ptr(kv), out, _ptr(scratch), scratch.numel() * scratch.element_size(), _stream(stream))
+    if rc != 0:
+        raise LaspError(rc, "lasp_bidir_seq_fwd")
+
+
+def lasp_bidir_seq_bwd(shapes, T, q, k, v, dout, kv, dkv, dq, dk, dv, scratch, stream=None) -> None:
+    """dkv = sum over T sub-sequences of q^T dout, and every dq, dk, dv; raises LaspError on a non-zero status."""
+    keep, (q, k, v, dout, dq, dk, dv) = _tables((q, T), (k, T), (v, T), (dout, T), (dq, T), (dk, T), (dv, T))
+    rc = lib.lasp_bidir_seq_bwd(shapes, T, q, k, v, dout, _ptr(kv), _ptr(dkv), dq, dk, dv, _ptr(scratch),
+                                scratch.numel() * scratch.element_size(), _stream(stream))
+    if rc != 0:
+        raise LaspError(rc, "lasp_bidir_seq_bwd")
 
 
 class Workspace:

@@ -161,37 +161,34 @@ class GraphedStep:
 class BidirSequence:
     """Bidirectional (unmasked) attention O = Q (K^T V) over sub-sequences of any lengths.
 
-    The state is a sum over every token, so nothing is handed from shard to shard: a first loop adds
-    each shard's K^T V into `kv` (on several devices: their partial states summed across them), a
-    second loop computes each shard's output from the complete state. Backward likewise with
-    dKV = Q^T dO. All buffers are allocated up front; the calls only enqueue kernels.
+    The state is a sum over every token, so nothing is handed from shard to shard: every shard's K^T V is
+    added into `kv` (on several devices: their partial states summed across them), then each shard's output
+    is computed from the complete state. Backward likewise with dKV = Q^T dO. The library takes several
+    shards through a launch (lasp_bidir_seq_*). All buffers are allocated up front; the calls only enqueue
+    kernels.
     """
 
     def __init__(self, B, H, lengths, D, chunk, dtype: torch.dtype, segments=0, device="cuda"):
         self.lengths = [int(n) for n in lengths]
+        self.T = len(self.lengths)
         self.shapes = [lasp.make_shape(B, H, n, D, chunk, dtype, segments) for n in self.lengths]
-        need = 0
         for shp in self.shapes:
-            nbytes = lasp.bidir_scratch_bytes(shp)
-            if nbytes == 0:
+            if lasp.bidir_scratch_bytes(shp) == 0:
                 raise lasp.LaspError(lasp.check_shape(shp) or 2, "BidirSequence")
-            need = max(need, nbytes)
+        self._shapes = (lasp.Shape * self.T)(*self.shapes)
+        need = lasp.bidir_seq_scratch_bytes(self._shapes, self.T) if self.T else 0
         self.scratch = torch.empty(need, dtype=torch.uint8, device=device)
         st = dict(dtype=torch.float32, device=device)
         self.kv = torch.empty(B, H, D, D, **st)
         self.dkv = torch.empty(B, H, D, D, **st)
 
     def forward(self, q: List[torch.Tensor], k, v, out: List[torch.Tensor]) -> torch.Tensor:
-        for t, shp in enumerate(self.shapes):
-            lasp.lasp_bidir_state(shp, k[t], v[t], self.kv, t > 0, self.scratch)
-        for t, shp in enumerate(self.shapes):
-            lasp.lasp_bidir_fwd(shp, q[t], self.kv, out[t])
+        if self.T:
+            lasp.lasp_bidir_seq_fwd(self._shapes, self.T, q, k, v, self.kv, out, self.scratch)
         return self.kv
 
     def backward(self, q, k, v, dout, dq, dk, dv) -> torch.Tensor:
         """Needs the state `kv` of the forward pass."""
-        for t, shp in enumerate(self.shapes):
-            lasp.lasp_bidir_state(shp, q[t], dout[t], self.dkv, t > 0, self.scratch)
-        for t, shp in enumerate(self.shapes):
-            lasp.lasp_bidir_bwd(shp, k[t], v[t], dout[t], self.kv, self.dkv, dq[t], dk[t], dv[t])
+        if self.T:
+            lasp.lasp_bidir_seq_bwd(self._shapes, self.T, q, k, v, dout, self.kv, self.dkv, dq, dk, dv, self.scratch)
         return self.dkv

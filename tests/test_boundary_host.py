@@ -367,6 +367,35 @@ def test_bidir_rejects_before_launch(L):
     assert bwd(*a) == 2
 
 
+def test_bidir_sequence_rejects_before_launch(L):
+    shapes = (L.Shape * 2)(L.make_shape(1, 2, 100, 64, 64, "bf16"), L.make_shape(1, 2, 70, 64, 64, "bf16"))
+    need = L.bidir_seq_scratch_bytes(shapes, 2)
+    assert need == 4 * 2 * 64 * 64 * 4            # two tiles each
+    bad = (L.Shape * 2)(shapes[0], L.make_shape(1, 2, 70, 128, 64, "bf16"))
+    assert L.bidir_seq_scratch_bytes(bad, 2) == 0 and L.bidir_seq_scratch_bytes(shapes, 0) == 0
+    names = ["q", "k", "v", "do", "out", "dq", "dk", "dv"]
+    at = {n: [_fake(1 + 2 * i).value, _fake(2 + 2 * i).value] for i, n in enumerate(names)}
+    kv, dkv, scr = _fake(20), _fake(21), _fake(22)
+
+    def call(fn, shp=shapes, T=2, kv=kv, dkv=dkv, scr=scr, size=need, **moved):
+        a = dict(at, **moved)
+        t = lambda n: (ctypes.c_size_t * 2)(*[x or 0 for x in a[n]])   # noqa: E731
+        if fn == "fwd":
+            return L.lib.lasp_bidir_seq_fwd(shp, T, t("q"), t("k"), t("v"), kv, t("out"), scr, size, None)
+        return L.lib.lasp_bidir_seq_bwd(shp, T, t("q"), t("k"), t("v"), t("do"), kv, dkv, t("dq"), t("dk"), t("dv"), scr, size, None)
+
+    for fn, reads, writes in (("fwd", "q k v", "out"), ("bwd", "q k v do", "dq dk dv")):
+        for n in (reads + " " + writes).split():
+            assert call(fn, **{n: [at[n][0], None]}) == 1, n
+            assert call(fn, **{n: [at[n][0], at[n][1] + 2]}) == 8, n
+        for n in writes.split():
+            assert call(fn, **{n: [at[n][0], kv.value]}) == 6, n
+        assert call(fn, kv=None) == 1 and call(fn, scr=None) == 5 and call(fn, size=need - 1) == 5
+        assert call(fn, shp=bad) == 2 and call(fn, T=0) == 2
+    assert call("bwd", dkv=None) == 1 and call("bwd", dkv=scr) == 6
+    assert call("bwd", dq=[at["do"][0], at["dq"][1]]) == 6 and call("bwd", dv=at["dk"]) == 6
+
+
 # ---------------------------------------------------------------- key and value dimensions that differ
 def test_value_dimension_shapes_and_sizes(L):
     base = dict(B=1, H=2, N=256, D=64, chunk=64, dtype="bf16")

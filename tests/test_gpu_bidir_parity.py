@@ -135,3 +135,33 @@ def test_b3_full_size(gpu, oracle):
         emax, efro = harness.rel_errors(got[nm][b, h, s], r)
         say(f"  b3 rows {nm:4s} max-rel {emax:.3e} fro-rel {efro:.3e}")
         assert emax <= TOL["bf16"] and efro <= TOL["bf16"], nm
+
+
+# Sub-sequences that share a launch (tiles numbered over all of them; five: a group of four and one), the gradient of q with the
+# sum over (Q, dO) or apart from it (d=128, one tile a workgroup), lengths below and above a tile.
+@pytest.mark.parametrize("dtype,D,lengths", [("bf16", 128, [1, 63, 64, 65, 130]), ("bf16", 128, [4500, 129]), ("bf16", 64, [64, 1, 127, 200]),
+                                             ("f32", 128, [33, 1, 31]), ("f32", 64, [70, 32, 5, 64, 31])])
+def test_shared_launches(gpu, oracle, dtype, D, lengths):
+    harness, lasp, si = gpu
+    cfg = si.Config("bshare", B=1, H=3, N=sum(lengths), D=D, chunk=64, dtype=dtype, seed=640 + D + len(lengths), decay="one", bidirectional=True)
+    say(f"case bidir shared dtype={dtype} D={D} lengths={lengths}")
+    inp = si.make_inputs(cfg)
+    compare(harness, harness.run_gpu_bidir(inp, lengths=lengths), oracle_all(oracle, inp), TOL[dtype], "bshare")
+
+
+def test_gradients_in_place(gpu):
+    """dq, dk, dv that take the places of q and of another sub-sequence's k, v: as with buffers of their own."""
+    import torch
+    from paper_2404_02882_amd.sequence import BidirSequence
+    g = torch.Generator(device="cuda").manual_seed(5)
+    new = lambda: [torch.randn(1, 2, n, 64, generator=g, device="cuda").bfloat16() for n in (200, 200)]   # noqa: E731
+    q, k, v, do = new(), new(), new(), new()
+    seq = BidirSequence(1, 2, [200, 200], 64, 64, torch.bfloat16)
+    out, dq, dk, dv = ([torch.empty_like(x) for x in q] for _ in range(4))
+    seq.forward(q, k, v, out)
+    seq.backward(q, k, v, do, dq, dk, dv)
+    want = [x.clone() for x in dq + dk + dv]
+    kept = k[0].clone()
+    seq.backward(q, k, v, do, q, [dk[0], k[0]], [dv[0], v[0]])   # (the second sub-sequence's dk, dv over the first's k, v)
+    assert all(torch.equal(a, b) for a, b in zip(q + [dk[0], k[0], dv[0], v[0]], want))
+    assert not torch.equal(kept, k[0])
