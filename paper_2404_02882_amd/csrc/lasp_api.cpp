@@ -63,11 +63,13 @@ int auto_segments(const lasp::Plan &p, Pass pass, int64_t chains) {
     // count is rounded up: 100 heads x 8000 tokens, five / six segments 152 / 142 us.
     if (p.dtype == LASP_BF16 && p.D == 64 && p.token && pass == kForward) round = chains - 1;
     int want = (int)((target + round) / chains);
-    // Backward by tiles at d=64, two workgroups a CU: 48 heads x 5056 tokens, 5 / 6 / 10 segments 79 / 90 / 67 us,
-    // 100 x 5056, 2 / 3 / 5 174 / 169 / 140; past 32 segments the scan costs more (8 x 5056, 32 / 64 28.3 / 31.1).
-    if (p.dtype == LASP_BF16 && p.D == 64 && pass == kBackward && p.cache_tiles == 1) {
-        want = (int)(kTargetWorkgroupsLatencyBound / chains);
-        if (want > 32) want = 32;
+    // Backward at d=64, two workgroups a CU. By tiles: 48 heads x 5056 tokens, 5 / 6 / 10 segments 79 / 90 / 67 us,
+    // 100 x 5056, 2 / 3 / 5 174 / 169 / 140; past 32 segments the scan costs more (8 x 5056, 32 / 64 28.3 / 31.1). In pairs, from two pairs a segment
+    // on, one / two workgroups a CU: 16 heads x 32768 tokens 258 / 240 us, 32 x 4096 86.3 / 82.0, 128 x 1024 78.8 / 72.9, but (one pair a
+    // segment) 16 x 4 x 1024 in shared launches 62.1 / 62.8, and 128 segments of few heads stay (2 x 32768, 32 / 128 133 / 95).
+    if (p.dtype == LASP_BF16 && p.D == 64 && pass == kBackward) {
+        const int two = (int)std::min<int64_t>(kTargetWorkgroupsLatencyBound / chains, 32);
+        want = p.cache_tiles == 1 ? two : std::max(want, std::min(two, p.ntiles / 4));
     }
     if (want > p.ntiles) want = p.ntiles;
     return want < 1 ? 1 : want;

@@ -97,16 +97,20 @@ DEVI Lane fresh_lane() {
     return Lane(t);
 }
 
-// LDS layout of bfloat16 tiles with 128-element rows (256 bytes = all 64 banks):
-// no padding; the 16-byte chunk c of row `row` is stored at chunk c ^ swz16(row).
-// A row stride of exactly 128 elements selects this layout in the loaders below.
-// It is conflict-free for 16 lanes reading one chunk of 16 consecutive rows, for
-// the four-row by two-chunk blocks of a transposing read, and for whole-row stores.
-constexpr int kSwzLd = 128;
-DEVI int swz16(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+// LDS layouts of bfloat16 tiles without padding: the 16-byte chunk c of row `row` is stored at chunk c ^ swz(row). Rows of 128
+// elements (256 bytes = all 64 banks), and 32 x 32 blocks; a row stride of kSwzLd or kBlockLd selects them in the loaders
+// below. Both are conflict-free for 16 lanes reading one chunk of 16 consecutive rows, for the four-row by two-chunk blocks of a
+// transposing read, and for whole-row stores; the pattern repeats every 16 rows.
+constexpr int kSwzLd = 128, kBlockLd = -32;
+constexpr bool swizzled(int ld) { return ld == kSwzLd || ld == kBlockLd; }
+constexpr int row_elems(int ld) { return ld < 0 ? -ld : ld; }
+DEVI int swz(int ld, int row) {
+    if (ld == kSwzLd) return ((row & 7) << 1) | ((row >> 3) & 1);
+    return (row >> 2) & 3;   // four rows share the banks
+}
 // element offset of (row, col) in a tile with row stride ld
 DEVI int lds_off(int ld, int row, int col) {
-    return ld == kSwzLd ? row * kSwzLd + ((((col >> 3) ^ swz16(row))) << 3) + (col & 7) : row * ld + col;
+    return swizzled(ld) ? row * row_elems(ld) + ((((col >> 3) ^ swz(ld, row))) << 3) + (col & 7) : row * ld + col;
 }
 template <typename T, int D>
 constexpr int tile_ld() { return (sizeof(T) == 2 && D == 128) ? kSwzLd : D + (sizeof(T) == 2 ? 24 : 4); }
@@ -159,9 +163,9 @@ struct Elem<bf16_t> {
     static DEVI f32x16 mfma(frag a, frag b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
     // row0 is a multiple of 16 and k0 a multiple of 16 wherever these are called.
     static DEVI frag ld_kc(const Lane &ln, const bf16_t *X, int ld, int row0, int k0) {
-        if (ld == kSwzLd) {
-            const int t = ln.h ^ swz16(ln.r);  // lane constant; chunk (k0/8 + h) ^ swz = (k0/8) ^ t since k0/8 is even
-            return *(const bf16x8 *)(X + (row0 + ln.r) * kSwzLd + (((k0 >> 3) ^ t) << 3));
+        if (swizzled(ld)) {
+            const int t = ln.h ^ swz(ld, ln.r);  // lane constant; chunk (k0/8 + h) ^ swz = (k0/8) ^ t since k0/8 is even
+            return *(const bf16x8 *)(X + (row0 + ln.r) * row_elems(ld) + (((k0 >> 3) ^ t) << 3));
         }
         return *(const bf16x8 *)(X + (row0 + ln.r) * ld + k0 + 8 * ln.h);
     }
@@ -173,12 +177,12 @@ struct Elem<bf16_t> {
         const int l16 = l & 15;
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         const bf16_t *plo, *phi;
-        if (ld == kSwzLd) {
+        if (swizzled(ld)) {
             const int rowl = 8 * ln.h + (l16 >> 2);                    // row inside the 16-row group (k0 % 16 == 0)
             const int c = (col0 >> 3) + 2 * ((l >> 4) & 1) + ((l16 & 3) >> 1);  // chunk of this lane's 8-byte piece
             const int e = 4 * (l16 & 1);                                // element inside the chunk
-            plo = X + (k0 + rowl) * kSwzLd + ((c ^ swz16(rowl)) << 3) + e;
-            phi = X + (k0 + rowl + 4) * kSwzLd + ((c ^ swz16(rowl + 4)) << 3) + e;
+            plo = X + (k0 + rowl) * row_elems(ld) + ((c ^ swz(ld, rowl)) << 3) + e;
+            phi = X + (k0 + rowl + 4) * row_elems(ld) + ((c ^ swz(ld, rowl + 4)) << 3) + e;
         } else {
             plo = X + (k0 + 8 * ln.h + (l16 >> 2)) * ld + col0 + 16 * ((l >> 4) & 1) + 4 * (l16 & 3);
             phi = plo + 4 * ld;
@@ -192,9 +196,9 @@ struct Elem<bf16_t> {
     }
     static DEVI frag ld_kp(const Lane &ln, const bf16_t *X, int ld, int row0, int kb, int m) {
         union { struct { bf16x4 a, b; } s; bf16x8 v; } u;
-        if (ld == kSwzLd) {
-            const int sw = swz16(ln.r), c = (kb >> 3) + 2 * m;
-            const bf16_t *p = X + (row0 + ln.r) * kSwzLd + 4 * ln.h;
+        if (swizzled(ld)) {
+            const int sw = swz(ld, ln.r), c = (kb >> 3) + 2 * m;
+            const bf16_t *p = X + (row0 + ln.r) * row_elems(ld) + 4 * ln.h;
             u.s.a = *(const bf16x4 *)(p + ((c ^ sw) << 3));
             u.s.b = *(const bf16x4 *)(p + (((c + 1) ^ sw) << 3));
         } else {
@@ -496,12 +500,12 @@ struct TileMover {
             r[i] = chunk * EPV < W && row0 + i * (NT / VPR) >= skip ? gload<u32x4, STREAM>(g + i * (NT / VPR) * W, lo) : u32x4{0, 0, 0, 0};
     }
     DEVI void store(T *s, int ld) const {
-        if (sizeof(T) == 2 && ld == kSwzLd) {
-            static_assert(sizeof(T) != 2 || COLS != 128 || (NT / VPR) % 16 == 0, "row step must keep row % 16");
+        if (sizeof(T) == 2 && swizzled(ld)) {
+            static_assert(sizeof(T) != 2 || (NT / VPR) % 16 == 0, "row step must keep row % 16");
             const int row = threadIdx.x / VPR, chunk = threadIdx.x % VPR;
-            const unsigned lo = row * kSwzLd + ((chunk ^ swz16(row)) << 3);
+            const unsigned lo = row * COLS + ((chunk ^ swz(ld, row)) << 3);
 #pragma unroll
-            for (int i = 0; i < NV; ++i) *(u32x4 *)(s + i * (NT / VPR) * kSwzLd + lo) = r[i];
+            for (int i = 0; i < NV; ++i) *(u32x4 *)(s + i * (NT / VPR) * COLS + lo) = r[i];
             return;
         }
         const unsigned lo = lane_off(ld);
@@ -1028,22 +1032,21 @@ DEVI void decay_and_add(const Lane &ln, f32x16 (&st)[DB], float decay, const bf1
                                 });
 }
 
-// Masked score tile (Alg. 2 / Alg. 3 mask M): the wave holds the transposed
+// Masked score block (Alg. 2 / Alg. 3 mask M): the wave holds the transposed
 // 32x32 block ST[j][i] = sum_d A[j][d] B[i][d] in accumulator layout (row = key j,
 // column = query i), multiplies by lambda^(i-j) for i >= j (zero above the
 // diagonal) and writes it as P[i][j] so that four consecutive keys land in one
-// store.
+// store. blk: row 32 ib, column 32 jb of the tile.
 template <typename T, int LDP, typename DK>
-DEVI void store_masked_scores(const Lane &ln, bf16_t *sP, const f32x16 &acc, int jb, int ib, const DK &dec) {
+DEVI void store_masked_scores(const Lane &ln, bf16_t *blk, const f32x16 &acc, int jb, int ib, const DK &dec) {
     static_assert(WalkElem<T>::PLANES == 1, "float data: score_block16");
-    const int iq = 32 * ib + ln.r;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        const int j0 = 32 * jb + 8 * g + 4 * ln.h;
+        const int j = 8 * g + 4 * ln.h;
         float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = dec.masked(acc[4 * g + e], iq, j0 + e);
-        WalkElem<T>::st4(sP + iq * LDP + j0, x[0], x[1], x[2], x[3]);
+        for (int e = 0; e < 4; ++e) x[e] = dec.masked(acc[4 * g + e], 32 * ib + ln.r, 32 * jb + j + e);
+        WalkElem<T>::st4(blk + lds_off(LDP, ln.r, j), x[0], x[1], x[2], x[3]);
     }
 }
 
@@ -1103,7 +1106,7 @@ DEVI void masked_scores(const Lane &ln, bf16_t *sP, const bf16_t *sA, const bf16
 #pragma unroll
                 for (int k0 = 0; k0 < D; k0 += E::KSTEP)
                     acc = E::mfma(E::ld_kc(ln, sA, LDD, 32 * jb, k0), E::ld_kc(ln, sB, LDD, 32 * ib, k0), acc);
-                store_masked_scores<T, LDP>(ln, sP, acc, jb, ib, dec);
+                store_masked_scores<T, LDP>(ln, sP + 32 * ib * LDP + 32 * jb, acc, jb, ib, dec);
             }
     }
 }

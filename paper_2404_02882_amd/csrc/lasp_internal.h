@@ -54,9 +54,14 @@ struct BwdShards {
     Offsets q, k, v, dout, cache, dq, dk, dv, dkv_in, yn, rstd;
 };
 
+#ifdef __HIPCC__
+#define LASP_BOTH __host__ __device__
+#else
+#define LASP_BOTH
+#endif
 // The pieces the local pass cuts the segments of a launch into, one workgroup and one state of the scratch each: whole
-// segments, or `n` pieces of each where whole ones would leave most of the device idle (local_pieces in lasp_rules.h). Pieces
-// are numbered over all sub-sequences of the launch.
+// segments, or two pieces of each where whole ones would leave most of the device idle (local_pieces in lasp_rules.h). Pieces
+// are numbered over all sub-sequences of the launch. (Kernels work this out: arguments cost a launch time.)
 struct Pieces {
     int n;           // pieces per segment
     int tiles;       // tiles of a piece (the last of a sub-sequence may be shorter)
@@ -64,6 +69,10 @@ struct Pieces {
     int first, end;  // the pieces that another segment's state depends on: the local pass sums these
     int base;        // the piece whose state is the scratch's first (of a chain)
     int slots;       // states of a chain in the scratch
+    LASP_BOTH Pieces(bool bwd, bool two, int shards, int nseg, int tiles_per_seg, int ntiles)
+        : n(two ? 2 : 1), tiles(two ? tiles_per_seg / 2 : tiles_per_seg),
+          per_shard(two ? 2 * nseg - (ntiles - (nseg - 1) * tiles_per_seg > tiles ? 0 : 1) : nseg), first(bwd ? n : 0),
+          end(shards * per_shard - (bwd ? 0 : per_shard - (nseg - 1) * n)), base(two ? first : 0), slots(two ? end - first : shards * nseg) {}
 };
 
 struct FwdArgs {

@@ -56,7 +56,7 @@ DEVI ptrdiff_t kv_shift(int chain, int H, int kvdiv, int ntok, int width) {
 // Where a walk takes its segment's start state from: a state that the forward pass kept (float dQ), its slot as k_scan left
 // it, the boundary state carried over the local states of the segments before (start_state), or the boundary state taken
 // through the tiles of those segments by the workgroup itself, which needs no local pass and no scratch.
-enum Start { kKept = -1, kScanned = 0, kCarried = 1, kOwn = 2 };
+enum Start { kKept = -1, kScanned = 0, kCarried = 1, kOwn = 2, kCarriedPieces = 3 };   // (the last: over two pieces a segment)
 // First element of tile `t` (CT tokens) of a chain in a token tensor whose rows hold `width` elements.
 DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
     return ((size_t)chain * ntok + (size_t)t * CT) * width;
@@ -81,8 +81,8 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM, int WX, int WY, typename SH>
 __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
-                                                  float *__restrict__ seglog, int H, int ntiles, Pieces pc,
-                                                  int ntok, int kvdiv, const T *__restrict__ yn,
+                                                  float *__restrict__ seglog, int H, int ntiles, int segs,
+                                                  int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn,
                                                   const float *__restrict__ rstd, SH sh) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
     using E = WalkElem<T>;
@@ -94,6 +94,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 
     constexpr bool SHARED = is_shared<SH>;
     const int chain = blockIdx.y, shard = SHARED ? blockIdx.z : 0;
+    const Pieces pc(BWD, segs < 0, SHARED ? gridDim.z : 1, segs < 0 ? -segs : segs, tiles_per_seg, ntiles);   // (segs < 0: two pieces a segment)
     const int seg = blockIdx.x + (SHARED ? 0 : pc.first), piece = shard * pc.per_shard + seg;
     if (SHARED && (piece < pc.first || piece >= pc.end)) return;   // (of several sub-sequences: the grid has them all)
     const size_t slot = (size_t)chain * pc.slots + (piece - pc.base);
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
                                                 const T *__restrict__ V, const float *__restrict__ decay,
                                                 T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
-                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, Pieces pc,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry,
                                                 int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, const T *__restrict__ yn,
                                                 const float *__restrict__ rstd, const T *__restrict__ q_rows, float *__restrict__ rtok,
@@ -416,11 +417,12 @@ __global__ __launch_bounds__(D * 2, (sizeof(T) == 4 && D == 128 && ROLE == kDq &
             if constexpr (DQ) state_load_t_w<D, WV, WK>(ln, s, g, w);   // stored [d_k][d_v] = [WV][WK]
             else state_load_w<D, WK, WV>(ln, s, g, w);
         };
-        if (carry > 0)
+        if (carry > 0) {
+            const Pieces pc(false, !OWN && carry == kCarriedPieces, shards, nseg, tiles_per_seg, ntiles);
             start_state<false, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, kv_in ? kv_in + (size_t)chain * WK * WV : nullptr,
                                SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
                                OWN && carry == kOwn ? 0 : piece_of<false>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
-        else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
+        } else load(st, states + (size_t)(kept ? seg : slot0) * WK * WV);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     typename E::frag vf[NKS];
@@ -652,7 +654,7 @@ template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, Role RO
 __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                 const float *__restrict__ decay, T *__restrict__ O, float *__restrict__ kv_out,
                                                 T *__restrict__ cache, int cache_tiles, const float *__restrict__ scratch,
-                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, Pieces pc, int H,
+                                                const float *__restrict__ kv_in, const float *__restrict__ seglog, int carry, int H,
                                                 int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                 float *__restrict__ rstd_out, float eps, float *__restrict__ kv_copy, SH sh) {
     using E = WalkElem<T>;
@@ -713,11 +715,12 @@ __global__ __launch_bounds__(D * 4) void k_fwd8(const T *__restrict__ Q, const T
     {
         const float *states = scratch + (size_t)chain * nslots * D * D;
         auto load = [&](f32x16(&s)[HB], const float *p) { state_load_w<D, D, D, HB>(ln, s, p + a0 * D, w); };
-        if (carry)
+        if (carry) {
+            const Pieces pc(false, !OWN && carry == kCarriedPieces, shards, nseg, tiles_per_seg, ntiles);
             start_state<false, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * D * D, kv_in ? kv_in + (size_t)chain * D * D : nullptr,
                                SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
                                OWN && carry == kOwn ? 0 : piece_of<false>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, D * D, load);
-        else load(st, states + (size_t)slot0 * D * D);
+        } else load(st, states + (size_t)slot0 * D * D);
     }
     const auto dec = DecaySel<TOKEN, T, CT>::make(pw, decay, chain, H);
     for (int t = 0; t < own; ++t) {   // the state alone (all of these tiles are whole)
@@ -879,7 +882,7 @@ template <typename T, int CT, int D, bool TOKEN, bool RAGGED, bool NORM, int WK,
 __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                                                  const T *__restrict__ dO, const float *__restrict__ decay, T *__restrict__ dK,
                                                  T *__restrict__ dV, float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                 const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry, Pieces pc,
+                                                 const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                  float *__restrict__ rtok, int H, int ntiles, int nseg, int tiles_per_seg,
                                                  int ntok, int kvdiv, const T *__restrict__ yn, const float *__restrict__ rstd,
                                                  float *__restrict__ dkv_copy, SH sh) {
@@ -977,11 +980,12 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
             if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
-        if (carry)
+        if (carry) {
+            const Pieces pc(true, !OWN && carry == kCarriedPieces, shards, nseg, tiles_per_seg, ntiles);
             start_state<true, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
                               SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
                               OWN && carry == kOwn ? pc.per_shard * shards - 1 : piece_of<true>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
-        else load(st, states + (size_t)slot0 * WK * WV);
+        } else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
     for (int t = ntiles - 1; t >= ntiles - own; --t) {
@@ -1114,16 +1118,25 @@ __global__ __launch_bounds__(D * 4) void k_bwdkv(const T *__restrict__ Q, const 
 // role, so that less code is fetched for a single tile.
 // ---------------------------------------------------------------------------
 enum BwdWalk { kPairs, kTiles, kHalves };
-template <typename T, int CT, int D, bool BY_TILES = false>
+template <typename T, int CT, int D, BwdWalk MODE = kPairs>
 struct Bwd8pSmem {
-    static constexpr int LDD = walk_ld<T, D>(), LDP = CT + WalkElem<T>::PAD;
+    static constexpr bool BY_TILES = MODE == kTiles;
+    // d = 64, in pairs: of the score tiles only the 32x32 blocks on and below the diagonal, and all four of the cross tile; the
+    // cached state in registers (each wave reads its own rows only). The space (108 -> 79 KB) lets a second workgroup onto the
+    // CU, which runs while one waits at a barrier: steps 16 heads x 32768 tokens 257 -> 237 us, 32 x 8192 136 -> 126, 128 x 2048
+    // 127 -> 115. (Unpadded rows of 64 elements in swizzled order instead of 72: 15 % more vector instructions, 5 % slower.)
+    static constexpr bool BLOCKS = D == 64 && MODE == kPairs;
+    static constexpr int LDD = BLOCKS ? 72 : walk_ld<T, D>(), LDP = BLOCKS ? kBlockLd : CT + WalkElem<T>::PAD;
     static constexpr size_t TILE = (size_t)CT * LDD * sizeof(T);
+    static constexpr int P_ELEMS = BLOCKS ? 3 * 1024 : CT * LDP, X_ELEMS = BY_TILES ? 0 : BLOCKS ? 4 * 1024 : CT * LDP;
     static constexpr size_t P_OFF = (BY_TILES ? 4 : 6) * TILE;
-    static constexpr size_t C_OFF = P_OFF + (BY_TILES ? 2 : 3) * (size_t)CT * LDP * sizeof(T);   // S, dS and the cross tile dS(O x E)
-    static constexpr size_t PW_OFF = C_OFF + (size_t)D * LDD * sizeof(T);
+    static constexpr size_t C_OFF = P_OFF + (2 * (size_t)P_ELEMS + X_ELEMS) * sizeof(T);   // S, dS and the cross tile dS(O x E)
+    // block of keys jb at queries ib
+    static DEVI T *block(T *tile, int ib, int jb) { return tile + (BLOCKS ? 1024 * (ib ? 1 + jb : 3 * jb) : 32 * ib * LDP + 32 * jb); }
+    static constexpr size_t PW_OFF = C_OFF + (BLOCKS ? 0 : (size_t)D * LDD * sizeof(T));
     // decay tables of the O tile and of the E tile, then one row of per-token partial sums per wave
     static constexpr int TABLES = (BY_TILES ? 1 : 2) * 3 * CT;
-    static constexpr size_t TOTAL = PW_OFF + (TABLES + 4 + 8 * CT) * sizeof(float);
+    static constexpr size_t TOTAL = PW_OFF + (TABLES + 4 + D / 16 * CT) * sizeof(float);
 };
 
 // WK, WV: elements per row of Q, K, dQ, dK and of V, dO, dV in memory (<= D; see k_local).
@@ -1133,7 +1146,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                                                   const float *__restrict__ decay, const T *__restrict__ cache,
                                                   T *__restrict__ dQ, T *__restrict__ dK, T *__restrict__ dV,
                                                   float *__restrict__ dkv_in, const float *__restrict__ scratch,
-                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry, Pieces pc,
+                                                  const float *__restrict__ dkv_out, const float *__restrict__ seglog, int carry,
                                                   float *__restrict__ rtok,
                                                   int H, int ntiles, int nseg, int tiles_per_seg, int ntok, int kvdiv,
                                                   const T *__restrict__ yn, const float *__restrict__ rstd, float *__restrict__ dkv_copy,
@@ -1141,7 +1154,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     using E = WalkElem<T>;
     using F = typename E::frag;
     constexpr bool BY_TILES = MODE == kTiles, HALVES = MODE == kHalves;
-    using SM = Bwd8pSmem<T, CT, D, BY_TILES>;
+    using SM = Bwd8pSmem<T, CT, D, MODE>;
     static_assert(CT == 64, "two 32-token blocks per tile");
     static_assert(!is_own<SH> || MODE != kPairs, "in pairs: from states in the scratch");
     static_assert(RAGGED || MODE == kPairs, "one by one: one instance for any number of tiles and any length of the last");
@@ -1155,8 +1168,8 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     T *sVE = BY_TILES ? sVO : sQ + CT * LDD;    // V of the E tile
     T *sKE = BY_TILES ? sKO : sVE + CT * LDD;   // K of the E tile
     T *sS = (T *)(smem + SM::P_OFF);
-    T *sDS = sS + CT * LDP;
-    T *sDX = sDS + CT * LDP;       // masked dS between the O tile's queries and the E tile's keys
+    T *sDS = sS + SM::P_ELEMS;
+    T *sDX = sDS + SM::P_ELEMS;    // masked dS between the O tile's queries and the E tile's keys
     T *sC = (T *)(smem + SM::C_OFF);
     float *pw = (float *)(smem + SM::PW_OFF);
 
@@ -1195,6 +1208,8 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     auto voff = [&](int t) { return tile_off(chain, ntok, t, CT, WV); };
     TileMover<T, CT, D, NT> mvO, moX, mkO, mqX, mvE, mkE;   // moX / mqX carry dO, Q of the O tile, then of the E tile
     TileMover<T, D, D, NT> mc;                               // cached state at the start of the E tile
+    constexpr bool C_REGS = SM::BLOCKS;                      // (or its fragments: the tile's in use, and the next)
+    F cf[C_REGS ? NKD : 1], cnext[C_REGS ? NKD : 1];
     const T *ctile = cache + (size_t)chain * (BY_TILES ? ntiles : (ntiles + 1) / 2) * WK * WV;   // [WK][WV] per slot
     // With a decay per token (`decay` = log g, [chain][token]) the O and the E tile have their own
     // tables; with one lambda per head both names refer to the same table.
@@ -1227,6 +1242,23 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
     };
     NormTile<T, CT, D, NT, WV> mnX;  // NORM: partner of moX (dO is dY; see NormTile)
     const float *rstd_c = rstd + (size_t)chain * ntok;
+    auto load_c = [&](int slot) __attribute__((always_inline)) {
+        const T *c = ctile + (size_t)slot * WK * WV;
+        if constexpr (C_REGS) {
+#pragma unroll
+            for (int ks = 0; ks < NKD; ++ks) cnext[ks] = gload<F>(c + 32 * w * WV + ks * E::KSTEP, (ln.r * WV + 8 * ln.h) * sizeof(T));
+        } else {
+            mc.template load_w<WV>(c, WK);   // rows and columns of padding read as zero
+        }
+    };
+    auto store_c = [&]() __attribute__((always_inline)) {
+        if constexpr (C_REGS) {
+#pragma unroll
+            for (int ks = 0; ks < NKD; ++ks) cf[ks] = cnext[ks];
+        } else {
+            mc.store(sC, LDD);
+        }
+    };
     // The requests for a pair come in two parts. K and V of both tiles go into registers that are idle
     // from the top of an iteration on, so inside the loop they are issued a whole tile early (during
     // the O tile of the pair before); dO, Q of the O tile and the cached state follow once the E tile
@@ -1237,7 +1269,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         mkO.template load_w<WK>(K + koff(tE + 1), nvalid(tE + 1));
         mvE.template load_w<WV>(V + voff(tE), nvalid(tE));
         mkE.template load_w<WK>(K + koff(tE), nvalid(tE));
-        mc.template load_w<WV>(ctile + (size_t)(tE / 2) * WK * WV, WK);   // rows and columns of padding read as zero
+        if constexpr (!C_REGS) load_c(tE / 2);
     };
     auto load_pair_rest = [&](int tE) {
         const int nvO = nvalid(tE + 1);
@@ -1250,6 +1282,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         }
         moX.template load_w<WV>(dO + voff(tE + 1), nvO);
         mqX.template load_w<WK>(Q + koff(tE + 1), nvO);
+        if constexpr (C_REGS) load_c(tE / 2);
     };
     auto load_pair = [&](int tE) {
         load_pair_kv(tE);
@@ -1260,7 +1293,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         mkE.template load_w<WK>(K + koff(t), n);
         moX.template load_w<WV>(dO + voff(t), n);
         mqX.template load_w<WK>(Q + koff(t), n);
-        mc.template load_w<WV>(ctile + (size_t)t * WK * WV, WK);
+        load_c(t);
         if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
         if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)t * CT, n);
     };
@@ -1273,7 +1306,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         }
         mvE.template load_w<WV>(V + voff(tE), nvalid(tE));
         mkE.template load_w<WK>(K + koff(tE), nvalid(tE));
-        mc.template load_w<WV>(ctile + (size_t)(tE / 2) * WK * WV, WK);
+        load_c(tE / 2);
         if constexpr (NORM) mnX.load(yn + voff(t), rstd_c + (size_t)t * CT, n);
         if constexpr (TOKEN) lgE = TokenDecay<T, CT>::fetch(lg + (size_t)tE * CT, nvalid(tE));
         moX.template load_w<WV>(dO + voff(t), n);
@@ -1297,7 +1330,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
 
     const T *sX2 = rg ? sQ : sdO;    // intra operand and state-update B operand: [token][feature in w]
     const T *sUA = rg ? sdO : sQ;    // state-update A operand: [token][feature of the state rows]
-    const T *sPm = rg ? sDS : sS;    // masked score tile of this group's product
+    T *sPm = rg ? sDS : sS;          // masked score tile of this group's product
     T *gOut = rg ? dK : dV;
 
     // st[blk][i]: group 0: dKV[32 blk + acc_row(i)][32 w + r]; group 1: dKV[32 w + r][32 blk + acc_row(i)]
@@ -1308,11 +1341,12 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             if (rg == 0) state_load_w<D, WK, WV>(ln, s, g, w);
             else state_load_t_w<D, WK, WV>(ln, s, g, w);
         };
-        if (carry)
+        if (carry) {
+            const Pieces pc(true, !OWN && carry == kCarriedPieces, shards, nseg, tiles_per_seg, ntiles);
             start_state<true, SHARED>(st, scratch + ((ptrdiff_t)chain * pc.slots - pc.base) * WK * WV, dkv_out ? dkv_out + (size_t)chain * WK * WV : nullptr,
                               SegDecay<TOKEN>(decay, seglog + ((ptrdiff_t)chain * pc.slots - pc.base), chain, H, pc.per_shard, pc.tiles * CT, ntok),
                               OWN && carry == kOwn ? pc.per_shard * shards - 1 : piece_of<true>(pc, shard, seg), pc.per_shard, pc.per_shard * shards, WK * WV, load);
-        else load(st, states + (size_t)slot0 * WK * WV);
+        } else load(st, states + (size_t)slot0 * WK * WV);
         if (dkv_copy && slot0 == nslots - 1 && rg == 0) state_store_w<D, WK, WV>(ln, st, dkv_copy + (size_t)chain * WK * WV, w);
     }
 
@@ -1348,7 +1382,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                 float x[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] = acc[4 * g + e] * cross_weight(iq, j0 + e);
-                E::st4(sDX + iq * LDP + j0, x[0], x[1], x[2], x[3]);
+                E::st4(SM::block(sDX, ib, jb) + lds_off(LDP, ln.r, j0 - 32 * jb), x[0], x[1], x[2], x[3]);
             }
         }
     };
@@ -1379,7 +1413,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             if (idx < NTRI) contract(std::integral_constant<int, WV / E::KSTEP / 2>{});
             else contract(std::integral_constant<int, WK / E::KSTEP / 2>{});
             acc += acc2;
-            store_masked_scores<T, LDP>(ln, idx < NTRI ? sDS : sS, acc, jb, ib, dec);
+            store_masked_scores<T, LDP>(ln, SM::block(idx < NTRI ? sDS : sS, ib, jb), acc, jb, ib, dec);
         }
     };
 
@@ -1438,15 +1472,21 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         auto dq_tile = [&](int qa, int r0, auto both) __attribute__((always_inline)) {
             f32x16 acc = {0};
             pipelined<WV / E::KSTEP>(   // (the cached state's real columns)
-                [&](int ks) { return FragPair<F>{E::ld_kc(ln, sC, LDD, 32 * qa, ks * E::KSTEP), E::ld_kc(ln, sdO, LDD, r0, ks * E::KSTEP)}; },
+                [&](int ks) {
+                    FragPair<F> f;
+                    if constexpr (C_REGS) f.a = cf[ks];   // (qa = w)
+                    else f.a = E::ld_kc(ln, sC, LDD, 32 * qa, ks * E::KSTEP);
+                    f.b = E::ld_kc(ln, sdO, LDD, r0, ks * E::KSTEP);
+                    return f;
+                },
                 [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); });
             acc *= cross ? far_upto(r0 + ln.r) : dec.upto(r0 + ln.r);
             auto fma = [&](int, const FragPair<F> &f) { acc = E::mfma(f.a, f.b, acc); };
             if (cross)
                 pipelined<NKS>(
-                    [&](int ks) { return FragPair<F>{E::ld_ks(ln, sKE, LDD, ks * E::KSTEP, 32 * qa), E::ld_kc(ln, sDX, LDP, r0, ks * E::KSTEP)}; },
+                    [&](int ks) { return FragPair<F>{E::ld_ks(ln, sKE, LDD, ks * E::KSTEP, 32 * qa), E::ld_kc(ln, SM::block(sDX, r0 / 32, ks / SPB), LDP, 0, ks % SPB * E::KSTEP)}; },
                     fma);
-            auto intra = [&](int ks) { return FragPair<F>{E::ld_ks(ln, pK, LDD, ks * E::KSTEP, 32 * qa), E::ld_kc(ln, sDS, LDP, r0, ks * E::KSTEP)}; };
+            auto intra = [&](int ks) { return FragPair<F>{E::ld_ks(ln, pK, LDD, ks * E::KSTEP, 32 * qa), E::ld_kc(ln, SM::block(sDS, r0 / 32, ks / SPB), LDP, 0, ks % SPB * E::KSTEP)}; };
             pipelined<decltype(both)::value ? 2 * SPB : SPB>(intra, fma);
             if constexpr (TOKEN) rq[r0 / 32] = rowdot<T>(ln, acc, sQ, LDD, r0, qa);   // (from the fp32 accumulators, before rounding)
             store_out_tile_t<T, D, WK>(ln, dQ + koff(t), acc, r0, qa, nrows);
@@ -1487,7 +1527,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
                     f.a = E::ld_ks(ln, sX2, LDD, ks * E::KSTEP, 32 * w);
 #pragma unroll
                     for (int jb = 0; jb < NB; ++jb)
-                        if (jb <= ks / SPB) f.b[jb] = E::ld_ks(ln, sPm, LDP, ks * E::KSTEP, 32 * jb);
+                        if (jb <= ks / SPB) f.b[jb] = E::ld_ks(ln, SM::block(sPm, ks / SPB, jb), LDP, ks % SPB * E::KSTEP, 0);
                     return f;
                 },
                 [&](int ks, const Three &f) {
@@ -1531,7 +1571,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
             moX.store(sdO, LDD);
             mkE.store(sKE, LDD);
             mqX.store(sQ, LDD);
-            mc.store(sC, LDD);
+            store_c();
             __syncthreads();
             ln = fresh_lane();
             if (t > t0) load_tile(t - 1, CT);   // (only the sub-sequence's last tile is short)
@@ -1563,7 +1603,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         mqX.store(sQ, LDD);
         mvE.store(sVE, LDD);
         mkE.store(sKE, LDD);
-        mc.store(sC, LDD);
+        store_c();
         __syncthreads();
         ln = fresh_lane();
         scores(dec, pV, pK);
@@ -1587,7 +1627,7 @@ __global__ __launch_bounds__(D * 4) void k_bwd8p(const T *__restrict__ Q, const 
         mqX.store(sQ, LDD);
         mvE.store(sVE, LDD);
         mkE.store(sKE, LDD);
-        mc.store(sC, LDD);   // the state the E tile starts from serves both tiles of the pair
+        store_c();   // the state the E tile starts from serves both tiles of the pair
         if (tE > t0) load_pair_kv(tE - 2);
         __syncthreads();
         ln = fresh_lane();
@@ -1730,25 +1770,25 @@ struct Bwd8hFam : Family<AloneOwn> {   // one cached state per pair of tiles, a 
 // differ ask for the walk's tile. The forward pass of one sub-sequence never sums over the segment with the short end.
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
-                            const T *yn, const float *rstd, const Pieces &pc, const Shards &all, hipStream_t s) {
+                            const T *yn, const float *rstd, Start start, const Shards &all, hipStream_t s) {
     const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.yn, all.rstd};
+    const Pieces pc(BWD, start == kCarriedPieces, p.shards, p.nseg, p.tiles_per_seg, p.ntiles);
+    const int segs = pc.n == 2 ? -p.nseg : p.nseg;
     const dim3 grid(p.shards > 1 ? pc.per_shard : pc.end - pc.first, p.B * p.H, p.shards), block(D * 2);
     Plan q = p;
     if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
         if (!(BWD && p.norm) && pc.tiles % 2 == 0) {
             if (!BWD) q.ragged = p.N % 128 != 0;
-            Pieces wide = pc;
-            wide.tiles /= 2;
             return by_shards(p, sh, [&](auto of) {
                 return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D, decltype(of)>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, wide, p.N, p.kvdiv,
+                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, segs, p.tiles_per_seg / 2, p.N, p.kvdiv,
                                      (const T *)nullptr, (const float *)nullptr, of);
             });
         }
     }
     return by_shards(p, sh, [&](auto of) {
         return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV, decltype(of)>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
-                             scratch, seglog, p.H, p.ntiles, pc, p.N, p.kvdiv, yn, rstd, of);
+                             scratch, seglog, p.H, p.ntiles, segs, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, of);
     });
 }
 
@@ -1758,27 +1798,18 @@ static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *
 // first tile (a state's loads, one after the other), the scan 3 - 11 us and a launch. bf16 d=128 forward / backward:
 // 128 heads x 1024 tokens (2 segments) 63.9 / 88.2 -> 56.8 / 79.2 us, 64 x 8192 (4) 195.4 / 302.4 -> 188.0 / 301.9,
 // but 16 x 1024 (8) 31.7 / 37.3 -> 39.7 / 47.3.
-static Start walk_start(const Plan &p) { return p.own_states ? kOwn : p.shards * p.nseg <= 4 ? kCarried : kScanned; }
-
-static Pieces pieces(const Plan &p, bool bwd) {
-    Pieces c;
-    c.n = local_pieces(p.shards * p.nseg, p.tiles_per_seg, (long long)p.B * p.H);
-    c.tiles = p.tiles_per_seg / c.n;
-    c.per_shard = c.n == 1 ? p.nseg : (p.ntiles + c.tiles - 1) / c.tiles;
-    const int all = p.shards * c.per_shard;
-    c.first = bwd ? c.n : 0;
-    c.end = bwd ? all : (p.shards - 1) * c.per_shard + (p.nseg - 1) * c.n;
-    c.base = c.n > 1 ? c.first : 0;
-    c.slots = c.n > 1 ? c.end - c.first : all;
-    return c;
+static Start walk_start(const Plan &p) {
+    if (p.own_states) return kOwn;
+    if (p.shards * p.nseg > 4) return kScanned;
+    return local_pieces(p.shards * p.nseg, p.tiles_per_seg, (long long)p.B * p.H) == 2 ? kCarriedPieces : kCarried;
 }
 
 // Local pass and scan of the forward states over K, V, as far as the walk's start asks for them.
 template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_states(const Plan &p, const void *k, const void *v, const float *kv_in, const float *decay, float *scratch,
-                             float *seglog, Start start, const Pieces &pc, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
+                             float *seglog, Start start, const Shards &sh, hipStream_t s, const KernelEvents *ke) {
     if (start != kOwn && p.shards * p.nseg > 1) {
-        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, pc, sh, s);
+        if (hipError_t e = run_local<T, CT, D, false, WK, WV>(p, (const T *)k, (const T *)v, decay, scratch, seglog, nullptr, nullptr, start, sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1789,10 +1820,9 @@ static hipError_t run_states(const Plan &p, const void *k, const void *v, const 
 template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const Start start = walk_start(p);
-    const Pieces pc = pieces(p, false);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
-    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, pc, a.sh, s, ke); e != hipSuccess) return e;
+    if (e = run_states<T, CT, D, WK, WV>(p, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, ke); e != hipSuccess) return e;
     if (ke) (void)hipEventRecord(ke->ev[2], s);
     static_assert(Smem<T, CT, D>::fwd <= 163840 / 2, "two workgroups of the walk share a CU's LDS");
     const FwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.cache, a.sh.out, a.sh.rstd, a.sh.kv_out, {}};
@@ -1810,7 +1840,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
                 const auto walk8 = a.states_only ? by_model<Fwd8Fam<T, CT, D, kStates, SH>>(p) : by_model<Fwd8Fam<T, CT, D, kOutputs, SH>>(p);
                 return launch_kernel(walk8, grid, dim3(D * 4), Fwd8Smem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                      (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache, p.cache_tiles,
-                                     (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, pc, p.H, p.ntiles, p.nseg,
+                                     (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
                                      p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, a.kv_copy, of);
             });
             if (e != hipSuccess) return e;
@@ -1823,7 +1853,7 @@ static hipError_t run_fwd(const Plan &p, const FwdArgs &a, hipStream_t s, const 
         const auto walk = a.states_only ? by_model<StatesFam<T, CT, D, WK, WV, SH>>(p) : by_model<FwdFam<T, CT, D, WK, WV, SH>>(p);
         return launch_kernel(walk, grid, dim3(D * 2), Smem<T, CT, D>::fwd, s,
                              (const T *)a.q, (const T *)a.k, (const T *)a.v, a.decay, (T *)a.out, a.kv_out, (T *)a.cache,
-                             p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, pc, p.H, p.ntiles, p.nseg,
+                             p.cache_tiles, (const float *)a.scratch, a.kv_in, (const float *)a.seglog, (int)start, p.H, p.ntiles, p.nseg,
                              p.tiles_per_seg, p.N, p.kvdiv, a.rstd_out, a.eps, (const T *)nullptr, (const float *)nullptr,
                              (const T *)nullptr, (float *)nullptr, a.kv_copy, of);
     });
@@ -1838,9 +1868,8 @@ template <typename T, int CT, int D, int WK, int WV>
 static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
     const Plan &f = *a.fwd;   // a segment per cached state
     const Start start = a.cache ? kKept : walk_start(f);   // kKept: a state per segment of every sub-sequence, in its own buffer
-    const Pieces pc = pieces(f, false);
     if (!a.cache) {
-        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, pc, a.sh, s, nullptr);
+        if (hipError_t e = run_states<T, CT, D, WK, WV>(f, a.k, a.v, a.kv_in, a.decay, a.scratch, a.seglog, start, a.sh, s, nullptr);
             e != hipSuccess)
             return e;
     }
@@ -1848,7 +1877,7 @@ static hipError_t run_dq(const BwdArgs &a, hipStream_t s) {
         return launch_kernel(by_model<DqFam<T, CT, D, WK, WV, decltype(of)>>(f), dim3(f.nseg, f.B * f.H, f.shards), dim3(D * 2), Smem<T, CT, D>::fwd,
                              s, (const T *)a.dout, (const T *)a.v, (const T *)a.k, a.decay, (T *)a.dq, (float *)nullptr, (T *)nullptr,
                              f.cache_tiles, a.cache ? (const float *)a.cache : (const float *)a.scratch, a.kv_in, (const float *)a.seglog,
-                             (int)start, pc, f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
+                             (int)start, f.H, f.ntiles, f.nseg, f.tiles_per_seg, f.N, f.kvdiv, (float *)nullptr, 0.0f, (const T *)a.yn, a.rstd,
                              (const T *)a.q, a.rtok, (float *)nullptr, of);
     });
 }
@@ -1857,7 +1886,6 @@ template <typename T, int CT, int D, int WK = D, int WV = D>
 static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const KernelEvents *ke) {
     const int chains = p.B * p.H;
     const Start start = walk_start(p);
-    const Pieces pc = pieces(p, true);
     hipError_t e;
     if (ke) (void)hipEventRecord(ke->ev[0], s);
     if constexpr (sizeof(T) == 4) {
@@ -1867,7 +1895,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     }
     if (start != kOwn && p.shards * p.nseg > 1) {
         if (e = run_local<T, CT, D, true, WK, WV>(p, (const T *)a.q, (const T *)a.dout, a.decay, a.scratch, a.seglog, (const T *)a.yn,
-                                          a.rstd, pc, a.sh, s);
+                                          a.rstd, start, a.sh, s);
             e != hipSuccess)
             return e;
     }
@@ -1881,7 +1909,8 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
     const BwdShards sh{a.sh.q, a.sh.k, a.sh.v, a.sh.dout, a.sh.cache, a.sh.dq, a.sh.dk, a.sh.dv, a.sh.dkv_in, a.sh.yn, a.sh.rstd};
     if constexpr (sizeof(T) == 2) {
         static_assert(Bwd8pSmem<T, CT, D>::TOTAL <= 163840, "LDS budget of one gfx950 CU exceeded");
-        static_assert(Bwd8pSmem<T, CT, D, true>::TOTAL <= 163840 / (D == 64 ? 2 : 1), "two workgroups by tiles share a CU at d=64");
+        static_assert(D != 64 || (Bwd8pSmem<T, CT, D>::TOTAL <= 163840 / 2 && Bwd8pSmem<T, CT, D, kTiles>::TOTAL <= 163840 / 2),
+                      "two workgroups share a CU at d=64");
         const bool by_tiles = p.cache_tiles == 1;
         auto go = [&](auto of) {
             using SH = decltype(of);
@@ -1889,9 +1918,9 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
                 if constexpr (is_own<SH>) return by_model<Bwd8hFam<T, CT, D, WK, WV>>(p);
                 else return by_model<Bwd8pFam<T, CT, D, WK, WV, SH>>(p);
             }();
-            return launch_kernel(walk, grid, block, by_tiles ? Bwd8pSmem<T, CT, D, true>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
+            return launch_kernel(walk, grid, block, by_tiles ? Bwd8pSmem<T, CT, D, kTiles>::TOTAL : is_own<SH> ? Bwd8pSmem<T, CT, D, kHalves>::TOTAL : Bwd8pSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (const T *)a.cache, (T *)a.dq, (T *)a.dk,
-                                 (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, pc, a.rtok, p.H,
+                                 (T *)a.dv, a.dkv_in, (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H,
                                  p.ntiles, p.nseg, p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
         };
         // (single tiles of pairs: also a sequence of one tile, whose workgroups have no tile behind them)
@@ -1904,7 +1933,7 @@ static hipError_t run_bwd(const Plan &p, const BwdArgs &a, hipStream_t s, const 
         e = by_start(p, start, sh, [&](auto of) {
             return launch_kernel(by_model<BwdkvFam<T, CT, D, WK, WV, decltype(of)>>(p), grid, block, BwdkvSmem<T, CT, D>::TOTAL, s, (const T *)a.q,
                                  (const T *)a.k, (const T *)a.v, (const T *)a.dout, a.decay, (T *)a.dk, (T *)a.dv, a.dkv_in,
-                                 (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, pc, a.rtok, p.H, p.ntiles, p.nseg,
+                                 (const float *)a.scratch, a.dkv_out, (const float *)a.seglog, (int)start, a.rtok, p.H, p.ntiles, p.nseg,
                                  p.tiles_per_seg, p.N, p.kvdiv, (const T *)a.yn, a.rstd, a.dkv_copy, of);
         });
     }

@@ -112,6 +112,18 @@ def test_local_pass_in_pieces_of_a_shard(gpu, oracle, dtype, n):
     check(harness, oracle, inp, dtype, False, harness.run_gpu(inp, T=2))
 
 
+# bfloat16 d=64 in pairs, cut for two workgroups a CU: 64 heads x 20 tiles, five segments of two pairs; a short last tile; an odd
+# last pair (whose cache has a state per tile: by tiles).
+@pytest.mark.parametrize("N", [64 * 20, 64 * 20 - 37, 64 * 19])
+@pytest.mark.parametrize("token,norm", [(False, False), (True, False), (False, True)])
+def test_two_workgroups_a_cu(gpu, oracle, N, token, norm):
+    harness, lasp, si = gpu
+    cfg = si.Config("two", B=1, H=64, N=N, D=64, chunk=64, dtype="bf16", seed=8900 + N, token_decay=token)
+    inp = si.make_inputs(cfg, with_states=True)
+    print(f"case N={N} token={token} norm={norm}", flush=True)
+    check(harness, oracle, inp, "bf16", norm, harness.run_gpu(inp, norm_eps=1e-5 if norm else None))
+
+
 def check(harness, oracle, inp, dtype, norm, got):
     decay = None if inp.log_g is not None else inp.decay
     o, kvo = oracle.dims_fwd_brute(inp.q, inp.k, inp.v, decay, inp.kv_in, log_g=inp.log_g)
