@@ -99,18 +99,15 @@ DEVI Lane fresh_lane() {
 
 // LDS layouts of bfloat16 tiles without padding: the 16-byte chunk c of row `row` is stored at chunk c ^ swz(row). Rows of 128
 // elements (256 bytes = all 64 banks), and 32 x 32 blocks; a row stride of kSwzLd or kBlockLd selects them in the loaders
-// below. Both are conflict-free for 16 lanes reading one chunk of 16 consecutive rows, for the four-row by two-chunk blocks of a
-// transposing read, and for whole-row stores; the pattern repeats every 16 rows.
+// below (blocks: in those that read score tiles). Both are conflict-free for 16 lanes reading one chunk of 16 consecutive rows, for
+// the four-row by two-chunk blocks of a transposing read, and for whole-row stores; the pattern repeats every 16 rows.
 constexpr int kSwzLd = 128, kBlockLd = -32;
-constexpr bool swizzled(int ld) { return ld == kSwzLd || ld == kBlockLd; }
-constexpr int row_elems(int ld) { return ld < 0 ? -ld : ld; }
-DEVI int swz(int ld, int row) {
-    if (ld == kSwzLd) return ((row & 7) << 1) | ((row >> 3) & 1);
-    return (row >> 2) & 3;   // four rows share the banks
-}
+DEVI int swz16(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+DEVI int swz4(int row) { return (row >> 2) & 3; }   // four rows of a block share the banks
 // element offset of (row, col) in a tile with row stride ld
 DEVI int lds_off(int ld, int row, int col) {
-    return swizzled(ld) ? row * row_elems(ld) + ((((col >> 3) ^ swz(ld, row))) << 3) + (col & 7) : row * ld + col;
+    if (ld == kBlockLd) return row * 32 + ((((col >> 3) ^ swz4(row))) << 3) + (col & 7);
+    return ld == kSwzLd ? row * kSwzLd + ((((col >> 3) ^ swz16(row))) << 3) + (col & 7) : row * ld + col;
 }
 template <typename T, int D>
 constexpr int tile_ld() { return (sizeof(T) == 2 && D == 128) ? kSwzLd : D + (sizeof(T) == 2 ? 24 : 4); }
@@ -163,9 +160,10 @@ struct Elem<bf16_t> {
     static DEVI f32x16 mfma(frag a, frag b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
     // row0 is a multiple of 16 and k0 a multiple of 16 wherever these are called.
     static DEVI frag ld_kc(const Lane &ln, const bf16_t *X, int ld, int row0, int k0) {
-        if (swizzled(ld)) {
-            const int t = ln.h ^ swz(ld, ln.r);  // lane constant; chunk (k0/8 + h) ^ swz = (k0/8) ^ t since k0/8 is even
-            return *(const bf16x8 *)(X + (row0 + ln.r) * row_elems(ld) + (((k0 >> 3) ^ t) << 3));
+        if (ld == kBlockLd) return *(const bf16x8 *)(X + (row0 + ln.r) * 32 + (((k0 >> 3) ^ (ln.h ^ swz4(ln.r))) << 3));
+        if (ld == kSwzLd) {
+            const int t = ln.h ^ swz16(ln.r);  // lane constant; chunk (k0/8 + h) ^ swz = (k0/8) ^ t since k0/8 is even
+            return *(const bf16x8 *)(X + (row0 + ln.r) * kSwzLd + (((k0 >> 3) ^ t) << 3));
         }
         return *(const bf16x8 *)(X + (row0 + ln.r) * ld + k0 + 8 * ln.h);
     }
@@ -177,12 +175,17 @@ struct Elem<bf16_t> {
         const int l16 = l & 15;
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         const bf16_t *plo, *phi;
-        if (swizzled(ld)) {
+        if (ld == kSwzLd || ld == kBlockLd) {
             const int rowl = 8 * ln.h + (l16 >> 2);                    // row inside the 16-row group (k0 % 16 == 0)
             const int c = (col0 >> 3) + 2 * ((l >> 4) & 1) + ((l16 & 3) >> 1);  // chunk of this lane's 8-byte piece
             const int e = 4 * (l16 & 1);                                // element inside the chunk
-            plo = X + (k0 + rowl) * row_elems(ld) + ((c ^ swz(ld, rowl)) << 3) + e;
-            phi = X + (k0 + rowl + 4) * row_elems(ld) + ((c ^ swz(ld, rowl + 4)) << 3) + e;
+            if (ld == kSwzLd) {
+                plo = X + (k0 + rowl) * kSwzLd + ((c ^ swz16(rowl)) << 3) + e;
+                phi = X + (k0 + rowl + 4) * kSwzLd + ((c ^ swz16(rowl + 4)) << 3) + e;
+            } else {
+                plo = X + (k0 + rowl) * 32 + ((c ^ swz4(rowl)) << 3) + e;
+                phi = X + (k0 + rowl + 4) * 32 + ((c ^ swz4(rowl + 4)) << 3) + e;
+            }
         } else {
             plo = X + (k0 + 8 * ln.h + (l16 >> 2)) * ld + col0 + 16 * ((l >> 4) & 1) + 4 * (l16 & 3);
             phi = plo + 4 * ld;
@@ -196,9 +199,9 @@ struct Elem<bf16_t> {
     }
     static DEVI frag ld_kp(const Lane &ln, const bf16_t *X, int ld, int row0, int kb, int m) {
         union { struct { bf16x4 a, b; } s; bf16x8 v; } u;
-        if (swizzled(ld)) {
-            const int sw = swz(ld, ln.r), c = (kb >> 3) + 2 * m;
-            const bf16_t *p = X + (row0 + ln.r) * row_elems(ld) + 4 * ln.h;
+        if (ld == kSwzLd) {
+            const int sw = swz16(ln.r), c = (kb >> 3) + 2 * m;
+            const bf16_t *p = X + (row0 + ln.r) * kSwzLd + 4 * ln.h;
             u.s.a = *(const bf16x4 *)(p + ((c ^ sw) << 3));
             u.s.b = *(const bf16x4 *)(p + (((c + 1) ^ sw) << 3));
         } else {
@@ -500,12 +503,12 @@ struct TileMover {
             r[i] = chunk * EPV < W && row0 + i * (NT / VPR) >= skip ? gload<u32x4, STREAM>(g + i * (NT / VPR) * W, lo) : u32x4{0, 0, 0, 0};
     }
     DEVI void store(T *s, int ld) const {
-        if (sizeof(T) == 2 && swizzled(ld)) {
-            static_assert(sizeof(T) != 2 || (NT / VPR) % 16 == 0, "row step must keep row % 16");
+        if (sizeof(T) == 2 && ld == kSwzLd) {
+            static_assert(sizeof(T) != 2 || COLS != 128 || (NT / VPR) % 16 == 0, "row step must keep row % 16");
             const int row = threadIdx.x / VPR, chunk = threadIdx.x % VPR;
-            const unsigned lo = row * COLS + ((chunk ^ swz(ld, row)) << 3);
+            const unsigned lo = row * kSwzLd + ((chunk ^ swz16(row)) << 3);
 #pragma unroll
-            for (int i = 0; i < NV; ++i) *(u32x4 *)(s + i * (NT / VPR) * COLS + lo) = r[i];
+            for (int i = 0; i < NV; ++i) *(u32x4 *)(s + i * (NT / VPR) * kSwzLd + lo) = r[i];
             return;
         }
         const unsigned lo = lane_off(ld);
