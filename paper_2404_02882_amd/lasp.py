@@ -176,17 +176,19 @@ def scratch_bytes(shape: Shape) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
+    """The address as a plain int, which the declared argument types take as it is: one new token for 8 x 16 heads 6.4 -> 5.9 us
+    (the kernel alone 4.7) against a c_void_p for every one."""
     if t is None:
         return None
     if not t.is_contiguous():
         raise ValueError("tensors handed to the library must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:   # the raw handle: building a Stream object takes 2.7 us of a 9 us call
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def lasp_fwd(shape: Shape, q, k, v, kv_in, decay, out, kv_out, state_cache, scratch, stream=None) -> None:
