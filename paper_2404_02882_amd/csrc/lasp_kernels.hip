@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "lasp_internal.h"
+#include "lasp_rules.h"
 #include "lasp_device.h"
 
 namespace lasp {
@@ -319,6 +320,190 @@ static hipError_t run_step(const Plan &p, const FwdArgs &a, hipStream_t s, const
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// k_short: forward of a short float sequence (a prompt; no cache, one lambda per head) as its definition, without states between
+// tiles: the workgroup of 32 queries takes the score product with every 32 keys before them on a wave of its own,
+//     out_i = sum_{j <= i} lambda^(i-j) (q_i . k_j) v_j + lambda^(i+1) KV_in^T q_i,
+// and d/32 more workgroups a head each sum 32 columns of kv_out, a wave for 32 tokens. Nothing goes through LDS but the
+// waves' sums: a lane loads its MFMA operands from memory and splits them itself (the scores' accumulators are the other
+// operand of the product with V as they are). Such a call is all latency: local pass, scan and walk one behind the other.
+// d=64: 2 heads x 256 tokens SHORT_FIGURES
+// ---------------------------------------------------------------------------
+constexpr int kShortTokens = 256, kShortWaves = kShortTokens / 32;
+template <int D>
+__global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V,
+                                                            const float *__restrict__ kv_in, const float *__restrict__ decay,
+                                                            float *__restrict__ O, float *__restrict__ kv_out, float *__restrict__ kv_copy,
+                                                            int H, int ntok, int kvdiv) {
+    using E = WalkElem<float>;
+    using F = typename E::frag;
+    constexpr int DB = D / 32, PART = DB * 1024;   // floats of a wave's sums
+    extern __shared__ __attribute__((aligned(16))) float sums[];
+    float *pw = sums + kShortWaves * PART;   // lambda^0 .. lambda^256
+    const int chain = blockIdx.y, ntiles = (ntok + 31) / 32, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Lane ln(threadIdx.x);
+    const int kvchain = (chain / H) * (H / kvdiv) + (chain % H) / kvdiv;   // this head's K, V
+    Q += (size_t)chain * ntok * D;
+    O += (size_t)chain * ntok * D;
+    K += (size_t)kvchain * ntok * D;
+    V += (size_t)kvchain * ntok * D;
+    const float lam = decay[chain % H];
+    if (threadIdx.x <= kShortTokens) pw[threadIdx.x] = (float)(threadIdx.x < kShortTokens ? pow_small(lam, threadIdx.x) : pow_n(lam, kShortTokens));
+    auto row8 = [&](const float *x, int row, int col) {   // eight features of a token (zero past the end)
+        const float *p = x + (size_t)row * D + col;
+        const f32x4 z = {0, 0, 0, 0}, lo = row < ntok ? *(const f32x4 *)p : z, hi = row < ntok ? *(const f32x4 *)(p + 4) : z;
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    auto split = [](const f32x8 &x) { return E::template split<false>(x, nullptr); };
+    f32x16 acc[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b) acc[b] = f32x16{0};
+    auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4 *)(sums + w * PART + ((4 * b + q) * 64 + ln.id) * 4) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
+    };
+    auto total = [&](int i, int waves) {   // i: four values of all waves' sums
+        f32x4 x = *(const f32x4 *)(sums + 4 * i);
+        for (int v = 1; v < waves; ++v) x += *(const f32x4 *)(sums + v * PART + 4 * i);
+        return x;
+    };
+    if ((int)blockIdx.x < ntiles) {
+        const int t = blockIdx.x, query = 32 * t + ln.r;
+        const bool keys = w <= t, state = kv_in && w == (t + 1 < kShortWaves ? t + 1 : 0);   // what this wave has to add
+        f32x16 s = {0};
+        f32x8 values[E::NSUB][DB];   // V, the keys in the order of the accumulator's rows
+        if (keys) {
+            // (requests first: a split has a branch in it, over which the compiler moves none)
+            constexpr int AHEAD = 4;
+#pragma unroll
+            for (int k0 = 0; k0 < D / E::KSTEP; k0 += AHEAD) {
+                f32x8 k[AHEAD], q[AHEAD];
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i) {
+                    k[i] = row8(K, 32 * w + ln.r, (k0 + i) * E::KSTEP + 8 * ln.h);
+                    q[i] = row8(Q, query, (k0 + i) * E::KSTEP + 8 * ln.h);
+                }
+                if (k0 + AHEAD == D / E::KSTEP) {
+#pragma unroll
+                    for (int m = 0; m < E::NSUB; ++m)
+#pragma unroll
+                        for (int b = 0; b < DB; ++b)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const int key = 32 * w + ln.acc_row(8 * m + e);
+                                values[m][b][e] = key < ntok ? V[(size_t)key * D + 32 * b + ln.r] : 0.0f;
+                            }
+                }
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i) s = E::mfma(split(k[i]), split(q[i]), s);
+            }
+        }
+        __syncthreads();   // the powers
+        if (state) {
+            const float *kv = kv_in + (size_t)chain * D * D;
+            for (int ks = 0; ks < D / E::KSTEP; ++ks) {
+                const f32x8 q = row8(Q, query, ks * E::KSTEP + 8 * ln.h);
+                f32x8 x[DB];
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[b][e] = kv[(ks * E::KSTEP + 8 * ln.h + e) * D + 32 * b + ln.r];
+                const F qf = split(q);
+#pragma unroll
+                for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(x[b]), qf, acc[b]);
+            }
+            const float up = pw[query + 1];
+#pragma unroll
+            for (int b = 0; b < DB; ++b) acc[b] *= up;
+        }
+        if (keys) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int back = query - (32 * w + ln.acc_row(i));
+                s[i] = back >= 0 ? s[i] * pw[back < 0 ? 0 : back] : 0.0f;
+            }
+#pragma unroll
+            for (int m = 0; m < E::NSUB; ++m) {
+                f32x8 p;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) p[e] = s[8 * m + e];
+                const F pf = split(p);
+#pragma unroll
+                for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(values[m][b]), pf, acc[b]);
+            }
+        }
+        if (keys || state) put();
+        __syncthreads();
+        const int waves = t + 1 + (kv_in && t + 1 < kShortWaves ? 1 : 0);
+        for (int i = threadIdx.x; i < PART / 4; i += 64 * kShortWaves) {
+            const Lane of(i);
+            const int token = 32 * t + of.r, feature = 8 * (i >> 6) + 4 * of.h;
+            if (token < ntok) *(f32x4 *)(O + (size_t)token * D + feature) = total(i, waves);
+        }
+    } else {
+        const int c = 32 * (blockIdx.x - ntiles) + ln.r;
+        constexpr int NKS = 32 / E::KSTEP;
+        f32x8 y[NKS], x[NKS][DB];
+        if (w < ntiles) {
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int token = 32 * w + ks * E::KSTEP + 8 * ln.h + e;
+                    y[ks][e] = token < ntok ? V[(size_t)token * D + c] : 0.0f;
+#pragma unroll
+                    for (int b = 0; b < DB; ++b) x[ks][b][e] = token < ntok ? K[(size_t)token * D + 32 * b + ln.r] : 0.0f;
+                }
+        }
+        __syncthreads();   // the powers
+        if (w < ntiles) {
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int after = ntok - 1 - (32 * w + ks * E::KSTEP + 8 * ln.h + e);
+                    y[ks][e] *= pw[after < 0 ? 0 : after];   // (past the end: zero times one)
+                }
+                const F v = split(y[ks]);
+#pragma unroll
+                for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(x[ks][b]), v, acc[b]);
+            }
+            put();
+        }
+        __syncthreads();
+        const float whole = pw[ntok];
+        for (int i = threadIdx.x; i < PART / 4; i += 64 * kShortWaves) {
+            const Lane of(i);
+            f32x4 x = total(i, ntiles);
+            const size_t at = ((size_t)chain * D + 8 * (i >> 6) + 4 * of.h) * D + 32 * (blockIdx.x - ntiles) + of.r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (kv_in) {
+                    const float in = kv_in[at + e * D];
+                    x[e] += whole * in;
+                    if (kv_copy) kv_copy[at + e * D] = in;
+                }
+                kv_out[at + e * D] = x[e];
+            }
+        }
+    }
+}
+template <int D>
+static hipError_t run_short(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
+    constexpr size_t lds = (kShortWaves * D / 32 * 1024 + kShortTokens + 4) * sizeof(float);
+    static_assert(lds <= 163840, "LDS of one CU");
+    if (hipError_t e = allow_dynamic_lds((const void *)k_short<D>, lds); e != hipSuccess) return e;
+    if (ke)
+        for (int i = 0; i < 3; ++i) (void)hipEventRecord(ke->ev[i], s);
+    k_short<D><<<dim3((p.N + 31) / 32 + D / 32, p.B * p.H), dim3(64 * kShortWaves), lds, s>>>(
+        (const float *)a.q, (const float *)a.k, (const float *)a.v, a.kv_in, a.decay, (float *)a.out, a.kv_out, a.kv_copy, p.H, p.N, p.kvdiv);
+    if (ke) (void)hipEventRecord(ke->ev[3], s);
+    return hipGetLastError();
+}
+
 // The walks by data type (float, bfloat16) and dimensions (d_k, d_v); see lasp_walks.hip.
 template <typename Fn>
 static Fn by_shape(const Plan &p, Fn f64, Fn f128, Fn f64_128, Fn f128_64, Fn b64, Fn b128, Fn b64_128, Fn b128_64) {
@@ -327,6 +512,8 @@ static Fn by_shape(const Plan &p, Fn f64, Fn f128, Fn f64_128, Fn f128_64, Fn b6
 }
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t stream, const KernelEvents *ke) {
     if (p.N <= kStepTokens && !a.cache && !p.norm && p.shards == 1) return p.dtype == 0 ? run_step<float>(p, a, stream, ke) : run_step<bf16_t>(p, a, stream, ke);
+    if (p.dtype == 0 && p.dk == p.dv && !p.token && !p.norm && !a.cache && !a.states_only && p.shards == 1 && short_forward(p.N, (long long)p.B * p.H, p.D))
+        return p.D == 64 ? run_short<64>(p, a, stream, ke) : run_short<128>(p, a, stream, ke);
     return by_shape(p, fwd_f32_64, fwd_f32_128, fwd_f32_64_128, fwd_f32_128_64, fwd_bf16_64, fwd_bf16_128, fwd_bf16_64_128,
                     fwd_bf16_128_64)(p, a, stream, ke);
 }

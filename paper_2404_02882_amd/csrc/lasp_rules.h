@@ -48,6 +48,12 @@ inline int segment_tiles(int want, int ntiles, long long chains, int D, bool eve
     return keep ? want : want + 1;
 }
 
+// Whether a float forward call that keeps no cache (one lambda per head, outputs as they are) goes through k_short.
+// Its work grows with the square of the tokens, and all of it is taken again by every head: while it leaves CUs idle it is
+// faster than the walks (32 heads x 256 tokens d=64 17.7 -> 15.2 us, d=128 33.4 -> 28.6), but not for 128 heads (x 128 17.3 / 20.0; d=128
+// 26.8 / 57.8), and at d=128 not for a single tile (9.4 / 11.5).
+inline bool short_forward(int tokens, long long chains, int D) { return tokens > (D == 64 ? 12 : 32) && tokens <= 256 && chains <= 32; }
+
 // Pieces that the local pass cuts a segment into. Where two segments (of a sequence, or of two sub-sequences) share a launch,
 // only one of them is summed, and its workgroups are at most half as many as there are CUs: in two pieces they fill them.
 // The walk then carries the boundary state over two pieces instead of one; two states are what the scratch holds anyway.

@@ -53,3 +53,30 @@ def test_float_start_states_are_the_scanned_ones(N, D, Dv):
         assert np.array_equal(got[0][name], got[1][name]), name
     # (the waves that make dK keep the state the other way round and weigh q instead of dO: two roundings of 2^-24 a product apart)
     assert max(harness.rel_errors(got[0]["dk"], got[1]["dk"])) <= 1e-6
+
+
+# Float forward calls without a cache, up to 256 tokens (k_short): edges of its 32-token tiles, the smallest and largest lengths that
+# take it, one token more, with and without an entering state, grouped heads, one tile whose state wave is the last or the first.
+@pytest.mark.parametrize("N", [13, 31, 32, 33, 64, 95, 223, 224, 255, 256, 257])
+@pytest.mark.parametrize("D,kv_heads,states", [(64, 0, True), (64, 2, False), (128, 0, True), (128, 0, False)])
+def test_short_float_forward(oracle, N, D, kv_heads, states):
+    import torch
+    from paper_2404_02882_amd import harness, lasp
+    from paper_2404_02882_amd import synth_inputs as si
+    cfg = si.Config("short", B=2, H=4, N=N, D=D, chunk=64, dtype="f32", seed=9700 + N + D)
+    inp = si.make_inputs(cfg, with_states=True)
+    G = 4 // kv_heads if kv_heads else 1
+    k, v = inp.k[:, ::G].copy(), inp.v[:, ::G].copy()
+    print(f"case N={N} D={D} kv_heads={kv_heads} states={states}", flush=True)
+    shape = lasp.make_shape(2, 4, N, D, 64, "f32", kv_heads=kv_heads)
+    dev = lambda x: torch.from_numpy(x).cuda()   # noqa: E731
+    q, kd, vd = (harness.to_device(x, "f32") for x in (inp.q, k, v))
+    out = torch.full_like(q, float("nan"))
+    kv_out = torch.full((2, 4, D, D), float("nan"), device="cuda")
+    scratch = torch.full((lasp.scratch_bytes(shape),), 0x7f, dtype=torch.uint8, device="cuda")
+    lasp.lasp_fwd(shape, q, kd, vd, dev(inp.kv_in) if states else None, dev(inp.decay), out, kv_out, None, scratch)
+    ref = oracle.dims_fwd_brute(inp.q, oracle.group_expand(k, G), oracle.group_expand(v, G), inp.decay, inp.kv_in if states else np.zeros_like(inp.kv_in))
+    for name, x, r in zip(("out", "kv_out"), (out, kv_out), ref):
+        emax, efro = harness.rel_errors(x.cpu().numpy(), r)
+        print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
+        assert np.isfinite(emax) and emax <= 1e-5 and efro <= 1e-6, name   # fp32 sums of at most 256 terms: 256^0.5 2^-24
