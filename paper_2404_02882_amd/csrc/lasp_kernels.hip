@@ -20,7 +20,10 @@ namespace lasp {
 // With per-token decay the factor of segment j is 2^seglog[chain][j] (written by k_local).
 // SHARED: over the segments of several sub-sequences (nslots), counting where each ends. In launches of one that counting took
 // the scan over 87 segments of one head from 12.2 to 13.3 us, over 33 of 16 heads, d=64, from 6.0 to 6.5: its own instance.
-template <bool BWD, bool TOKEN, bool SHARED>
+// U: segments whose local states are fetched together. The scan is a chain of as many waits for memory as it has such batches:
+// steps with 8 / 16 / 32, us: 2 heads x 32768 tokens (128 segments) 117.8 / 115.1 / 111.3, 16 x 1024 x 4, d=64 (32) 58.8 / 58.2 / 59.1,
+// 16 x 2048 (16) 73.8 / 74.8 / 75.8: the line for each count below.
+template <bool BWD, bool TOKEN, bool SHARED, int U>
 __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const float *__restrict__ boundary,
                                               const float *__restrict__ decay, const float *__restrict__ seglog,
                                               int H, int DD, int nseg, int slots, int seg_tokens, int ntok) {
@@ -33,7 +36,6 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
     if (boundary) carry = *(const f32x4 *)(boundary + (size_t)chain * DD + e);
     float *s = scratch + (size_t)chain * nslots * DD + e;
     ShardEnds<BWD, SHARED> ends(nseg);
-    constexpr int U = 8;  // segments whose local states are fetched together (independent loads)
     for (int n0 = 0; n0 < nslots; n0 += U) {
         f32x4 local[U];
         float factor[U];
@@ -58,12 +60,17 @@ __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const
 
 hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boundary, const float *decay, const float *seglog,
                        hipStream_t s) {
-    const int DD = p.dk * p.dv;   // states hold the real rows and columns only
+    const int DD = p.dk * p.dv, nslots = p.shards * p.nseg;   // states hold the real rows and columns only
     const dim3 grid((DD / 4 + 255) / 256, p.B * p.H);
-    const auto kernel = p.shards > 1 ? (bwd ? k_scan<true, false, true> : k_scan<false, false, true>)
-                        : bwd        ? (p.token ? k_scan<true, true, false> : k_scan<true, false, false>)
-                                     : (p.token ? k_scan<false, true, false> : k_scan<false, false, false>);
-    kernel<<<grid, dim3(256), 0, s>>>(states, boundary, p.token ? nullptr : decay, seglog, p.H, DD, p.nseg, p.shards * p.nseg,
+    const auto of = [&](auto u) {
+        constexpr int U = decltype(u)::value;
+        return p.shards > 1 ? (bwd ? k_scan<true, false, true, U> : k_scan<false, false, true, U>)
+               : bwd        ? (p.token ? k_scan<true, true, false, U> : k_scan<true, false, false, U>)
+                            : (p.token ? k_scan<false, true, false, U> : k_scan<false, false, false, U>);
+    };
+    const auto kernel = nslots <= 16 ? of(std::integral_constant<int, 8>{})
+                        : nslots <= 32 ? of(std::integral_constant<int, 16>{}) : of(std::integral_constant<int, 32>{});
+    kernel<<<grid, dim3(256), 0, s>>>(states, boundary, p.token ? nullptr : decay, seglog, p.H, DD, p.nseg, nslots,
                                       p.tiles_per_seg * p.tile, p.N);
     return hipGetLastError();
 }
