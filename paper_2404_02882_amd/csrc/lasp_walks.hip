@@ -78,15 +78,16 @@ DEVI size_t tile_off(int chain, int ntok, int t, int CT, int width) {
 // it every row count is CT and known at compile time.
 // WX, WY: elements per row of X and Y in memory (<= D; narrower rows are zero-padded on their way to LDS,
 // which serves key and value dimensions that differ).
-template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM, int WX, int WY, typename SH>
-__global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
+// G: groups of D/32 waves, each with its share of the state's rows (see run_local).
+template <typename T, int CT, int D, bool BWD, bool TOKEN, bool RAGGED, bool NORM, int WX, int WY, typename SH, int G>
+__global__ __launch_bounds__(D * 2 * G, 2) void k_local(const T *__restrict__ X, const T *__restrict__ Y,
                                                   const float *__restrict__ decay, float *__restrict__ scratch,
                                                   float *__restrict__ seglog, int H, int ntiles, int segs,
                                                   int tiles_per_seg, int ntok, int kvdiv, const T *__restrict__ yn,
                                                   const float *__restrict__ rstd, SH sh) {
     static_assert(!NORM || BWD, "the Norm prologue belongs to the backward pass");
     using E = WalkElem<T>;
-    constexpr int NT = D * 2, LDD = walk_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
+    constexpr int NT = D * 2 * G, LDD = walk_ld<T, D>(), DB = D / 32 / G, NKS = CT / E::KSTEP, TILE = walk_tile<T>(CT, LDD);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16_t *sX = (bf16_t *)smem;
     bf16_t *sY = sX + TILE;
@@ -100,7 +101,8 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     const size_t slot = (size_t)chain * pc.slots + (piece - pc.base);
     const int t0 = seg * pc.tiles;
     const int t1 = min(t0 + pc.tiles, ntiles);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, scalar
+    const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = w8 % (D / 32);  // wave index, scalar; its column block
+    const int a0 = 32 * DB * (w8 / (D / 32));   // first of its state rows
     Lane ln = fresh_lane();
     if constexpr (SHARED) {
         if (shard) {
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
     f32x16 low[DB];
     auto add_tile = [&](const typename E::frag(&y)[NKS]) __attribute__((always_inline)) {
         if constexpr (E::PLANES == 3)
-            pipelined_flat<DB * NKS, 1>([&](int i) { return E::ld_ks(ln, sX, LDD, (i % NKS) * E::KSTEP, 32 * (i / NKS)); },
+            pipelined_flat<DB * NKS, 1>([&](int i) { return E::ld_ks(ln, sX, LDD, (i % NKS) * E::KSTEP, a0 + 32 * (i / NKS)); },
                                         [&](int i, const typename E::frag &x) {
                                             st[i / NKS] = E::mfma_high(x, y[i % NKS], st[i / NKS]);
                                             low[i / NKS] = E::mfma_low(x, y[i % NKS], low[i / NKS]);
@@ -217,7 +219,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                     Step f;
                     f.y = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
 #pragma unroll
-                    for (int ab = 0; ab < DB; ++ab) f.x[ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, 32 * ab);
+                    for (int ab = 0; ab < DB; ++ab) f.x[ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, a0 + 32 * ab);
                     return f;
                 },
                 [&](int ks, const Step &f) {
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
             for (int ks = 0; ks < NKS; ++ks) {
                 yf[ks] = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
 #pragma unroll
-                for (int ab = 0; ab < DB; ++ab) xf[ks][ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, 32 * ab);
+                for (int ab = 0; ab < DB; ++ab) xf[ks][ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, a0 + 32 * ab);
             }
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
                     Step f;
                     f.y = E::ld_ks(ln, sY, LDD, ks * E::KSTEP, 32 * w);
 #pragma unroll
-                    for (int ab = 0; ab < DB; ++ab) f.x[ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, 32 * ab);
+                    for (int ab = 0; ab < DB; ++ab) f.x[ab] = E::ld_ks(ln, sX, LDD, ks * E::KSTEP, a0 + 32 * ab);
                     return f;
                 },
                 [&](int ks, const Step &f) {
@@ -300,7 +302,8 @@ __global__ __launch_bounds__(D * 2, 2) void k_local(const T *__restrict__ X, con
 #pragma unroll
         for (int ab = 0; ab < DB; ++ab) st[ab] += low[ab];
     }
-    state_store_w<D, WX, WY>(ln, st, scratch + slot * WX * WY, w);
+    if constexpr (G == 1) state_store_w<D, WX, WY>(ln, st, scratch + slot * WX * WY, w);
+    else state_store_w<D, D, D, DB>(ln, st, scratch + slot * D * D + a0 * D, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -1720,10 +1723,10 @@ template <typename SH>
 struct Family {
     static constexpr bool kShared = is_shared<SH>;
 };
-template <typename T, int CT, int D, bool BWD, bool WITH_NORM, int WX, int WY, typename SH>
+template <typename T, int CT, int D, bool BWD, int WX, int WY, typename SH, int G>
 struct LocalFam : Family<SH> {   // the Norm prologue exists in the backward pass only; alone the forward pass never sums over a short end
     template <bool TK, bool RG, bool NM>
-    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG && (BWD || is_shared<SH>), NM && BWD && WITH_NORM, WX, WY, SH>;
+    static constexpr auto fn = k_local<T, CT, D, BWD, TK, RG && (BWD || is_shared<SH>), NM && BWD, WX, WY, SH, G>;
 };
 template <typename T, int CT, int D, int WK, int WV, typename SH>
 struct FwdFam : Family<SH> {
@@ -1769,28 +1772,32 @@ struct Bwd8hFam : Family<AloneOwn> {   // one cached state per pair of tiles, a 
 // The local pass only sums over its segment, so its tile need not be the walk's:
 // bfloat16 segments of an even number of 64-token tiles are read 128 tokens
 // at a time (half the barriers, twice the bytes in flight per workgroup), unless
-// the Norm prologue (a third tile in registers) or key and value dimensions that
-// differ ask for the walk's tile. The forward pass of one sub-sequence never sums over the segment with the short end.
+// key and value dimensions that differ ask for the walk's tile. Two groups of waves where the dimensions are the same, half of
+// the state's rows each: a second wave per SIMD to run while one waits, half of the stores into LDS (and of Norm's
+// arithmetic) a wave. Steps, d=128, one group / two: 16 heads x 8192 tokens 156.5 / 151.4 us, 32 x 2048 98.8 / 95.3, 2 x 32 x 5000 with
+// states 181.0 / 175.6, Norm 16 x 8192 (64-token tiles / 128) 170.2 / 164.6; d=64 16 x 8192
+// 79.9 / 78.1, 32 x 2048 57.5 / 56.3.
+// The forward pass of one sub-sequence never sums over the segment with the short end.
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
                             const T *yn, const float *rstd, Start start, const Shards &all, hipStream_t s) {
+    constexpr int G = sizeof(T) == 2 && WK == D && WV == D ? 2 : 1;
     const LocalShards sh{BWD ? all.q : all.k, BWD ? all.dout : all.v, all.yn, all.rstd};
     const Pieces pc(BWD, start == kCarriedPieces, p.shards, p.nseg, p.tiles_per_seg, p.ntiles);
     const int segs = pc.n == 2 ? -p.nseg : p.nseg;
-    const dim3 grid(p.shards > 1 ? pc.per_shard : pc.end - pc.first, p.B * p.H, p.shards), block(D * 2);
+    const dim3 grid(p.shards > 1 ? pc.per_shard : pc.end - pc.first, p.B * p.H, p.shards), block(D * 2 * G);
     Plan q = p;
-    if constexpr (sizeof(T) == 2 && CT == 64 && WK == D && WV == D) {
-        if (!(BWD && p.norm) && pc.tiles % 2 == 0) {
+    if constexpr (G == 2 && CT == 64) {
+        if (pc.tiles % 2 == 0) {
             if (!BWD) q.ragged = p.N % 128 != 0;
             return by_shards(p, sh, [&](auto of) {
-                return launch_kernel(by_model<LocalFam<T, 128, D, BWD, false, D, D, decltype(of)>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
-                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, segs, p.tiles_per_seg / 2, p.N, p.kvdiv,
-                                     (const T *)nullptr, (const float *)nullptr, of);
+                return launch_kernel(by_model<LocalFam<T, 128, D, BWD, D, D, decltype(of), G>>(q), grid, block, Smem<T, 128, D>::local, s, x, y,
+                                     decay, scratch, seglog, p.H, (p.ntiles + 1) / 2, segs, p.tiles_per_seg / 2, p.N, p.kvdiv, yn, rstd, of);
             });
         }
     }
     return by_shards(p, sh, [&](auto of) {
-        return launch_kernel(by_model<LocalFam<T, CT, D, BWD, true, WK, WV, decltype(of)>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
+        return launch_kernel(by_model<LocalFam<T, CT, D, BWD, WK, WV, decltype(of), G>>(q), grid, block, Smem<T, CT, D>::local, s, x, y, decay,
                              scratch, seglog, p.H, p.ntiles, segs, p.tiles_per_seg, p.N, p.kvdiv, yn, rstd, of);
     });
 }
