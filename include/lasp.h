@@ -388,6 +388,9 @@ int lasp_bidir_bwd(const lasp_shape *shape, const void *k, const void *v, const 
  * of T device pointers, themselves in host memory, not kept. Up to four sub-sequences go through a launch together
  * (segments = 0; sums are then cut over the tokens of all of them), and dq comes with the sum, which has dO on chip,
  * where no gradient overlaps an input. scratch: lasp_bidir_seq_scratch_bytes() bytes (0 on invalid shapes).
+ * LASP_ERR_ALIAS: kv (backward: dkv) or scratch overlaps any input; an output overlaps kv, dkv or what the call of its
+ * own sub-sequence reads beside it (out[t]: q[t]; dq[t], dk[t], dv[t]: k[t], v[t], dout[t] and each other). The other
+ * overlaps between sub-sequences' tensors (dq[t] over q[t], dk[t] over k[t - 1]) are taken, with what the loops would leave.
  */
 size_t lasp_bidir_seq_scratch_bytes(const lasp_shape *shapes, int32_t T);
 int lasp_bidir_seq_fwd(const lasp_shape *shapes, int32_t T, const void *const *q, const void *const *k,

@@ -120,7 +120,8 @@ int lasp_bidir_seq_fwd(const lasp_shape *shapes, int32_t T, const void *const *q
     all.in(kv, b.state);
     for (int t = 0; t < T; ++t) {
         const size_t tb = b.token * shapes[t].N;
-        if (int rc = lasp::check_buffers({{k[t], tb}, {v[t], tb}}, {{kv, b.state}, {scratch, need}}); rc != LASP_OK) return rc;
+        // (the sum and the partial sums are written before the products read their inputs)
+        if (int rc = lasp::check_buffers({{q[t], tb}, {k[t], tb}, {v[t], tb}}, {{kv, b.state}, {scratch, need}}); rc != LASP_OK) return rc;
         if (int rc = lasp::check_buffers({{q[t], tb}, {kv, b.state}}, {{out[t], tb}}); rc != LASP_OK) return rc;
         all.in(q[t], tb);
         all.out(out[t], tb);
@@ -148,7 +149,9 @@ int lasp_bidir_seq_bwd(const lasp_shape *shapes, int32_t T, const void *const *q
     all.out(scratch, need);
     for (int t = 0; t < T; ++t) {
         const size_t tb = b.token * shapes[t].N;
-        if (int rc = lasp::check_buffers({{q[t], tb}, {dout[t], tb}}, {{dkv, b.state}, {scratch, need}}); rc != LASP_OK) return rc;
+        if (int rc = lasp::check_buffers({{q[t], tb}, {k[t], tb}, {v[t], tb}, {dout[t], tb}, {kv, b.state}}, {{dkv, b.state}, {scratch, need}});
+            rc != LASP_OK)
+            return rc;
         if (int rc = lasp::check_buffers({{k[t], tb}, {v[t], tb}, {dout[t], tb}, {kv, b.state}, {dkv, b.state}}, {{dq[t], tb}, {dk[t], tb}, {dv[t], tb}});
             rc != LASP_OK)
             return rc;

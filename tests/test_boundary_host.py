@@ -393,6 +393,13 @@ def test_bidir_sequence_rejects_before_launch(L):
         assert call(fn, kv=None) == 1 and call(fn, scr=None) == 5 and call(fn, size=need - 1) == 5
         assert call(fn, shp=bad) == 2 and call(fn, T=0) == 2
     assert call("bwd", dkv=None) == 1 and call("bwd", dkv=scr) == 6
+    # the sum (kv, dkv) and the scratch are written before the products read the other inputs
+    for fn, reads in (("fwd", "q k v"), ("bwd", "q k v do")):
+        for n in reads.split():
+            for at_t in (0, 1):
+                assert call(fn, scr=at[n][at_t]) == 6, (fn, n)
+                assert call(fn, **{"kv" if fn == "fwd" else "dkv": at[n][at_t]}) == 6, (fn, n)
+    assert call("bwd", dkv=kv) == 6 and call("bwd", scr=kv) == 6
     assert call("bwd", dq=[at["do"][0], at["dq"][1]]) == 6 and call("bwd", dv=at["dk"]) == 6
 
 
