@@ -31,6 +31,7 @@
  *     a factor is rounded to a multiple of 2^-133). Infinities, NaN and the largest
  *     floats enter sums as in float arithmetic; a product of two finite floats that
  *     exceeds the largest float by more than 2^8 may come out NaN instead of infinite.
+ *     Which product of a chain is formed first, q k or k v, depends on the lengths.
  *   - Outputs must not alias inputs or each other. Calls that share a scratch
  *     or state_cache buffer must be ordered on one stream.
  */

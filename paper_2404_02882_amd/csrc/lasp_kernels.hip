@@ -334,8 +334,12 @@ static hipError_t run_step(const Plan &p, const FwdArgs &a, hipStream_t s, const
 // and d/32 more workgroups a head each sum 32 columns of kv_out, a wave for 32 tokens. Nothing goes through LDS but the
 // waves' sums: a lane loads its MFMA operands from memory and splits them itself (the scores' accumulators are the other
 // operand of the product with V as they are). Such a call is all latency: local pass, scan and walk one behind the other.
+// Float weights reach over a tile at most, from tile to tile the sums decay, and the state's weight is a double: lambda^245 may be
+// below the smallest float, and an infinity would meet that zero. (Two floats for lambda^32, whose rounded seventh power is 1e-7 off.)
 // Bound by the splits of a wave's operands and the way to memory and back. 2 heads x 256 tokens, d=64, 14.1 -> 10.1 us, x 128
-// 11.9 -> 7.0, x 64 8.6 -> 6.3 (the call through the Python binding takes 6); d=128 16 x 256 26.8 -> 17.0.
+// 11.9 -> 7.0, x 64 8.6 -> 6.3 (the call through the Python binding takes 6); d=128 16 x 256 26.8 -> 17.0, with a state 26.7 -> 23.0.
+// Error against 64 bits, the walks / this, out and kv_out: 2 x 256, d=64, 1.56e-7, 1.02e-7 / 1.00e-7, 6.9e-8; 16 x 13 1.02e-7, 3.7e-8 /
+// 6.6e-8, 3.4e-8; d=128 with a state 16 x 250 2.07e-7, 1.58e-7 / 1.65e-7, 2.7e-8.
 // ---------------------------------------------------------------------------
 constexpr int kShortTokens = 256, kShortWaves = kShortTokens / 32;
 template <int D>
@@ -347,7 +351,9 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
     using F = typename E::frag;
     constexpr int DB = D / 32, PART = DB * 1024;   // floats of a wave's sums
     extern __shared__ __attribute__((aligned(16))) float sums[];
-    float *pw = sums + kShortWaves * PART;   // lambda^0 .. lambda^256
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    float *pw = sums + (kShortWaves + 1) * PART;   // (the state's part behind the waves'); lambda^0 .. lambda^32
+    f32x2 *factor = (f32x2 *)(pw + 34);      // the same in two parts
     const int chain = blockIdx.y, ntiles = (ntok + 31) / 32, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln(threadIdx.x);
     const int kvchain = (chain / H) * (H / kvdiv) + (chain % H) / kvdiv;   // this head's K, V
@@ -356,7 +362,13 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
     K += (size_t)kvchain * ntok * D;
     V += (size_t)kvchain * ntok * D;
     const float lam = decay[chain % H];
-    if (threadIdx.x <= kShortTokens) pw[threadIdx.x] = (float)(threadIdx.x < kShortTokens ? pow_small(lam, threadIdx.x) : pow_n(lam, kShortTokens));
+    if (threadIdx.x <= 32) {
+        const double p = pow_small(lam, threadIdx.x);
+        float hi = (float)p;
+        pw[threadIdx.x] = hi;
+        if (hi > p) hi = __uint_as_float(__float_as_uint(hi) - 1);
+        factor[threadIdx.x] = f32x2{hi, fmaxf((float)(p - hi), hi * 0x1p-60f)};   // (none zero: an infinity stays one)
+    }
     auto row8 = [&](const float *x, int row, int col) {   // eight features of a token (zero past the end)
         const float *p = x + (size_t)row * D + col;
         const f32x4 z = {0, 0, 0, 0}, lo = row < ntok ? *(const f32x4 *)p : z, hi = row < ntok ? *(const f32x4 *)(p + 4) : z;
@@ -366,22 +378,26 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
     f32x16 acc[DB];
 #pragma unroll
     for (int b = 0; b < DB; ++b) acc[b] = f32x16{0};
-    auto put = [&]() __attribute__((always_inline)) {
+    auto put = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < DB; ++b)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *(f32x4 *)(sums + w * PART + ((4 * b + q) * 64 + ln.id) * 4) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
+                *(f32x4 *)(sums + slot * PART + ((4 * b + q) * 64 + ln.id) * 4) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
     };
-    auto total = [&](int i, int waves) {   // i: four values of all waves' sums
-        f32x4 x = *(const f32x4 *)(sums + 4 * i);
-        for (int v = 1; v < waves; ++v) x += *(const f32x4 *)(sums + v * PART + 4 * i);
-        return x;
+    auto part = [&](int v, int i) { return *(const f32x4 *)(sums + v * PART + 4 * i); };   // i: four values of a wave's sums
+    auto decayed = [](f32x2 f, const f32x4 &x, const f32x4 &y) {   // f x + y
+        f32x4 z;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = __builtin_fmaf(f[0], x[e], __builtin_fmaf(f[1], x[e], y[e]));
+        return z;
     };
+    // the state's weight at the lane's query (in kv_out: at the end)
+    const double up = kv_in ? fmax(pow_small(lam, (int)blockIdx.x < ntiles ? 32 * blockIdx.x + ln.r : ntok - 1) * lam, 0x1p-1000) : 0.0;
     if ((int)blockIdx.x < ntiles) {
         const int t = blockIdx.x, query = 32 * t + ln.r;
         const bool keys = w <= t, state = kv_in && w == (t + 1 < kShortWaves ? t + 1 : 0);   // what this wave has to add
-        f32x16 s = {0};
+        f32x16 s = {0}, low = {0};   // (the small terms apart, as in the local pass)
         f32x8 values[E::NSUB][DB];   // V, the keys in the order of the accumulator's rows
         if (keys) {
             // (requests first: a split has a branch in it, over which the compiler moves none)
@@ -406,8 +422,13 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
                             }
                 }
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) s = E::mfma(split(k[i]), split(q[i]), s);
+                for (int i = 0; i < AHEAD; ++i) {
+                    const F kf = split(k[i]), qf = split(q[i]);
+                    low = E::mfma_low(kf, qf, low);
+                    s = E::mfma_high(kf, qf, s);
+                }
             }
+            s += low;
         }
         __syncthreads();   // the powers
         if (state) {
@@ -423,14 +444,14 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
 #pragma unroll
                 for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(x[b]), qf, acc[b]);
             }
-            const float up = pw[query + 1];
+            put(kShortWaves);
 #pragma unroll
-            for (int b = 0; b < DB; ++b) acc[b] *= up;
+            for (int b = 0; b < DB; ++b) acc[b] = f32x16{0};
         }
         if (keys) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int back = query - (32 * w + ln.acc_row(i));
+            for (int i = 0; i < 16; ++i) {   // to the query in its own tile, to the tile's end in those before
+                const int back = (w == t ? ln.r : 31) - ln.acc_row(i);
                 s[i] = back >= 0 ? s[i] * pw[back < 0 ? 0 : back] : 0.0f;
             }
 #pragma unroll
@@ -443,13 +464,21 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
                 for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(values[m][b]), pf, acc[b]);
             }
         }
-        if (keys || state) put();
+        if (keys) put(w);
         __syncthreads();
-        const int waves = t + 1 + (kv_in && t + 1 < kShortWaves ? 1 : 0);
+        const f32x2 tile = factor[32];
         for (int i = threadIdx.x; i < PART / 4; i += 64 * kShortWaves) {
             const Lane of(i);
             const int token = 32 * t + of.r, feature = 8 * (i >> 6) + 4 * of.h;
-            if (token < ntok) *(f32x4 *)(O + (size_t)token * D + feature) = total(i, waves);
+            f32x4 x = {0, 0, 0, 0};
+            for (int v = 0; v < t; ++v) x = decayed(tile, x, part(v, i));
+            x = decayed(factor[of.r + 1], x, part(t, i));
+            if (kv_in) {
+                const f32x4 in = part(kShortWaves, i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = (float)fma(up, (double)in[e], (double)x[e]);
+            }
+            if (token < ntok) *(f32x4 *)(O + (size_t)token * D + feature) = x;
         }
     } else {
         const int c = 32 * (blockIdx.x - ntiles) + ln.r;
@@ -468,30 +497,42 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
         }
         __syncthreads();   // the powers
         if (w < ntiles) {
+            F v[NKS];
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const int after = ntok - 1 - (32 * w + ks * E::KSTEP + 8 * ln.h + e);
+                    const int after = min(32, ntok - 32 * w) - 1 - (ks * E::KSTEP + 8 * ln.h + e);
                     y[ks][e] *= pw[after < 0 ? 0 : after];   // (past the end: zero times one)
                 }
-                const F v = split(y[ks]);
-#pragma unroll
-                for (int b = 0; b < DB; ++b) acc[b] = E::mfma(split(x[ks][b]), v, acc[b]);
+                v[ks] = split(y[ks]);
             }
-            put();
+#pragma unroll
+            for (int b = 0; b < DB; ++b) {
+                f32x16 low = {0};
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    const F k = split(x[ks][b]);
+                    low = E::mfma_low(k, v[ks], low);
+                    acc[b] = E::mfma_high(k, v[ks], acc[b]);
+                }
+                acc[b] += low;
+            }
+            put(w);
         }
         __syncthreads();
-        const float whole = pw[ntok];
+        const f32x2 tile = factor[32];
         for (int i = threadIdx.x; i < PART / 4; i += 64 * kShortWaves) {
             const Lane of(i);
-            f32x4 x = total(i, ntiles);
+            f32x4 x = {0, 0, 0, 0};
             const size_t at = ((size_t)chain * D + 8 * (i >> 6) + 4 * of.h) * D + 32 * (blockIdx.x - ntiles) + of.r;
+            for (int v = 0; v + 1 < ntiles; ++v) x = decayed(tile, x, part(v, i));
+            x = decayed(factor[ntok - 32 * (ntiles - 1)], x, part(ntiles - 1, i));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (kv_in) {
                     const float in = kv_in[at + e * D];
-                    x[e] += whole * in;
+                    x[e] = (float)fma(up, (double)in, (double)x[e]);
                     if (kv_copy) kv_copy[at + e * D] = in;
                 }
                 kv_out[at + e * D] = x[e];
@@ -501,7 +542,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
 }
 template <int D>
 static hipError_t run_short(const Plan &p, const FwdArgs &a, hipStream_t s, const KernelEvents *ke) {
-    constexpr size_t lds = (kShortWaves * D / 32 * 1024 + kShortTokens + 4) * sizeof(float);
+    constexpr size_t lds = ((kShortWaves + 1) * D / 32 * 1024 + 3 * 34) * sizeof(float);
     static_assert(lds <= 163840, "LDS of one CU");
     if (hipError_t e = allow_dynamic_lds((const void *)k_short<D>, lds); e != hipSuccess) return e;
     if (ke)

@@ -100,3 +100,62 @@ def test_small_magnitudes(gpu, oracle, D, scale):
     got, ref = run(harness, oracle, inp)
     for name in ("out", "kv_out", "dq", "dk", "dv", "dkv_in"):
         close(name, got[name], ref[name])
+
+
+# Forward calls without a cache (up to 256 tokens and 32 heads: k_short; decay 0.5 falls below the smallest float within 256 tokens)
+def forward_alone(gpu, oracle, D, lam, N=256):
+    harness, si = gpu
+    inp = make(si, N, D, D, False)
+    if lam is not None:
+        inp = replace(inp, decay=np.full_like(inp.decay, lam))
+    with np.errstate(all="ignore"):
+        o, kvo = oracle.dims_fwd_brute(inp.q, inp.k, inp.v, inp.decay, inp.kv_in)
+    return inp, dict(out=o, kv_out=kvo), lambda: harness.run_gpu(inp, backward=False)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("lam", [None, 0.5])
+@pytest.mark.parametrize("value", [np.inf, np.nan, -np.inf])
+@pytest.mark.parametrize("N,s", [(256, 10), (250, 200)])
+def test_non_finite_value_forward_alone(gpu, oracle, D, lam, value, N, s):
+    inp, ref, run_it = forward_alone(gpu, oracle, D, lam, N)
+    print(f"case forward alone D={D} lambda={lam} value={value} N={N}", flush=True)
+    c = 13
+    inp.v[0, 1, s, c] = value
+    got = run_it()
+    ref["kv_out"][0, 1, :, c] = value
+    close("kv_out", got["kv_out"], ref["kv_out"])
+    ref["out"][0, 1, s:, c] = value
+    rows = np.r_[0:s // TILE * TILE, s:N]
+    close("out", got["out"][:, :, rows], ref["out"][:, :, rows])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("lam", [None, 0.5])
+@pytest.mark.parametrize("N", [100, 230, 256])   # (256: the state's part on a wave that has keys too)
+@pytest.mark.parametrize("value", [np.inf, np.nan, -np.inf])
+def test_non_finite_state_forward_alone(gpu, oracle, D, lam, N, value):
+    inp, ref, run_it = forward_alone(gpu, oracle, D, lam, N)
+    print(f"case forward alone, state, D={D} lambda={lam} value={value} N={N}", flush=True)
+    inp.kv_in[0, 1, 5, 40] = value
+    got = run_it()
+    ref["kv_out"][0, 1, 5, 40] = value
+    ref["out"][0, 1, :, 40] = value
+    for name in ("out", "kv_out"):
+        close(name, got[name], ref[name])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_largest_finite_values_forward_alone(gpu, oracle, D):
+    inp, _, run_it = forward_alone(gpu, oracle, D, None)
+    big = np.finfo(np.float32).max
+    inp.k[0, 0, 40] = big
+    inp.kv_in[0, 1, 3, 50] = big
+    for x in (inp.q, inp.v):
+        x *= np.float32(1e-3)
+    print(f"case forward alone, largest, D={D}", flush=True)
+    o, kvo = oracle.dims_fwd_brute(inp.q, inp.k, inp.v, inp.decay, inp.kv_in)
+    assert np.isfinite(o).all() and np.abs(o).max() < big and np.abs(kvo).max() <= big
+    got = run_it()
+    for name, r in (("out", o), ("kv_out", kvo)):
+        close(name, got[name], r)

@@ -80,3 +80,18 @@ def test_short_float_forward(oracle, N, D, kv_heads, states):
         emax, efro = harness.rel_errors(x.cpu().numpy(), r)
         print(f"  {name:7s} max-rel {emax:.3e} fro-rel {efro:.3e}", flush=True)
         assert np.isfinite(emax) and emax <= 1e-5 and efro <= 1e-6, name   # fp32 sums of at most 256 terms: 256^0.5 2^-24
+
+
+@pytest.mark.parametrize("D,N", [(64, 100), (128, 256)])
+def test_short_float_forward_keeps_the_entering_state(D, N):
+    """A sequence object without a backward pass: the copy of the entering state comes with the launch."""
+    import torch
+    from paper_2404_02882_amd.sequence import LaspSequence
+    g = torch.Generator(device="cuda").manual_seed(N)
+    new = lambda *s: torch.randn(*s, generator=g, device="cuda")   # noqa: E731
+    q, k, v, kv_in = new(1, 4, N, D), new(1, 4, N, D), new(1, 4, N, D), new(1, 4, D, D)
+    seq = LaspSequence(1, 4, N, D, 64, torch.float32, need_backward=False)
+    seq.kv[0].fill_(float("nan"))
+    print(f"case kv copy D={D} N={N}", flush=True)
+    seq.forward([q], [k], [v], torch.full((4,), 0.97, device="cuda"), [torch.empty_like(q)], kv_in)
+    assert torch.equal(seq.kv[0], kv_in)
