@@ -364,6 +364,8 @@ hipError_t launch_bidir_state(const BidirPlan &p, const void *x, const void *y, 
 
 // The apply pass keeps no state between tiles, so it reads long tiles: 128 tokens of bfloat16,
 // 64 of float (more bytes in flight per workgroup, fewer barriers).
+int bidir_product_tile(int dtype) { return dtype == 0 ? 64 : 128; }
+
 template <int N>
 static hipError_t products_of(const BidirPlan &p, const BidirProducts &a, hipStream_t s, const KernelEvents *ke) {
     if (p.dtype == 0) return p.D == 64 ? run_bidir_apply<float, 64, 64, N>(p, a, s, ke) : run_bidir_apply<float, 64, 128, N>(p, a, s, ke);

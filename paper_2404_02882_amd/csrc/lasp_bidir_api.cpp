@@ -6,6 +6,7 @@
 
 #include "lasp_checks.h"
 #include "lasp_internal.h"
+#include "lasp_rules.h"
 
 namespace {
 
@@ -31,11 +32,16 @@ BidirPlan group_plan(const lasp_shape *shapes, int n) {
 // Sub-sequences of a launch: as many as there is room for, but one by one where the caller chose the segments of each.
 int group_size(const lasp_shape *shapes, int T) { return shapes[0].segments != 0 ? 1 : std::min(T, kMaxShards); }
 
-// Whether dQ comes with the sum dKV = Q^T dO, which has dO on chip, or with the other two products. At d = 128 a reduction of one
-// tile a workgroup is all latency, and the product makes it longer while the other launch has CUs to spare. Forward + backward,
-// dQ apart / with the sum, us: d=128 16 heads x 512 tokens (one tile) 35.5 / 38.9, 2 x 8192 (one) 58.4 / 61.0, 16 x 2000 (two) 51.9 /
-// 50.0, 16 x 16384 187.6 / 180.6, 128 x 8192 657 / 602; d=64 16 x 512 27.9 / 24.2, 2 x 8192 39.4 / 39.9, 128 x 8192 346 / 328.
-bool dq_with_sum(const BidirPlan &p) { return p.D == 64 || p.tiles_per_seg >= 2; }
+// Whether dQ comes with the sum over the first `n` sub-sequences (all but the last launches take as many).
+bool dq_with_sum(const lasp_shape *shapes, int n) {
+    const BidirPlan p = group_plan(shapes, n);
+    const int tile = lasp::bidir_product_tile(p.dtype);
+    int tiles = 0;
+    for (int t = 0; t < n; ++t) tiles += (shapes[t].N + tile - 1) / tile;
+    const long long chains = (long long)p.B * p.H, three = lasp::blocks_time(tiles, 3 * chains, lasp::kBidirTargetWorkgroups),
+                    two = lasp::blocks_time(tiles, 2 * chains, lasp::kBidirTargetWorkgroups);
+    return lasp::dq_with_sum(p.dtype == LASP_BF16, p.D, chains, p.tiles_per_seg, p.nseg, three - two);
+}
 
 int check_shapes(const lasp_shape *shapes, int32_t T) {
     if (!shapes) return LASP_ERR_NULL;
@@ -164,7 +170,7 @@ int lasp_bidir_seq_bwd(const lasp_shape *shapes, int32_t T, const void *const *q
     // Where a gradient takes the place of something that is still read then (dQ that of Q, say): all three behind the sum, one
     // sub-sequence after the other.
     const bool apart = all.disjoint();
-    const bool ok = apart && dq_with_sum(group_plan(shapes, std::min(group, T)))
+    const bool ok = apart && dq_with_sum(shapes, std::min(group, T))
                         ? sums(shapes, T, group, q, dout, dkv, scratch, dq, kv, s, 1) && products(shapes, T, group, {of_k, of_v}, s, 1)
                         : sums(shapes, T, group, q, dout, dkv, scratch, nullptr, nullptr, s, 1) &&
                               products(shapes, T, apart ? group : 1, {of_q, of_k, of_v}, s, 1);

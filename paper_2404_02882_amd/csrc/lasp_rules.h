@@ -90,5 +90,29 @@ inline Blocks blocks_for(int ntiles, long long chains, int slots) {
     return best;
 }
 
+
+// Rounds x tiles of a launch of blocks_for(): what it takes in tiles, one workgroup behind the other.
+inline long long blocks_time(int ntiles, long long chains, int slots) {
+    const Blocks b = blocks_for(ntiles, chains, slots);
+    return (chains * b.count + slots - 1) / slots * b.tiles;
+}
+
+// Bidirectional backward: whether dQ = dO KV^T comes with the sum dKV = Q^T dO, which has dO on chip, or with the products for dK
+// and dV. In the sum's launch (segments of tiles_per_seg tiles, chains x nseg workgroups, one a CU) a tile's product takes longer,
+// by about a fifth of what a tile takes in the products' launch, which is `saved` (blocks_time) shorter with two products than
+// with three. And the sum has to fill the CUs, else the product waits on few of them: from 13/16 of them on (float, whose products
+// are longer, 3/4). At d = 64 and so many heads that a block of one head is more than half of the slots, three products fill the
+// device as well as two: only bfloat16, and only long segments. Forward + backward, dQ apart / with the sum, us:
+//   bf16 d=128 16 heads x 1024 tokens (one tile) 44.3 / 45.3, x 1152 (144 workgroups) 42.8 / 46.7, 32 x 636 (160) 43.4 / 46.1, 16 x 2048 (two
+//   tiles) 51.2 / 49.5, 128 x 512 74.0 / 72.4, 3 x 16512 (258 workgroups) 68.0 / 72.2, 100 x 1920 (300, ten tiles) 166 / 146, 16 x 16384 (16)
+//   187.6 / 180.6, 128 x 8192 657 / 602; d=64 16 x 2048 30.7 / 28.3, 128 x 768 44.1 / 46.6, 128 x 2048 87.2 / 85.9, 128 x 8192 346 / 328;
+//   float d=64 32 x 384 (192 workgroups) 32.0 / 34.1, 64 x 256 39.9 / 35.6, 128 x 512 79.1 / 85.4; d=128 64 x 512 105.9 / 100.8.
+inline bool dq_with_sum(bool two_byte, int D, long long chains, int tiles_per_seg, int nseg, long long saved) {
+    const long long workgroups = chains * nseg, rounds = (workgroups + kOnePerCu - 1) / kOnePerCu;
+    if (two_byte ? 16 * workgroups < 13 * kOnePerCu : 4 * workgroups <= 3 * kOnePerCu) return false;
+    if (D == 64 && 3 * chains > kOnePerCu) return two_byte && tiles_per_seg >= 16;
+    return 5 * saved >= rounds * tiles_per_seg + 3;
+}
+
 }  // namespace lasp
 #endif

@@ -7,6 +7,8 @@ import sys
 import numpy as np
 import pytest
 
+from test_sequence_launches import DQ_WITH_SUM
+
 pytestmark = pytest.mark.gpu
 
 TOL = {"f32": 1e-4, "bf16": 2e-2}
@@ -137,8 +139,8 @@ def test_b3_full_size(gpu, oracle):
         assert emax <= TOL["bf16"] and efro <= TOL["bf16"], nm
 
 
-# Sub-sequences that share a launch (tiles numbered over all of them; five: a group of four and one), the gradient of q with the
-# sum over (Q, dO) or apart from it (d=128, one tile a workgroup), lengths below and above a tile.
+# Sub-sequences that share a launch (tiles numbered over all of them; five: a group of four and one), lengths below and above a tile.
+# (The gradient of q apart from the sum over (Q, dO): too few heads.)
 @pytest.mark.parametrize("dtype,D,lengths", [("bf16", 128, [1, 63, 64, 65, 130]), ("bf16", 128, [4500, 129]), ("bf16", 64, [64, 1, 127, 200]),
                                              ("f32", 128, [33, 1, 31]), ("f32", 64, [70, 32, 5, 64, 31])])
 def test_shared_launches(gpu, oracle, dtype, D, lengths):
@@ -147,6 +149,18 @@ def test_shared_launches(gpu, oracle, dtype, D, lengths):
     say(f"case bidir shared dtype={dtype} D={D} lengths={lengths}")
     inp = si.make_inputs(cfg)
     compare(harness, harness.run_gpu_bidir(inp, lengths=lengths), oracle_all(oracle, inp), TOL[dtype], "bshare")
+
+
+# The gradient of q with the sum over (Q, dO) (test_sequence_launches.py has the launches), tiles of one and of several sub-sequences
+# in a segment, short last tiles. (The first, a middle and the last head are compared.)
+@pytest.mark.parametrize("dtype,D,H,lengths", DQ_WITH_SUM + [("bf16", 64, 64, [512]), ("bf16", 128, 64, [450]), ("f32", 64, 64, [250])])
+def test_dq_with_the_sum(gpu, oracle, dtype, D, H, lengths):
+    harness, lasp, si = gpu
+    cfg = si.Config("bwith", B=1, H=H, N=sum(lengths), D=D, chunk=64, dtype=dtype, seed=660 + D + len(lengths), decay="one", bidirectional=True)
+    say(f"case bidir dQ with the sum dtype={dtype} D={D} H={H} lengths={lengths}")
+    inp = si.make_inputs(cfg)
+    heads = [0, H // 2, H - 1]
+    compare(harness, harness.run_gpu_bidir(inp, lengths=lengths), oracle_all(oracle, inp, heads), TOL[dtype], "bwith", heads)
 
 
 def test_gradients_in_place(gpu):

@@ -1,4 +1,4 @@
-"""What the host layer of a whole sequence (lasp_seq_fwd, lasp_seq_bwd) checks, launches and copies: csrc/lasp_api.cpp built
+"""What the host layer of a whole sequence (lasp_seq_*, lasp_bidir_seq_*) checks, launches and copies: csrc/lasp*_api.cpp built
 with the host compiler against launches that only write down what they were asked for. Addresses are never dereferenced."""
 import ctypes
 import os
@@ -9,14 +9,17 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2404_02882_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+PIECES_OF_A_SHARD = [(96, 64 * 12), (128, 64 * 12 - 37), (96, 64 * 14), (128, 64 * 13 + 1), (86, 64 * 15 - 5)]   # heads, tokens; bf16, d=128
 ERR_NULL, ERR_SHAPE, ERR_WORKSPACE, ERR_ALIAS, ERR_ALIGN = 1, 2, 5, 6, 8
 
 RECORDER = r"""
 #include "%(csrc)s/lasp_internal.h"
+#include "%(csrc)s/lasp_rules.h"
 #include <cstring>
-namespace { int n; long long rec[256][8]; }
+namespace { int n; long long rec[256][9]; }
 static hipError_t put(int kind, int shards, const void *a, const void *b, const void *c, const lasp::Plan *p = nullptr) {
-    long long r[8] = {kind, shards, (long long)a, (long long)b, (long long)c, p && p->own_states, p ? p->nseg : 0, p ? p->scratch_segs : 0};
+    long long r[9] = {kind, shards, (long long)a, (long long)b, (long long)c, p && p->own_states, p ? p->nseg : 0, p ? p->scratch_segs : 0,
+                      p ? lasp::local_pieces(p->shards * p->nseg, p->tiles_per_seg, (long long)p->B * p->H) : 0};
     std::memcpy(rec[n++ & 255], r, sizeof r);
     return hipSuccess;
 }
@@ -29,7 +32,10 @@ extern "C" int recorded(long long *out) {
 namespace lasp {
 int tile_tokens(int dtype, int, int) { return dtype == 0 ? 32 : 64; }
 hipError_t static_scratch(void **) { return hipErrorUnknown; }
-int bidir_reduce_tile(int) { return 64; }
+int bidir_reduce_tile(int dtype) { return dtype == 0 ? 32 : 64; }
+int bidir_product_tile(int dtype) { return dtype == 0 ? 64 : 128; }
+hipError_t launch_bidir_sums(const BidirPlan &, const BidirSums &a, hipStream_t, const KernelEvents *) { return put(4, a.n, a.x[0], a.dq ? a.dq[0] : nullptr, nullptr); }
+hipError_t launch_bidir_products(const BidirPlan &, const BidirProducts &a, hipStream_t, const KernelEvents *) { return put(4 + a.nops, a.n, a.x[0][0], a.out[0][0], nullptr); }
 hipError_t launch_fwd(const Plan &p, const FwdArgs &a, hipStream_t, const KernelEvents *) {
     return put(a.states_only ? 2 : 0, p.shards, a.k, a.kv_in, a.kv_copy, &p);
 }
@@ -58,9 +64,9 @@ def api(tmp_path_factory):
     src, lib = d / "recorder.cpp", d / "recorder.so"
     src.write_text(RECORDER % dict(csrc=CSRC))
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{ROOT}/include",
-                    str(src), os.path.join(CSRC, "lasp_api.cpp"), "-o", str(lib)], check=True)
+                    str(src), os.path.join(CSRC, "lasp_api.cpp"), os.path.join(CSRC, "lasp_bidir_api.cpp"), "-o", str(lib)], check=True)
     handle = ctypes.CDLL(str(lib), mode=os.RTLD_LOCAL | os.RTLD_NOW)
-    lasp._bind(handle)
+    lasp._bind_bidir_sequence(lasp._bind(handle))
     return Api(handle, lasp)
 
 
@@ -85,10 +91,11 @@ class Api:
         self.lib, self.lasp = lib, lasp
 
     def record(self):
-        out = (ctypes.c_longlong * (256 * 8))()
+        out = (ctypes.c_longlong * (256 * 9))()
         n = self.lib.recorded(out)
-        return [tuple(out[8 * i:8 * i + 8]) for i in range(n)]   # kind (0 forward, 1 backward, 2 states, 3 copy), shards, k, in,
-                                                                  # copy, own start states, segments, segments in the scratch
+        return [tuple(out[9 * i:9 * i + 9]) for i in range(n)]   # kind (0 forward, 1 backward, 2 states, 3 copy), shards, k, in,
+                                                                  # copy, own start states, segments, segments in the scratch,
+                                                                  # pieces of a segment in the local pass
 
     def shape(self, H=4, N=1024, D=64, dtype="bf16", **kw):
         return self.lasp.make_shape(1, H, N, D, 64, dtype, **kw)
@@ -342,3 +349,52 @@ def test_rejects_before_launch(api):
     for at in (2, 3, 4, 7, 8, 10, 13, 14, 15, 17):
         assert lib.lasp_seq_bwd(*args[:at], None, *args[at + 1:]) == ERR_NULL
     assert api.record() == []
+
+
+def test_local_pass_of_two_sub_sequences_in_pieces(api):
+    """(The sequences that the GPU test of pieces in shared launches takes: one segment each, two pieces of it, in both passes.)"""
+    for H, n in PIECES_OF_A_SHARD:
+        shape, s = api.shape(H, n, 128), Sequence(2)
+        for cache in (True, False):
+            for rc, r in (api.fwd(shape, 2, s, cache=cache), api.bwd(shape, 2, s, cache=cache, norm=True)):
+                assert rc == 0 and len(r) in (1, 2) and all((x[1], x[6], x[8]) == (2, 1, 2) for x in r), (H, n, r)
+
+
+# Bidirectional sequences whose dQ comes with the sum: dtype, d, heads, lengths (the GPU test takes them, too)
+DQ_WITH_SUM = [("bf16", 64, 64, [192, 200]), ("bf16", 128, 64, [200, 129, 1]), ("f32", 64, 64, [100, 97]), ("f32", 128, 64, [200, 40, 5, 1])]
+
+
+def bidir(api, dtype, D, H, lengths, moved=()):
+    """Records of the forward and of the backward call: (4 sum / 4 + number of products, sub-sequences, first input, first output)."""
+    T, s = len(lengths), Sequence(len(lengths))
+    for a, i, b, j in moved:
+        getattr(s, a)[i] = getattr(s, b)[j]
+    shapes = (api.lasp.Shape * T)(*[api.shape(H, n, D, dtype) for n in lengths])
+    size = api.lib.lasp_bidir_seq_scratch_bytes(shapes, T)
+    t = api.table
+    fwd = api.lib.lasp_bidir_seq_fwd(shapes, T, t(s.q), t(s.k), t(s.v), s.kv_in, t(s.out), s.scratch, size, None), api.record()
+    bwd = api.lib.lasp_bidir_seq_bwd(shapes, T, t(s.q), t(s.k), t(s.v), t(s.dout), s.kv_in, s.dkv_out, t(s.dq), t(s.dk), t(s.dv), s.scratch,
+                                     size, None), api.record()
+    return s, fwd, bwd
+
+
+def test_bidirectional_launches(api):
+    """Up to four sub-sequences a launch; dQ with the sum where that fills the device and is long enough to pay, with the other
+    products elsewhere; an output over another sub-sequence's input: one by one, dQ behind the sum."""
+    for dtype, D, H, lengths in DQ_WITH_SUM:
+        s, (rc, f), (rc2, b) = bidir(api, dtype, D, H, lengths)
+        n = len(lengths)
+        assert rc == rc2 == 0 and [x[:4] for x in f] == [(4, n, s.k[0], 0), (5, n, s.q[0], s.out[0])]
+        assert [x[:4] for x in b] == [(4, n, s.q[0], s.dq[0]), (6, n, s.v[0], s.dk[0])], (dtype, D)
+    apart = [("bf16", 128, 16, [1152]), ("bf16", 128, 32, [636]), ("bf16", 128, 2, [8192]), ("bf16", 128, 3, [16512]), ("bf16", 64, 128, [768]),
+             ("bf16", 64, 3, [64, 1, 127, 200]), ("f32", 64, 128, [1024]), ("f32", 64, 2, [21705]), ("f32", 64, 32, [384])]
+    for dtype, D, H, lengths in apart:
+        s, _, (rc, b) = bidir(api, dtype, D, H, lengths)
+        assert rc == 0 and [x[:4] for x in b] == [(4, len(lengths), s.q[0], 0), (7, len(lengths), s.dout[0], s.dq[0])], (dtype, D, H)
+    s, (rc, f), (rc2, b) = bidir(api, "bf16", 64, 64, [192] * 5)
+    assert rc == rc2 == 0 and [x[:2] for x in f] == [(4, 4), (4, 1), (5, 4), (5, 1)] and [x[:2] for x in b] == [(4, 4), (4, 1), (6, 4), (6, 1)]
+    for moved in (("dq", 0, "q", 0), ("dk", 1, "k", 0), ("dv", 0, "dout", 1)):
+        s, _, (rc, b) = bidir(api, "bf16", 64, 64, [192, 192], [moved])
+        assert rc == 0 and [x[:2] for x in b] == [(4, 2), (7, 1), (7, 1)] and b[0][3] == 0, moved
+    s, (rc, f), _ = bidir(api, "bf16", 64, 64, [192, 192], [("out", 0, "q", 1)])
+    assert rc == 0 and [x[:2] for x in f] == [(4, 2), (5, 1), (5, 1)]
