@@ -1,5 +1,5 @@
-"""GPU parity of the bidirectional entry points (lasp_bidir_state / lasp_bidir_fwd / lasp_bidir_bwd,
-called through the C-ABI) against the fp64 oracle's definition O = (Q K^T) V on the same seeded
+"""GPU parity of the bidirectional entry points (whole sequences: lasp_bidir_seq_*, one sub-sequence's part:
+lasp_bidir_state / lasp_bidir_fwd / lasp_bidir_bwd, called through the C-ABI) against the fp64 oracle's definition O = (Q K^T) V on the same seeded
 inputs. Tolerances as for the causal path (per tensor, max-norm and Frobenius relative error):
 1e-4 for float data, 2e-2 for bfloat16 data. Outputs and states are pre-filled with NaN."""
 import sys
@@ -179,3 +179,31 @@ def test_gradients_in_place(gpu):
     seq.backward(q, k, v, do, q, [dk[0], k[0]], [dv[0], v[0]])   # (the second sub-sequence's dk, dv over the first's k, v)
     assert all(torch.equal(a, b) for a, b in zip(q + [dk[0], k[0], dv[0], v[0]], want))
     assert not torch.equal(kept, k[0])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_one_sub_sequence_after_the_other(gpu, oracle, dtype, D):
+    """The loop of a caller who sums partial states himself: states of all sub-sequences, then the products of each."""
+    import torch
+    harness, lasp, si = gpu
+    lengths = [200, 129, 64]
+    cfg = si.Config("bloop", B=1, H=3, N=sum(lengths), D=D, chunk=64, dtype=dtype, seed=650 + D, decay="one", bidirectional=True)
+    say(f"case bidir loop dtype={dtype} D={D}")
+    inp = si.make_inputs(cfg)
+    edges = np.concatenate([[0], np.cumsum(lengths)])
+    cut = lambda x: [harness.to_device(x[:, :, a:b], dtype) for a, b in zip(edges[:-1], edges[1:])]   # noqa: E731
+    q, k, v, do = (cut(x) for x in (inp.q, inp.k, inp.v, inp.dout))
+    out, dq, dk, dv = ([torch.full_like(x, float("nan")) for x in q] for _ in range(4))
+    kv, dkv = (torch.full((1, 3, D, D), float("nan"), device="cuda") for _ in range(2))
+    shapes = [lasp.make_shape(1, 3, n, D, 64, dtype) for n in lengths]
+    scratch = torch.empty(max(lasp.bidir_scratch_bytes(s) for s in shapes), dtype=torch.uint8, device="cuda")
+    for t, s in enumerate(shapes):
+        lasp.lasp_bidir_state(s, k[t], v[t], kv, t > 0, scratch)
+        lasp.lasp_bidir_state(s, q[t], do[t], dkv, t > 0, scratch)
+    for t, s in enumerate(shapes):
+        lasp.lasp_bidir_fwd(s, q[t], kv, out[t])
+        lasp.lasp_bidir_bwd(s, k[t], v[t], do[t], kv, dkv, dq[t], dk[t], dv[t])
+    got = {n: harness.to_host(x) for n, x in dict(out=out, dq=dq, dk=dk, dv=dv).items()}
+    got.update(kv=kv.cpu().numpy().astype(np.float64), dkv=dkv.cpu().numpy().astype(np.float64))
+    compare(harness, got, oracle_all(oracle, inp), TOL[dtype], "bloop")
