@@ -1,7 +1,11 @@
 """The state cache serves a backward call with another `segments` than the forward call's (the cut into segments is
 each call's own affair), against the fp64 oracle. Tolerances 1e-4 float, 2e-2 bfloat16 as everywhere."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
+
+from test_sequence_launches import PIECES_OF_A_SHARD
 
 pytestmark = pytest.mark.gpu
 
@@ -89,9 +93,9 @@ def test_odd_segments(gpu, oracle, N, segments, D, Dv, kv_heads, token, norm):
 
 
 # Two segments, of which the local pass cuts the one it sums in two pieces (local_pieces, from 12 tiles a segment on): the shortest
-# that is cut, one tile less, pieces of an odd number of 64-token tiles, short last tiles, a last segment of a single piece or
-# little more.
-@pytest.mark.parametrize("dtype,N", [("bf16", 64 * 24), ("bf16", 64 * 22), ("bf16", 64 * 25 + 1), ("bf16", 64 * 23 - 37), ("bf16", 64 * 28),
+# that is cut (22 tiles: 12 and 10 of them), the longest that is not (20), pieces of an odd number of 64-token tiles, short last
+# tiles, a last segment of a single piece or little more.
+@pytest.mark.parametrize("dtype,N", [("bf16", 64 * 24), ("bf16", 64 * 22), ("bf16", 64 * 20), ("bf16", 64 * 25 + 1), ("bf16", 64 * 23 - 37), ("bf16", 64 * 28),
                                      ("f32", 32 * 24), ("f32", 32 * 23 + 7), ("f32", 32 * 28 - 1)])
 @pytest.mark.parametrize("D,Dv,token,norm", [(128, 128, False, False), (64, 64, True, False), (64, 128, False, True), (128, 128, True, True)])
 def test_local_pass_in_pieces(gpu, oracle, dtype, N, D, Dv, token, norm):
@@ -102,11 +106,27 @@ def test_local_pass_in_pieces(gpu, oracle, dtype, N, D, Dv, token, norm):
     check(harness, oracle, inp, dtype, norm, harness.run_gpu(inp, segments=2, norm_eps=1e-5 if norm else None))
 
 
-# The same in launches that two sub-sequences share, each in one segment (72 heads).
-@pytest.mark.parametrize("dtype,n", [("bf16", 64 * 12), ("bf16", 64 * 13 - 5), ("f32", 32 * 13 - 3)])
-def test_local_pass_in_pieces_of_a_shard(gpu, oracle, dtype, n):
+# The same in launches that two sub-sequences share, each in one segment: 86 to 128 heads at d=128 (test_sequence_launches.py has
+# the plans), pieces of an even and an odd number of tiles, short last tiles. (The first, a middle and the last head are compared.)
+@pytest.mark.parametrize("H,n", PIECES_OF_A_SHARD)
+@pytest.mark.parametrize("norm", [False, True])
+def test_local_pass_in_pieces_of_a_shard(gpu, oracle, H, n, norm):
     harness, lasp, si = gpu
-    cfg = si.Config("pieces", B=1, H=72, N=2 * n, D=64, chunk=64, dtype=dtype, seed=8800 + n)
+    cfg = si.Config("pieces", B=1, H=H, N=2 * n, D=128, chunk=64, dtype="bf16", seed=8800 + n)
+    inp = si.make_inputs(cfg, with_states=True)
+    print(f"case H={H} 2 x {n} norm={norm}", flush=True)
+    got = harness.run_gpu(inp, T=2, norm_eps=1e-5 if norm else None)
+    heads = [0, H // 2, H - 1]
+    few = replace(inp, decay=inp.decay[heads], **{x: np.ascontiguousarray(getattr(inp, x)[:, heads])
+                                                  for x in ("q", "k", "v", "dout", "kv_in", "dkv_out")})
+    check(harness, oracle, few, "bf16", norm, {x: y[:, heads] for x, y in got.items()})
+
+
+# 72 heads at d=64, two sub-sequences of three or seven segments: a shared launch that is scanned, or one by one.
+@pytest.mark.parametrize("dtype,n", [("bf16", 64 * 12), ("bf16", 64 * 13 - 5), ("f32", 32 * 13 - 3)])
+def test_two_sub_sequences_of_several_segments(gpu, oracle, dtype, n):
+    harness, lasp, si = gpu
+    cfg = si.Config("several", B=1, H=72, N=2 * n, D=64, chunk=64, dtype=dtype, seed=8800 + n)
     inp = si.make_inputs(cfg, with_states=True)
     print(f"case {dtype} 2 x {n}", flush=True)
     check(harness, oracle, inp, dtype, False, harness.run_gpu(inp, T=2))
