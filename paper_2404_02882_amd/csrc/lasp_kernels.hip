@@ -20,9 +20,12 @@ namespace lasp {
 // With per-token decay the factor of segment j is 2^seglog[chain][j] (written by k_local).
 // SHARED: over the segments of several sub-sequences (nslots), counting where each ends. In launches of one that counting took
 // the scan over 87 segments of one head from 12.2 to 13.3 us, over 33 of 16 heads, d=64, from 6.0 to 6.5: its own instance.
-// U: segments whose local states are fetched together. The scan is a chain of as many waits for memory as it has such batches:
-// steps with 8 / 16 / 32, us: 2 heads x 32768 tokens (128 segments) 117.8 / 115.1 / 111.3, 16 x 1024 x 4, d=64 (32) 58.8 / 58.2 / 59.1,
-// 16 x 2048 (16) 73.8 / 74.8 / 75.8: the line for each count below.
+// U: segments whose local states are fetched together. The scan is a chain of as many waits for memory as it has such batches,
+// but a batch costs its whole length, and where many states are scanned their loads are in flight side by side anyway. Steps with
+// 8 / 16 / 32, us: 2 heads x 32768 tokens (128 segments) 117.8 / 115.1 / 111.3, 2 x 6031 (48) 61.0 / 59.8 / 60.3, 2 x 1280 (10) 42.1 / 41.7 / 43.0,
+// d=64 8 x 8192 (64) 58.6 / 57.2 / 56.4; 16 x 2048 (16) 73.8 / 74.8 / 75.8; float 1 x 1400 (44) 61.2 / 60.2 / 60.5, 8 x 895 x 4 (112, twice the
+// states) 213.4 / 213.2 / 214.6. With a decay per token, whose factors are computed, long batches pay later: 2 x 2300 (18) 56.0 / 56.5 /
+// 56.8, 2 x 2080 (33) 50.7 / 50.8 / 53.5, 2 x 16384 (128) 109.2 / 106.4 / 106.6.
 template <bool BWD, bool TOKEN, bool SHARED, int U>
 __global__ __launch_bounds__(256) void k_scan(float *__restrict__ scratch, const float *__restrict__ boundary,
                                               const float *__restrict__ decay, const float *__restrict__ seglog,
@@ -68,8 +71,9 @@ hipError_t launch_scan(const Plan &p, bool bwd, float *states, const float *boun
                : bwd        ? (p.token ? k_scan<true, true, false, U> : k_scan<true, false, false, U>)
                             : (p.token ? k_scan<false, true, false, U> : k_scan<false, false, false, U>);
     };
-    const auto kernel = nslots <= 16 ? of(std::integral_constant<int, 8>{})
-                        : nslots <= 32 ? of(std::integral_constant<int, 16>{}) : of(std::integral_constant<int, 32>{});
+    const bool few_states = (long long)p.B * p.H * DD <= 65536;   // of four heads at d = 128, 16 at d = 64
+    const auto kernel = nslots <= (p.token ? 22 : 16)               ? of(std::integral_constant<int, 8>{})
+                        : !p.token && nslots >= 48 && few_states ? of(std::integral_constant<int, 32>{}) : of(std::integral_constant<int, 16>{});
     kernel<<<grid, dim3(256), 0, s>>>(states, boundary, p.token ? nullptr : decay, seglog, p.H, DD, p.nseg, nslots,
                                       p.tiles_per_seg * p.tile, p.N);
     return hipGetLastError();
