@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <initializer_list>
+#include <new>
 #include <vector>
 
 #include "../../include/lasp.h"
@@ -54,15 +55,21 @@ class Together {
         bool out;
     };
     std::vector<Item> items;
+    bool full = false;   // no memory to note them all: not together, then
+    void note(const void *p, size_t n, bool out) {
+        if (!p || full) return;
+        try {
+            items.push_back({(const char *)p, (const char *)p + n, out});
+        } catch (const std::bad_alloc &) {
+            full = true;
+        }
+    }
 
 public:
-    void in(const void *p, size_t n) {
-        if (p) items.push_back({(const char *)p, (const char *)p + n, false});
-    }
-    void out(const void *p, size_t n) {
-        if (p) items.push_back({(const char *)p, (const char *)p + n, true});
-    }
+    void in(const void *p, size_t n) { note(p, n, false); }
+    void out(const void *p, size_t n) { note(p, n, true); }
     bool disjoint() {
+        if (full) return false;
         std::sort(items.begin(), items.end(), [](const Item &a, const Item &b) { return a.begin < b.begin; });
         const char *any_end = nullptr, *out_end = nullptr;   // ends of what has begun so far
         for (const Item &x : items) {

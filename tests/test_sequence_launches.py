@@ -15,8 +15,17 @@ ERR_NULL, ERR_SHAPE, ERR_WORKSPACE, ERR_ALIAS, ERR_ALIGN = 1, 2, 5, 6, 8
 RECORDER = r"""
 #include "%(csrc)s/lasp_internal.h"
 #include "%(csrc)s/lasp_rules.h"
+#include <cstdlib>
 #include <cstring>
-namespace { int n; long long rec[256][9]; }
+#include <new>
+namespace { int n; long long rec[256][9]; bool no_memory; }
+void *operator new(size_t size) {
+    if (no_memory) throw std::bad_alloc();
+    return std::malloc(size);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+extern "C" void out_of_memory(int yes) { no_memory = yes; }
 static hipError_t put(int kind, int shards, const void *a, const void *b, const void *c, const lasp::Plan *p = nullptr) {
     long long r[9] = {kind, shards, (long long)a, (long long)b, (long long)c, p && p->own_states, p ? p->nseg : 0, p ? p->scratch_segs : 0,
                       p ? lasp::local_pieces(p->shards * p->nseg, p->tiles_per_seg, (long long)p->B * p->H) : 0};
@@ -398,3 +407,15 @@ def test_bidirectional_launches(api):
         assert rc == 0 and [x[:2] for x in b] == [(4, 2), (7, 1), (7, 1)] and b[0][3] == 0, moved
     s, (rc, f), _ = bidir(api, "bf16", 64, 64, [192, 192], [("out", 0, "q", 1)])
     assert rc == 0 and [x[:2] for x in f] == [(4, 2), (5, 1), (5, 1)]
+
+
+def test_host_memory_runs_out(api):
+    """What the buffers are compared in cannot be had: one sub-sequence after the other, which needs no comparison."""
+    shape, T, s = api.shape(), 3, Sequence(3)
+    api.lib.out_of_memory(1)
+    try:
+        (rc, f), (rc2, b), (_, (rc3, bf), (rc4, bb)) = api.fwd(shape, T, s), api.bwd(shape, T, s), bidir(api, "bf16", 64, 64, [192, 192])
+    finally:
+        api.lib.out_of_memory(0)
+    assert rc == rc2 == rc3 == rc4 == 0 and groups(f) == groups(b) == [1] * T
+    assert [x[:2] for x in bf] == [(4, 2), (5, 1), (5, 1)] and [x[:2] for x in bb] == [(4, 2), (7, 1), (7, 1)]
