@@ -27,6 +27,8 @@ extern "C" {
  * calls record too: lasp_bidir_state as a forward call (reduction under "local
  * pass", sum of the partials under "scan"), lasp_bidir_fwd as a forward call and
  * lasp_bidir_bwd as a backward call (their one kernel under "tile walk").
+ * lasp_bidir_seq_fwd / _bwd record two calls of their own kind for every launch of
+ * sub-sequences: the sum as lasp_bidir_state does, the products as one kernel.
  * begin: LASP_ERR_SHAPE if max_calls <= 0 or profiling is already on,
  * LASP_ERR_HIP if events cannot be created. end: LASP_ERR_NULL on NULL
  * arguments, LASP_ERR_SHAPE if profiling is off.

@@ -23,7 +23,7 @@ namespace lasp {
 
 // Sub-sequences that a launch takes, at most N, their tiles numbered one after the other.
 template <int N>
-struct Span {
+struct TileSpan {
     int ntok[N];
     int first[N];   // first tile of each (none: beyond all tiles)
     int tiles;      // of all
@@ -36,7 +36,7 @@ struct Distances {
     long long at[N];
 };
 template <int N>
-DEVI int shard_of(const Span<N> &sp, int t) {
+DEVI int shard_of(const TileSpan<N> &sp, int t) {
     int s = 0;
 #pragma unroll
     for (int i = 1; i < N; ++i) s += t >= sp.first[i];
@@ -56,7 +56,7 @@ template <int N, int CT, int D>
 struct Place {
     int shard, nvalid;
     size_t off;
-    DEVI Place(const Span<N> &sp, int chain, int t) : shard(shard_of(sp, t)) {
+    DEVI Place(const TileSpan<N> &sp, int chain, int t) : shard(shard_of(sp, t)) {
         const int ntok = pick(sp.ntok, shard), lt = t - pick(sp.first, shard);
         nvalid = min(CT, ntok - lt * CT);
         off = ((size_t)chain * ntok + (size_t)lt * CT) * D;
@@ -128,7 +128,7 @@ DEVI void write_tile(T *o, const T *sO, int nrows) {
 // ---------------------------------------------------------------------------
 template <typename T, int CT, int D, bool DQ, int N>
 __global__ __launch_bounds__(D * 2, 2) void k_bidir_reduce(const T *__restrict__ X, const T *__restrict__ Y, float *__restrict__ part,
-                                                         Span<N> sp, Distances<N> dx, Distances<N> dy, int nseg, int tiles_per_seg,
+                                                         TileSpan<N> sp, Distances<N> dx, Distances<N> dy, int nseg, int tiles_per_seg,
                                                          T *__restrict__ dQ, Distances<N> ddq, const float *__restrict__ kv) {
     using E = Elem<T>;
     constexpr int NT = D * 2, LDD = tile_ld<T, D>(), DB = D / 32, NKS = CT / E::KSTEP;
@@ -231,7 +231,7 @@ struct Ops {
     Distances<N> dx[3], dout[3];
 };
 template <typename T, int CT, int D, int N>
-__global__ __launch_bounds__(D * 2, 2) void k_bidir_apply(Ops<N> ops, Span<N> sp, int tiles_per_blk) {
+__global__ __launch_bounds__(D * 2, 2) void k_bidir_apply(Ops<N> ops, TileSpan<N> sp, int tiles_per_blk) {
     using E = Elem<T>;
     constexpr int NT = D * 2, LDD = tile_ld<T, D>(), DB = D / 32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(D * 2, 2) void k_bidir_apply(Ops<N> ops, Span<N> sp
 // Host-side launchers. N: sub-sequences of a launch (1 or kMaxShards): launches of one carry fewer arguments and no selects.
 // ---------------------------------------------------------------------------
 template <int N>
-static Span<N> span(int n, const int *ntok, int tile) {
-    Span<N> sp{};
+static TileSpan<N> span(int n, const int *ntok, int tile) {
+    TileSpan<N> sp{};
     for (int i = 0; i < N; ++i) {
         sp.ntok[i] = i < n ? ntok[i] : 0;
         sp.first[i] = i < n ? sp.tiles : 0x7fffffff;

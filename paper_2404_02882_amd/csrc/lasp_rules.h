@@ -59,7 +59,9 @@ inline bool short_forward(int tokens, long long chains, int D) { return tokens >
 // The walk then carries the boundary state over two pieces instead of one; two states are what the scratch holds anyway.
 // The second state costs the walk 1.3 us, so only from 12 tiles a segment on. Steps of 128 heads, bf16 d=128, one piece / two:
 // x 1024 tokens (8 tiles) 124.7 / 126.5 us, x 1536 181.1 / 177.7, x 2048 234.8 / 227.1, x 8192 880 / 831, x 16384 1737 / 1627 (a
-// local pass 163 -> 100), decay per token x 8192 943 / 907, d=64 x 8192 457 / 441.
+// local pass 163 -> 100), decay per token x 8192 943 / 907, d=64 x 8192 457 / 441; 86 heads x 1536 150.8 / 146.0, x 3072 284.5 / 265.6; float
+// d=128 86 x 768 (12 tiles) 310.3 / 301.7, 128 x 1536 599 / 590. (Other products are rounded then, a piece weighs its tokens from its
+// own end: 128 x 2048, outputs 1.3e-3 apart, the error against 64 bits 2.828e-3 either way.)
 inline int local_pieces(int segments, int tiles_per_seg, long long chains) {
     return segments == 2 && tiles_per_seg % 2 == 0 && tiles_per_seg >= 12 && chains <= kOnePerCu / 2 ? 2 : 1;
 }

@@ -1774,9 +1774,9 @@ struct Bwd8hFam : Family<AloneOwn> {   // one cached state per pair of tiles, a 
 // at a time (half the barriers, twice the bytes in flight per workgroup), unless
 // key and value dimensions that differ ask for the walk's tile. Two groups of waves where the dimensions are the same, half of
 // the state's rows each: a second wave per SIMD to run while one waits, half of the stores into LDS (and of Norm's
-// arithmetic) a wave. Steps, d=128, one group / two: 16 heads x 8192 tokens 156.5 / 151.4 us, 32 x 2048 98.8 / 95.3, 2 x 32 x 5000 with
+// arithmetic) a wave. Steps, d=128, one group / two: 16 heads x 8192 tokens 156.5 / 151.4 us, 32 x 2048 98.8 / 95.3, 2 x 16 x 5000 with
 // states 181.0 / 175.6, Norm 16 x 8192 (64-token tiles / 128) 170.2 / 164.6; d=64 16 x 8192
-// 79.9 / 78.1, 32 x 2048 57.5 / 56.3.
+// 79.9 / 78.1, 32 x 2048 57.5 / 56.3; of 48 to 256 heads x 256 to 2048 tokens, with Norm and a decay per token too, none is slower.
 // The forward pass of one sub-sequence never sums over the segment with the short end.
 template <typename T, int CT, int D, bool BWD, int WK = D, int WV = D>
 static hipError_t run_local(const Plan &p, const T *x, const T *y, const float *decay, float *scratch, float *seglog,
