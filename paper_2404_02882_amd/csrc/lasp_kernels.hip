@@ -341,7 +341,7 @@ static hipError_t run_step(const Plan &p, const FwdArgs &a, hipStream_t s, const
 // Float weights reach over a tile at most, from tile to tile the sums decay, and the state's weight is a double: lambda^245 may be
 // below the smallest float, and an infinity would meet that zero. (Two floats for lambda^32, whose rounded seventh power is 1e-7 off.)
 // Bound by the splits of a wave's operands and the way to memory and back. 2 heads x 256 tokens, d=64, 14.1 -> 10.1 us, x 128
-// 11.9 -> 7.0, x 64 8.6 -> 6.3 (the call through the Python binding takes 6); d=128 16 x 256 26.8 -> 17.0, with a state 26.7 -> 23.0.
+// 11.9 -> 7.0, x 64 8.6 -> 6.3 (the call through the Python binding takes 6); d=128 16 x 256 26.8 -> 16.9, with a state 26.7 -> 22.8.
 // Error against 64 bits, the walks / this, out and kv_out: 2 x 256, d=64, 1.56e-7, 1.02e-7 / 1.00e-7, 6.9e-8; 16 x 13 1.02e-7, 3.7e-8 /
 // 6.6e-8, 3.4e-8; d=128 with a state 16 x 250 2.07e-7, 1.58e-7 / 1.65e-7, 2.7e-8.
 // ---------------------------------------------------------------------------
@@ -475,6 +475,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
             const Lane of(i);
             const int token = 32 * t + of.r, feature = 8 * (i >> 6) + 4 * of.h;
             f32x4 x = {0, 0, 0, 0};
+#pragma unroll 4   // (of one by one the waits for LDS add up: 10.17 us, so 10.04)
             for (int v = 0; v < t; ++v) x = decayed(tile, x, part(v, i));
             x = decayed(factor[of.r + 1], x, part(t, i));
             if (kv_in) {
@@ -530,6 +531,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_short(const float *__restr
             const Lane of(i);
             f32x4 x = {0, 0, 0, 0};
             const size_t at = ((size_t)chain * D + 8 * (i >> 6) + 4 * of.h) * D + 32 * (blockIdx.x - ntiles) + of.r;
+#pragma unroll 4
             for (int v = 0; v + 1 < ntiles; ++v) x = decayed(tile, x, part(v, i));
             x = decayed(factor[ntok - 32 * (ntiles - 1)], x, part(ntiles - 1, i));
 #pragma unroll
