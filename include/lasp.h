@@ -388,7 +388,7 @@ int lasp_bidir_bwd(const lasp_shape *shape, const void *k, const void *v, const 
  * (dkv = sum over all of them, and every dq, dk, dv). shapes: T shapes that differ in N only; the tensors are arrays
  * of T device pointers, themselves in host memory, not kept. Up to four sub-sequences go through a launch together
  * (segments = 0; sums are then cut over the tokens of all of them), and dq comes with the sum, which has dO on chip,
- * where no gradient overlaps an input. scratch: lasp_bidir_seq_scratch_bytes() bytes (0 on invalid shapes).
+ * where that is the faster way and no gradient overlaps an input. scratch: lasp_bidir_seq_scratch_bytes() bytes (0 on invalid shapes).
  * LASP_ERR_ALIAS: kv (backward: dkv) or scratch overlaps any input; an output overlaps kv, dkv or what the call of its
  * own sub-sequence reads beside it (out[t]: q[t]; dq[t], dk[t], dv[t]: k[t], v[t], dout[t] and each other). The other
  * overlaps between sub-sequences' tensors (dq[t] over q[t], dk[t] over k[t - 1]) are taken, with what the loops would leave.
